@@ -30,6 +30,8 @@ import numpy as np
 PEAK_LDS_GATHER_TFLOPS = 256 * 256 * 2.4e9 / 4 / 1e12
 PEAK_ALU_ADD_TFLOPS = 157.3 / 2
 PEAK_HBM_GBS = 8000.0
+# The matrix-core path multiplies three bf16 planes of X by W, zeros included: 6 M K N floating-point operations.
+PEAK_BF16_TFLOPS = 2516.0
 PEAK_ALU_INSTR_T = 256 * 64 * 2.4e9 / 1e12     # vector lane-instructions per second (an FMA counts once)
 
 # HBM bytes (read + written) of one launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
@@ -47,6 +49,18 @@ MEASURED_TRAFFIC = {
 }
 ORACLE_FLAGS = "gcc -O3 -fstrict-aliasing -DNDEBUG -fopenmp (the paper's flags, Sec. 4, without -march=native)"
 INFINITY_CACHE_BYTES = 256 << 20
+
+
+def takes_matrix_cores(M, K, N, n_pad, density, cus):
+    """Whether a call with M > 8 and no launch-shape override goes through the matrix cores: the library's own rule
+    (tstgemm_matrix.hip, matrix_wins) with its estimate of the matrix-core time at the power limit, which is the larger
+    one wherever the row-set kernel can be ahead."""
+    if M > 64:
+        if n_pad % 128:
+            return True
+        rounds = -(-(-(-M // 256) * (n_pad // 128)) // (2 * cus))
+        return 6.0 * (-(-M // 64) * 64) * n_pad * K / 1.5e9 + 4.39 < 20.0 + rounds * K * (0.0281 + 0.464 * density)
+    return density >= 0.13 or N >= 2048
 
 
 def cpu_baseline(W, X, b, nnz, variant="tcsc", budget_s=10.0):
@@ -232,6 +246,10 @@ def main():
 
     decode = wl.M <= 8          # the library's rules for its decode kernel ...
     small = 8 < wl.M <= 64      # ... and its small-tile kernel
+    shaped = args.cols_per_wave or getattr(args, "k_slices", 0) or getattr(args, "slab_tiles", 0) or getattr(args, "list_walk", 0)
+    matrix = (not decode and args.variant == "tcsc" and not shaped and
+              takes_matrix_cores(wl.M, wl.K, wl.N, lay.n_pad, nnz / (wl.K * wl.N),
+                                 torch.cuda.get_device_properties(0).multi_processor_count))
     # index data one call reads (what must not be in the Infinity Cache for an HBM figure)
     narrow = (decode and args.variant == "tcsc" and bool(lay.has_lists16) and not args.wide_lists
               and wl.K <= 150 * 1024 // (4 * wl.M) - 1)   # the library's rule for its padded 16-bit lists
@@ -365,6 +383,13 @@ def main():
         alg_bytes = index_bytes + 8 * (wl.N + 1) + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
         roof = {"bound": "hbm", "achieved": alg_bytes / (kernel_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                 "unit": "GB/s", "traffic": traffic}
+    elif matrix:
+        # the row sets, X, Y and b once; the work is the dense one, whatever the density
+        alg_bytes = 16 * lay.n_kblocks * lay.n_pad + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
+        traffic = measured = None      # the counter runs behind the constants were of the gather kernels
+        roof = {"bound": "mfma", "achieved": 6.0 * wl.M * wl.K * wl.N / (kernel_ms * 1e-3) / 1e12, "peak": PEAK_BF16_TFLOPS,
+                "unit": "TFLOP/s", "traffic": None,
+                "note": "three bf16 planes of X times W, zeros included: 6 M K N operations; peak = dense bf16"}
     else:
         # index data the kernel reads (small tile: the TCSC row numbers and the list cuts; else the 64-bit row sets)
         # + X + Y + b
@@ -376,7 +401,7 @@ def main():
                 "alu_add_peak": PEAK_ALU_ADD_TFLOPS}
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["kernel"] = ("k_packed" if args.variant == "packed" else "k_decode (signed lists)" if args.variant == "signed"
-                      else "k_decode" if decode else "k_small" if small else "k_large")
+                      else "k_decode" if decode else "k_matrix" if matrix else "k_small" if small else "k_large")
     if decode and args.variant == "tcsc":
         roof["kernel"] += " (16-bit lists)" if narrow else " (32-bit lists)"
     roof["kernel_ms"] = kernel_ms
@@ -397,7 +422,7 @@ def main():
     roof["call_ms_median"] = float(np.median(region_ms))
     roof["call_ms_min"] = float(np.min(region_ms))
     roof["call_frac"] = roof["frac"] * kernel_ms / call_ms   # the same work over the time of the whole call
-    if not decode:
+    if not decode and not matrix:
         roof["alu_frac"] = roof["achieved"] / PEAK_ALU_ADD_TFLOPS
         # What this build can reach at most: without packed fp32 a compute unit issues one vector instruction per
         # clock (64 lanes), which is the same 39.3 T lane-operations/s as the LDS port's gathers, and every 16-byte
@@ -405,7 +430,7 @@ def main():
         # C2 at nine tenths of it (counters: profiles/shader_counters_all_configs.md).
         roof["valu_issue_bound"] = PEAK_LDS_GATHER_TFLOPS * 4.0 / 5.0
         roof["frac_of_valu_issue_bound"] = roof["achieved"] / roof["valu_issue_bound"]
-    if not decode and not small:
+    if not decode and not small and not matrix:
         # Bytes the main kernel copies from the packed X (in the L2s) into the LDS: every workgroup one K-block of its
         # row tile (64 rows of W x TM rows of X x 4 bytes) per K-block it walks, whatever the density.  The columns
         # per workgroup follow the library's own rule for its launch shape (tstgemm_large.hip, choose_shape), restated

@@ -13,9 +13,9 @@
  * Y is fp32 (M x N, row-major).  W is held in the TCSC format of Sec. 2: four int32 arrays,
  * col_start_pos / col_start_neg (N+1 column pointers) and row_index_pos / row_index_neg
  * (row numbers of the +1 / -1 entries, column after column, ascending inside a column; the
- * entries of column j are [col_start[j], col_start[j+1])).  The product is evaluated with
- * additions and subtractions only (BaseTCSC, Sec. 2): X entries whose weight is 0 are never
- * read, so a non-finite value there does not reach Y.
+ * entries of column j are [col_start[j], col_start[j+1])).  The product is that of additions and
+ * subtractions only (BaseTCSC, Sec. 2): X entries whose weight is 0 take no part in it, so a
+ * non-finite value there does not reach Y, whichever kernel runs.
  */
 #ifndef TSTGEMM_H
 #define TSTGEMM_H
@@ -177,7 +177,10 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * chunks of K if it is larger than 150 KiB; TCSC lists streamed -- their padded 16-bit copy where there is one
  * and X fits the LDS whole), 8 < M <= 64 the small-tile kernel (one tile of
  * X, lists read from the TCSC arrays between the list cuts; not for matrices with 2^30 or more entries of one sign,
- * whose lists its 32-bit byte offsets do not reach), everything else the large-M path (row sets).
+ * whose lists its 32-bit byte offsets do not reach), everything else the large-M path (row sets).  Where the buffer
+ * holds the row sets and W is not too sparse for it to pay, M > 8 goes through the matrix cores instead: X is cut
+ * exactly into three bf16 planes and multiplied by the row sets, spread into weights, with fp32 sums.  What a call
+ * needs (its form, the least workspace) is the same either way.
  * Asynchronous: the kernels are enqueued on `stream` (a hipStream_t, NULL = null stream), no host
  * synchronisation, no allocation.
  * Device data are not validated.  Errors: EINVAL, ENOTUPLOADED, ENOFORM, EWORKSPACE, EHIP (launch failure).
@@ -214,7 +217,8 @@ typedef struct tstgemm_opts {
                                 whose kernels may overlap (different streams) need different workspaces, calls on one
                                 stream can share one across any number of matrices */
     size_t workspace_bytes;  /* at least the min_bytes of tstgemm_workspace_bytes(), else EWORKSPACE */
-    /* Launch-shape overrides for the tiled paths (M > 8), for tuning runs and tests; 0 = the built-in choice.
+    /* Launch-shape overrides for the tiled paths (M > 8), for tuning runs and tests; 0 = the built-in choice (a call
+     * that sets one of them or list_walk runs the list or row-set kernels, not the matrix cores).
      * cols_per_wave: 1, 2, 4 or 8 columns of Y per wavefront (the small-tile kernel has 1, 2, 4 and takes 8 as 4; 8 is
      * the large-M path's wide shape, which needs a padded column count that is a multiple of 128, else it runs as 4);
      * k_slices: 1..8 slices of K computed by different workgroups and summed in slice order (also the workgroups per

@@ -416,6 +416,8 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
     c.event_before = static_cast<hipEvent_t>(o.event_before);
     c.event_after = static_cast<hipEvent_t>(o.event_after);
 
+    // a call that asks for a launch shape of the list and row-set kernels gets those kernels
+    const bool shaped = o.cols_per_wave || o.k_slices || o.slab_tiles || o.list_walk;
     hipError_t e;
     if (o.encoding == 1) {
         if (!(l.forms & TCSC_FORM_SIGNED)) return TSTGEMM_ENOFORM;
@@ -427,10 +429,19 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
         e = tst::launch_decode(X, t, b, Y, M, c);
     } else if (M <= 64 && tst::small_supported(l)) {
         if (!(l.forms & TCSC_FORM_CUTS)) return TSTGEMM_ENOFORM;
-        e = tst::launch_small(X, t, b, Y, M, c);
+        if (!shaped && (l.forms & TCSC_FORM_ROWSETS) && c.ws && c.ws_bytes >= tst::small_tile_bytes(M, K) &&
+            tst::matrix_wins(l, M, c))
+            e = tst::launch_matrix(X, t, b, Y, M, c);
+        else
+            e = tst::launch_small(X, t, b, Y, M, c);
     } else {
         if (!(l.forms & TCSC_FORM_ROWSETS)) return TSTGEMM_ENOFORM;
-        e = tst::launch_large(X, t, b, Y, M, c);
+        size_t least = 0, best = 0;
+        tst::large_workspace_bytes(M, K, l.n_pad, &least, &best);
+        if (!shaped && c.ws && c.ws_bytes >= least && tst::matrix_wins(l, M, c))
+            e = tst::launch_matrix(X, t, b, Y, M, c);
+        else
+            e = tst::launch_large(X, t, b, Y, M, c);
     }
     return e == hipSuccess ? TSTGEMM_OK : e == tst::kErrWorkspace ? TSTGEMM_EWORKSPACE : TSTGEMM_EHIP;
 }

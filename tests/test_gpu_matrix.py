@@ -1,0 +1,120 @@
+"""The matrix-core kernels (X cut into three bf16 planes) through the ordinary entry points: sizes at the edges of their
+tiles and steps, X that their planes cannot hold, and the same calls through the list and row-set kernels, against the
+oracle element by element."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2510_06957_amd as tg
+import synth_inputs as si
+from gpu_util import assert_close, gpu_tstgemm
+
+pytestmark = pytest.mark.gpu
+
+# Sums of at most K terms in fp32, each product exact: bounded by K 2^-24 of sum |X W| in any order, and measured at
+# 1e-7 of the result's norm.  The walk of the lists is held to 1e-5 of sum |X W| (gpu_util); here a tenth of it, which a
+# lost third plane (2^-16 = 1.5e-5 of every entry) cannot pass.
+TIGHT = 1e-6
+
+
+def tight(Y, Yd, A, what):
+    err = np.abs(Y.astype(np.float64) - Yd)
+    assert np.all(err <= TIGHT * A), f"{what}: {np.max(err / A):.2e}"
+
+
+# rows: 32- and 64-row tiles and one more or less; K: below, at and above steps of 32, blocks of 64, groups and slices of
+# them, not a multiple of 4; N: columns of a fragment, of a tile, odd
+@pytest.mark.parametrize("M,K,N", [(11, 1, 1), (31, 31, 33), (32, 32, 32), (33, 33, 31), (64, 64, 64), (63, 65, 130),
+                                   (65, 127, 63), (17, 257, 300), (100, 515, 129), (129, 1027, 257), (255, 2050, 255),
+                                   (257, 64, 1025), (40, 8195, 100), (700, 333, 700), (1025, 100, 513)])
+def test_tile_edges(M, K, N):
+    W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=700 + M + K + N)
+    ot = oracle.tcsc_build(W)
+    Yd, A, _ = oracle.tstgemm(X, ot, b)
+    Y, h = gpu_tstgemm(W, X, b)
+    tight(Y, Yd, A, f"{M}x{K}x{N}")
+    _, Xi, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=701 + M)
+    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h)
+    assert np.array_equal(Yi, oracle.tstgemm(Xi, ot, b)[0].astype(np.float32))
+    # the same call through the kernels that walk lists and row sets
+    other = dict(wide_lists=True) if M <= 8 else dict(list_walk=1) if M <= 64 else dict(cols_per_wave=4)
+    Yo, _ = gpu_tstgemm(W, X, b, handle=h, **other)
+    assert np.all(np.abs(Yo.astype(np.float64) - Y) <= 1.1e-5 * A)
+
+
+def _same(Y, Yd):
+    """Equal in what is not finite; else within the tolerance of the finite part of the sum."""
+    return np.array_equal(np.isnan(Y), np.isnan(Yd)) and np.array_equal(np.isposinf(Y), np.isposinf(Yd)) \
+        and np.array_equal(np.isneginf(Y), np.isneginf(Yd))
+
+
+@pytest.mark.parametrize("M,K,N", [(3, 300, 70), (8, 1500, 40), (40, 300, 70), (40, 4100, 200), (300, 333, 130)])
+@pytest.mark.parametrize("alpha", [None, 0.25])
+def test_infinities_and_nans(M, K, N, alpha):
+    """X with infinities and NaNs: exactly the outputs whose lists hold them are not finite, as a plain sum gives it."""
+    W, X, b = si.make_inputs(M, K, N, 0.25, "normal", seed=720 + M + K)
+    rng = np.random.default_rng(721)
+    for v in (np.inf, -np.inf, np.nan):
+        X[rng.integers(0, M, 2), rng.integers(0, K, 2)] = v
+    X[0, 5], X[0, K - 1] = np.inf, np.inf
+    Yd = np.zeros((M, N))
+    for m in range(M):
+        used = np.where(W != 0, X[m][:, None].astype(np.float64) * W, 0.0)
+        with np.errstate(invalid="ignore"):
+            Yd[m] = used.sum(axis=0)
+    with np.errstate(invalid="ignore"):
+        A = np.where(np.isfinite(Yd), np.abs(np.where(np.isfinite(X), X, 0)).astype(np.float64) @ np.abs(W), 0) + np.abs(b)
+        Yd = Yd + b
+        if alpha is not None:
+            Yd = np.where(Yd > 0, Yd, alpha * Yd)
+    Y, _ = gpu_tstgemm(W, X, b, alpha=alpha)
+    assert np.isfinite(Yd).any() and not np.isfinite(Yd).all()
+    assert _same(Y, Yd)
+    ok = np.isfinite(Yd)
+    assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-5 * A[ok])
+
+
+@pytest.mark.parametrize("M,K,N", [(5, 300, 70), (40, 300, 70), (130, 4100, 70)])
+@pytest.mark.parametrize("exponent", [-149, -140, -126, -110, 0, 60, 99, 110, 116])
+def test_range_of_x(M, K, N, exponent):
+    """Integers times a power of two, from the smallest float to where the sums just fit: exact, as with any order of
+    additions."""
+    W, X, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=740 + M)
+    ot = oracle.tcsc_build(W)
+    Yd = oracle.tstgemm(X, ot, None)[0]
+    scale = np.ldexp(1.0, exponent)
+    Xs = (X.astype(np.float64) * scale).astype(np.float32)
+    assert np.array_equal(Xs.astype(np.float64), X.astype(np.float64) * scale)
+    Y, _ = gpu_tstgemm(W, Xs, None)
+    assert np.array_equal(Y.astype(np.float64), Yd * scale)
+
+
+def test_full_significands():
+    """Floats whose last bits are set and whose exponents lie far apart, one entry of W per column: nothing of X is lost."""
+    M, K = 70, 200
+    rng = np.random.default_rng(760)
+    X = (rng.integers(2**23, 2**24, (M, K)) * np.exp2(rng.integers(-120, 60, (M, K)).astype(np.float64))).astype(np.float32)
+    W = np.zeros((K, K), np.int8)
+    W[np.arange(K), rng.permutation(K)] = rng.choice([-1, 1], K)
+    for m in (1, 8, 20, 70):
+        Y, _ = gpu_tstgemm(W, X[:m], None)
+        assert np.array_equal(Y.astype(np.float64), X[:m].astype(np.float64) @ W)
+
+
+@pytest.mark.parametrize("M", [64, 256])
+def test_without_the_row_sets_or_with_little_scratch(M):
+    """What decides beside the sizes: M <= 64 without the row sets takes the lists; the least workspace is enough."""
+    import torch
+    K, N = 2048, 256
+    W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=770 + M)
+    Yd, A, _ = oracle.tstgemm(X, oracle.tcsc_build(W), b)
+    Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda()
+    least = tg.tstgemm_workspace_bytes(M, K, N)[0]
+    for forms in ([tg.FORM_CUTS, tg.FORM_CUTS | tg.FORM_ROWSETS] if M <= 64 else [tg.FORM_ROWSETS]):
+        t = tg.tcsc_upload(tg.tcsc_build(W), forms=forms)
+        for size in (least, 64 << 20):
+            ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+            assert_close(tg.tstgemm(Xd, t, bd, workspace=ws).cpu().numpy(), Yd, A, f"forms {forms} {size} bytes")
+        with pytest.raises(tg.TstgemmError) as err:
+            tg.tstgemm(Xd, t, bd, workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+        assert err.value.code == -8
