@@ -53,14 +53,14 @@ INFINITY_CACHE_BYTES = 256 << 20
 
 def takes_matrix_cores(M, K, N, n_pad, density, cus):
     """Whether a call with M > 8 and no launch-shape override goes through the matrix cores: the library's own rule
-    (tstgemm_matrix.hip, matrix_wins) with its estimate of the matrix-core time at the power limit, which is the larger
+    (tstgemm_matrix.hip, matrix_plan) with its estimate of the matrix-core time at the power limit, which is the larger
     one wherever the row-set kernel can be ahead."""
     if M > 64:
         if n_pad % 128:
             return True
         rounds = -(-(-(-M // 256) * (n_pad // 128)) // (2 * cus))
-        return 6.0 * (-(-M // 64) * 64) * n_pad * K / 1.5e9 + 4.39 < 20.0 + rounds * K * (0.0281 + 0.464 * density)
-    return density >= 0.13 or N >= 2048
+        return 6.0 * (-(-M // 64) * 64) * n_pad * K / 1.5e9 + 3.36 < 20.0 + rounds * K * (0.0281 + 0.464 * density)
+    return True                 # (and for M <= 64 wherever a column list is not extremely short)
 
 
 def cpu_baseline(W, X, b, nnz, variant="tcsc", budget_s=10.0):

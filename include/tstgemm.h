@@ -178,7 +178,7 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * and X fits the LDS whole), 8 < M <= 64 the small-tile kernel (one tile of
  * X, lists read from the TCSC arrays between the list cuts; not for matrices with 2^30 or more entries of one sign,
  * whose lists its 32-bit byte offsets do not reach), everything else the large-M path (row sets).  Where the buffer
- * holds the row sets and W is not too sparse for it to pay, M > 8 goes through the matrix cores instead: X is cut
+ * holds the row sets and W is not too sparse for it to pay, a call goes through the matrix cores instead: X is cut
  * exactly into three bf16 planes and multiplied by the row sets, spread into weights, with fp32 sums.  What a call
  * needs (its form, the least workspace) is the same either way.
  * Asynchronous: the kernels are enqueued on `stream` (a hipStream_t, NULL = null stream), no host
@@ -228,9 +228,9 @@ typedef struct tstgemm_opts {
                                 1 = the plain walk of the lists (best on short lists), 2 = the walk that requests the
                                 entries of a list two steps ahead (best from about 40 entries per list and 256 rows of
                                 W on).  Same sums, added in a different order */
-    int decode_wide_lists;   /* != 0: M <= 8 reads the 32-bit TCSC lists even where the padded 16-bit copy exists.  The two
-                                deal the entries of a list to the lanes differently, so fp32 rounding can differ in the
-                                last bits; integer-valued inputs give the same, exact result */
+    int decode_wide_lists;   /* != 0: M <= 8 reads the 32-bit TCSC lists even where the padded 16-bit copy or the row sets
+                                exist.  Each adds in an order of its own, so fp32 rounding can differ in the last bits;
+                                integer-valued inputs give the same, exact result */
     void *event_before, *event_after;   /* hipEvent_t pair (both or neither), recorded on the call's stream right before
                                 and after the launch of the main (gather-add) kernel, not around the packing
                                 pre-pass and the reduction of K slices; a call with several slabs of rows records

@@ -418,6 +418,7 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
 
     // a call that asks for a launch shape of the list and row-set kernels gets those kernels
     const bool shaped = o.cols_per_wave || o.k_slices || o.slab_tiles || o.list_walk;
+    const bool row_sets = (l.forms & TCSC_FORM_ROWSETS) != 0;
     hipError_t e;
     if (o.encoding == 1) {
         if (!(l.forms & TCSC_FORM_SIGNED)) return TSTGEMM_ENOFORM;
@@ -426,22 +427,20 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
         if (!(l.forms & TCSC_FORM_PACKED)) return TSTGEMM_ENOFORM;
         e = tst::launch_packed(X, t, b, Y, M, c);
     } else if (tst::decode_supported(M)) {
-        e = tst::launch_decode(X, t, b, Y, M, c);
+        const tst::MatrixPlan p = row_sets && !c.decode_wide_lists ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
+        e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_decode(X, t, b, Y, M, c);
     } else if (M <= 64 && tst::small_supported(l)) {
         if (!(l.forms & TCSC_FORM_CUTS)) return TSTGEMM_ENOFORM;
-        if (!shaped && (l.forms & TCSC_FORM_ROWSETS) && c.ws && c.ws_bytes >= tst::small_tile_bytes(M, K) &&
-            tst::matrix_wins(l, M, c))
-            e = tst::launch_matrix(X, t, b, Y, M, c);
-        else
-            e = tst::launch_small(X, t, b, Y, M, c);
+        const bool scratch = c.ws && c.ws_bytes >= tst::small_tile_bytes(M, K);
+        const tst::MatrixPlan p = row_sets && scratch && !shaped ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
+        e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_small(X, t, b, Y, M, c);
     } else {
-        if (!(l.forms & TCSC_FORM_ROWSETS)) return TSTGEMM_ENOFORM;
+        if (!row_sets) return TSTGEMM_ENOFORM;
         size_t least = 0, best = 0;
         tst::large_workspace_bytes(M, K, l.n_pad, &least, &best);
-        if (!shaped && c.ws && c.ws_bytes >= least && tst::matrix_wins(l, M, c))
-            e = tst::launch_matrix(X, t, b, Y, M, c);
-        else
-            e = tst::launch_large(X, t, b, Y, M, c);
+        const bool scratch = c.ws && c.ws_bytes >= least;
+        const tst::MatrixPlan p = scratch && !shaped ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
+        e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_large(X, t, b, Y, M, c);
     }
     return e == hipSuccess ? TSTGEMM_OK : e == tst::kErrWorkspace ? TSTGEMM_EWORKSPACE : TSTGEMM_EHIP;
 }

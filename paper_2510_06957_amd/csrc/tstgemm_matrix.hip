@@ -12,7 +12,8 @@
 // X held an infinity, a NaN or something beyond about 2^100 -- is taken again from X itself by gather_output(), member by
 // member of the lists, so an entry of X under a zero weight never reaches Y here either.
 //
-// k_matrix is for M > 10, k_rows for M <= 10; choose_tile() and rows_plan() have the rules, with what was measured.
+// k_matrix is for M > 8, k_rows for M <= 10; choose_tile(), rows_plan() and matrix_plan() have the rules, with what was
+// measured.
 #include <cmath>
 
 #include "tstgemm_internal.h"
@@ -68,6 +69,37 @@ __device__ __forceinline__ uint4v load16(__amdgpu_buffer_rsrc_t buf, unsigned of
     return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)offset, 0, 0));
 }
 
+// A descriptor over `bytes` from p on (at most 4 GiB; none for a null pointer).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0,
+                                             p == nullptr ? 0 : (int)(unsigned)min(bytes, (size_t)0xfffffffcu), kRawBuffer);
+}
+constexpr unsigned kNowhere = 0xffffff00u;   // an offset beyond every buffer: reads as zero, stores nothing
+
+// Bias and PReLU of columns, requested before the sums are there; zero for columns >= N and without a bias.
+struct Epilogue {
+    __amdgpu_buffer_rsrc_t bias, slope;
+    int alpha_stride;
+    bool prelu;
+    __device__ __forceinline__ Epilogue(const float *b, const float *alpha, int stride, int N)
+        : bias(raw_buffer(b, (size_t)N * 4)), slope(raw_buffer(alpha, stride ? (size_t)N * 4 : 4)), alpha_stride(stride),
+          prelu(alpha != nullptr) {}
+    __device__ __forceinline__ float bias_of(int n) const
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bias, n * 4, 0, 0));
+    }
+    __device__ __forceinline__ float slope_of(int n) const
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(slope, n * 4 * alpha_stride, 0, 0));
+    }
+    __device__ __forceinline__ float operator()(float v, float bias_n, float slope_n) const
+    {
+        v += bias_n;
+        return prelu && !(v > 0.f) ? slope_n * v : v;
+    }
+};
+
 // X W for one output straight from X: adds and subtracts the members of the two sets of every block.  For outputs whose
 // sum the matrix cores could not hold; a NaN stays one, so the walk ends there.
 __device__ __forceinline__ float gather_output(const float *__restrict__ X, const uint4v *__restrict__ masks, int n_pad,
@@ -106,7 +138,7 @@ struct MatrixArgs {
 // count, M = 4096, K = N = 8192 took 1.20 ms in place of 1.10).
 // Bound: long calls by the power limit (M = 4096, K = N = 8192: 1.10 ms, i.e. 1.50 PFLOP/s of bf16 products at about
 // 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here), short ones by the start of the first loads, the
-// sums at the end and the second launch where K is sliced (M = 256, K = N = 4096: 31 us against 89).
+// sums at the end and the second launch where K is sliced (M = 256, K = N = 4096: 28 us against 89).
 // Rows beyond M and rows of W beyond K: X reads as zero, or as the next row of X where the weights are zero.
 template <int WK, int WM, int WN, int RF, int CF>
 __global__ void __launch_bounds__(64 * WK * WM * WN, 2)
@@ -141,11 +173,8 @@ k_matrix(const MatrixArgs a)
 
     // X from the first row of the tile on, and the row sets up to the end of the group's blocks: what lies beyond reads
     // as zero
-    const size_t x_bytes = (size_t)(a.M - m0) * a.K * sizeof(float);
-    const __amdgpu_buffer_rsrc_t xbuf = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(a.X + (size_t)m0 * a.K), 0, (int)(unsigned)min(x_bytes, (size_t)0xfffffffcu), kRawBuffer);
-    const __amdgpu_buffer_rsrc_t wbuf = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint4v *>(a.masks), 0, (int)((unsigned)kb1 * (unsigned)a.n_pad * 16u), kRawBuffer);
+    const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(a.X + (size_t)m0 * a.K, (size_t)(a.M - m0) * a.K * 4);
+    const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(a.masks, (size_t)kb1 * a.n_pad * 16);
     unsigned xoff[kUnits], woff[CF];
     int unit[kUnits];
 #pragma unroll
@@ -196,6 +225,15 @@ k_matrix(const MatrixArgs a)
 #pragma unroll
         for (int j = 0; j < CF; ++j) bw[j] = SignedWord(w[set][j][t] >> (4 * g), w[set][j][2 + t] >> (4 * g)).eight(8 * u);
     };
+
+    const int col0 = n0 + wc * CF * 32 + l32;
+    const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);
+    float bias[CF], slope[CF];
+#pragma unroll
+    for (int j = 0; j < CF; ++j) {
+        bias[j] = finish.bias_of(col0 + 32 * j);
+        slope[j] = finish.slope_of(col0 + 32 * j);
+    }
 
     float16v acc[2][RF][CF];   // [hi | mid + lo]
 #pragma unroll
@@ -298,51 +336,49 @@ k_matrix(const MatrixArgs a)
         if (group > 0) return;
     }
 
-    // element e of a fragment is row 8 (e / 4) + 4 g + e % 4, column l32
-    const int row0 = m0 + wr * RF * 32 + 4 * g, col0 = n0 + wc * CF * 32 + l32;
+    // element e of a fragment is row 8 (e / 4) + 4 g + e % 4, column l32.  The stores are range-checked (rows beyond M,
+    // columns beyond the last): guarded by branches they waited for each other, 1.4 us of a short call
+    const int row0 = wr * RF * 32 + 4 * g;
     auto row_of = [&](int i, int e) { return row0 + 32 * i + 8 * (e / 4) + e % 4; };
     if (a.k_slices > 1) {
-        float *P = a.partials + (size_t)slice * a.M * a.n_pad;
+        const __amdgpu_buffer_rsrc_t pbuf =
+            raw_buffer(a.partials + ((size_t)slice * a.M + m0) * a.n_pad, (size_t)(a.M - m0) * a.n_pad * 4);
 #pragma unroll
         for (int j = 0; j < CF; ++j) {
             const int n = col0 + 32 * j;
 #pragma unroll
             for (int i = 0; i < RF; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = row_of(i, e);
-                    if (m < a.M && n < a.n_pad) P[(size_t)m * a.n_pad + n] = acc[0][i][j][e];
-                }
+                for (int e = 0; e < 16; ++e)
+                    __builtin_amdgcn_raw_buffer_store_b32(
+                        __float_as_uint(acc[0][i][j][e]), pbuf,
+                        (int)(n < a.n_pad ? ((unsigned)row_of(i, e) * (unsigned)a.n_pad + n) * 4u : kNowhere), 0, 0);
         }
         return;
     }
+    const __amdgpu_buffer_rsrc_t ybuf = raw_buffer(a.Y + (size_t)m0 * a.N, (size_t)(a.M - m0) * a.N * 4);
     bool again = false;
 #pragma unroll
     for (int j = 0; j < CF; ++j) {
         const int n = col0 + 32 * j;
-        const float bias = (a.b != nullptr && n < a.N) ? a.b[n] : 0.f;
-        const float slope = (a.alpha != nullptr && n < a.N) ? a.alpha[(size_t)n * a.alpha_stride] : 0.f;
 #pragma unroll
         for (int i = 0; i < RF; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int m = row_of(i, e);
                 again |= !finite(acc[0][i][j][e]);
-                float v = acc[0][i][j][e] * kScaleDown + bias;
-                if (a.alpha != nullptr) v = v > 0.f ? v : slope * v;
-                if (m < a.M && n < a.N) a.Y[(size_t)m * a.N + n] = v;
+                __builtin_amdgcn_raw_buffer_store_b32(
+                    __float_as_uint(finish(acc[0][i][j][e] * kScaleDown, bias[j], slope[j])), ybuf,
+                    (int)(n < a.N ? ((unsigned)row_of(i, e) * (unsigned)a.N + n) * 4u : kNowhere), 0, 0);
             }
     }
     if (!again) return;
     for (int j = 0; j < CF; ++j) {
         const int n = col0 + 32 * j;
         if (n >= a.N) break;
-        const float bias = a.b != nullptr ? a.b[n] : 0.f;
         for (int i = 0; i < RF * 16; ++i) {
-            const int m = row_of(i / 16, i % 16);
+            const int m = m0 + row_of(i / 16, i % 16);
             if (m >= a.M || finite(a.Y[(size_t)m * a.N + n])) continue;   // the lane's own store
-            const float v = gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K) + bias;
-            a.Y[(size_t)m * a.N + n] = activate(v, a.alpha, a.alpha_stride, n);
+            a.Y[(size_t)m * a.N + n] = finish(gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K), bias[j], slope[j]);
         }
     }
 }
@@ -414,19 +450,19 @@ hipError_t launch_tiles(const MatrixArgs &a, int m_tiles, const Call &c)
 // (per_cu workgroups at a time); a call takes kCall us more, slices kSlice us and 0.4 us per MB of partial sums; and no
 // call is faster than the matrix cores at the power limit (1.5 PFLOP/s).  Fitted to 13 tiles x 6 slice counts on 77
 // shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among these five is 2 % slower than the best of all on
-// average, 15 % at worst.
+// average, 16 % at worst.
 struct TileShape {
     int rows, cols, groups, per_cu;
     double fixed, step, work;
 };
 constexpr TileShape kTiles[] = {
-    {64, 256, 1, 2, 1.23, 0.574, 0.457},   // long calls: two independent workgroups per unit fill each other's barriers
-    {64, 256, 2, 1, 2.08, 0.964, 0.964},   // half the slices of the first where rows x columns leave units idle
-    {64, 128, 1, 3, 0.29, 0.417, 0.307},   // short K: little to start with
-    {32, 64, 4, 2, 0.52, 0.483, 0.461},    // small Y
-    {32, 128, 2, 2, 0.30, 0.449, 0.381},   // M <= 32
+    {64, 256, 1, 2, 1.27, 0.578, 0.466},   // long calls: two independent workgroups per unit fill each other's barriers
+    {64, 256, 2, 1, 2.15, 0.972, 0.972},   // half the slices of the first where rows x columns leave units idle
+    {64, 128, 1, 3, 0.31, 0.420, 0.311},   // short K: little to start with
+    {32, 64, 4, 2, 0.65, 0.501, 0.461},    // small Y
+    {32, 128, 2, 2, 0.34, 0.456, 0.383},   // M <= 32
 };
-constexpr double kCall = 4.39, kSlice = 1.30, kSliceMb = 0.40, kPeak = 1.5e9;   // us, us, us per MB, flops per us
+constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374, kPeak = 1.5e9;   // us, us, us per MB, flops per us
 
 struct TilePlan {
     int tile, k_slices;
@@ -441,7 +477,8 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
         const double tiles = (double)((M + s.rows - 1) / s.rows) * (double)((l.n_pad + s.cols - 1) / s.cols);
         const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / kPeak;
         if (tiles * kMaxKSlices > 2e9) continue;
-        for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks; ++k) {
+        // (slices beyond two full rounds only add partial sums)
+        for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || tiles * k <= 2.0 * units * s.per_cu); ++k) {
             const int per = (l.n_kblocks + k - 1) / k;
             const double mb = 4e-6 * (double)k * M * l.n_pad;
             if (k > 1 && ((l.n_kblocks + per - 1) / per != k || M > 65535 || mb * 1e6 > (double)ws_bytes)) continue;
@@ -457,53 +494,275 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
     return best;
 }
 
-// Offsets inside a tile of X and inside the row sets are 32 bits wide, with some steps to spare.
+// ------------------------------------------------------------------------------------------------------------------
+// k_rows: M <= MM rows (MM <= 10).  The three planes of X are the rows of A: 3 M of them, in T tiles of 16, so up to five
+// rows of X cost one matrix instruction where k_matrix would need three.  A workgroup is KW wavefronts with the same 16 B
+// columns, each with every KW-th group of four blocks (256 rows of W): a lane's 16-byte load is one block of one column,
+// and serves eight matrix instructions, so the row sets are read once, 2 bits an entry, with no LDS in between.  A group of X
+// is cut by its wavefront alone and goes through a piece of the LDS of its own, a plane at a time, into fragments that all
+// B tiles of columns use; the next group's loads are under way meanwhile.  The sums of the KW wavefronts meet in the LDS.
+// Bound by the latency of that chain (2.5 us with one group a wavefront, of which launch and first loads are most) and
+// then by spreading and cutting on the vector ALU.  Against the lists, at 50 % non-zeros: M = 1, 4096 x 11008 10.4 -> 5.5 us,
+// M = 8 23.7 -> 7.9 us, M = 4, 16384 x 4096 31 -> 11 us.  Without the next group's loads 6.7, 8.9 and 13.9 us; KW = 16
+// gains 5 % at K = 16384 and loses 2 % at 4096.
+constexpr int kMaxRows = 10;
+constexpr int kRowUnits = 33;   // 16-byte units per staged row of 256 entries (32 + 1: other banks)
+
+template <int MM, int B, int KW>
+__global__ void __launch_bounds__(64 * KW)
+k_rows(const MatrixArgs a)
+{
+    constexpr int T = (3 * MM + 15) / 16, kItems = (MM + 1) / 2;
+    constexpr int kStage = KW * MM * kRowUnits, kSums = KW * B * T * 64;
+    __shared__ uint4v lds[kStage > kSums ? kStage : kSums];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.x * (16 * B), M = a.M, n_groups = (a.n_kblocks + 3) / 4;
+    uint4v *stage = lds + wave * (MM * kRowUnits);
+    const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(a.masks, (size_t)a.n_kblocks * a.n_pad * 16);
+    const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(a.X, (size_t)M * a.K * 4);
+
+    uint4v w_next[B];
+    float4v x0_next[kItems], x1_next[kItems];   // item: four entries of a row and the four 16 further on
+    auto load = [&](int group) {
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const unsigned n = (unsigned)min(n0 + 16 * b + r, a.n_pad - 1);
+            w_next[b] = load16(wbuf, ((unsigned)(4 * group + g) * (unsigned)a.n_pad + n) * 16u);
+        }
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            const int it = lane + 64 * i, m = it >> 5, quad = it & 31;
+            const unsigned k = 256u * group + 64 * (quad >> 3) + 32 * ((quad >> 2) & 1) + 4 * (quad & 3);
+            const unsigned off = m < M ? ((unsigned)m * (unsigned)a.K + k) * 4u : kNowhere;
+            x0_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off));
+            x1_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off + 64u));
+        }
+    };
+
+    float4v acc[B][T];
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[b][t] = float4v{0.f, 0.f, 0.f, 0.f};
+
+    load(wave);
+    // of the column this thread finishes first
+    const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);
+    const int n_first = n0 + 16 * ((int)(threadIdx.x >> 4) % B) + (threadIdx.x & 15);
+    float bias = finish.bias_of(n_first), slope = finish.slope_of(n_first);
+    for (int group = wave; group < n_groups; group += KW) {
+        uint4v w[B];
+        float4v x0[kItems], x1[kItems];
+#pragma unroll
+        for (int b = 0; b < B; ++b) w[b] = w_next[b];
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            x0[i] = x0_next[i] * kScaleUp;
+            x1[i] = x1_next[i] * kScaleUp;
+        }
+        if (group + KW < n_groups) load(group + KW);
+        bf16x8 x[T][8];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) x[t][s] = __builtin_bit_cast(bf16x8, uint4v{0, 0, 0, 0});
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+#pragma unroll
+            for (int i = 0; i < kItems; ++i) {
+                const int it = lane + 64 * i, m = it >> 5, quad = it & 31;
+                uint4v d;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    d[e] = top_halves(x0[i][e], x1[i][e]);
+                    x0[i][e] = below_top(x0[i][e]);
+                    x1[i][e] = below_top(x1[i][e]);
+                }
+                if (m < M) stage[m * kRowUnits + quad] = d;
+            }
+            // the wavefront's own piece of the LDS, and its LDS operations stay in order: no barrier
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int m = 16 * t + r - p * M;   // row 16 t + r of A is row m of this plane
+                if (m >= 0 && m < M)
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) x[t][s] = __builtin_bit_cast(bf16x8, stage[m * kRowUnits + 8 * g + s]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const SignedWord half(w[b][h], w[b][2 + h]);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const bf16x8 bw = half.eight(4 * s);
+#pragma unroll
+                    for (int t = 0; t < T; ++t)
+                        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t][4 * h + s], bw, acc[b][t], 0, 0, 0);
+                }
+            }
+    }
+
+    // sums of the wavefronts, [wave][b][row of A][column]: element e of a fragment is row 4 g + e, column r
+    __syncthreads();
+    float *sums = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sums[(((wave * B + b) * T + t) * 16 + 4 * g + e) * 16 + r] = acc[b][t][e];
+    __syncthreads();
+    for (int o = threadIdx.x; o < 16 * B * M; o += 64 * KW) {
+        const int c = o & 15, b = (o >> 4) % B, m = (o >> 4) / B, n = n0 + 16 * b + c;
+        if (n >= a.N) continue;
+        if (o != (int)threadIdx.x) {
+            bias = finish.bias_of(n);
+            slope = finish.slope_of(n);
+        }
+        float plane[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            plane[p] = 0.f;
+#pragma unroll
+            for (int k = 0; k < KW; ++k) plane[p] += sums[((k * B + b) * T * 16 + p * M + m) * 16 + c];
+        }
+        float v = (plane[0] + (plane[1] + plane[2])) * kScaleDown;
+        if (!finite(v)) v = gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K);
+        a.Y[(size_t)m * a.N + n] = finish(v, bias, slope);
+    }
+}
+
+template <int MM, int B, int KW>
+hipError_t launch_rows_kernel(const MatrixArgs &a, const Call &c)
+{
+    hipError_t e;
+    if ((e = c.record_before()) != hipSuccess) return e;
+    hipLaunchKernelGGL((k_rows<MM, B, KW>), dim3((a.N + 16 * B - 1) / (16 * B)), dim3(64 * KW), 0, c.stream, a);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = c.record_after();
+    return e;
+}
+
+// Shape of a call with M <= 10: eight wavefronts from five groups of 256 rows on, else four; as few tiles of 16 columns per
+// workgroup as leave one workgroup per compute unit (more of the small ones: they fit side by side), because every
+// workgroup cuts X anew.  us: 2.0 .. 2.7 + turns through the groups x (cutting + spreading) (microseconds, measured on
+// M = 1 .. 10, K = 512 .. 16384, N = 512 .. 16384).
+struct RowsPlan {
+    int tiles, waves;
+    double us;
+};
+RowsPlan rows_plan(const tcsc_layout_t &l, int M)
+{
+    const int groups = (l.n_kblocks + 3) / 4, units = compute_units();
+    const double tiles = (double)((l.N + 15) / 16);
+    RowsPlan p;
+    p.waves = groups > 4 ? 8 : 4;
+    const int slots = p.waves == 8 ? units : M <= 5 ? 4 * units : 2 * units;
+    p.tiles = (int)fmin(ceil(tiles / slots), p.waves == 8 ? 4.0 : 2.0);
+    const double rounds = fmax(1.0, tiles / ((double)p.tiles * slots));
+    const double cut = M <= 2 ? 0.45 : M <= 5 ? 0.70 : 1.1, spread = M <= 2 ? 0.35 : M <= 5 ? 0.37 : 0.55;
+    p.us = (p.waves == 4 ? 2.0 : M <= 2 ? 2.5 : 2.7) + ((groups + p.waves - 1) / p.waves) * rounds * (cut + spread * p.tiles);
+    return p;
+}
+
+template <int MM>
+hipError_t pick_rows(const MatrixArgs &a, const MatrixPlan &p, const Call &c)
+{
+    if (p.split == 4) return p.shape == 1 ? launch_rows_kernel<MM, 1, 4>(a, c) : launch_rows_kernel<MM, 2, 4>(a, c);
+    switch (p.shape) {
+    case 1: return launch_rows_kernel<MM, 1, 8>(a, c);
+    case 2: return launch_rows_kernel<MM, 2, 8>(a, c);
+    case 3: return launch_rows_kernel<MM, 3, 8>(a, c);
+    default: return launch_rows_kernel<MM, 4, 8>(a, c);
+    }
+}
+
+hipError_t launch_rows(const MatrixArgs &a, const MatrixPlan &p, const Call &c)
+{
+    if (a.M <= 2) return pick_rows<2>(a, p, c);
+    if (a.M <= 5) return pick_rows<5>(a, p, c);
+    if (a.M <= 8) return pick_rows<8>(a, p, c);
+    return pick_rows<10>(a, p, c);
+}
+
+// Offsets inside a tile of X or Y and inside the row sets are 32 bits wide, with some steps to spare.
 bool offsets_fit(const tcsc_layout_t &l)
 {
-    return l.K <= (1 << 22) && ((long long)l.n_kblocks + 64) * l.n_pad * 16 < (1LL << 32);
+    return l.K <= (1 << 22) && l.N <= (1 << 22) && ((long long)l.n_kblocks + 64) * l.n_pad * 16 < (1LL << 32);
 }
 
 double density(const tcsc_layout_t &l) { return (double)(l.nnz_pos + l.nnz_neg) / ((double)l.K * (double)l.N); }
 
 }  // namespace
 
-// Whether the matrix cores take a call with M > 8 (the lists or the row-set walk being the other choice).  They do unless
-// W is so sparse that those, whose time goes with the number of non-zeros, are ahead:
+// Whether the matrix cores take a call (the lists or the row-set walk being the other choice).  They do unless W is so
+// sparse that those, whose time goes with the number of non-zeros, are ahead:
 //  * M > 64, tall and wide: k_large with 128 columns per workgroup takes 20 us + 0.0281 + 0.464 density us per row of W
 //    and round of its workgroups (measured M = 4096, K = N = 8192: 928 us at 1/16, 2318 us at 1/4; here 1100 us at any
 //    density).  Its other shapes are 1.3 to 5 times slower than this path down to a density of 1/16.
-//  * M <= 64: k_small needs about 4.5 + 0.52 us per 1000 rows of W however few the non-zeros are; it is ahead (up to
-//    12 %, measured on M = 16, K = 15000, N = 600 below 1/8) where a few columns meet a long K.
-bool matrix_wins(const tcsc_layout_t &l, int M, const Call &c)
+//  * 8 < M <= 64: k_small, with a tile of 16 rows, takes 6.1 us, or 9.6 us where K is cut into slices (beyond 1024 rows),
+//    + 0.1 per 1000 rows of W + 0.12 per million entries + 0.8 per million non-zeros, 1.3 and 1.7 times that for 32 and
+//    64 rows (M = 16: 1024 x 4096 at 1/16 6.6 against 7.4 us, 15000 x 600 12.6 against 14.2; from 17 rows on it is behind
+//    everywhere down to 1/16).
+//  * M <= 8: k_decode takes 2.7 + 0.3 M + (0.17 + 0.08 M) us per million non-zeros for one or two rows, 1.6 + 0.67 M +
+//    (0.22 + 0.08 M) for more, and 2 us for each further time that X fills the LDS (less than measured wherever K is
+//    long, so that a tie goes to the lists).  It stays ahead
+//    for one or two rows at 1/8 and below (M = 1, 16384 x 4096: 5.1 against 9.1 us at 1/8; at 1/4 8.8 against 9.1, at 1/2
+//    14.1 against 9.1) and for a few columns over a long K (M = 1, 15000 x 600 at 1/4: 5.0 against 7.6).
+MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
 {
-    if (!offsets_fit(l)) return false;
-    const TilePlan p = choose_tile(l, M, c.ws_bytes);
-    if (p.tile < 0) return false;
-    const double d = density(l);
-    if (M > 64) {
-        if (l.n_pad % 128 != 0) return true;
-        const double groups = ceil(M / 256.0) * (l.n_pad / 128);
-        return p.us < 20.0 + ceil(groups / (2.0 * compute_units())) * l.K * (0.0281 + 0.464 * d);
+    MatrixPlan none{};
+    if (!offsets_fit(l)) return none;
+    const double d = density(l), entries = 1e-6 * (double)l.K * (double)l.N;
+    RowsPlan r{};
+    if (M <= kMaxRows) {
+        r = rows_plan(l, M);
+        if (M <= 8) {
+            const double lists = M <= 2 ? 2.7 + 0.3 * M + entries * d * (0.17 + 0.08 * M)
+                                        : 1.6 + 0.67 * M + 2.0 * floor(M * (double)l.K / 38400.0) +
+                                              entries * d * (0.22 + 0.08 * M);
+            if (r.us >= lists) return none;
+            return MatrixPlan{true, r.tiles, r.waves};
+        }
     }
-    return d >= 0.13 || l.N >= 2048 || p.us < 4.5 + 0.52e-3 * l.K;
+    const TilePlan p = choose_tile(l, M, c.ws_bytes);
+    const bool rows = M <= kMaxRows && (p.tile < 0 || r.us < p.us);
+    if (!rows && p.tile < 0) return none;
+    const double us = rows ? r.us : p.us;
+    double other;
+    if (M <= 64) {
+        other = (M <= 16 ? 1.0 : M <= 32 ? 1.3 : 1.7) *
+                ((l.K <= 1024 ? 6.1 : 9.6) + 0.1e-3 * l.K + entries * (0.12 + 0.8 * d));
+    } else {
+        if (l.n_pad % 128 != 0) return MatrixPlan{false, p.tile, p.k_slices};
+        const double groups = ceil(M / 256.0) * (l.n_pad / 128);
+        other = 20.0 + ceil(groups / (2.0 * compute_units())) * l.K * (0.0281 + 0.464 * d);
+    }
+    if (us >= other) return none;
+    return rows ? MatrixPlan{true, r.tiles, r.waves} : MatrixPlan{false, p.tile, p.k_slices};
 }
 
-hipError_t launch_matrix(const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
+hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
 {
     const tcsc_layout_t &l = t->layout;
-    const TilePlan p = choose_tile(l, M, c.ws_bytes);
-    if (p.tile < 0) return hipErrorInvalidValue;
-    const TileShape &s = kTiles[p.tile];
     MatrixArgs a{};
     a.X = X; a.masks = reinterpret_cast<const uint4v *>(device_view(t).masks); a.b = b; a.Y = Y;
     a.alpha = c.act.alpha; a.alpha_stride = c.act.alpha_stride;
     a.partials = reinterpret_cast<float *>(c.ws);
     a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_kblocks;
+    if (p.rows) return launch_rows(a, p, c);
+    const TileShape &s = kTiles[p.shape];
     a.n_tiles = (l.n_pad + s.cols - 1) / s.cols;
-    a.k_slices = p.k_slices;
-    a.kb_per_slice = (l.n_kblocks + p.k_slices - 1) / p.k_slices;
+    a.k_slices = p.split;
+    a.kb_per_slice = (l.n_kblocks + p.split - 1) / p.split;
     const int m_tiles = (M + s.rows - 1) / s.rows;
-    switch (p.tile) {
+    switch (p.shape) {
     case 0: return launch_tiles<1, 1, 4, 2, 2>(a, m_tiles, c);
     case 1: return launch_tiles<2, 1, 4, 2, 2>(a, m_tiles, c);
     case 2: return launch_tiles<1, 1, 4, 2, 1>(a, m_tiles, c);

@@ -42,6 +42,27 @@ def test_tile_edges(M, K, N):
     assert np.all(np.abs(Yo.astype(np.float64) - Y) <= 1.1e-5 * A)
 
 
+# rows of X around every instance of the small kernel (2, 5, 8, 10); groups of 256 rows of W for four and for eight
+# wavefronts, fewer and more than these, not a multiple of 4; one to four tiles of 16 columns per workgroup, and more
+@pytest.mark.parametrize("M", range(1, 11))
+@pytest.mark.parametrize("K,N", [(1, 1), (65, 33), (1023, 17), (1029, 40), (2307, 31), (4097, 16), (300, 16400), (1500, 5000),
+                                 (1300, 9000), (1280, 13000), (1281, 20000)])
+def test_few_rows(M, K, N):
+    W, X, b = si.make_inputs(M, K, N, 0.75, "normal", seed=710 + M + K)
+    ot = oracle.tcsc_build(W)
+    Yd, A, _ = oracle.tstgemm(X, ot, b)
+    # the row sets and (M > 8) what else the call asks for; then the lists alone
+    t = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_ROWSETS | tg.FORM_CUTS | tg.FORM_WORKSPACE)
+    Y, _ = gpu_tstgemm(W, X, b, handle=t)
+    tight(Y, Yd, A, f"{M}x{K}x{N}")
+    Xi = np.random.default_rng(712).integers(-8, 9, (M, K)).astype(np.float32)
+    Yi, _ = gpu_tstgemm(W, Xi, b, handle=t)
+    assert np.array_equal(Yi, oracle.tstgemm(Xi, ot, b)[0].astype(np.float32))
+    if M <= 8:
+        Yo, _ = gpu_tstgemm(W, X, b, handle=tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_LISTS16))
+        assert_close(Yo, Yd, A, f"{M}x{K}x{N} lists")
+
+
 def _same(Y, Yd):
     """Equal in what is not finite; else within the tolerance of the finite part of the sum."""
     return np.array_equal(np.isnan(Y), np.isnan(Yd)) and np.array_equal(np.isposinf(Y), np.isposinf(Yd)) \
