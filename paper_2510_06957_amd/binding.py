@@ -210,6 +210,17 @@ def _stream_ptr(stream):
     return s.cuda_stream
 
 
+def _launch_stream(stream, device: int) -> int:
+    """The HIP stream of a launch on `device`, which is the current one: torch's current stream unless one is given.  The raw
+    handle comes from torch as it is; torch.cuda.current_stream() builds a Stream object around it first (2.9 us of the
+    10.1 us that a short call took)."""
+    if stream is not None:
+        return stream.cuda_stream
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream(device).cuda_stream if raw is None else raw(device)
+
+
 def tcsc_select_forms(t: Tcsc, forms: int):
     """Which device forms the next tcsc_upload() builds (FORM_* bits; a new handle has FORM_ALL)."""
     _check(_load().tcsc_select_forms(t.handle, int(forms)), "tcsc_select_forms")
@@ -241,28 +252,28 @@ def tcsc_upload(t: Tcsc, device="cuda:0", stream=None, forms=None) -> Tcsc:
 
 
 def _gemm_args(X, t: Tcsc, b, Y):
-    """Checks shared by the tstgemm* wrappers; returns (M, K, N, b_ptr, Y)."""
+    """Checks shared by the tstgemm* wrappers; returns (M, K, N, b_ptr, Y, device index)."""
     import torch
     f32 = torch.float32
     if not (X.is_cuda and X.dtype == f32 and X.dim() == 2 and X.is_contiguous()):
         raise ValueError("X must be a contiguous float32 CUDA matrix")
     M, K = X.shape
     N = t.N
-    dev = X.device.index
+    dev = X.get_device()
     if dev != getattr(t, "device_index", dev) or dev != torch.cuda.current_device():
         raise ValueError("X, the uploaded handle and the current device must be the same GPU")
     if b is None:
         b_ptr = None
-    elif b.is_cuda and b.dtype == f32 and b.is_contiguous() and b.numel() == N and b.device.index == dev:
+    elif b.is_cuda and b.dtype == f32 and b.is_contiguous() and b.numel() == N and b.get_device() == dev:
         b_ptr = b.data_ptr()
     else:
         raise ValueError("b must be a contiguous float32 CUDA vector of length N on X's device")
     if Y is None:
         Y = torch.empty((M, N), dtype=f32, device=X.device)
     elif not (Y.is_cuda and Y.dtype == f32 and Y.dim() == 2 and Y.shape[0] == M and Y.shape[1] == N
-              and Y.is_contiguous() and Y.device.index == dev):
+              and Y.is_contiguous() and Y.get_device() == dev):
         raise ValueError("Y must be a contiguous float32 CUDA matrix of shape [M, N] on X's device")
-    return M, K, N, b_ptr, Y
+    return M, K, N, b_ptr, Y, dev
 
 
 def _opts(X, N, encoding=0, alpha=None, workspace=None, cols_per_wave=0, k_slices=0, slab_tiles=0, wide_lists=False,
@@ -301,27 +312,27 @@ def tstgemm(X, t: Tcsc, b=None, Y=None, stream=None, alpha=None, **options):
 
     Launches on `stream` (default: torch's current stream) of the current device, which must be the device the
     handle was uploaded to and the one holding X, b, alpha and Y."""
-    M, K, N, b_ptr, Y = _gemm_args(X, t, b, Y)
+    M, K, N, b_ptr, Y, dev = _gemm_args(X, t, b, Y)
     o = _opts(X, N, 0, alpha, **options)
     if o is None:
-        rc = _load().tstgemm(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _stream_ptr(stream))
+        rc = _load().tstgemm(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _launch_stream(stream, dev))
     elif not options:
         rc = _load().tstgemm_prelu(X.data_ptr(), t.handle, b_ptr, o.alpha, o.alpha_count, Y.data_ptr(), M, K, N,
-                                   _stream_ptr(stream))
+                                   _launch_stream(stream, dev))
     else:
-        rc = _load().tstgemm_ex(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, ctypes.byref(o), _stream_ptr(stream))
+        rc = _load().tstgemm_ex(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, ctypes.byref(o), _launch_stream(stream, dev))
     if rc != 0:
         raise TstgemmError(rc, "tstgemm")
     return Y
 
 
 def _variant(name, encoding, X, t, b, Y, stream, options):
-    M, K, N, b_ptr, Y = _gemm_args(X, t, b, Y)
+    M, K, N, b_ptr, Y, dev = _gemm_args(X, t, b, Y)
     if options:
         o = _opts(X, N, encoding, None, **options)
-        rc = _load().tstgemm_ex(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, ctypes.byref(o), _stream_ptr(stream))
+        rc = _load().tstgemm_ex(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, ctypes.byref(o), _launch_stream(stream, dev))
     else:
-        rc = getattr(_load(), name)(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _stream_ptr(stream))
+        rc = getattr(_load(), name)(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _launch_stream(stream, dev))
     if rc != 0:
         raise TstgemmError(rc, name)
     return Y
@@ -335,8 +346,8 @@ def tstgemm_noalloc(X, t: Tcsc, b, Y, stream=None):
     wrapper allocates nothing either."""
     if Y is None:
         raise ValueError("tstgemm_noalloc needs an output tensor")
-    M, K, N, b_ptr, Y = _gemm_args(X, t, b, Y)
-    rc = _load().tstgemm_noalloc(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _stream_ptr(stream))
+    M, K, N, b_ptr, Y, dev = _gemm_args(X, t, b, Y)
+    rc = _load().tstgemm_noalloc(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _launch_stream(stream, dev))
     if rc != 0:
         raise TstgemmError(rc, "tstgemm_noalloc")
     return Y

@@ -139,3 +139,29 @@ def test_without_the_row_sets_or_with_little_scratch(M):
         with pytest.raises(tg.TstgemmError) as err:
             tg.tstgemm(Xd, t, bd, workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
         assert err.value.code == -8
+
+
+def test_calls_follow_torchs_current_stream():
+    """Without a stream argument a call goes to torch's current stream, whichever that is: behind a long piece of work on a
+    side stream it reads what that work writes, and torch's own work behind it reads its result."""
+    import torch
+    M, K, N = 4, 512, 256
+    W, X, b = si.make_inputs(M, K, N, 0.5, "int8", seed=780)
+    Yd, _, _ = oracle.tstgemm(X, oracle.tcsc_build(W), b)
+    t = tg.tcsc_upload(tg.tcsc_build(W))
+    Xh, bd = torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda()
+    big = torch.randn(4096, 4096, device="cuda")
+    Xd = torch.zeros_like(Xh)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for _ in range(10):
+            big = big @ big * 1e-3
+        Xd.copy_(Xh)
+        Y = tg.tstgemm(Xd, t, bd)
+        twice = Y * 2
+    torch.cuda.synchronize()
+    assert np.array_equal(twice.cpu().numpy(), 2 * Yd.astype(np.float32))
+    Y2 = tg.tstgemm(Xd, t, bd, stream=side)
+    side.synchronize()
+    assert torch.equal(Y2, Y)
