@@ -59,7 +59,7 @@ def takes_matrix_cores(M, K, N, n_pad, density, cus):
         if n_pad % 128:
             return True
         rounds = -(-(-(-M // 256) * (n_pad // 128)) // (2 * cus))
-        return 6.0 * (-(-M // 64) * 64) * n_pad * K / 1.5e9 + 3.36 < 20.0 + rounds * K * (0.0281 + 0.464 * density)
+        return 6.0 * (-(-M // 64) * 64) * n_pad * K / 1.61e9 + 3.36 < 20.0 + rounds * K * (0.0281 + 0.464 * density)
     return True                 # (and for M <= 64 wherever a column list is not extremely short)
 
 

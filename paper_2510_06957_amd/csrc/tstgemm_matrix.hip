@@ -136,8 +136,9 @@ struct MatrixArgs {
 // has 6 RF CF matrix instructions of 32 cycles; the cuts, the spreading and the LDS traffic are dealt over their six
 // stages, each ended by a scheduling barrier (without the stages, and with loads whose number the compiler could not
 // count, M = 4096, K = N = 8192 took 1.20 ms in place of 1.10).
-// Bound: long calls by the power limit (M = 4096, K = N = 8192: 1.10 ms, i.e. 1.50 PFLOP/s of bf16 products at about
-// 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here), short ones by the start of the first loads, the
+// Bound: long calls by the power limit (M = 4096, K = N = 8192: 1.04 ms, i.e. 1.59 PFLOP/s of bf16 products, the clock down
+// to about 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here; without any cutting and spreading, which
+// gives wrong sums, it would take 0.99 ms), short ones by the start of the first loads, the
 // sums at the end and the second launch where K is sliced (M = 256, K = N = 4096: 28 us against 89).
 // Rows beyond M and rows of W beyond K: X reads as zero, or as the next row of X where the weights are zero.
 template <int WK, int WM, int WN, int RF, int CF>
@@ -448,21 +449,23 @@ hipError_t launch_tiles(const MatrixArgs &a, int m_tiles, const Call &c)
 // Tile and K slices of a call: the combination whose estimated time is least.  A workgroup takes `fixed` us and `step`
 // us for each of its steps of 32 rows of W while its compute unit has time to spare, `work` us when the unit is full
 // (per_cu workgroups at a time); a call takes kCall us more, slices kSlice us and 0.4 us per MB of partial sums; and no
-// call is faster than the matrix cores at the power limit (1.5 PFLOP/s).  Fitted to 13 tiles x 6 slice counts on 77
-// shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among these five is 2 % slower than the best of all on
+// call is faster than `peak` operations per us, what the tile reaches on long calls under the power limit (64 x 512 against
+// 64 x 256: M = 4096, K = N = 8192 1073 -> 1038 us, 2048 x 4096 x 4096 138 -> 132, 1024 x 2048 x 8192 74 -> 70).  Fitted to 13 tiles x 6 slice counts on 77
+// shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five is 2 % slower than the best of all on
 // average, 16 % at worst.
 struct TileShape {
     int rows, cols, groups, per_cu;
-    double fixed, step, work;
+    double fixed, step, work, peak;
 };
 constexpr TileShape kTiles[] = {
-    {64, 256, 1, 2, 1.27, 0.578, 0.466},   // long calls: two independent workgroups per unit fill each other's barriers
-    {64, 256, 2, 1, 2.15, 0.972, 0.972},   // half the slices of the first where rows x columns leave units idle
-    {64, 128, 1, 3, 0.31, 0.420, 0.311},   // short K: little to start with
-    {32, 64, 4, 2, 0.65, 0.501, 0.461},    // small Y
-    {32, 128, 2, 2, 0.34, 0.456, 0.383},   // M <= 32
+    {64, 512, 1, 1, 1.90, 0.900, 0.900, 1.61e9},   // long and wide calls: X is cut half as often as by the next
+    {64, 256, 1, 2, 1.27, 0.578, 0.466, 1.55e9},   // two independent workgroups per unit fill each other's barriers
+    {64, 256, 2, 1, 2.15, 0.972, 0.972, 1.50e9},   // half the slices of that where rows x columns leave units idle
+    {64, 128, 1, 3, 0.31, 0.420, 0.311, 1.45e9},   // short K: little to start with
+    {32, 64, 4, 2, 0.65, 0.501, 0.461, 1.30e9},    // small Y
+    {32, 128, 2, 2, 0.34, 0.456, 0.383, 1.40e9},   // M <= 32
 };
-constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374, kPeak = 1.5e9;   // us, us, us per MB, flops per us
+constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
 
 struct TilePlan {
     int tile, k_slices;
@@ -475,7 +478,7 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const TileShape &s = kTiles[i];
         const double tiles = (double)((M + s.rows - 1) / s.rows) * (double)((l.n_pad + s.cols - 1) / s.cols);
-        const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / kPeak;
+        const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
         if (tiles * kMaxKSlices > 2e9) continue;
         // (slices beyond two full rounds only add partial sums)
         for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || tiles * k <= 2.0 * units * s.per_cu); ++k) {
@@ -704,7 +707,7 @@ double density(const tcsc_layout_t &l) { return (double)(l.nnz_pos + l.nnz_neg) 
 // Whether the matrix cores take a call (the lists or the row-set walk being the other choice).  They do unless W is so
 // sparse that those, whose time goes with the number of non-zeros, are ahead:
 //  * M > 64, tall and wide: k_large with 128 columns per workgroup takes 20 us + 0.0281 + 0.464 density us per row of W
-//    and round of its workgroups (measured M = 4096, K = N = 8192: 928 us at 1/16, 2318 us at 1/4; here 1100 us at any
+//    and round of its workgroups (measured M = 4096, K = N = 8192: 928 us at 1/16, 2318 us at 1/4; here 1040 us at any
 //    density).  Its other shapes are 1.3 to 5 times slower than this path down to a density of 1/16.
 //  * 8 < M <= 64: k_small, with a tile of 16 rows, takes 6.1 us, or 9.6 us where K is cut into slices (beyond 1024 rows),
 //    + 0.1 per 1000 rows of W + 0.12 per million entries + 0.8 per million non-zeros, 1.3 and 1.7 times that for 32 and
@@ -763,10 +766,11 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     a.kb_per_slice = (l.n_kblocks + p.split - 1) / p.split;
     const int m_tiles = (M + s.rows - 1) / s.rows;
     switch (p.shape) {
-    case 0: return launch_tiles<1, 1, 4, 2, 2>(a, m_tiles, c);
-    case 1: return launch_tiles<2, 1, 4, 2, 2>(a, m_tiles, c);
-    case 2: return launch_tiles<1, 1, 4, 2, 1>(a, m_tiles, c);
-    case 3: return launch_tiles<4, 1, 2, 1, 1>(a, m_tiles, c);
+    case 0: return launch_tiles<1, 1, 8, 2, 2>(a, m_tiles, c);
+    case 1: return launch_tiles<1, 1, 4, 2, 2>(a, m_tiles, c);
+    case 2: return launch_tiles<2, 1, 4, 2, 2>(a, m_tiles, c);
+    case 3: return launch_tiles<1, 1, 4, 2, 1>(a, m_tiles, c);
+    case 4: return launch_tiles<4, 1, 2, 1, 1>(a, m_tiles, c);
     default: return launch_tiles<2, 1, 4, 1, 1>(a, m_tiles, c);
     }
 }
