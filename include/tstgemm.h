@@ -301,9 +301,9 @@ int tstgemm_signed(const float *X, const tcsc_t *t, const float *b, float *Y, in
 
 /*
  * Y = X W + b for M <= 8 from the value-compression form in the device buffer: every byte is decoded
- * through a 243-entry table (as in the paper) into five weights, and ALL entries take part in the sum,
- * the zeros as x * 0.  Unlike every other entry point this one therefore reads X entries whose weight is
- * zero: X must be finite.  Products with -1, 0, +1 are exact, so the rounding is that of the additions,
+ * through a 243-entry table (as in the paper) into five weights, and ALL entries may take part in the sum,
+ * the zeros as x * 0.  Unlike every other entry point this one may therefore let X entries whose weight is
+ * zero reach Y: X must be finite.  Products with -1, 0, +1 are exact, so the rounding is that of the additions,
  * in an order fixed by (M, K, N) and the options.  Arguments otherwise as for tstgemm() (it may
  * use the handle's workspace, so calls on one handle must be ordered).  Errors: as tstgemm(), and EINVAL
  * for M > 8.

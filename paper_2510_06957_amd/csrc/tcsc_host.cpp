@@ -425,7 +425,8 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
         e = tst::launch_decode_signed(X, t, b, Y, M, c);
     } else if (o.encoding == 2) {
         if (!(l.forms & TCSC_FORM_PACKED)) return TSTGEMM_ENOFORM;
-        e = tst::launch_packed(X, t, b, Y, M, c);
+        e = o.k_slices == 0 && tst::packed_rows_win(l, M) ? tst::launch_packed_rows(X, t, b, Y, M, c)
+                                                          : tst::launch_packed(X, t, b, Y, M, c);
     } else if (tst::decode_supported(M)) {
         const tst::MatrixPlan p = row_sets && !c.decode_wide_lists ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
         e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_decode(X, t, b, Y, M, c);

@@ -170,6 +170,8 @@ struct MatrixPlan {
 };
 MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c);
 hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);
+bool packed_rows_win(const tcsc_layout_t &l, int M);   // M <= 8 from the base-3 codes: on the matrix cores?
+hipError_t launch_packed_rows(const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);
 // tstgemm_decode.hip -- small-M kernel (M <= 8; X in the LDS, in chunks of K if need be).
 bool decode_supported(int M);
 hipError_t launch_decode(const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);

@@ -508,16 +508,53 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
 // then by spreading and cutting on the vector ALU.  Against the lists, at 50 % non-zeros: M = 1, 4096 x 11008 10.4 -> 5.5 us,
 // M = 8 23.7 -> 7.9 us, M = 4, 16384 x 4096 31 -> 11 us.  Without the next group's loads 6.7, 8.9 and 13.9 us; KW = 16
 // gains 5 % at K = 16384 and loses 2 % at 4096.
+//
+// PACKED: W from the base-3 codes (a.masks, a.n_kblocks: 16-byte pieces of 80 rows, [piece][n_pad]).  A table in the LDS
+// gives the five weights of a code, sign and non-zero bit side by side; the words of codes j and j + 8 make dwords for
+// rows 5 j + i and 40 more, again one shift and one AND each.  A group is 320 rows and ten matrix instructions a tile.
+// Against the kernel that multiplies on the vector ALU, 4096 x 11008: M = 2 9.3 -> 8.4 us, M = 8 21.5 -> 10.6 us; 4096 x 4096: M = 1 7.3 -> 5.4 us,
+// M = 5 14.8 -> 6.8.  Sixteen copies of the table, so that few lanes meet in a bank, cost more to fill than they saved.
 constexpr int kMaxRows = 10;
-constexpr int kRowUnits = 33;   // 16-byte units per staged row of 256 entries (32 + 1: other banks)
 
-template <int MM, int B, int KW>
+// The five weights of a code (81 d0 + 27 d1 + 9 d2 + 3 d3 + d4; digit 1: +1, 2: -1): bits 2 i (non-zero) and 2 i + 1 (sign).
+__device__ __forceinline__ unsigned weights_of_code(int code)
+{
+    unsigned bits = 0;
+#pragma unroll
+    for (int i = 4; i >= 0; --i) {
+        const unsigned digit = code % 3;
+        code /= 3;
+        bits |= (digit == 0 ? 0u : digit == 1 ? 1u : 3u) << (2 * i);
+    }
+    return bits;
+}
+
+// X W for one output from X and the codes, as gather_output().
+__device__ __forceinline__ float gather_packed(const float *__restrict__ X, const uint4v *__restrict__ codes, int n_pad,
+                                               int m, int n, int K)
+{
+    float s = 0.f;
+    const float *x = X + (size_t)m * K;
+    const unsigned char *bytes = reinterpret_cast<const unsigned char *>(codes);
+    for (int group = 0; 5 * group < K; ++group) {
+        const unsigned w = weights_of_code(bytes[((size_t)(group / 16) * n_pad + n) * 16 + group % 16]);
+        for (int i = 0; i < 5 && 5 * group + i < K; ++i)
+            if (w >> (2 * i) & 1) s += (w >> (2 * i) & 2) ? -x[5 * group + i] : x[5 * group + i];
+    }
+    return s;
+}
+
+template <int MM, int B, int KW, bool PACKED>
 __global__ void __launch_bounds__(64 * KW)
 k_rows(const MatrixArgs a)
 {
-    constexpr int T = (3 * MM + 15) / 16, kItems = (MM + 1) / 2;
+    constexpr int kSteps = PACKED ? 10 : 8;                  // matrix instructions per block of W and tile
+    constexpr int kUnits = 4 * kSteps, kRowUnits = kUnits + 1;   // 16-byte units per staged row of a group (+ 1: other banks)
+    constexpr int kBlockRows = 8 * kSteps, kPartner = PACKED ? 40 : 16;
+    constexpr int T = (3 * MM + 15) / 16, kItems = (MM * kUnits + 63) / 64;
     constexpr int kStage = KW * MM * kRowUnits, kSums = KW * B * T * 64;
     __shared__ uint4v lds[kStage > kSums ? kStage : kSums];
+    __shared__ unsigned table[PACKED ? 256 : 1];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
@@ -527,7 +564,7 @@ k_rows(const MatrixArgs a)
     const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(a.X, (size_t)M * a.K * 4);
 
     uint4v w_next[B];
-    float4v x0_next[kItems], x1_next[kItems];   // item: four entries of a row and the four 16 further on
+    float4v x0_next[kItems], x1_next[kItems];   // item: four entries of a row and the four kPartner further on
     auto load = [&](int group) {
 #pragma unroll
         for (int b = 0; b < B; ++b) {
@@ -536,11 +573,12 @@ k_rows(const MatrixArgs a)
         }
 #pragma unroll
         for (int i = 0; i < kItems; ++i) {
-            const int it = lane + 64 * i, m = it >> 5, quad = it & 31;
-            const unsigned k = 256u * group + 64 * (quad >> 3) + 32 * ((quad >> 2) & 1) + 4 * (quad & 3);
+            const int it = lane + 64 * i, m = it / kUnits, unit = it % kUnits, step = unit % kSteps;
+            const unsigned k = (unsigned)(kBlockRows * (4 * group + unit / kSteps)) +
+                               (PACKED ? 4 * step : 32 * (step >> 2) + 4 * (step & 3));
             const unsigned off = m < M ? ((unsigned)m * (unsigned)a.K + k) * 4u : kNowhere;
             x0_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off));
-            x1_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off + 64u));
+            x1_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off + 4u * kPartner));
         }
     };
 
@@ -551,6 +589,10 @@ k_rows(const MatrixArgs a)
         for (int t = 0; t < T; ++t) acc[b][t] = float4v{0.f, 0.f, 0.f, 0.f};
 
     load(wave);
+    if constexpr (PACKED) {
+        for (int i = threadIdx.x; i < 256; i += 64 * KW) table[i] = weights_of_code(i);
+        __syncthreads();
+    }
     // of the column this thread finishes first
     const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);
     const int n_first = n0 + 16 * ((int)(threadIdx.x >> 4) % B) + (threadIdx.x & 15);
@@ -566,16 +608,16 @@ k_rows(const MatrixArgs a)
             x1[i] = x1_next[i] * kScaleUp;
         }
         if (group + KW < n_groups) load(group + KW);
-        bf16x8 x[T][8];
+        bf16x8 x[T][kSteps];
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
-            for (int s = 0; s < 8; ++s) x[t][s] = __builtin_bit_cast(bf16x8, uint4v{0, 0, 0, 0});
+            for (int s = 0; s < kSteps; ++s) x[t][s] = __builtin_bit_cast(bf16x8, uint4v{0, 0, 0, 0});
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
 #pragma unroll
             for (int i = 0; i < kItems; ++i) {
-                const int it = lane + 64 * i, m = it >> 5, quad = it & 31;
+                const int it = lane + 64 * i, m = it / kUnits, unit = it % kUnits;
                 uint4v d;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -583,7 +625,7 @@ k_rows(const MatrixArgs a)
                     x0[i][e] = below_top(x0[i][e]);
                     x1[i][e] = below_top(x1[i][e]);
                 }
-                if (m < M) stage[m * kRowUnits + quad] = d;
+                if (m < M) stage[m * kRowUnits + unit] = d;
             }
             // the wavefront's own piece of the LDS, and its LDS operations stay in order: no barrier
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -592,23 +634,40 @@ k_rows(const MatrixArgs a)
                 const int m = 16 * t + r - p * M;   // row 16 t + r of A is row m of this plane
                 if (m >= 0 && m < M)
 #pragma unroll
-                    for (int s = 0; s < 8; ++s) x[t][s] = __builtin_bit_cast(bf16x8, stage[m * kRowUnits + 8 * g + s]);
+                    for (int s = 0; s < kSteps; ++s)
+                        x[t][s] = __builtin_bit_cast(bf16x8, stage[m * kRowUnits + kSteps * g + s]);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
 #pragma unroll
-        for (int b = 0; b < B; ++b)
+        for (int b = 0; b < B; ++b) {
+            auto multiply = [&](int step, bf16x8 bw) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const SignedWord half(w[b][h], w[b][2 + h]);
+                for (int t = 0; t < T; ++t)
+                    acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t][step], bw, acc[b][t], 0, 0, 0);
+            };
+            if constexpr (PACKED) {
+                unsigned pair[8];
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const bf16x8 bw = half.eight(4 * s);
+                for (int j = 0; j < 8; ++j)
+                    pair[j] = table[w[b][j / 4] >> (8 * (j % 4)) & 255u] | table[w[b][2 + j / 4] >> (8 * (j % 4)) & 255u] << 16;
 #pragma unroll
-                    for (int t = 0; t < T; ++t)
-                        acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t][4 * h + s], bw, acc[b][t], 0, 0, 0);
+                for (int step = 0; step < kSteps; ++step) {
+                    uint4v d;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        d[e] = pair[(4 * step + e) / 5] << (14 - 2 * ((4 * step + e) % 5)) & 0xC000C000u;
+                    multiply(step, __builtin_bit_cast(bf16x8, d));
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const SignedWord half(w[b][h], w[b][2 + h]);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) multiply(4 * h + s, half.eight(4 * s));
                 }
             }
+        }
     }
 
     // sums of the wavefronts, [wave][b][row of A][column]: element e of a fragment is row 4 g + e, column r
@@ -636,17 +695,19 @@ k_rows(const MatrixArgs a)
             for (int k = 0; k < KW; ++k) plane[p] += sums[((k * B + b) * T * 16 + p * M + m) * 16 + c];
         }
         float v = (plane[0] + (plane[1] + plane[2])) * kScaleDown;
-        if (!finite(v)) v = gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K);
+        if (!finite(v))
+            v = PACKED ? gather_packed(a.X, a.masks, a.n_pad, m, n, a.K)
+                       : gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K);
         a.Y[(size_t)m * a.N + n] = finish(v, bias, slope);
     }
 }
 
-template <int MM, int B, int KW>
+template <int MM, int B, int KW, bool PACKED>
 hipError_t launch_rows_kernel(const MatrixArgs &a, const Call &c)
 {
     hipError_t e;
     if ((e = c.record_before()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rows<MM, B, KW>), dim3((a.N + 16 * B - 1) / (16 * B)), dim3(64 * KW), 0, c.stream, a);
+    hipLaunchKernelGGL((k_rows<MM, B, KW, PACKED>), dim3((a.N + 16 * B - 1) / (16 * B)), dim3(64 * KW), 0, c.stream, a);
     e = hipGetLastError();
     if (e == hipSuccess) e = c.record_after();
     return e;
@@ -660,38 +721,47 @@ struct RowsPlan {
     int tiles, waves;
     double us;
 };
-RowsPlan rows_plan(const tcsc_layout_t &l, int M)
+RowsPlan rows_plan(const tcsc_layout_t &l, int M, bool packed)
 {
-    const int groups = (l.n_kblocks + 3) / 4, units = compute_units();
+    const int blocks = packed ? l.n_chunks5 : l.n_kblocks, groups = (blocks + 3) / 4, units = compute_units();
     const double tiles = (double)((l.N + 15) / 16);
     RowsPlan p;
     p.waves = groups > 4 ? 8 : 4;
-    const int slots = p.waves == 8 ? units : M <= 5 ? 4 * units : 2 * units;
+    const int slots = p.waves == 8 ? units : M <= 5 && !packed ? 4 * units : 2 * units;
     p.tiles = (int)fmin(ceil(tiles / slots), p.waves == 8 ? 4.0 : 2.0);
     const double rounds = fmax(1.0, tiles / ((double)p.tiles * slots));
-    const double cut = M <= 2 ? 0.45 : M <= 5 ? 0.70 : 1.1, spread = M <= 2 ? 0.35 : M <= 5 ? 0.37 : 0.55;
-    p.us = (p.waves == 4 ? 2.0 : M <= 2 ? 2.5 : 2.7) + ((groups + p.waves - 1) / p.waves) * rounds * (cut + spread * p.tiles);
+    double start = p.waves == 4 ? 2.0 : M <= 2 ? 2.5 : 2.7;
+    double cut = M <= 2 ? 0.45 : M <= 5 ? 0.70 : 1.1, spread = M <= 2 ? 0.35 : M <= 5 ? 0.37 : 0.55;
+    if (packed) {
+        start = p.waves == 4 ? 2.2 : M <= 5 ? 2.9 : 3.2;
+        cut = M <= 2 ? 0.48 : M <= 5 ? 1.0 : 1.35;
+        spread = 0.70;
+    }
+    p.us = start + ((groups + p.waves - 1) / p.waves) * rounds * (cut + spread * p.tiles);
     return p;
 }
 
-template <int MM>
+template <int MM, bool PACKED>
 hipError_t pick_rows(const MatrixArgs &a, const MatrixPlan &p, const Call &c)
 {
-    if (p.split == 4) return p.shape == 1 ? launch_rows_kernel<MM, 1, 4>(a, c) : launch_rows_kernel<MM, 2, 4>(a, c);
+    if (p.split == 4)
+        return p.shape == 1 ? launch_rows_kernel<MM, 1, 4, PACKED>(a, c) : launch_rows_kernel<MM, 2, 4, PACKED>(a, c);
     switch (p.shape) {
-    case 1: return launch_rows_kernel<MM, 1, 8>(a, c);
-    case 2: return launch_rows_kernel<MM, 2, 8>(a, c);
-    case 3: return launch_rows_kernel<MM, 3, 8>(a, c);
-    default: return launch_rows_kernel<MM, 4, 8>(a, c);
+    case 1: return launch_rows_kernel<MM, 1, 8, PACKED>(a, c);
+    case 2: return launch_rows_kernel<MM, 2, 8, PACKED>(a, c);
+    case 3: return launch_rows_kernel<MM, 3, 8, PACKED>(a, c);
+    default: return launch_rows_kernel<MM, 4, 8, PACKED>(a, c);
     }
 }
 
+template <bool PACKED>
 hipError_t launch_rows(const MatrixArgs &a, const MatrixPlan &p, const Call &c)
 {
-    if (a.M <= 2) return pick_rows<2>(a, p, c);
-    if (a.M <= 5) return pick_rows<5>(a, p, c);
-    if (a.M <= 8) return pick_rows<8>(a, p, c);
-    return pick_rows<10>(a, p, c);
+    if (a.M <= 2) return pick_rows<2, PACKED>(a, p, c);
+    if (a.M <= 5) return pick_rows<5, PACKED>(a, p, c);
+    if (a.M <= 8) return pick_rows<8, PACKED>(a, p, c);
+    if constexpr (PACKED) return hipErrorInvalidValue;
+    else return pick_rows<10, false>(a, p, c);
 }
 
 // Offsets inside a tile of X or Y and inside the row sets are 32 bits wide, with some steps to spare.
@@ -725,7 +795,7 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
     const double d = density(l), entries = 1e-6 * (double)l.K * (double)l.N;
     RowsPlan r{};
     if (M <= kMaxRows) {
-        r = rows_plan(l, M);
+        r = rows_plan(l, M, false);
         if (M <= 8) {
             const double lists = M <= 2 ? 2.7 + 0.3 * M + entries * d * (0.17 + 0.08 * M)
                                         : 1.6 + 0.67 * M + 2.0 * floor(M * (double)l.K / 38400.0) +
@@ -759,7 +829,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     a.alpha = c.act.alpha; a.alpha_stride = c.act.alpha_stride;
     a.partials = reinterpret_cast<float *>(c.ws);
     a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_kblocks;
-    if (p.rows) return launch_rows(a, p, c);
+    if (p.rows) return launch_rows<false>(a, p, c);
     const TileShape &s = kTiles[p.shape];
     a.n_tiles = (l.n_pad + s.cols - 1) / s.cols;
     a.k_slices = p.split;
@@ -773,6 +843,31 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     case 4: return launch_tiles<4, 1, 2, 1, 1>(a, m_tiles, c);
     default: return launch_tiles<2, 1, 4, 1, 1>(a, m_tiles, c);
     }
+}
+
+// Whether k_rows takes the base-3 codes, or k_packed, which multiplies on the vector ALU: a workgroup of that takes
+// 2.6 us + (0.65 + 0.43 M) us per 1000 rows of W, and 3 us more where it deals K to several workgroups (measured
+// M = 1 .. 8, the shapes of rows_plan()).  k_packed stays ahead on one row over many columns (M = 1, 4096 x 11008 7.6
+// against 8.1 us) and on short K (M <= 5, 512 x 16384; M <= 3, 512 x 512).
+bool packed_rows_win(const tcsc_layout_t &l, int M)
+{
+    if (l.K > (1 << 22) || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return false;
+    const int units = compute_units(), groups = l.n_pad / 64;
+    int parts = 2 * groups <= units && M * l.n_chunks5 >= 400 ? units / groups : 1;
+    if (parts > 4) parts = 4;
+    const double rounds = ceil((double)groups * parts / units);
+    const double other = 2.6 + rounds * l.K / parts * 1e-3 * (0.65 + 0.43 * M) + (parts > 1 ? 3.0 : 0.0);
+    return rows_plan(l, M, true).us < other;
+}
+
+hipError_t launch_packed_rows(const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
+{
+    const tcsc_layout_t &l = t->layout;
+    MatrixArgs a{};
+    a.X = X; a.masks = reinterpret_cast<const uint4v *>(device_view(t).packed); a.b = b; a.Y = Y;
+    a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_chunks5;
+    const RowsPlan r = rows_plan(l, M, true);
+    return launch_rows<true>(a, MatrixPlan{true, r.tiles, r.waves}, c);
 }
 
 }  // namespace tst

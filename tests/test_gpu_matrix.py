@@ -64,6 +64,30 @@ def test_few_rows(M, K, N):
         assert_close(Yo, Yd, A, f"{M}x{K}x{N} lists")
 
 
+# the base-3 codes: pieces of 80 rows, groups of four of them, four and eight wavefronts, K in and beyond its last byte
+@pytest.mark.parametrize("M", range(1, 9))
+@pytest.mark.parametrize("K,N", [(1, 1), (79, 17), (81, 16), (319, 33), (320, 40), (1283, 31), (1601, 5000), (2563, 9000),
+                                 (700, 16400), (1290, 13000), (5121, 70)])
+def test_packed_codes(M, K, N):
+    import torch
+    W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=790 + M + K)
+    ot = oracle.tcsc_build(W)
+    Yd, A, _ = oracle.tstgemm(X, ot, b)
+    t = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_PACKED)
+    bd = torch.from_numpy(b).cuda()
+    Xi = np.random.default_rng(791).integers(-8, 9, (M, K)).astype(np.float32)
+    Ydi = oracle.tstgemm(Xi, ot, b)[0].astype(np.float32)
+    tight(tg.tstgemm_packed(torch.from_numpy(X).cuda(), t, bd).cpu().numpy(), Yd, A, f"{M}x{K}x{N}")
+    assert np.array_equal(tg.tstgemm_packed(torch.from_numpy(Xi).cuda(), t, bd).cpu().numpy(), Ydi)
+    # the kernel on the vector ALU, which a request for parts of K still gets
+    assert np.array_equal(tg.tstgemm_packed(torch.from_numpy(Xi).cuda(), t, bd, k_slices=1).cpu().numpy(), Ydi)
+    # finite, but beyond what the scaled planes hold
+    Xl = np.ldexp(Xi, 112).astype(np.float32)
+    Yl = tg.tstgemm_packed(torch.from_numpy(Xl).cuda(), t, None).cpu().numpy()
+    Ye = np.ldexp(oracle.tstgemm(Xi, ot, None)[0], 112)
+    assert np.array_equal(Yl.astype(np.float64), Ye)
+
+
 def _same(Y, Yd):
     """Equal in what is not finite; else within the tolerance of the finite part of the sum."""
     return np.array_equal(np.isnan(Y), np.isnan(Yd)) and np.array_equal(np.isposinf(Y), np.isposinf(Yd)) \
