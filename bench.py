@@ -250,11 +250,18 @@ def main():
     matrix = (not decode and args.variant == "tcsc" and not shaped and
               takes_matrix_cores(wl.M, wl.K, wl.N, lay.n_pad, nnz / (wl.K * wl.N),
                                  torch.cuda.get_device_properties(0).multi_processor_count))
+    # ... whose place k_rows (matrix cores) takes, for the lists except where W is sparse or a few columns meet a long K,
+    # for the base-3 codes except with one row over many columns or a short K (matrix_plan, packed_rows_win)
+    rows = decode and not shaped and (
+        (args.variant == "tcsc" and not args.wide_lists and nnz >= 0.2 * wl.K * wl.N and wl.N >= 1024) or
+        (args.variant == "packed" and wl.K > 1024 and (wl.M > 1 or wl.N <= 8192)))
     # index data one call reads (what must not be in the Infinity Cache for an HBM figure)
-    narrow = (decode and args.variant == "tcsc" and bool(lay.has_lists16) and not args.wide_lists
+    narrow = (decode and not rows and args.variant == "tcsc" and bool(lay.has_lists16) and not args.wide_lists
               and wl.K <= 150 * 1024 // (4 * wl.M) - 1)   # the library's rule for its padded 16-bit lists
     if args.variant == "packed":
         index_bytes = lay.n_chunks5 * lay.n_pad * 16
+    elif rows:
+        index_bytes = 16 * lay.n_kblocks * lay.n_pad
     elif decode:
         index_bytes = 2 * (lay.nnz16_pos + lay.nnz16_neg) if narrow else 4 * nnz
     elif small:
@@ -367,7 +374,13 @@ def main():
 
     measured = MEASURED_TRAFFIC.get((wl.name, args.variant))
     traffic = measured[0] if measured else None
-    if args.variant == "packed":
+    if rows:
+        # the row sets or codes once, each entry of W one product of three planes; the constants were of other kernels
+        traffic = measured = None
+        alg_bytes = index_bytes + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
+        roof = {"bound": "hbm", "achieved": alg_bytes / (kernel_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
+                "unit": "GB/s", "traffic": None}
+    elif args.variant == "packed":
         # dense decode: every entry of the padded W costs one conversion and M multiply-adds on the vector ALUs
         # (256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-instructions/s); the codes are 1.6 bits per entry
         entries = lay.n_chunks5 * 80 * lay.n_pad
@@ -400,9 +413,9 @@ def main():
                         "2.4 GHz; the fp32 add rate of the vector ALUs (alu_add_peak) is twice that",
                 "alu_add_peak": PEAK_ALU_ADD_TFLOPS}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    roof["kernel"] = ("k_packed" if args.variant == "packed" else "k_decode (signed lists)" if args.variant == "signed"
+    roof["kernel"] = ("k_rows" if rows else "k_packed" if args.variant == "packed" else "k_decode (signed lists)" if args.variant == "signed"
                       else "k_decode" if decode else "k_matrix" if matrix else "k_small" if small else "k_large")
-    if decode and args.variant == "tcsc":
+    if decode and not rows and args.variant == "tcsc":
         roof["kernel"] += " (16-bit lists)" if narrow else " (32-bit lists)"
     roof["kernel_ms"] = kernel_ms
     roof["kernel_ms_median"] = kernel_ms_median
