@@ -69,17 +69,20 @@ __device__ __forceinline__ uint4v load16(__amdgpu_buffer_rsrc_t buf, unsigned of
     return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)offset, 0, 0));
 }
 
-// A descriptor over `bytes` from p on (at most 4 GiB; none for a null pointer).
+constexpr unsigned kNowhere = 0xffffff00u;   // an offset beyond every buffer: reads as zero, stores nothing
+// K and N of a call are at most this (offsets_fit()), so an offset inside a tile of X, Y or partial sums is far below kNowhere.
+constexpr int kMaxExtent = 1 << 22;
+
+// A descriptor over `bytes` from p on (at most up to kNowhere; none for a null pointer).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const void *p, size_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0,
-                                             p == nullptr ? 0 : (int)(unsigned)min(bytes, (size_t)0xfffffffcu), kRawBuffer);
+                                             p == nullptr ? 0 : (int)(unsigned)min(bytes, (size_t)kNowhere), kRawBuffer);
 }
 // Cache bits of a buffer store (sc0, sc1): written through the L2.  What a kernel leaves there dirty is written back when it
 // ends, before the next one starts; 16 MB of Y written through save 2 us (1024 x 1024 x 4096: 22.9 -> 20.9 us;
 // 4096 x 1024 x 8192: 149 -> 142), partial sums 1 to 3 % of a sliced call.
 constexpr int kWriteThrough = 17;
-constexpr unsigned kNowhere = 0xffffff00u;   // an offset beyond every buffer: reads as zero, stores nothing
 
 // Bias and PReLU of columns, requested before the sums are there; zero for columns >= N and without a bias.
 struct Epilogue {
@@ -152,6 +155,7 @@ k_matrix(const MatrixArgs a)
     constexpr int NG = 64 * WM * WN, TM = 32 * RF * WM, TN = 32 * CF * WN, PD = 2;
     constexpr int kUnits = TM * 4 > NG ? TM * 4 / NG : 1;   // pieces of X (8 floats of a row) per lane and step
     static_assert(TM * 4 % NG == 0 || TM * 4 < NG, "units");
+    static_assert(((size_t)TM + NG / 4 + 1) * kMaxExtent * 4 < kNowhere, "offsets inside a tile");
     constexpr int kChunk = TM + 2;                          // 16-byte units per plane and piece; + 2: other banks
     constexpr int kPlane = 4 * kChunk, kBuffer = 3 * kPlane;
     constexpr int kStageUnits = WK * 2 * kBuffer, kSumUnits = (WK / 2) * (TM * TN / 4);
@@ -176,9 +180,10 @@ k_matrix(const MatrixArgs a)
     kb0 += group * blocks;
     kb1 = min(kb0 + blocks, kb1);
 
-    // X from the first row of the tile on, and the row sets up to the end of the group's blocks: what lies beyond reads
-    // as zero
-    const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(a.X + (size_t)m0 * a.K, (size_t)(a.M - m0) * a.K * 4);
+    // The rows of the tile, and the row sets up to the end of the group's blocks: what lies beyond reads as zero.  No buffer
+    // reaches beyond its tile, whatever M is
+    const int rows = min(TM, a.M - m0);
+    const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(a.X + (size_t)m0 * a.K, (size_t)rows * a.K * 4);
     const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(a.masks, (size_t)kb1 * a.n_pad * 16);
     unsigned xoff[kUnits], woff[CF];
     int unit[kUnits];
@@ -347,7 +352,7 @@ k_matrix(const MatrixArgs a)
     auto row_of = [&](int i, int e) { return row0 + 32 * i + 8 * (e / 4) + e % 4; };
     if (a.k_slices > 1) {
         const __amdgpu_buffer_rsrc_t pbuf =
-            raw_buffer(a.partials + ((size_t)slice * a.M + m0) * a.n_pad, (size_t)(a.M - m0) * a.n_pad * 4);
+            raw_buffer(a.partials + ((size_t)slice * a.M + m0) * a.n_pad, (size_t)rows * a.n_pad * 4);
 #pragma unroll
         for (int j = 0; j < CF; ++j) {
             const int n = col0 + 32 * j;
@@ -361,7 +366,7 @@ k_matrix(const MatrixArgs a)
         }
         return;
     }
-    const __amdgpu_buffer_rsrc_t ybuf = raw_buffer(a.Y + (size_t)m0 * a.N, (size_t)(a.M - m0) * a.N * 4);
+    const __amdgpu_buffer_rsrc_t ybuf = raw_buffer(a.Y + (size_t)m0 * a.N, (size_t)rows * a.N * 4);
     bool again = false;
 #pragma unroll
     for (int j = 0; j < CF; ++j) {
@@ -771,7 +776,7 @@ hipError_t launch_rows(const MatrixArgs &a, const MatrixPlan &p, const Call &c)
 // Offsets inside a tile of X or Y and inside the row sets are 32 bits wide, with some steps to spare.
 bool offsets_fit(const tcsc_layout_t &l)
 {
-    return l.K <= (1 << 22) && l.N <= (1 << 22) && ((long long)l.n_kblocks + 64) * l.n_pad * 16 < (1LL << 32);
+    return l.K <= kMaxExtent && l.N <= kMaxExtent && ((long long)l.n_kblocks + 64) * l.n_pad * 16 < (1LL << 32);
 }
 
 double density(const tcsc_layout_t &l) { return (double)(l.nnz_pos + l.nnz_neg) / ((double)l.K * (double)l.N); }
@@ -855,7 +860,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
 // against 8.1 us) and on short K (M <= 5, 512 x 16384; M <= 3, 512 x 512).
 bool packed_rows_win(const tcsc_layout_t &l, int M)
 {
-    if (l.K > (1 << 22) || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return false;
+    if (l.K > kMaxExtent || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return false;
     const int units = compute_units(), groups = l.n_pad / 64;
     int parts = 2 * groups <= units && M * l.n_chunks5 >= 400 ? units / groups : 1;
     if (parts > 4) parts = 4;

@@ -166,6 +166,28 @@ def test_without_the_row_sets_or_with_little_scratch(M):
         assert err.value.code == -8
 
 
+def test_y_beyond_four_gib():
+    """A Y of more than 2^32 bytes whose column count is not a multiple of a tile's: every element, integer X.  (A lane whose
+    column does not exist must store nowhere, also where the rest of Y would reach as far as a 32-bit offset does.)"""
+    import torch
+    M, K, N = 1_150_000, 20, 950
+    assert M * N * 4 > (1 << 32) + (64 << 20) and N % 64
+    g = torch.Generator(device="cuda").manual_seed(785)
+    W = np.random.default_rng(786).integers(-1, 2, (K, N)).astype(np.int8)
+    X = torch.randint(-8, 9, (M, K), generator=g, device="cuda").float()
+    b = torch.randint(-8, 9, (N,), generator=g, device="cuda").float()
+    t = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_ROWSETS)
+    ws = torch.empty(tg.tstgemm_workspace_bytes(M, K, N)[0], dtype=torch.uint8, device="cuda")
+    Y = tg.tstgemm(X, t, b, torch.full((M, N), float("nan"), device="cuda"), workspace=ws)
+    Wd = torch.from_numpy(W).cuda().float()
+    for m in range(0, M, 1 << 17):
+        Xs = X[m:m + (1 << 17)]
+        assert torch.equal(Y[m:m + (1 << 17)], Xs @ Wd + b), f"rows from {m}"   # small integers: exact in any order
+    rows = torch.tensor([0, 1, M // 2, M - 1], device="cuda")
+    Yd = oracle.tstgemm(X[rows].cpu().numpy(), oracle.tcsc_build(W), b.cpu().numpy())[0]
+    assert np.array_equal(Y[rows].cpu().numpy(), Yd.astype(np.float32))
+
+
 def test_calls_follow_torchs_current_stream():
     """Without a stream argument a call goes to torch's current stream, whichever that is: behind a long piece of work on a
     side stream it reads what that work writes, and torch's own work behind it reads its result."""
