@@ -386,8 +386,8 @@ k_matrix(const MatrixArgs a)
         const int n = col0 + 32 * j;
         if (n >= a.N) break;
         for (int i = 0; i < RF * 16; ++i) {
-            const int m = m0 + row_of(i / 16, i % 16);
-            if (m >= a.M || finite(a.Y[(size_t)m * a.N + n])) continue;   // the lane's own store
+            const int row = row_of(i / 16, i % 16), m = m0 + row;
+            if (row >= rows || finite(a.Y[(size_t)m * a.N + n])) continue;   // the lane's own store
             a.Y[(size_t)m * a.N + n] = finish(gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K), bias[j], slope[j]);
         }
     }
@@ -443,11 +443,11 @@ hipError_t launch_sum(const MatrixArgs &a, hipStream_t stream)
 }
 
 template <int WK, int WM, int WN, int RF, int CF>
-hipError_t launch_tiles(const MatrixArgs &a, int m_tiles, const Call &c)
+hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 {
     hipError_t e;
     if ((e = c.record_before()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_matrix<WK, WM, WN, RF, CF>), dim3((unsigned)((long long)m_tiles * a.n_tiles * a.k_slices)),
+    hipLaunchKernelGGL((k_matrix<WK, WM, WN, RF, CF>), dim3((unsigned)(m_tiles * a.n_tiles * a.k_slices)),
                        dim3(64 * WK * WM * WN), 0, c.stream, a);
     e = hipGetLastError();
     if (e == hipSuccess) e = c.record_after();
@@ -463,16 +463,16 @@ hipError_t launch_tiles(const MatrixArgs &a, int m_tiles, const Call &c)
 // shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five is 2 % slower than the best of all on
 // average, 16 % at worst.
 struct TileShape {
-    int rows, cols, groups, per_cu;
+    int rows, cols, groups, waves, per_cu;
     double fixed, step, work, peak;
 };
 constexpr TileShape kTiles[] = {
-    {64, 512, 1, 1, 1.90, 0.900, 0.900, 1.61e9},   // long and wide calls: X is cut half as often as by the next
-    {64, 256, 1, 2, 1.27, 0.578, 0.466, 1.55e9},   // two independent workgroups per unit fill each other's barriers
-    {64, 256, 2, 1, 2.15, 0.972, 0.972, 1.50e9},   // half the slices of that where rows x columns leave units idle
-    {64, 128, 1, 3, 0.31, 0.420, 0.311, 1.45e9},   // short K: little to start with
-    {32, 64, 4, 2, 0.65, 0.501, 0.461, 1.30e9},    // small Y
-    {32, 128, 2, 2, 0.34, 0.456, 0.383, 1.40e9},   // M <= 32
+    {64, 512, 1, 8, 1, 1.90, 0.900, 0.900, 1.61e9},   // long and wide calls: X is cut half as often as by the next
+    {64, 256, 1, 4, 2, 1.27, 0.578, 0.466, 1.55e9},   // two independent workgroups per unit fill each other's barriers
+    {64, 256, 2, 8, 1, 2.15, 0.972, 0.972, 1.50e9},   // half the slices of that where rows x columns leave units idle
+    {64, 128, 1, 4, 3, 0.31, 0.420, 0.311, 1.45e9},   // short K: little to start with
+    {32, 64, 4, 8, 2, 0.65, 0.501, 0.461, 1.30e9},    // small Y
+    {32, 128, 2, 8, 2, 0.34, 0.456, 0.383, 1.40e9},   // M <= 32
 };
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
 
@@ -486,9 +486,11 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
     const int units = compute_units();
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const TileShape &s = kTiles[i];
-        const double tiles = (double)((M + s.rows - 1) / s.rows) * (double)((l.n_pad + s.cols - 1) / s.cols);
+        const double tiles = ceil((double)M / s.rows) * ceil((double)l.n_pad / s.cols);
         const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
-        if (tiles * kMaxKSlices > 2e9) continue;
+        // a launch has less than 2^32 threads; a call with more tiles than that (K slices are for few tiles only) goes to
+        // k_large, which takes X in slabs
+        if (tiles * (64 * s.waves) >= 4294967296.0) continue;
         // (slices beyond two full rounds only add partial sums)
         for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || tiles * k <= 2.0 * units * s.per_cu); ++k) {
             const int per = (l.n_kblocks + k - 1) / k;
@@ -843,7 +845,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     a.n_tiles = (l.n_pad + s.cols - 1) / s.cols;
     a.k_slices = p.split;
     a.kb_per_slice = (l.n_kblocks + p.split - 1) / p.split;
-    const int m_tiles = (M + s.rows - 1) / s.rows;
+    const long long m_tiles = ((long long)M + s.rows - 1) / s.rows;
     switch (p.shape) {
     case 0: return launch_tiles<1, 1, 8, 2, 2>(a, m_tiles, c);
     case 1: return launch_tiles<1, 1, 4, 2, 2>(a, m_tiles, c);

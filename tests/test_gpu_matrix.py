@@ -188,6 +188,19 @@ def test_y_beyond_four_gib():
     assert np.array_equal(Y[rows].cpu().numpy(), Yd.astype(np.float32))
 
 
+@pytest.mark.parametrize("M", [(1 << 30) - 64, 1 << 30, (1 << 31) - 1])
+def test_as_many_rows_as_an_int_holds(M):
+    """Rows over a single column: as many tiles as one launch may have (its threads number less than 2^32), one more, and
+    row numbers that leave no room to round up in 32 bits."""
+    import torch
+    X = torch.empty((M, 1), device="cuda")
+    X.view(-1).copy_(torch.arange(M, device="cuda", dtype=torch.int32) % 1001)
+    b = torch.full((1,), 3.0, device="cuda")
+    t = tg.tcsc_upload(tg.tcsc_build(np.array([[-1]], np.int8)))
+    Y = tg.tstgemm(X, t, b)
+    assert torch.equal(Y, 3.0 - X)
+
+
 def test_calls_follow_torchs_current_stream():
     """Without a stream argument a call goes to torch's current stream, whichever that is: behind a long piece of work on a
     side stream it reads what that work writes, and torch's own work behind it reads its result."""
