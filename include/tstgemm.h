@@ -180,7 +180,10 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * whose lists its 32-bit byte offsets do not reach), everything else the large-M path (row sets).  Where the buffer
  * holds the row sets and W is not too sparse for it to pay, a call goes through the matrix cores instead: X is cut
  * exactly into three bf16 planes and multiplied by the row sets, spread into weights, with fp32 sums.  What a call
- * needs (its form, the least workspace) is the same either way.
+ * needs (its form, the least workspace) is the same either way.  Rows of X with an infinity, a NaN or entries beyond about
+ * 2^100 give the same results there, at the price of taking these rows (16 at a time) once more: a call with one such
+ * row takes two to three times as long, about what the list and row-set kernels take; one where every row is such, up to
+ * ten times.
  * Asynchronous: the kernels are enqueued on `stream` (a hipStream_t, NULL = null stream), no host
  * synchronisation, no allocation.
  * Device data are not validated.  Errors: EINVAL, ENOTUPLOADED, ENOFORM, EWORKSPACE, EHIP (launch failure).

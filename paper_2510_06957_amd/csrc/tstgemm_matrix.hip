@@ -9,8 +9,8 @@
 // K = N = 8192, where one fp32 sum over a list gives 1.1e-6; 5e-8 .. 8e-8 on every shape from K = 512 to 16384 (lists:
 // 9e-8 .. 5e-7).  X goes in times 2^24, so that the pieces of the smallest floats are bf16 numbers too, and a weight is
 // 2.0 with its sign (one bit beside the sign bit); sums leave times 2^-25, exactly.  A scaled sum that is not finite --
-// X held an infinity, a NaN or something beyond about 2^100 -- is taken again from X itself by gather_output(), member by
-// member of the lists, so an entry of X under a zero weight never reaches Y here either.
+// X held an infinity, a NaN or something beyond about 2^100 -- is taken again from X by sums_of_any(), which keeps such
+// entries apart, so an entry of X under a zero weight never reaches Y here either.
 //
 // k_matrix is for M > 8, k_rows for M <= 10; choose_tile(), rows_plan() and matrix_plan() have the rules, with what was
 // measured.
@@ -29,6 +29,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kScaleUp = 16777216.f;            // 2^24
 constexpr float kScaleDown = 1.f / 33554432.f;    // 2^-25
+constexpr float kLarge = 18446744073709551616.f;  // 2^64
 constexpr int kRawBuffer = 0x00020000;            // descriptor word 3: plain bytes; reads beyond num_records give zero
 
 __device__ __forceinline__ bool finite(float v) { return fabsf(v) < __builtin_inff(); }
@@ -107,28 +108,103 @@ struct Epilogue {
     }
 };
 
-// X W for one output straight from X: adds and subtracts the members of the two sets of every block.  For outputs whose
-// sum the matrix cores could not hold; a NaN stays one, so the walk ends there.
-__device__ __forceinline__ float gather_output(const float *__restrict__ X, const uint4v *__restrict__ masks, int n_pad,
-                                               int n_kblocks, int m, int n, int K)
+// X W for 16 x 16 outputs over blocks of rows of W whatever X holds: what k_matrix and k_rows do again for outputs whose
+// scaled sums are not finite.  X is split by size: entries below 2^64 go in times 2^24 as everywhere, larger ones times
+// 2^-24 (2^22 of the largest floats do not overflow so), and infinities and NaNs as ones in two planes of their own (a NaN in
+// both), multiplied by the +1 rows and by the -1 rows, which counts the members that push a sum up and those that push it
+// down.  Bound by cutting X, which every 16 columns do anew, and by the latency of its loads.  Single calls with one
+// infinity (with one in every row; with all of X near 1e35), 50 % non-zeros, against the list and row-set kernels, whose time
+// does not depend on X: 256 x 4096 x 4096 90 us (184; 363) against 108, 1024 x 2048 x 8192 248 (623; 937) against 359,
+// M = 1, 4096 x 4096 16 (14; 24) against 11; finite X 38, 82, 14.  One lane per output that walked the members one by one
+// took 1128 (1630), 442 (9361) and 263.  Where K is not a multiple of 64 the first entries of a row also meet the zero
+// weights beyond the end of the row before, so an infinity there sends that row here too.
+// X: the first of `rows` <= 16 rows; the blocks from kb0 on up to kb1, groups of four of them, every `stride`-th from
+// `first` on.  Lane l holds column n = n0 + l % 16 of Y, element e of the result is row 4 (l / 16) + e.
+__device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, const uint4v *masks, int n_pad, int n, int kb0,
+                                               int kb1, int first, int stride)
 {
-    float s = 0.f;
-    const float *x = X + (size_t)m * K;
-    for (int kb = 0; kb < n_kblocks; ++kb) {
-        const uint4v w = masks[(size_t)kb * n_pad + n];
-        unsigned long long pos = w[0] | ((unsigned long long)w[1] << 32), neg = w[2] | ((unsigned long long)w[3] << 32);
-        for (; pos; pos &= pos - 1) s += x[kb * kKBlock + __builtin_ctzll(pos)];
-        for (; neg; neg &= neg - 1) s -= x[kb * kKBlock + __builtin_ctzll(neg)];
-        if (s != s) break;
+    const int r = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(X, (size_t)rows * K * 4);
+    const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(masks, (size_t)kb1 * n_pad * 16);
+    float4v top{0.f, 0.f, 0.f, 0.f}, low = top, large = top, up = top, down = top;
+    auto multiply = [](float4v &c, uint4v a, bf16x8 b) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
+    };
+    for (int group = first; kb0 + 4 * group < kb1; group += stride) {
+        const unsigned kb = kb0 + 4 * group + g;
+        const uint4v w = load16(wbuf, (kb * (unsigned)n_pad + (unsigned)n) * 16u);
+        for (int h = 0; h < 2; ++h) {
+            const unsigned plus = h ? w[1] : w[0], minus = h ? w[3] : w[2];
+            const SignedWord both(plus, minus), of_plus(plus, 0), of_minus(minus, 0);
+            const unsigned off = r < rows ? ((unsigned)r * (unsigned)K + 64 * kb + 32 * h) * 4u : kNowhere;
+            float4v x0[4], x1[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                x0[s] = __builtin_bit_cast(float4v, load16(xbuf, r < rows ? off + 16 * s : off));
+                x1[s] = __builtin_bit_cast(float4v, load16(xbuf, r < rows ? off + 16 * s + 64 : off));
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bf16x8 bw = both.eight(4 * s);
+                uint4v hi, mid, lo;
+                auto cut = [&](int e, float a0, float a1) {
+                    hi[e] = top_halves(a0, a1);
+                    a0 = below_top(a0);
+                    a1 = below_top(a1);
+                    mid[e] = top_halves(a0, a1);
+                    lo[e] = top_halves(below_top(a0), below_top(a1));
+                };
+                bool rest = false;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool small0 = fabsf(x0[s][e]) < kLarge, small1 = fabsf(x1[s][e]) < kLarge;
+                    rest |= !small0 || !small1;
+                    cut(e, small0 ? x0[s][e] * kScaleUp : 0.f, small1 ? x1[s][e] * kScaleUp : 0.f);
+                }
+                multiply(top, hi, bw);
+                multiply(low, mid, bw);
+                multiply(low, lo, bw);
+                if (!__any(rest)) continue;
+                uint4v plus_inf, minus_inf;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float a[2] = {x0[s][e], x1[s][e]};
+                    float big[2];
+                    plus_inf[e] = minus_inf[e] = 0;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        big[i] = finite(a[i]) && !(fabsf(a[i]) < kLarge) ? a[i] * (1.f / kScaleUp) : 0.f;
+                        plus_inf[e] |= !(a[i] < __builtin_inff()) ? 0x3f80u << (16 * i) : 0u;      // bf16 1.0
+                        minus_inf[e] |= !(a[i] > -__builtin_inff()) ? 0x3f80u << (16 * i) : 0u;
+                    }
+                    cut(e, big[0], big[1]);
+                }
+                multiply(large, hi, bw);
+                multiply(large, mid, bw);
+                multiply(large, lo, bw);
+                const bf16x8 pw = of_plus.eight(4 * s), mw = of_minus.eight(4 * s);
+                multiply(up, plus_inf, pw);
+                multiply(up, minus_inf, mw);
+                multiply(down, plus_inf, mw);
+                multiply(down, minus_inf, pw);
+            }
+        }
     }
-    return s;
+    float4v v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = (top[e] + low[e]) * kScaleDown + large[e] * (0.5f * kScaleUp);
+        if (up[e] > 0.f || down[e] > 0.f)
+            v[e] = (up[e] > 0.f ? __builtin_inff() : 0.f) - (down[e] > 0.f ? __builtin_inff() : 0.f);
+    }
+    return v;
 }
 
 struct MatrixArgs {
     const float *X;
     const uint4v *masks;             // [n_kblocks][n_pad] {+1 rows low, high, -1 rows low, high}
     const float *b, *alpha;
-    float *Y, *partials;             // partials[slice][M][n_pad], scaled sums
+    float *Y, *partials;             // partials[slice][M][n_pad]
     int alpha_stride;
     int M, K, N, n_pad, n_kblocks;
     int n_tiles, k_slices, kb_per_slice;
@@ -350,50 +426,54 @@ k_matrix(const MatrixArgs a)
     // columns beyond the last): guarded by branches they waited for each other, 1.4 us of a short call
     const int row0 = wr * RF * 32 + 4 * g;
     auto row_of = [&](int i, int e) { return row0 + 32 * i + 8 * (e / 4) + e % 4; };
-    if (a.k_slices > 1) {
-        const __amdgpu_buffer_rsrc_t pbuf =
-            raw_buffer(a.partials + ((size_t)slice * a.M + m0) * a.n_pad, (size_t)rows * a.n_pad * 4);
+    const bool sliced = a.k_slices > 1;
+    float *out = sliced ? a.partials + ((size_t)slice * a.M + m0) * a.n_pad : a.Y + (size_t)m0 * a.N;
+    const int width = sliced ? a.n_pad : a.N;
+    const __amdgpu_buffer_rsrc_t obuf = raw_buffer(out, (size_t)rows * width * 4);
+    float spoilt = 0.f;   // NaN as soon as one sum is not finite
+    auto store = [&](auto value) {
 #pragma unroll
         for (int j = 0; j < CF; ++j) {
             const int n = col0 + 32 * j;
 #pragma unroll
             for (int i = 0; i < RF; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
+                for (int e = 0; e < 16; ++e) {
+                    spoilt = fmaf(acc[0][i][j][e], 0.f, spoilt);
                     __builtin_amdgcn_raw_buffer_store_b32(
-                        __float_as_uint(acc[0][i][j][e]), pbuf,
-                        (int)(n < a.n_pad ? ((unsigned)row_of(i, e) * (unsigned)a.n_pad + n) * 4u : kNowhere), 0, kWriteThrough);
+                        __float_as_uint(value(i, j, e)), obuf,
+                        (int)(n < width ? ((unsigned)row_of(i, e) * (unsigned)width + n) * 4u : kNowhere), 0, kWriteThrough);
+                }
         }
-        return;
-    }
-    const __amdgpu_buffer_rsrc_t ybuf = raw_buffer(a.Y + (size_t)m0 * a.N, (size_t)rows * a.N * 4);
-    bool again = false;
+    };
+    if (sliced) store([&](int i, int j, int e) { return acc[0][i][j][e] * kScaleDown; });
+    else store([&](int i, int j, int e) { return finish(acc[0][i][j][e] * kScaleDown, bias[j], slope[j]); });
+    if (!__any(spoilt != 0.f)) return;
+
+    // Pieces of 16 x 16 with a value that is not finite: again, from X.  (The wavefront reads what its own lanes stored.)
+    __threadfence();
+    const int first_block = slice * a.kb_per_slice, end_block = min(first_block + a.kb_per_slice, a.n_kblocks);
+    const int r16 = lane & 15, g16 = lane >> 4;
+    for (int piece = 0; piece < 4 * RF * CF; ++piece) {
+        const int row = wr * RF * 32 + 16 * (piece / (2 * CF)), n = n0 + wc * CF * 32 + 16 * (piece % (2 * CF)) + r16;
+        if (row >= rows) break;
+        bool bad[4];
 #pragma unroll
-    for (int j = 0; j < CF; ++j) {
-        const int n = col0 + 32 * j;
-#pragma unroll
-        for (int i = 0; i < RF; ++i)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                again |= !finite(acc[0][i][j][e]);
-                __builtin_amdgcn_raw_buffer_store_b32(
-                    __float_as_uint(finish(acc[0][i][j][e] * kScaleDown, bias[j], slope[j])), ybuf,
-                    (int)(n < a.N ? ((unsigned)row_of(i, e) * (unsigned)a.N + n) * 4u : kNowhere), 0, kWriteThrough);
-            }
-    }
-    if (!again) return;
-    for (int j = 0; j < CF; ++j) {
-        const int n = col0 + 32 * j;
-        if (n >= a.N) break;
-        for (int i = 0; i < RF * 16; ++i) {
-            const int row = row_of(i / 16, i % 16), m = m0 + row;
-            if (row >= rows || finite(a.Y[(size_t)m * a.N + n])) continue;   // the lane's own store
-            a.Y[(size_t)m * a.N + n] = finish(gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K), bias[j], slope[j]);
+        for (int e = 0; e < 4; ++e) {
+            const int m = row + 4 * g16 + e;
+            bad[e] = m < rows && n < width && !finite(out[(size_t)m * width + n]);
         }
+        if (!__any(bad[0] || bad[1] || bad[2] || bad[3])) continue;
+        const float4v v = sums_of_any(a.X + (size_t)(m0 + row) * a.K, min(rows - row, 16), a.K, a.masks, a.n_pad,
+                                      min(n, a.n_pad - 1), first_block, end_block, 0, 1);
+        const float bias_n = finish.bias_of(n), slope_n = finish.slope_of(n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (bad[e]) out[(size_t)(row + 4 * g16 + e) * width + n] = sliced ? v[e] : finish(v[e], bias_n, slope_n);
     }
 }
 
-// k_matrix_sum: Y = (slice 0 + slice 1 + ...) 2^-25 + b, then the optional PReLU; four columns per thread, all slices
+// k_matrix_sum: Y = slice 0 + slice 1 + ... + b, then the optional PReLU; four columns per thread, all slices
 // requested together.  Bound by its launch and one trip to memory (4 slices of 256 x 4096: about 5 us).
 template <int S>
 __global__ void __launch_bounds__(256)
@@ -412,7 +492,7 @@ k_matrix_sum(const MatrixArgs a)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (n + i >= a.N) break;
-        float v = finite(y[i]) ? y[i] * kScaleDown : gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n + i, a.K);
+        float v = y[i];
         if (a.b != nullptr) v += a.b[n + i];
         y[i] = activate(v, a.alpha, a.alpha_stride, n + i);
     }
@@ -555,8 +635,9 @@ __device__ __forceinline__ float gather_packed(const float *__restrict__ X, cons
     return s;
 }
 
+// (Up to five rows of X and 16 columns: four wavefronts per SIMD, so that four workgroups of four fit side by side.)
 template <int MM, int B, int KW, bool PACKED>
-__global__ void __launch_bounds__(64 * KW)
+__global__ void __launch_bounds__(64 * KW, !PACKED && MM <= 5 && B == 1 ? 4 : 1)
 k_rows(const MatrixArgs a)
 {
     constexpr int kSteps = PACKED ? 10 : 8;                  // matrix instructions per block of W and tile
@@ -566,6 +647,7 @@ k_rows(const MatrixArgs a)
     constexpr int kStage = KW * MM * kRowUnits, kSums = KW * B * T * 64;
     __shared__ uint4v lds[kStage > kSums ? kStage : kSums];
     __shared__ unsigned table[PACKED ? 256 : 1];
+    __shared__ int spoilt;   // a sum was not finite
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
@@ -682,6 +764,7 @@ k_rows(const MatrixArgs a)
     }
 
     // sums of the wavefronts, [wave][b][row of A][column]: element e of a fragment is row 4 g + e, column r
+    if (threadIdx.x == 0) spoilt = 0;
     __syncthreads();
     float *sums = reinterpret_cast<float *>(lds);
 #pragma unroll
@@ -706,10 +789,31 @@ k_rows(const MatrixArgs a)
             for (int k = 0; k < KW; ++k) plane[p] += sums[((k * B + b) * T * 16 + p * M + m) * 16 + c];
         }
         float v = (plane[0] + (plane[1] + plane[2])) * kScaleDown;
-        if (!finite(v))
-            v = PACKED ? gather_packed(a.X, a.masks, a.n_pad, m, n, a.K)
-                       : gather_output(a.X, a.masks, a.n_pad, a.n_kblocks, m, n, a.K);
+        if (!finite(v)) {
+            if constexpr (PACKED) v = gather_packed(a.X, a.masks, a.n_pad, m, n, a.K);
+            else spoilt = 1;
+        }
         a.Y[(size_t)m * a.N + n] = finish(v, bias, slope);
+    }
+    if constexpr (!PACKED) {
+        __syncthreads();
+        if (!spoilt) return;
+        // again from X, the groups dealt to the wavefronts as before: [wave][b][row][column]
+#pragma unroll 1
+        for (int b = 0; b < B; ++b) {
+            const float4v v = sums_of_any(a.X, M, a.K, a.masks, a.n_pad, min(n0 + 16 * b + r, a.n_pad - 1), 0, a.n_kblocks, wave, KW);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sums[((wave * B + b) * 16 + 4 * g + e) * 16 + r] = v[e];
+        }
+        __syncthreads();
+        for (int o = threadIdx.x; o < 16 * B * M; o += 64 * KW) {
+            const int c = o & 15, b = (o >> 4) % B, m = (o >> 4) / B, n = n0 + 16 * b + c;
+            if (n >= a.N || finite(a.Y[(size_t)m * a.N + n])) continue;   // the thread's own store
+            float v = 0.f;
+#pragma unroll
+            for (int k = 0; k < KW; ++k) v += sums[((k * B + b) * 16 + m) * 16 + c];
+            a.Y[(size_t)m * a.N + n] = finish(v, finish.bias_of(n), finish.slope_of(n));
+        }
     }
 }
 

@@ -120,6 +120,72 @@ def test_infinities_and_nans(M, K, N, alpha):
     assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-5 * A[ok])
 
 
+@pytest.mark.parametrize("M,K,N", [(1, 65, 17), (5, 2100, 70), (10, 300, 5000), (17, 65, 40), (40, 4100, 200), (64, 512, 512),
+                                   (130, 4100, 70), (300, 333, 130), (700, 300, 1100)])
+def test_infinities_beside_numbers_of_any_size(M, K, N):
+    """Rows of integers times powers of two from the smallest float to where the sums just fit, one of them mixed, each with
+    an infinity under a weight that is zero in most columns: there the result is exact (the mixed row: within the bound of
+    an fp32 sum); where the weight is not zero, the infinity of its sign, or NaN where two of them meet."""
+    W, X, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=750 + M + K)
+    W[K // 3] = 0
+    W[K // 3, ::7], W[K // 3, 3::7] = 1, -1
+    W[K - 1] = W[K // 3] * np.where(np.arange(N) % 2, 1, -1)
+    exponents = np.array([0, -149, 116, -100, 62, 70, 100, -126])[np.arange(M) % 8]
+    X = np.ldexp(X.astype(np.float64), exponents[:, None])
+    mixed = np.arange(M) % 8 == 5
+    X[mixed, ::2] = np.ldexp(X[mixed, ::2], -140)
+    X[:, K - 1] = 0
+    Xc = X.copy()
+    Xc[:, K // 3] = 0
+    Yd, A = Xc @ W, np.abs(Xc) @ np.abs(W)
+    sign = np.where(np.arange(M) % 3, 1.0, -1.0)
+    X[:, K // 3] = sign * np.inf
+    X[::4, K - 1] = np.inf
+    with np.errstate(invalid="ignore"):
+        for k in (K // 3, K - 1):
+            held = np.isinf(X[:, k])[:, None] & (W[k] != 0)[None, :]
+            Yd[held] += (X[:, k][:, None] * np.where(W[k] == 0, 1, W[k]))[held]
+    Y, h = gpu_tstgemm(W, X.astype(np.float32), None)
+    assert np.isfinite(Yd).any() and np.isinf(Yd).any() and _same(Y, Yd)
+    ok = np.isfinite(Yd)
+    exact = ok & ~mixed[:, None]
+    assert np.array_equal(Y[exact].astype(np.float64), Yd[exact])
+    assert np.all(np.abs(Y[ok] - Yd[ok]) <= TIGHT * A[ok])
+    # the list and row-set kernels agree
+    other = dict(wide_lists=True) if M <= 8 else dict(list_walk=1) if M <= 64 else dict(cols_per_wave=4)
+    assert _same(gpu_tstgemm(W, X.astype(np.float32), None, handle=h, **other)[0], Yd)
+
+
+@pytest.mark.parametrize("M,K,N,every_row", [(1, 4096, 4096, True), (8, 4096, 4096, False), (256, 4096, 4096, False),
+                                             (1024, 1024, 4096, True)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e35])
+def test_x_that_is_not_finite_does_not_stall_a_call(M, K, N, every_row, value):
+    """What X holds must not change a call's time by much: with an infinity, a NaN or a number beyond the scaled range at
+    most four times what the list and row-set kernels take (they do not look at X), and 30 us for the launches.  (Walking
+    the members of each such output by one lane took 10 to 35 times as long as they.)"""
+    import torch
+    W = si.draw_ternary(np.random.default_rng(755), K, N, 0.5)
+    X = torch.randn(M, K, device="cuda")
+    X[slice(None) if every_row else M // 2, K // 3] = value
+    ws = torch.empty(tg.tstgemm_workspace_bytes(M, K, N)[1] + 256, dtype=torch.uint8, device="cuda")
+    t = tg.tcsc_upload(tg.tcsc_build(W))
+    lists = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_LISTS16) if M <= 8 else t
+
+    def us(handle, **options):
+        Y = torch.empty(M, N, device="cuda")
+        best = float("inf")
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            tg.tstgemm(X, handle, None, Y, workspace=ws, **options)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * e0.elapsed_time(e1))
+        return best
+
+    assert us(t) <= 4.0 * us(lists, **({} if M <= 8 else dict(cols_per_wave=4))) + 30.0
+
+
 @pytest.mark.parametrize("M,K,N", [(5, 300, 70), (40, 300, 70), (130, 4100, 70)])
 @pytest.mark.parametrize("exponent", [-149, -140, -126, -110, 0, 60, 99, 110, 116])
 def test_range_of_x(M, K, N, exponent):
