@@ -250,6 +250,20 @@ int tstgemm_ex(const float *X, const tcsc_t *t, const float *b, float *Y, int M,
                const tstgemm_opts_t *opts, void *stream);
 
 /*
+ * Which kernel a call of tstgemm_ex() with these arguments launches, for benchmarks and tests: on the host alone, by the
+ * rule the call itself follows; the handle need not be uploaded yet (the workspace counts by its size).  kernel: static
+ * text, "k_decode", "k_decode_signed", "k_packed", "k_rows_packed", "k_rows", "k_small", "k_large" or "k_matrix"; for the
+ * three on the matrix cores also the rows and columns of Y a workgroup computes, the groups of wavefronts that share K in it
+ * and the slices of K that workgroups share, else 0.
+ * Errors: as tstgemm_ex() for opts, M and the handle's forms (EINVAL, ENOFORM).
+ */
+typedef struct tstgemm_route {
+    const char *kernel;
+    int tile_rows, tile_cols, k_groups, k_slices;
+} tstgemm_route_t;
+int tstgemm_query_route(const tcsc_t *t, int M, const tstgemm_opts_t *opts, tstgemm_route_t *out);
+
+/*
  * Y = PReLU(X W + b): tstgemm() with the activation fused behind the bias add.  The paper fuses
  * PReLU into its vectorised kernels (Sec. 2 "Implementation Note", Sec. 4) without giving the
  * formula or the slope; here it is the usual one, PReLU(v) = v for v > 0 and alpha * v otherwise,

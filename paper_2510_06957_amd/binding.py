@@ -44,6 +44,16 @@ class TstgemmOpts(ctypes.Structure):
                 ("list_walk", ctypes.c_int), ("decode_wide_lists", ctypes.c_int), ("event_before", ctypes.c_void_p), ("event_after", ctypes.c_void_p)]
 
 
+class TstgemmRoute(ctypes.Structure):
+    """tstgemm_route_t of include/tstgemm.h."""
+    _fields_ = [("_kernel", ctypes.c_char_p), ("tile_rows", ctypes.c_int), ("tile_cols", ctypes.c_int), ("k_groups", ctypes.c_int),
+                ("k_slices", ctypes.c_int)]
+
+    @property
+    def kernel(self) -> str:
+        return self._kernel.decode()
+
+
 # TCSC_FORM_* of include/tstgemm.h
 FORM_ROWSETS, FORM_CUTS, FORM_LISTS16, FORM_SIGNED, FORM_PACKED, FORM_WORKSPACE, FORM_ALL = 1, 2, 4, 8, 16, 32, 63
 
@@ -87,6 +97,7 @@ def _load():
     lib.tstgemm_noalloc.argtypes = [vp, vp, vp, vp, ci, ci, ci, vp]
     lib.tstgemm_ex.argtypes = [vp, vp, vp, vp, ci, ci, ci, ctypes.POINTER(TstgemmOpts), vp]
     lib.tstgemm_workspace_bytes.argtypes = [ci, ci, ci, ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t)]
+    lib.tstgemm_query_route.argtypes = [vp, ci, ctypes.POINTER(TstgemmOpts), ctypes.POINTER(TstgemmRoute)]
     lib.tcsc_select_forms.argtypes = [vp, ctypes.c_uint32]
     lib.tstgemm_probe_lds_read.argtypes = [ci, ctypes.POINTER(ctypes.c_int64), vp]
     lib.tstgemm_probe_lds_read.restype = ci
@@ -97,7 +108,7 @@ def _load():
     for name in ("tcsc_build", "tcsc_from_arrays", "tcsc_to_dense", "tcsc_dims", "tcsc_arrays", "tcsc_device_bytes",
                  "tcsc_layout", "tcsc_upload", "tstgemm", "tstgemm_prelu", "tstgemm_signed", "tstgemm_packed",
                  "tcsc_signed_arrays", "tcsc_packed_codes", "tstgemm_ex", "tstgemm_workspace_bytes", "tcsc_select_forms",
-                 "tstgemm_noalloc"):
+                 "tstgemm_noalloc", "tstgemm_query_route"):
         getattr(lib, name).restype = ci
     _lib = lib
     return lib
@@ -362,6 +373,21 @@ def tstgemm_packed(X, t: Tcsc, b=None, Y=None, stream=None, **options):
     """Y = X W + b for M <= 8 from the value-compression form of the uploaded matrix (tstgemm_packed of the C ABI);
     X must be finite."""
     return _variant("tstgemm_packed", 2, X, t, b, Y, stream, options)
+
+
+def tstgemm_query_route(t: Tcsc, M: int, encoding=0, workspace_bytes=0, cols_per_wave=0, k_slices=0, slab_tiles=0, list_walk=0,
+                        wide_lists=False) -> TstgemmRoute:
+    """The kernel that tstgemm() (encoding 0), tstgemm_signed() (1) or tstgemm_packed() (2) launches for M rows of X with these
+    options, its tile of Y and slices of K (host only; workspace_bytes: of a workspace argument, 0 = the handle's own)."""
+    o = TstgemmOpts()
+    o.struct_size = ctypes.sizeof(TstgemmOpts)
+    o.encoding, o.decode_wide_lists = int(encoding), int(bool(wide_lists))
+    o.cols_per_wave, o.k_slices, o.slab_tiles, o.list_walk = int(cols_per_wave), int(k_slices), int(slab_tiles), int(list_walk)
+    if workspace_bytes:
+        o.workspace, o.workspace_bytes = 256, int(workspace_bytes)   # an aligned address that is not looked at
+    route = TstgemmRoute()
+    _check(_load().tstgemm_query_route(t.handle, int(M), ctypes.byref(o), ctypes.byref(route)), "tstgemm_query_route")
+    return route
 
 
 def tcsc_signed_arrays(t: Tcsc):

@@ -382,22 +382,25 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream)
 
 namespace {
 
-// One product: checks, the call's context from the options, dispatch on encoding and M.
-int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K, int N, const tstgemm_opts_t &o, void *stream)
+// What a call's arguments may be, before anything is looked at on the device.
+int check_call(const tcsc_t *t, int M, const tstgemm_opts_t &o)
 {
-    if (!X || !t || !Y || M < 1) return TSTGEMM_EINVAL;
-    if (K != t->K || N != t->N) return TSTGEMM_EINVAL;
+    if (!t || M < 1) return TSTGEMM_EINVAL;
     if (o.encoding < 0 || o.encoding > 2 || (o.encoding != 0 && (M > 8 || o.alpha))) return TSTGEMM_EINVAL;
-    if (o.alpha && o.alpha_count != 1 && o.alpha_count != N) return TSTGEMM_EINVAL;
+    if (o.alpha && o.alpha_count != 1 && o.alpha_count != t->N) return TSTGEMM_EINVAL;
     if (o.cols_per_wave != 0 && o.cols_per_wave != 1 && o.cols_per_wave != 2 && o.cols_per_wave != 4 && o.cols_per_wave != 8)
         return TSTGEMM_EINVAL;
     if (o.k_slices < 0 || o.k_slices > tst::kMaxKSlices || o.slab_tiles < 0) return TSTGEMM_EINVAL;
     if (o.list_walk < 0 || o.list_walk > 2) return TSTGEMM_EINVAL;
     if ((o.event_before == nullptr) != (o.event_after == nullptr)) return TSTGEMM_EINVAL;
     if (o.workspace && reinterpret_cast<uintptr_t>(o.workspace) % kAlign) return TSTGEMM_EINVAL;
-    if (!t->uploaded) return TSTGEMM_ENOTUPLOADED;
-    const tcsc_layout_t &l = t->layout;
+    return TSTGEMM_OK;
+}
 
+// The call's context from its options and the handle.
+tst::Call make_call(const tcsc_t *t, const tstgemm_opts_t &o, void *stream)
+{
+    const tcsc_layout_t &l = t->layout;
     tst::Call c{};
     c.stream = static_cast<hipStream_t>(stream);
     c.act = tst::Activation{o.alpha, (o.alpha && o.alpha_count != 1) ? 1 : 0};
@@ -405,7 +408,7 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
         c.ws = static_cast<char *>(o.workspace);
         c.ws_bytes = o.workspace_bytes;
     } else if (l.forms & TCSC_FORM_WORKSPACE) {
-        c.ws = static_cast<char *>(t->dev) + l.off_workspace;
+        c.ws = t->dev ? static_cast<char *>(t->dev) + l.off_workspace : nullptr;
         c.ws_bytes = l.workspace_bytes;
     }
     c.cols_per_wave = o.cols_per_wave;
@@ -415,33 +418,61 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
     c.decode_wide_lists = o.decode_wide_lists != 0;
     c.event_before = static_cast<hipEvent_t>(o.event_before);
     c.event_after = static_cast<hipEvent_t>(o.event_after);
+    return c;
+}
 
+// Which kernel takes a call, by its encoding, M, the uploaded forms, the workspace and the options.
+enum class Path { decode, decode_signed, packed, packed_rows, small_tile, large, matrix };
+struct Route {
+    int error;
+    Path path;
+    tst::MatrixPlan plan;   // packed_rows, matrix
+};
+Route choose_route(const tcsc_layout_t &l, int M, const tstgemm_opts_t &o, const tst::Call &c)
+{
     // a call that asks for a launch shape of the list and row-set kernels gets those kernels
     const bool shaped = o.cols_per_wave || o.k_slices || o.slab_tiles || o.list_walk;
     const bool row_sets = (l.forms & TCSC_FORM_ROWSETS) != 0;
-    hipError_t e;
     if (o.encoding == 1) {
-        if (!(l.forms & TCSC_FORM_SIGNED)) return TSTGEMM_ENOFORM;
-        e = tst::launch_decode_signed(X, t, b, Y, M, c);
-    } else if (o.encoding == 2) {
-        if (!(l.forms & TCSC_FORM_PACKED)) return TSTGEMM_ENOFORM;
-        e = o.k_slices == 0 && tst::packed_rows_win(l, M) ? tst::launch_packed_rows(X, t, b, Y, M, c)
-                                                          : tst::launch_packed(X, t, b, Y, M, c);
-    } else if (tst::decode_supported(M)) {
+        if (!(l.forms & TCSC_FORM_SIGNED)) return Route{TSTGEMM_ENOFORM};
+        return Route{TSTGEMM_OK, Path::decode_signed};
+    }
+    if (o.encoding == 2) {
+        if (!(l.forms & TCSC_FORM_PACKED)) return Route{TSTGEMM_ENOFORM};
+        const tst::MatrixPlan p = o.k_slices == 0 ? tst::packed_plan(l, M) : tst::MatrixPlan{};
+        return Route{TSTGEMM_OK, p.taken() ? Path::packed_rows : Path::packed, p};
+    }
+    if (tst::decode_supported(M)) {
         const tst::MatrixPlan p = row_sets && !c.decode_wide_lists ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
-        e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_decode(X, t, b, Y, M, c);
-    } else if (M <= 64 && tst::small_supported(l)) {
-        if (!(l.forms & TCSC_FORM_CUTS)) return TSTGEMM_ENOFORM;
-        const bool scratch = c.ws && c.ws_bytes >= tst::small_tile_bytes(M, K);
-        const tst::MatrixPlan p = row_sets && scratch && !shaped ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
-        e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_small(X, t, b, Y, M, c);
-    } else {
-        if (!row_sets) return TSTGEMM_ENOFORM;
-        size_t least = 0, best = 0;
-        tst::large_workspace_bytes(M, K, l.n_pad, &least, &best);
-        const bool scratch = c.ws && c.ws_bytes >= least;
-        const tst::MatrixPlan p = scratch && !shaped ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
-        e = p.taken() ? tst::launch_matrix(p, X, t, b, Y, M, c) : tst::launch_large(X, t, b, Y, M, c);
+        return Route{TSTGEMM_OK, p.taken() ? Path::matrix : Path::decode, p};
+    }
+    size_t least = 0, best = 0;
+    const bool small_tile = M <= 64 && tst::small_supported(l);
+    if (small_tile) least = tst::small_tile_bytes(M, l.K);
+    else tst::large_workspace_bytes(M, l.K, l.n_pad, &least, &best);
+    if (!(l.forms & (small_tile ? TCSC_FORM_CUTS : TCSC_FORM_ROWSETS))) return Route{TSTGEMM_ENOFORM};
+    const tst::MatrixPlan p = row_sets && !shaped && c.ws_bytes >= least ? tst::matrix_plan(l, M, c) : tst::MatrixPlan{};
+    return Route{TSTGEMM_OK, p.taken() ? Path::matrix : small_tile ? Path::small_tile : Path::large, p};
+}
+
+// One product: checks, the call's context from the options, the route, its launch.
+int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K, int N, const tstgemm_opts_t &o, void *stream)
+{
+    if (!X || !t || !Y || K != t->K || N != t->N) return TSTGEMM_EINVAL;
+    if (int rc = check_call(t, M, o)) return rc;
+    if (!t->uploaded) return TSTGEMM_ENOTUPLOADED;
+    const tst::Call c = make_call(t, o, stream);
+    const Route r = choose_route(t->layout, M, o, c);
+    if (r.error) return r.error;
+    hipError_t e = hipErrorInvalidValue;
+    switch (r.path) {
+    case Path::decode: e = tst::launch_decode(X, t, b, Y, M, c); break;
+    case Path::decode_signed: e = tst::launch_decode_signed(X, t, b, Y, M, c); break;
+    case Path::packed: e = tst::launch_packed(X, t, b, Y, M, c); break;
+    case Path::packed_rows: e = tst::launch_packed_rows(r.plan, X, t, b, Y, M, c); break;
+    case Path::small_tile: e = tst::launch_small(X, t, b, Y, M, c); break;
+    case Path::large: e = tst::launch_large(X, t, b, Y, M, c); break;
+    case Path::matrix: e = tst::launch_matrix(r.plan, X, t, b, Y, M, c); break;
     }
     return e == hipSuccess ? TSTGEMM_OK : e == tst::kErrWorkspace ? TSTGEMM_EWORKSPACE : TSTGEMM_EHIP;
 }
@@ -462,6 +493,27 @@ int tstgemm_ex(const float *X, const tcsc_t *t, const float *b, float *Y, int M,
 {
     if (opts && opts->struct_size != sizeof(tstgemm_opts_t)) return TSTGEMM_EINVAL;
     return run(X, t, b, Y, M, K, N, opts ? *opts : default_opts(), stream);
+}
+
+int tstgemm_query_route(const tcsc_t *t, int M, const tstgemm_opts_t *opts, tstgemm_route_t *out)
+{
+    if (!out || (opts && opts->struct_size != sizeof(tstgemm_opts_t))) return TSTGEMM_EINVAL;
+    const tstgemm_opts_t o = opts ? *opts : default_opts();
+    if (int rc = check_call(t, M, o)) return rc;
+    const Route r = choose_route(t->layout, M, o, make_call(t, o, nullptr));
+    if (r.error) return r.error;
+    *out = tstgemm_route_t{};
+    switch (r.path) {
+    case Path::decode: out->kernel = "k_decode"; break;
+    case Path::decode_signed: out->kernel = "k_decode_signed"; break;
+    case Path::packed: out->kernel = "k_packed"; break;
+    case Path::packed_rows: out->kernel = "k_rows_packed"; break;
+    case Path::small_tile: out->kernel = "k_small"; break;
+    case Path::large: out->kernel = "k_large"; break;
+    case Path::matrix: out->kernel = r.plan.rows ? "k_rows" : "k_matrix"; break;
+    }
+    if (r.plan.taken()) tst::matrix_tile(r.plan, M, out);
+    return TSTGEMM_OK;
 }
 
 int tstgemm(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K, int N, void *stream)

@@ -936,6 +936,14 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
     return rows ? MatrixPlan{true, r.tiles, r.waves} : MatrixPlan{false, p.tile, p.k_slices};
 }
 
+void matrix_tile(const MatrixPlan &p, int M, tstgemm_route_t *out)
+{
+    out->tile_rows = p.rows ? M : kTiles[p.shape].rows;
+    out->tile_cols = p.rows ? 16 * p.shape : kTiles[p.shape].cols;
+    out->k_groups = p.rows ? p.split : kTiles[p.shape].groups;
+    out->k_slices = p.rows ? 1 : p.split;
+}
+
 hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
 {
     const tcsc_layout_t &l = t->layout;
@@ -964,25 +972,25 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
 // 2.6 us + (0.65 + 0.43 M) us per 1000 rows of W, and 3 us more where it deals K to several workgroups (measured
 // M = 1 .. 8, the shapes of rows_plan()).  k_packed stays ahead on one row over many columns (M = 1, 4096 x 11008 7.6
 // against 8.1 us) and on short K (M <= 5, 512 x 16384; M <= 3, 512 x 512).
-bool packed_rows_win(const tcsc_layout_t &l, int M)
+MatrixPlan packed_plan(const tcsc_layout_t &l, int M)
 {
-    if (l.K > kMaxExtent || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return false;
+    if (l.K > kMaxExtent || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return MatrixPlan{};
     const int units = compute_units(), groups = l.n_pad / 64;
     int parts = 2 * groups <= units && M * l.n_chunks5 >= 400 ? units / groups : 1;
     if (parts > 4) parts = 4;
     const double rounds = ceil((double)groups * parts / units);
     const double other = 2.6 + rounds * l.K / parts * 1e-3 * (0.65 + 0.43 * M) + (parts > 1 ? 3.0 : 0.0);
-    return rows_plan(l, M, true).us < other;
+    const RowsPlan r = rows_plan(l, M, true);
+    return r.us < other ? MatrixPlan{true, r.tiles, r.waves} : MatrixPlan{};
 }
 
-hipError_t launch_packed_rows(const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
+hipError_t launch_packed_rows(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
 {
     const tcsc_layout_t &l = t->layout;
     MatrixArgs a{};
     a.X = X; a.masks = reinterpret_cast<const uint4v *>(device_view(t).packed); a.b = b; a.Y = Y;
     a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_chunks5;
-    const RowsPlan r = rows_plan(l, M, true);
-    return launch_rows<true>(a, MatrixPlan{true, r.tiles, r.waves}, c);
+    return launch_rows<true>(a, p, c);
 }
 
 }  // namespace tst

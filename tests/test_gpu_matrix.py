@@ -23,11 +23,15 @@ def tight(Y, Yd, A, what):
 
 
 # rows: 32- and 64-row tiles and one more or less; K: below, at and above steps of 32, blocks of 64, groups and slices of
-# them, not a multiple of 4; N: columns of a fragment, of a tile, odd
-@pytest.mark.parametrize("M,K,N", [(11, 1, 1), (31, 31, 33), (32, 32, 32), (33, 33, 31), (64, 64, 64), (63, 65, 130),
-                                   (65, 127, 63), (17, 257, 300), (100, 515, 129), (129, 1027, 257), (255, 2050, 255),
-                                   (257, 64, 1025), (40, 8195, 100), (700, 333, 700), (1025, 100, 513),
-                                   (1300, 4100, 5000), (2049, 2053, 4100)])
+# them, not a multiple of 4; N: columns of a fragment, of a tile, odd.  Every tile shape is taken with K whole and in slices
+# (test_host_api.py has the list).
+EDGES = [(11, 1, 1), (31, 31, 33), (32, 32, 32), (33, 33, 31), (64, 64, 64), (63, 65, 130), (65, 127, 63), (17, 257, 300),
+         (100, 515, 129), (129, 1027, 257), (255, 2050, 255), (257, 64, 1025), (40, 8195, 100), (700, 333, 700), (1025, 100, 513),
+         (1300, 4100, 5000), (2049, 2053, 4100), (36, 985, 23), (297, 2355, 1685), (777, 3001, 2999), (255, 4033, 4031),
+         (1410, 1529, 1955), (640, 4099, 4099)]
+
+
+@pytest.mark.parametrize("M,K,N", EDGES)
 def test_tile_edges(M, K, N):
     W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=700 + M + K + N)
     ot = oracle.tcsc_build(W)

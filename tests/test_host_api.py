@@ -230,6 +230,64 @@ def test_workspace_bytes():
     assert lib.tstgemm_workspace_bytes(0, 1, 1, None, None) == -1 and lib.tstgemm_workspace_bytes(1, 1, 1, None, None) == 0
 
 
+def empty_matrix(K, N):
+    none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
+    return tg.tcsc_from_arrays(starts, starts, none, none, K, N)
+
+
+def test_routes_of_calls():
+    """tstgemm_query_route(): the kernel of a call by its encoding, M, forms, workspace and options; no form or a bad option is
+    refused as the call refuses it."""
+    W, _, _ = si.make_inputs(1, 1000, 2000, 0.5, "uniform", seed=160)
+    t = tg.tcsc_build(W)
+
+    def kernel(M, forms=tg.FORM_ALL, **options):
+        tg.tcsc_select_forms(t, forms)
+        return tg.tstgemm_query_route(t, M, **options).kernel
+
+    assert [kernel(M) for M in (1, 8, 9, 17, 64, 65, 1000)] == ["k_rows"] * 3 + ["k_matrix"] * 4
+    assert [kernel(M, encoding=1) for M in (1, 8)] == ["k_decode_signed"] * 2
+    assert kernel(8, encoding=2) == "k_rows_packed" and kernel(8, encoding=2, k_slices=1) == "k_packed"
+    # without the row sets, with a launch shape, with less scratch than the tiled paths need
+    assert kernel(8, tg.FORM_LISTS16) == kernel(8, 0) == kernel(8, wide_lists=True) == "k_decode"
+    assert kernel(64, tg.FORM_CUTS) == kernel(64, tg.FORM_CUTS | tg.FORM_ROWSETS) == "k_small"
+    assert kernel(64, tg.FORM_CUTS | tg.FORM_ROWSETS, workspace_bytes=1 << 20) == "k_matrix"
+    assert kernel(100, tg.FORM_ROWSETS) == "k_large" and kernel(100, tg.FORM_ROWSETS, workspace_bytes=1 << 20) == "k_matrix"
+    for option in (dict(cols_per_wave=4), dict(k_slices=2), dict(slab_tiles=1), dict(list_walk=1)):
+        assert (kernel(8, **option), kernel(64, **option), kernel(65, **option)) == ("k_rows", "k_small", "k_large")
+    for M, forms, options, code in ((64, tg.FORM_ROWSETS, {}, -7), (65, tg.FORM_CUTS, {}, -7), (8, 0, dict(encoding=1), -7),
+                                    (8, 0, dict(encoding=2), -7), (9, tg.FORM_ALL, dict(encoding=2), -1), (0, tg.FORM_ALL, {}, -1),
+                                    (9, tg.FORM_ALL, dict(cols_per_wave=3), -1)):
+        with pytest.raises(tg.TstgemmError) as e:
+            kernel(M, forms, **options)
+        assert e.value.code == code
+
+
+def test_routes_of_extreme_calls():
+    """Where 32-bit offsets and launches end: K beyond 2^22, row sets of 4 GiB, and tiles of 2^32 threads and more go to the
+    kernels that have no such limit."""
+    def route(K, N, M):
+        return tg.tstgemm_query_route(empty_matrix(K, N), M, workspace_bytes=1 << 40)
+
+    assert route(1 << 22, 64, 100).kernel == "k_matrix" and route((1 << 22) + 1, 64, 100).kernel == "k_large"
+    assert route(1 << 22, 4032, 100).kernel == "k_matrix" and route(1 << 22, 4160, 100).kernel == "k_large"
+    last = route(1, 1, (1 << 30) - 64)
+    assert (last.kernel, last.tile_rows, last.tile_cols) == ("k_matrix", 64, 128)
+    assert route(1, 1, 1 << 30).kernel == route(1, 1, (1 << 31) - 1).kernel == "k_large"
+
+
+def test_matrix_core_tests_take_every_tile():
+    """The shapes of test_gpu_matrix.py reach each of the six tile shapes with K whole and in slices."""
+    from test_gpu_matrix import EDGES
+    taken = set()
+    for M, K, N in EDGES:
+        r = tg.tstgemm_query_route(tg.tcsc_build(si.draw_ternary(np.random.default_rng(1), K, N, 0.5)), M)
+        assert r.kernel == "k_matrix"
+        taken.add((r.tile_rows, r.tile_cols, r.k_groups, r.k_slices > 1))
+    tiles = [(64, 512, 1), (64, 256, 1), (64, 256, 2), (64, 128, 1), (32, 64, 4), (32, 128, 2)]
+    assert taken == {tile + (sliced,) for tile in tiles for sliced in (False, True)}
+
+
 def test_too_many_entries_for_the_signed_form():
     """The inverted-index form numbers the entries of both signs together with 32-bit positions: arrays whose two
     lists have more than 2^31 - 1 entries together are refused before anything is read."""
