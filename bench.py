@@ -37,30 +37,18 @@ PEAK_ALU_INSTR_T = 256 * 64 * 2.4e9 / 1e12     # vector lane-instructions per se
 # HBM bytes (read + written) of one launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
 # script, each counter scaled by what it reads for a copy kernel of known size in the same run.  A counter run cannot
 # be part of a timed run, so these are constants: (bytes, the tracked summary they come from).  Keyed by (workload,
-# variant); workloads without a counter run report null.
+# kernel); workloads without a counter run report null.
 _T_ALL = "profiles/hbm_traffic_all_configs.md"
 _T_OTHER = "profiles/hbm_traffic_other_workloads.md"
 MEASURED_TRAFFIC = {
-    ("C1", "tcsc"): (1820253, _T_ALL), ("C2", "tcsc"): (46305018, _T_ALL), ("C3a", "tcsc"): (46361795, _T_ALL),
-    ("C3b", "tcsc"): (46404792, _T_ALL), ("C4-1", "tcsc"): (46039073, _T_ALL), ("C4-8", "tcsc"): (47360812, _T_ALL),
-    ("C5a", "tcsc"): (929168828, _T_ALL), ("C5b", "tcsc"): (922709707, _T_ALL), ("C5c", "tcsc"): (902583812, _T_ALL),
-    ("M64-K16384-N4096-d0.5", "tcsc"): (163358221, _T_OTHER),
-    ("C4-1", "packed"): (9610285, _T_OTHER), ("C4-8", "packed"): (11881214, _T_OTHER),
+    ("C1", "k_matrix"): (947109, _T_ALL), ("C2", "k_matrix"): (42220854, _T_ALL), ("C3a", "k_matrix"): (42221048, _T_ALL),
+    ("C3b", "k_matrix"): (42220905, _T_ALL), ("C4-1", "k_rows"): (11621610, _T_ALL), ("C4-8", "k_rows"): (12881026, _T_ALL),
+    ("C5a", "k_matrix"): (808063679, _T_ALL), ("C5b", "k_matrix"): (808058858, _T_ALL), ("C5c", "k_large"): (902535837, _T_ALL),
+    ("M64-K16384-N4096-d0.5", "k_matrix"): (60309157, _T_OTHER),
+    ("C4-1", "k_packed"): (9610282, _T_OTHER), ("C4-8", "k_rows_packed"): (10809682, _T_OTHER),
 }
 ORACLE_FLAGS = "gcc -O3 -fstrict-aliasing -DNDEBUG -fopenmp (the paper's flags, Sec. 4, without -march=native)"
 INFINITY_CACHE_BYTES = 256 << 20
-
-
-def takes_matrix_cores(M, K, N, n_pad, density, cus):
-    """Whether a call with M > 8 and no launch-shape override goes through the matrix cores: the library's own rule
-    (tstgemm_matrix.hip, matrix_plan) with its estimate of the matrix-core time at the power limit, which is the larger
-    one wherever the row-set kernel can be ahead."""
-    if M > 64:
-        if n_pad % 128:
-            return True
-        rounds = -(-(-(-M // 256) * (n_pad // 128)) // (2 * cus))
-        return 6.0 * (-(-M // 64) * 64) * n_pad * K / 1.61e9 + 3.36 < 20.0 + rounds * K * (0.0281 + 0.464 * density)
-    return True                 # (and for M <= 64 wherever a column list is not extremely short)
 
 
 def cpu_baseline(W, X, b, nnz, variant="tcsc", budget_s=10.0):
@@ -244,27 +232,22 @@ def main():
     steps = args.steps if args.steps is not None else int(min(5000, max(20, 500.0 / est_ms)))
     warmup = args.warmup if args.warmup is not None else 10
 
-    decode = wl.M <= 8          # the library's rules for its decode kernel ...
-    small = 8 < wl.M <= 64      # ... and its small-tile kernel
-    shaped = args.cols_per_wave or getattr(args, "k_slices", 0) or getattr(args, "slab_tiles", 0) or getattr(args, "list_walk", 0)
-    matrix = (not decode and args.variant == "tcsc" and not shaped and
-              takes_matrix_cores(wl.M, wl.K, wl.N, lay.n_pad, nnz / (wl.K * wl.N),
-                                 torch.cuda.get_device_properties(0).multi_processor_count))
-    # ... whose place k_rows (matrix cores) takes, for the lists except where W is sparse or a few columns meet a long K,
-    # for the base-3 codes except with one row over many columns or a short K (matrix_plan, packed_rows_win)
-    rows = decode and not shaped and (
-        (args.variant == "tcsc" and not args.wide_lists and nnz >= 0.2 * wl.K * wl.N and wl.N >= 1024) or
-        (args.variant == "packed" and wl.K > 1024 and (wl.M > 1 or wl.N <= 8192)))
+    # the kernel that the library launches for these calls, by its own rule
+    tuning = {k: v for k, v in (("cols_per_wave", args.cols_per_wave), ("k_slices", args.k_slices),
+                                ("wide_lists", args.wide_lists), ("list_walk", args.list_walk)) if v}
+    route = tg.tstgemm_query_route(t, wl.M, encoding={"tcsc": 0, "signed": 1, "packed": 2}[args.variant], **tuning)
+    kernel = route.kernel
+    decode = wl.M <= 8
+    matrix = kernel == "k_matrix"
+    rows = kernel in ("k_rows", "k_rows_packed")
     # index data one call reads (what must not be in the Infinity Cache for an HBM figure)
-    narrow = (decode and not rows and args.variant == "tcsc" and bool(lay.has_lists16) and not args.wide_lists
+    narrow = (kernel == "k_decode" and bool(lay.has_lists16) and not args.wide_lists
               and wl.K <= 150 * 1024 // (4 * wl.M) - 1)   # the library's rule for its padded 16-bit lists
     if args.variant == "packed":
         index_bytes = lay.n_chunks5 * lay.n_pad * 16
-    elif rows:
-        index_bytes = 16 * lay.n_kblocks * lay.n_pad
-    elif decode:
+    elif kernel in ("k_decode", "k_decode_signed"):
         index_bytes = 2 * (lay.nnz16_pos + lay.nnz16_neg) if narrow else 4 * nnz
-    elif small:
+    elif kernel == "k_small":
         index_bytes = 4 * nnz + 8 * (lay.n_cuts + 1) * lay.n_pad
     else:
         index_bytes = 16 * lay.n_kblocks * lay.n_pad
@@ -278,9 +261,6 @@ def main():
     stream = torch.cuda.current_stream()
     copies = [t] + [tg.tcsc_upload(tg.tcsc_build(W)) for _ in range(n_copies - 1)]
     turn = [0]
-
-    tuning = {k: v for k, v in (("cols_per_wave", args.cols_per_wave), ("k_slices", args.k_slices),
-                                ("wide_lists", args.wide_lists), ("list_walk", args.list_walk)) if v}
 
     def gemm_next(**options):
         h = copies[turn[0] % len(copies)]
@@ -366,20 +346,19 @@ def main():
     kernel_ms = kernel_raw_ms - pair_ms
     kernel_ms_median = float(np.median(kernel_raw)) - pair_ms
     kernel_ms_min = float(np.min(kernel_raw)) - pair_ms
-    if decode:
-        # The M <= 8 paths are ONE kernel per call: the time per call of the back-to-back timed region is that kernel's
+    if decode or rows:
+        # The paths for few rows are ONE kernel per call: the time per call of the back-to-back timed region is that kernel's
         # time (with the gap between two launches), and it is what agrees with the profiler's average duration; the
         # event pair between two such kernels delays them and then takes off too much.
         kernel_ms, kernel_ms_median, kernel_ms_min = call_ms, float(np.median(region_ms)), float(np.min(region_ms))
 
-    measured = MEASURED_TRAFFIC.get((wl.name, args.variant))
+    measured = MEASURED_TRAFFIC.get((wl.name, kernel))
     traffic = measured[0] if measured else None
     if rows:
-        # the row sets or codes once, each entry of W one product of three planes; the constants were of other kernels
-        traffic = measured = None
+        # the row sets or codes once, each entry of W one product of three planes
         alg_bytes = index_bytes + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
         roof = {"bound": "hbm", "achieved": alg_bytes / (kernel_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
-                "unit": "GB/s", "traffic": None}
+                "unit": "GB/s", "traffic": traffic}
     elif args.variant == "packed":
         # dense decode: every entry of the padded W costs one conversion and M multiply-adds on the vector ALUs
         # (256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-instructions/s); the codes are 1.6 bits per entry
@@ -399,9 +378,8 @@ def main():
     elif matrix:
         # the row sets, X, Y and b once; the work is the dense one, whatever the density
         alg_bytes = 16 * lay.n_kblocks * lay.n_pad + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
-        traffic = measured = None      # the counter runs behind the constants were of the gather kernels
         roof = {"bound": "mfma", "achieved": 6.0 * wl.M * wl.K * wl.N / (kernel_ms * 1e-3) / 1e12, "peak": PEAK_BF16_TFLOPS,
-                "unit": "TFLOP/s", "traffic": None,
+                "unit": "TFLOP/s", "traffic": traffic,
                 "note": "three bf16 planes of X times W, zeros included: 6 M K N operations; peak = dense bf16"}
     else:
         # index data the kernel reads (small tile: the TCSC row numbers and the list cuts; else the 64-bit row sets)
@@ -413,10 +391,11 @@ def main():
                         "2.4 GHz; the fp32 add rate of the vector ALUs (alu_add_peak) is twice that",
                 "alu_add_peak": PEAK_ALU_ADD_TFLOPS}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    roof["kernel"] = ("k_rows" if rows else "k_packed" if args.variant == "packed" else "k_decode (signed lists)" if args.variant == "signed"
-                      else "k_decode" if decode else "k_matrix" if matrix else "k_small" if small else "k_large")
-    if decode and not rows and args.variant == "tcsc":
+    roof["kernel"] = kernel
+    if kernel == "k_decode":
         roof["kernel"] += " (16-bit lists)" if narrow else " (32-bit lists)"
+    elif matrix:
+        roof["kernel"] += f" ({route.tile_rows} x {route.tile_cols} tiles, {route.k_groups} groups, {route.k_slices} slices of K)"
     roof["kernel_ms"] = kernel_ms
     roof["kernel_ms_median"] = kernel_ms_median
     roof["kernel_ms_min"] = kernel_ms_min
@@ -435,7 +414,7 @@ def main():
     roof["call_ms_median"] = float(np.median(region_ms))
     roof["call_ms_min"] = float(np.min(region_ms))
     roof["call_frac"] = roof["frac"] * kernel_ms / call_ms   # the same work over the time of the whole call
-    if not decode and not matrix:
+    if kernel in ("k_small", "k_large"):
         roof["alu_frac"] = roof["achieved"] / PEAK_ALU_ADD_TFLOPS
         # What this build can reach at most: without packed fp32 a compute unit issues one vector instruction per
         # clock (64 lanes), which is the same 39.3 T lane-operations/s as the LDS port's gathers, and every 16-byte
@@ -443,7 +422,7 @@ def main():
         # C2 at nine tenths of it (counters: profiles/shader_counters_all_configs.md).
         roof["valu_issue_bound"] = PEAK_LDS_GATHER_TFLOPS * 4.0 / 5.0
         roof["frac_of_valu_issue_bound"] = roof["achieved"] / roof["valu_issue_bound"]
-    if not decode and not small and not matrix:
+    if kernel == "k_large":
         # Bytes the main kernel copies from the packed X (in the L2s) into the LDS: every workgroup one K-block of its
         # row tile (64 rows of W x TM rows of X x 4 bytes) per K-block it walks, whatever the density.  The columns
         # per workgroup follow the library's own rule for its launch shape (tstgemm_large.hip, choose_shape), restated
