@@ -22,6 +22,28 @@ def gpu_tstgemm(W, X, b, handle=None, alpha=None, **options):
     return Yd.cpu().numpy(), handle
 
 
+def kernel_choice(M, path):
+    """(forms, options) of an upload and a call with M rows of X.  path "own": the library's choice with every form there.
+    "lists": the list or row-set kernel for this M, which also serves sparse matrices and handles without row sets, in the
+    launch shape that it chooses by itself (M > 64: a bound on the slab that no call reaches asks for it)."""
+    if path == "own":
+        return tg.FORM_ALL, {}
+    if M <= 8:
+        return tg.FORM_LISTS16, {}
+    if M <= 64:
+        return tg.FORM_CUTS | tg.FORM_WORKSPACE, {}
+    return tg.FORM_ROWSETS | tg.FORM_WORKSPACE, dict(slab_tiles=1 << 20)
+
+
+def upload_for(W, M, path):
+    """(handle, options) for kernel_choice(M, path); the "lists" kernels by name."""
+    forms, options = kernel_choice(M, path)
+    t = tg.tcsc_upload(tg.tcsc_build(W), forms=forms)
+    if path == "lists":
+        assert tg.tstgemm_query_route(t, M, **options).kernel == ("k_decode" if M <= 8 else "k_small" if M <= 64 else "k_large")
+    return t, options
+
+
 def assert_close(Y, Yd, A, what=""):
     err = np.abs(Y.astype(np.float64) - Yd)
     bad = ~(err <= REL_TOL * A)

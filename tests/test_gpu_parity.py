@@ -7,7 +7,7 @@ import pytest
 import oracle
 import paper_2510_06957_amd as tg
 import synth_inputs as si
-from gpu_util import assert_close, assert_exact, decode_device_form, gpu_tstgemm
+from gpu_util import assert_close, assert_exact, decode_device_form, gpu_tstgemm, upload_for
 
 pytestmark = pytest.mark.gpu
 
@@ -70,14 +70,16 @@ def test_degenerate_matrices(M):
     assert np.array_equal(Y[:, 2:], X[:, pick])
 
 
-def test_zero_weight_entries_of_x_are_never_read():
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_zero_weight_entries_of_x_are_never_read(path):
     """Gather semantics (additions and subtractions only, Sec. 2): a non-finite X entry whose weights are all zero
     must not reach Y -- also not through the padding of the index streams."""
-    for M in (4, 80):
+    for M in (4, 40, 80):
         W, X, b = si.make_inputs(M, 300, 50, 0.5, "normal", seed=29)
         W[[0, 7, 64, 299], :] = 0
         X[:, [0, 7, 64, 299]] = [np.nan, np.inf, -np.inf, np.nan]
-        Y, _ = gpu_tstgemm(W, X, b)
+        h, options = upload_for(W, M, path)
+        Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
         assert np.all(np.isfinite(Y))
         Xf = X.copy()
         Xf[:, [0, 7, 64, 299]] = 0
@@ -182,13 +184,16 @@ def test_eight_columns_per_wavefront(M, K, N, density):
     assert np.array_equal(Yi, Ydi.astype(np.float32))
 
 
-def test_low_density_tall_and_wide_picks_its_own_shape():
-    """Tall X, wide and sparse W: rows x columns fill the chip with 128-column workgroups, so the library takes the
-    low-density launch shape by itself.  Whole rows and scattered elements against the oracle; integer inputs exact."""
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_low_density_tall_and_wide_picks_its_own_shape(path):
+    """Tall X, wide and sparse W: rows x columns fill the chip with 128-column workgroups, so the row-set kernel takes its
+    low-density launch shape by itself (the library's own choice are the matrix cores here).  Whole rows and scattered
+    elements against the oracle; integer inputs exact."""
     M, K, N = 4096, 200, 4096
     W, X, b = si.make_inputs(M, K, N, 0.05, "uniform", seed=777)
     ot = oracle.tcsc_build(W)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
     rows = np.array([0, 1, 255, 256, 2047, 4095], dtype=np.int32)
     Yd, A, _ = oracle.tstgemm(X, ot, b, rows=rows)
     assert_close(Y[rows], Yd, A, "rows")
@@ -197,7 +202,7 @@ def test_low_density_tall_and_wide_picks_its_own_shape():
     Yp, Ap = oracle.tstgemm_points(X, ot, b, ms, ns)
     assert_close(Y[ms, ns], Yp, Ap, "points")
     Xi = si.draw_dense(np.random.Generator(np.random.PCG64(5)), X.shape, "int8")
-    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h)
+    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h, **options)
     Ydi, _, _ = oracle.tstgemm(Xi, ot, b, rows=rows)
     assert np.array_equal(Yi[rows], Ydi.astype(np.float32))
 
@@ -247,26 +252,30 @@ def test_small_tile_slice_lengths(M, K, N, density, list_walk):
 
 @pytest.mark.parametrize("M,K,N,density", [(40, 40000, 70, 0.25), (64, 300, 20000, 0.5), (20, 70000, 33, 0.0625),
                                            (9, 513, 30000, 0.125)])
-def test_small_tile_long_k_and_wide_n(M, K, N, density):
-    """The small-tile path with many blocks of K per workgroup (more than eight K slices' worth) and with thousands of
-    column groups."""
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_small_tile_long_k_and_wide_n(M, K, N, density, path):
+    """The small-tile path (and whatever the library takes by itself) with many blocks of K per workgroup (more than eight K
+    slices' worth) and with thousands of column groups."""
     W, X, b = si.make_inputs(M, K, N, density, "normal", seed=71 + M)
     _, Xi, _ = si.make_inputs(M, K, N, density, "int8", seed=72 + M)
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
     assert_close(Y, Yd, A, f"{M}x{K}x{N}")
-    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h)
+    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h, **options)
     assert np.array_equal(Yi, oracle.tstgemm(Xi, ot, b)[0].astype(np.float32))
 
 
-def test_very_tall_x():
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_very_tall_x(path):
     """M = 70000 rows against a small matrix: hundreds of row tiles, several of them per workgroup column."""
     M, K, N = 70000, 70, 33
     W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=95)
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
     assert_close(Y, Yd, A, f"{M}x{K}x{N}")
     # the same through slabs of three row tiles; K is then sliced, which is another summation order: the oracle is
     # the yardstick again
@@ -274,40 +283,45 @@ def test_very_tall_x():
     assert_close(Y3, Yd, A, f"{M}x{K}x{N} in slabs")
 
 
-def test_very_tall_x_wide_columns():
-    """Tall X against 256 columns: enough (row tile, 128-column group) pairs for the shape with 8 columns per
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_very_tall_x_wide_columns(path):
+    """Tall X against 256 columns: enough (row tile, 128-column group) pairs for the row-set kernel's shape with 8 columns per
     wavefront to be taken by itself; the same forced through slabs of three row tiles."""
     M, K, N = 70000, 70, 256
     W, X, b = si.make_inputs(M, K, N, 0.3, "normal", seed=96)
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
     assert_close(Y, Yd, A, f"{M}x{K}x{N}")
     Y3, _ = gpu_tstgemm(W, X, b, handle=h, cols_per_wave=8, slab_tiles=3)
     assert_close(Y3, Yd, A, f"{M}x{K}x{N} in slabs, 8 columns per wavefront")
 
 
+@pytest.mark.parametrize("path", ["own", "lists"])
 @pytest.mark.parametrize("M", [3, 40, 130, 300])
-def test_very_long_k(M):
+def test_very_long_k(M, path):
     """K = 100000 (1563 K-blocks, 391 list cuts, several LDS chunks of the decode kernel) with a handful of columns:
     every path with far more blocks of K per workgroup than any benchmark shape has."""
     K, N = 100000, 70
     W, X, b = si.make_inputs(M, K, N, 0.25, "normal", seed=91 + M)
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
     assert_close(Y, Yd, A, f"{M}x{K}x{N}")
     Xi = si.draw_dense(np.random.Generator(np.random.PCG64(92)), X.shape, "int8")
-    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h)
+    Yi, _ = gpu_tstgemm(W, Xi, b, handle=h, **options)
     assert np.array_equal(Yi, oracle.tstgemm(Xi, ot, b)[0].astype(np.float32))
 
 
 @pytest.mark.parametrize("M,K,N", [(70, 130, 67), (300, 516, 100), (6, 130, 40), (40, 130, 67)])
-def test_unaligned_operands(M, K, N):
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_unaligned_operands(M, K, N, path):
     """X, b and Y that start 4 bytes off a 16-byte boundary (views into larger tensors): the element-wise paths."""
     import torch
     W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=43)
-    t = tg.tcsc_upload(tg.tcsc_build(W))
+    t, options = upload_for(W, M, path)
     Xbuf = torch.zeros(M * K + 1, dtype=torch.float32, device="cuda")
     bbuf = torch.zeros(N + 1, dtype=torch.float32, device="cuda")
     Ybuf = torch.full((M * N + 1,), float("nan"), dtype=torch.float32, device="cuda")
@@ -315,7 +329,7 @@ def test_unaligned_operands(M, K, N):
     assert Xd.data_ptr() % 16 == 4
     Xd.copy_(torch.from_numpy(X))
     bd.copy_(torch.from_numpy(b))
-    tg.tstgemm(Xd, t, bd, Yd_)
+    tg.tstgemm(Xd, t, bd, Yd_, **options)
     torch.cuda.synchronize()
     Yd, A, _ = oracle.tstgemm(X, oracle.tcsc_build(W), b)
     assert_close(Yd_.cpu().numpy(), Yd, A, f"unaligned {M}x{K}x{N}")
@@ -353,16 +367,19 @@ def test_profile_events_bracket_the_main_kernel():
 @pytest.mark.parametrize("M,K,N", [(1, 300, 70), (8, 513, 65), (40, 700, 130), (40, 2100, 130), (20, 1100, 70),
                                    (200, 640, 96), (300, 1000, 200)])
 @pytest.mark.parametrize("per_column", [False, True])
-def test_prelu_epilogue(M, K, N, per_column):
-    """The fused PReLU (after the bias add) in the decode kernel, the small-tile and large-M kernels and the split-K
-    reduction kernel, against the oracle's; integer inputs with power-of-two slopes bit for bit."""
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_prelu_epilogue(M, K, N, per_column, path):
+    """The fused PReLU (after the bias add) in the decode kernel, the small-tile and large-M kernels, the split-K
+    reduction kernel and those on the matrix cores, against the oracle's; integer inputs with power-of-two slopes bit for
+    bit."""
     W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=61 + M)
     rng = np.random.default_rng(62)
     alpha = rng.uniform(-1.5, 2.5, N).astype(np.float32) if per_column else np.array([0.25], np.float32)
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
     Yp, Ap = oracle.prelu(Yd, A, alpha)
-    Y, h = gpu_tstgemm(W, X, b, alpha=alpha)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, alpha=alpha, **options)
     assert (Yd < 0).any() and (Yd > 0).any()
     assert_close(Y, Yp, Ap, f"prelu {M}x{K}x{N}")
     # exact: integer X and b, slopes that are powers of two
@@ -371,7 +388,7 @@ def test_prelu_epilogue(M, K, N, per_column):
         if per_column else np.array([0.5], np.float32)
     Ydi, _, _ = oracle.tstgemm(Xi, ot, bi)
     Ypi, _ = oracle.prelu(Ydi, None, a2)
-    Yi, _ = gpu_tstgemm(W, Xi, bi, handle=h, alpha=a2)
+    Yi, _ = gpu_tstgemm(W, Xi, bi, handle=h, alpha=a2, **options)
     assert_exact(Yi, Ypi, f"prelu integer {M}x{K}x{N}")
 
 
@@ -427,25 +444,26 @@ def test_decode_k_chunks(M, K, N):
     assert_exact(Yi, Ydi, f"decode chunks integer {M}x{K}x{N}")
 
 
+@pytest.mark.parametrize("path", ["own", "lists"])
 @pytest.mark.parametrize("M", [4, 40, 300])
-def test_calls_can_be_captured_in_a_hip_graph(M):
+def test_calls_can_be_captured_in_a_hip_graph(M, path):
     """tstgemm() enqueues kernels only (no allocation, no host synchronisation, no memset), so a stream capture
     records it; every replay, with new contents of X in the same buffer and eager work in between, must give
     the eager result bit for bit."""
     import torch
     K, N = 700, 200
     W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=81 + M)
-    t = tg.tcsc_upload(tg.tcsc_build(W))
+    t, options = upload_for(W, M, path)
     Xd = torch.from_numpy(X).cuda()
     bd = torch.from_numpy(b).cuda()
     Yg = torch.empty((M, N), dtype=torch.float32, device="cuda")
-    tg.tstgemm(Xd, t, bd, Yg)                       # first call outside the capture (one-time kernel attributes)
+    tg.tstgemm(Xd, t, bd, Yg, **options)            # first call outside the capture (one-time kernel attributes)
     torch.cuda.synchronize()
     side = torch.cuda.Stream()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.stream(side):
         with torch.cuda.graph(graph, stream=side):
-            tg.tstgemm(Xd, t, bd, Yg, stream=side)
+            tg.tstgemm(Xd, t, bd, Yg, stream=side, **options)
     torch.cuda.synchronize()
     rng = np.random.default_rng(82)
     for rep in range(4):
@@ -455,18 +473,19 @@ def test_calls_can_be_captured_in_a_hip_graph(M):
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        Ye = tg.tstgemm(Xd, t, bd)                  # eager, same inputs
+        Ye = tg.tstgemm(Xd, t, bd, **options)       # eager, same inputs
         torch.cuda.synchronize()
         assert torch.equal(Yg, Ye), f"replay {rep}"
         Yd, A, _ = oracle.tstgemm(Xn, oracle.tcsc_build(W), b)
         assert_close(Yg.cpu().numpy(), Yd, A, f"graph replay {rep}")
 
 
-def test_handles_share_one_workspace_and_streams_run_side_by_side():
+@pytest.mark.parametrize("path", ["own", "lists"])
+def test_handles_share_one_workspace_and_streams_run_side_by_side(path):
     """Matrices uploaded without a workspace of their own: two of them go through ONE caller-supplied workspace on one
     stream, call after call, while a third runs on a second stream with a workspace of its own; every result against
     the oracle, integer inputs bit for bit.  The shapes take the large-M path (with K slices), the small-tile path and
-    the large-M path again."""
+    the large-M path again, or the matrix cores where the choice is the library's."""
     import torch
     shapes = [(256, 1024, 512), (40, 2100, 130), (300, 700, 200)]
     forms = tg.FORM_ROWSETS | tg.FORM_CUTS
@@ -482,13 +501,17 @@ def test_handles_share_one_workspace_and_streams_run_side_by_side():
     own = torch.empty(need[2][1], dtype=torch.uint8, device="cuda")
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
     torch.cuda.synchronize()
+    options = {} if path == "own" else dict(slab_tiles=1 << 20)   # (any launch-shape option asks for the list kernels)
+    for (M, _, _), (t, _, _, _, _) in zip(shapes, problems):
+        taken = tg.tstgemm_query_route(t, M, workspace_bytes=own.numel(), **options).kernel
+        assert taken == ("k_matrix" if path == "own" else "k_small" if M <= 64 else "k_large")
     outs = [[], [], []]
     for rep in range(3):
         for i in (0, 1):
             t, Xd, bd, _, _ = problems[i]
-            outs[i].append(tg.tstgemm(Xd, t, bd, stream=s1, workspace=shared))
+            outs[i].append(tg.tstgemm(Xd, t, bd, stream=s1, workspace=shared, **options))
         t, Xd, bd, _, _ = problems[2]
-        outs[2].append(tg.tstgemm(Xd, t, bd, stream=s2, workspace=own))
+        outs[2].append(tg.tstgemm(Xd, t, bd, stream=s2, workspace=own, **options))
     torch.cuda.synchronize()
     for i, (t, Xd, bd, Yd, A) in enumerate(problems):
         for Y in outs[i]:
@@ -500,16 +523,16 @@ def test_handles_share_one_workspace_and_streams_run_side_by_side():
     # no workspace at all, one below the minimum, a form that was not uploaded
     t, Xd, bd, _, _ = problems[0]
     with pytest.raises(tg.TstgemmError) as err:
-        tg.tstgemm(Xd, t, bd)
+        tg.tstgemm(Xd, t, bd, **options)
     assert err.value.code == -8
     with pytest.raises(tg.TstgemmError) as err:
-        tg.tstgemm(Xd, t, bd, workspace=shared[:need[0][0] - 256])
+        tg.tstgemm(Xd, t, bd, workspace=shared[:need[0][0] - 256], **options)
     assert err.value.code == -8
     with pytest.raises(tg.TstgemmError) as err:
         tg.tstgemm_signed(Xd[:4].contiguous(), t, bd)
     assert err.value.code == -7
     # the minimum is enough (K is then not sliced; another summation order, the oracle decides)
-    Ymin = tg.tstgemm(Xd, t, bd, workspace=shared[:need[0][0]])
+    Ymin = tg.tstgemm(Xd, t, bd, workspace=shared[:need[0][0]], **options)
     torch.cuda.synchronize()
     assert_close(Ymin.cpu().numpy(), problems[0][3], problems[0][4], "minimum workspace")
 
@@ -555,6 +578,9 @@ def test_random_shapes_and_densities():
         Xi = si.draw_dense(np.random.Generator(np.random.PCG64(6000 + case)), X.shape, "int8")
         Yi, _ = gpu_tstgemm(W, Xi, b, handle=h)
         assert np.array_equal(Yi, oracle.tstgemm(Xi, ot, b)[0].astype(np.float32)), f"case {case}: {M}x{K}x{N}"
+        hl, options = upload_for(W, M, "lists")
+        assert_close(gpu_tstgemm(W, X, b, handle=hl, **options)[0], Yd, A, f"case {case}, lists: {M}x{K}x{N} d={density}")
+        assert np.array_equal(gpu_tstgemm(W, Xi, b, handle=hl, **options)[0], Yi), f"case {case}, lists: {M}x{K}x{N}"
         if M <= 8:
             import torch
             Xd = torch.from_numpy(Xi).cuda()
@@ -565,9 +591,10 @@ def test_random_shapes_and_densities():
                 assert np.array_equal(Yv.cpu().numpy(), Yi), f"case {case} {fn.__name__}: {M}x{K}x{N}"
 
 
+@pytest.mark.parametrize("path", ["own", "lists"])
 @pytest.mark.parametrize("M,K,N", [(1, 300, 70), (8, 513, 65), (3, 4096, 200), (8, 8229, 70), (1, 30000, 40),
                                    (5, 65535, 33), (2, 65536, 20), (4, 70000, 9)])
-def test_decode_list_widths(M, K, N):
+def test_decode_list_widths(M, K, N, path):
     """The small-M kernel on the padded 16-bit copy of the lists (K <= 65535, X whole in the LDS) and on the 32-bit TCSC
     arrays: both within tolerance of the oracle, integer inputs bit for bit; K in chunks or beyond 16 bits takes the
     32-bit arrays either way."""
@@ -576,7 +603,8 @@ def test_decode_list_widths(M, K, N):
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
     Ydi = oracle.tstgemm(Xi, ot, b)[0].astype(np.float32)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, _ = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h)
     assert tg.tcsc_layout(h).has_lists16 == (1 if K <= 65535 else 0)
     assert_close(Y, Yd, A, f"{M}x{K}x{N}")
     assert np.array_equal(gpu_tstgemm(W, Xi, b, handle=h)[0], Ydi)
@@ -586,23 +614,26 @@ def test_decode_list_widths(M, K, N):
     assert np.array_equal(Ywi, Ydi)
 
 
+@pytest.mark.parametrize("path", ["own", "lists"])
 @pytest.mark.parametrize("M", [1, 2])
 @pytest.mark.parametrize("K,N", [(300, 9000), (300, 8192), (257, 33000), (4096, 70), (64, 11008)])
-def test_decode_whole_columns_and_dealt_lists(M, K, N):
+def test_decode_whole_columns_and_dealt_lists(M, K, N, path):
     """One or two rows of X on the 16-bit lists: the launch either gives every wavefront whole columns or deals the
     lists of a run of columns to the wavefronts of a workgroup, depending on how well whole columns fill the chip
     (on 256 compute units: 8192 and 70 columns whole, 9000, 11008 and 33000 dealt, the last with more columns per
-    workgroup than it keeps sums for at a time).  PReLU and the bias go through the same epilogue in both."""
+    workgroup than it keeps sums for at a time).  PReLU and the bias go through the same epilogue in both.  (With the row
+    sets there most of these shapes go to the matrix cores.)"""
     W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=131 + M + N)
     _, Xi, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=132 + M + N)
     W[:, 3] = 0          # an empty column
     W[:, 4] = 1          # a column without a -1 list
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
-    Y, h = gpu_tstgemm(W, X, b)
+    h, options = upload_for(W, M, path)
+    Y, _ = gpu_tstgemm(W, X, b, handle=h, **options)
     assert_close(Y, Yd, A, f"{M}x{K}x{N}")
-    assert np.array_equal(gpu_tstgemm(W, Xi, b, handle=h)[0], oracle.tstgemm(Xi, ot, b)[0].astype(np.float32))
+    assert np.array_equal(gpu_tstgemm(W, Xi, b, handle=h, **options)[0], oracle.tstgemm(Xi, ot, b)[0].astype(np.float32))
     alpha = np.linspace(-0.5, 1.5, N).astype(np.float32)
-    Ya, _ = gpu_tstgemm(W, X, b, handle=h, alpha=alpha)
+    Ya, _ = gpu_tstgemm(W, X, b, handle=h, alpha=alpha, **options)
     Yp, Ap = oracle.prelu(Yd, A, alpha)
     assert_close(Ya, Yp, Ap, f"{M}x{K}x{N} PReLU")

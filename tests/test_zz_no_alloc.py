@@ -56,6 +56,25 @@ def test_noalloc_in_slabs():
     assert_close(Y1, Yd, A, "noalloc in slabs")
 
 
+def test_noalloc_in_slabs_of_the_row_set_kernel():
+    """The row-set kernel, which tall X against sparse and wide W still takes, in slabs of what the static array holds: whole
+    rows of the first, a middle and the last slab against the oracle, the rest against the workspace entry point."""
+    import torch
+    M, K, N = 40000, 512, 4096
+    W, X, b = si.make_inputs(M, K, N, 0.01, "normal", seed=996)
+    t = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_ROWSETS)
+    assert tg.tstgemm_query_route(t, M, workspace_bytes=tg.NOALLOC_SCRATCH_BYTES).kernel == "k_large"
+    assert M * K * 4 > tg.NOALLOC_SCRATCH_BYTES
+    Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda()
+    Y1 = torch.full((M, N), float("nan"), device="cuda")
+    tg.tstgemm_noalloc(Xd, t, bd, Y1)
+    Y2 = tg.tstgemm(Xd, t, bd, workspace=torch.empty(tg.NOALLOC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(Y1, Y2)
+    rows = np.array([0, 1, 255, 20000, 24575, 24576, 39999], dtype=np.int32)
+    Yd, A, _ = oracle.tstgemm(X, oracle.tcsc_build(W), b, rows=rows)
+    assert_close(Y1[torch.from_numpy(rows).long().cuda()].cpu().numpy(), Yd, A, "noalloc, row-set kernel in slabs")
+
+
 def test_noalloc_under_graph_capture():
     """What the entry point is for: a stream capture records it (kernels only, nothing allocated, the array's address
     looked up by the call before the capture); every replay, with new contents of X and eager work in between, gives
