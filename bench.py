@@ -3,7 +3,7 @@
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload C2] [--variant tcsc|signed|packed]
 
-One step = one tstgemm() call (the whole hot path: X packing / tile staging, gather-add, K-block carry,
+One step = one tstgemm() call (the whole hot path: tile staging, the products or gather-adds, K-block carry,
 split-K reduction, bias epilogue) on one batch of synthetic input that is already resident in HBM.  The
 TCSC build and the GPU re-blocking pass run once per matrix before the timed region ("at load time",
 Sec. 3 of the paper) and are reported separately in the config object.  Prints ONE JSON line.
@@ -37,15 +37,15 @@ PEAK_ALU_INSTR_T = 256 * 64 * 2.4e9 / 1e12     # vector lane-instructions per se
 # HBM bytes (read + written) of one launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
 # script, each counter scaled by what it reads for a copy kernel of known size in the same run.  A counter run cannot
 # be part of a timed run, so these are constants: (bytes, the tracked summary they come from).  Keyed by (workload,
-# kernel); workloads without a counter run report null.
+# variant), for calls without launch-shape options; workloads without a counter run report null.
 _T_ALL = "profiles/hbm_traffic_all_configs.md"
 _T_OTHER = "profiles/hbm_traffic_other_workloads.md"
 MEASURED_TRAFFIC = {
-    ("C1", "k_matrix"): (947109, _T_ALL), ("C2", "k_matrix"): (42220854, _T_ALL), ("C3a", "k_matrix"): (42221048, _T_ALL),
-    ("C3b", "k_matrix"): (42220905, _T_ALL), ("C4-1", "k_rows"): (11621610, _T_ALL), ("C4-8", "k_rows"): (12881026, _T_ALL),
-    ("C5a", "k_matrix"): (808063679, _T_ALL), ("C5b", "k_matrix"): (808058858, _T_ALL), ("C5c", "k_large"): (902535837, _T_ALL),
-    ("M64-K16384-N4096-d0.5", "k_matrix"): (60309157, _T_OTHER),
-    ("C4-1", "k_packed"): (9610282, _T_OTHER), ("C4-8", "k_rows_packed"): (10809682, _T_OTHER),
+    ("C1", "tcsc"): (947109, _T_ALL), ("C2", "tcsc"): (42220854, _T_ALL), ("C3a", "tcsc"): (42221048, _T_ALL),
+    ("C3b", "tcsc"): (42220905, _T_ALL), ("C4-1", "tcsc"): (11621610, _T_ALL), ("C4-8", "tcsc"): (12881026, _T_ALL),
+    ("C5a", "tcsc"): (808063679, _T_ALL), ("C5b", "tcsc"): (808058858, _T_ALL), ("C5c", "tcsc"): (902535837, _T_ALL),
+    ("M64-K16384-N4096-d0.5", "tcsc"): (60309157, _T_OTHER),
+    ("C4-1", "packed"): (9610282, _T_OTHER), ("C4-8", "packed"): (10809682, _T_OTHER),
 }
 ORACLE_FLAGS = "gcc -O3 -fstrict-aliasing -DNDEBUG -fopenmp (the paper's flags, Sec. 4, without -march=native)"
 INFINITY_CACHE_BYTES = 256 << 20
@@ -346,13 +346,13 @@ def main():
     kernel_ms = kernel_raw_ms - pair_ms
     kernel_ms_median = float(np.median(kernel_raw)) - pair_ms
     kernel_ms_min = float(np.min(kernel_raw)) - pair_ms
-    if decode or rows:
-        # The paths for few rows are ONE kernel per call: the time per call of the back-to-back timed region is that kernel's
-        # time (with the gap between two launches), and it is what agrees with the profiler's average duration; the
-        # event pair between two such kernels delays them and then takes off too much.
+    if decode or rows or (matrix and route.k_slices == 1):
+        # The paths for few rows, and k_matrix with K whole, are ONE kernel per call: the time per call of the back-to-back
+        # timed region is that kernel's time (with the gap between two launches), and it is what agrees with the profiler's
+        # average duration; the event pair between two such kernels delays them and then takes off too much.
         kernel_ms, kernel_ms_median, kernel_ms_min = call_ms, float(np.median(region_ms)), float(np.min(region_ms))
 
-    measured = MEASURED_TRAFFIC.get((wl.name, kernel))
+    measured = None if tuning else MEASURED_TRAFFIC.get((wl.name, args.variant))
     traffic = measured[0] if measured else None
     if rows:
         # the row sets or codes once, each entry of W one product of three planes
@@ -395,7 +395,8 @@ def main():
     if kernel == "k_decode":
         roof["kernel"] += " (16-bit lists)" if narrow else " (32-bit lists)"
     elif matrix:
-        roof["kernel"] += f" ({route.tile_rows} x {route.tile_cols} tiles, {route.k_groups} groups, {route.k_slices} slices of K)"
+        roof["kernel"] += (f" ({route.tile_rows} x {route.tile_cols} tiles, K over {route.k_groups} groups"
+                           f"{f' and {route.k_slices} slices' if route.k_slices > 1 else ''})")
     roof["kernel_ms"] = kernel_ms
     roof["kernel_ms_median"] = kernel_ms_median
     roof["kernel_ms_min"] = kernel_ms_min
