@@ -137,10 +137,11 @@ typedef struct tcsc_layout {
  * Device forms besides the four TCSC arrays (which are always uploaded: the decode kernel of tstgemm() for
  * M <= 8 reads them, and every other form is derived from them on the GPU):
  */
-#define TCSC_FORM_ROWSETS 1u     /* masks: the large-M path of tstgemm(), M > 64 */
-#define TCSC_FORM_CUTS 2u        /* list_cuts: the small-tile path of tstgemm(), 8 < M <= 64 (a matrix with 2^30 or more
-                                    entries of one sign takes the large-M path for these M too: ROWSETS) */
-#define TCSC_FORM_LISTS16 4u     /* padded 16-bit lists (only where K <= 65535): M <= 8 reads half the bytes */
+#define TCSC_FORM_ROWSETS 1u     /* masks: needed for M > 64; for fewer rows the matrix cores run from them (not needed, but
+                                    several times faster unless W is sparse) */
+#define TCSC_FORM_CUTS 2u        /* list_cuts: needed for 8 < M <= 64, whichever kernel runs (a matrix with 2^30 or more
+                                    entries of one sign needs ROWSETS for these M in its place) */
+#define TCSC_FORM_LISTS16 4u     /* padded 16-bit lists (only where K <= 65535): M <= 8 reads half the bytes where it walks lists */
 #define TCSC_FORM_SIGNED 8u      /* signed_index: tstgemm_signed() */
 #define TCSC_FORM_PACKED 16u     /* packed: tstgemm_packed(); built from the row sets, so it selects ROWSETS too */
 #define TCSC_FORM_WORKSPACE 32u  /* scratch inside the buffer, for calls without a workspace argument */
@@ -149,8 +150,10 @@ typedef struct tcsc_layout {
 /*
  * Choose what tcsc_upload() puts into the device buffer (a new handle has TCSC_FORM_ALL).  Changes
  * tcsc_device_bytes() and tcsc_layout(); a handle that was already uploaded must be uploaded again.  A matrix that
- * serves one shape of X needs one form: e.g. ROWSETS alone for M > 64 with a caller-supplied workspace
- * (tstgemm_ex) is 16 bytes per column and 64 rows of W beside the TCSC arrays.
+ * serves one shape of X needs few of them: with a caller-supplied workspace (tstgemm_ex) ROWSETS alone for M > 64
+ * (16 bytes per column and 64 rows of W beside the TCSC arrays), ROWSETS and CUTS for 8 < M <= 64, ROWSETS for M <= 8
+ * (and LISTS16 where W is sparse).  Without the row sets calls with M <= 64 run, on the lists alone: 1 x 4096 x 11008 at
+ * 50 % 13 us in place of 8, 8 rows 24 in place of 8, 64 x 16384 x 4096 110 in place of 31.
  * Errors: EINVAL for a NULL handle or bits outside TCSC_FORM_ALL.
  */
 int tcsc_select_forms(tcsc_t *t, uint32_t forms);

@@ -218,7 +218,9 @@ struct MatrixArgs {
 // an entry, and are spread into fragments in registers.  Loads run PD steps ahead.  Per step a wavefront
 // has 6 RF CF matrix instructions of 32 cycles; the cuts, the spreading and the LDS traffic are dealt over their six
 // stages, each ended by a scheduling barrier (without the stages, and with loads whose number the compiler could not
-// count, M = 4096, K = N = 8192 took 1.20 ms in place of 1.10).
+// count, M = 4096, K = N = 8192 took 1.20 ms in place of 1.10).  In the 64 x 512 and 32 x 128 tiles a step has half as many
+// pieces of X as the group has lanes: half of the wavefronts stage X, and the compiler puts their whole cut behind the guard
+// of their LDS writes, into the last stage.
 // Bound: long calls by the power limit (M = 4096, K = N = 8192: 1.04 ms, i.e. 1.59 PFLOP/s of bf16 products, the clock down
 // to about 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here; without any cutting and spreading, which
 // gives wrong sums, it would take 0.99 ms), short ones by the start of the first loads, the
@@ -890,14 +892,19 @@ double density(const tcsc_layout_t &l) { return (double)(l.nnz_pos + l.nnz_neg) 
 }  // namespace
 
 // Whether the matrix cores take a call (the lists or the row-set walk being the other choice).  They do unless W is so
-// sparse that those, whose time goes with the number of non-zeros, are ahead:
+// sparse that those, whose time goes with the number of non-zeros, are ahead.  Measured on 12 shapes (K, N = 512 .. 16384),
+// M = 1 .. 4096 and densities from 1/16 to 0: a call taken here is never more than 4 % behind the lists or the row-set walk
+// (1024 x 8192 x 8192 at 1/256: 231 against 223 us), but for 0.2 us of 2.9 at M = 2 with an empty W.  Some of the calls that
+// are left to those, below 1/64, would be faster here (64 x 4096 x 11008 at 1/256: 39 us; at 1/64, here, 24).
 //  * M > 64, tall and wide: k_large with 128 columns per workgroup takes 20 us + 0.0281 + 0.464 density us per row of W
 //    and round of its workgroups (measured M = 4096, K = N = 8192: 928 us at 1/16, 2318 us at 1/4; here 1040 us at any
-//    density).  Its other shapes are 1.3 to 5 times slower than this path down to a density of 1/16.
+//    density).  Its other shapes are behind this path at every density, by 1.2 to 5 times down to 1/16 and 1.0 to 3 times
+//    with an empty W, so where the column count leaves only those this path is always taken, and where K would be sliced
+//    there the figure above, too high for that, does no harm.
 //  * 8 < M <= 64: k_small, with a tile of 16 rows, takes 6.1 us, or 9.6 us where K is cut into slices (beyond 1024 rows),
 //    + 0.1 per 1000 rows of W + 0.12 per million entries + 0.8 per million non-zeros, 1.3 and 1.7 times that for 32 and
 //    64 rows (M = 16: 1024 x 4096 at 1/16 6.6 against 7.4 us, 15000 x 600 12.6 against 14.2; from 17 rows on it is behind
-//    everywhere down to 1/16).
+//    everywhere, down to an empty W).
 //  * M <= 8: k_decode takes 2.7 + 0.3 M + (0.17 + 0.08 M) us per million non-zeros for one or two rows, 1.6 + 0.67 M +
 //    (0.22 + 0.08 M) for more, and 2 us for each further time that X fills the LDS (less than measured wherever K is
 //    long, so that a tie goes to the lists).  It stays ahead

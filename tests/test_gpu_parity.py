@@ -115,8 +115,8 @@ def test_benchmark_configs_full(name, dist):
 @pytest.mark.parametrize("name", ["M64-K16384-N4096-d0.5", "M64-K4096-N4096-d0.0625", "M32-K16384-N1024-d0.25",
                                   "M8-K8192-N4096-d0.5", "M1024-K4096-N1024-d0.25"])
 def test_paper_sweep_shapes_full(name):
-    """Every element of the largest shapes of the paper's own sweeps (Sec. 4), one per kernel and tile height, in the
-    launch configuration bench.py times; an integer-valued run bit for bit."""
+    """Every element of the largest shapes of the paper's own sweeps (Sec. 4), in the launch configuration bench.py times;
+    an integer-valued run bit for bit."""
     W, X, b = si.make_workload(name)
     ot = oracle.tcsc_build(W)
     Y, h = gpu_tstgemm(W, X, b)
@@ -129,9 +129,10 @@ def test_paper_sweep_shapes_full(name):
 
 @pytest.mark.parametrize("name", ["C5a", "C5b", "C5c"])
 def test_prefill_configs_full(name):
-    """M=4096, K=N=8192 at 50 %, 25 % and 6.25 %: EVERY element of Y, in the launch configuration bench.py times
-    (16 row tiles, 128-column workgroups, no K slices), against the oracle, which goes through the rows in slabs of
-    512 to bound host memory; then an integer-valued X, every element bit for bit (real-valued bias: one rounding)."""
+    """M=4096, K=N=8192 at 50 %, 25 % (64 x 512 tiles on the matrix cores) and 6.25 % (the row-set kernel: 16 row tiles,
+    128-column workgroups, no K slices): EVERY element of Y, in the launch configuration bench.py times, against the
+    oracle, which goes through the rows in slabs of 512 to bound host memory; then an integer-valued X, every element bit
+    for bit (real-valued bias: one rounding)."""
     w = si.WORKLOADS[name]
     W, X, b = si.make_workload(name)
     ot = oracle.tcsc_build(W)
