@@ -116,7 +116,8 @@ struct Epilogue {
 // infinity (with one in every row; with all of X near 1e35), 50 % non-zeros, against the list and row-set kernels, whose time
 // does not depend on X: 256 x 4096 x 4096 90 us (184; 363) against 108, 1024 x 2048 x 8192 248 (623; 937) against 359,
 // M = 1, 4096 x 4096 16 (14; 24) against 11; finite X 38, 82, 14.  One lane per output that walked the members one by one
-// took 1128 (1630), 442 (9361) and 263.  Where K is not a multiple of 64 the first entries of a row also meet the zero
+// took 1128 (1630), 442 (9361) and 263, and 508 from the base-3 codes (M = 1, 4096 x 4096, one entry of 1e35; 14 now, from the
+// row sets, which the codes are built from and uploaded with).  Where K is not a multiple of 64 the first entries of a row also meet the zero
 // weights beyond the end of the row before, so an infinity there sends that row here too.
 // X: the first of `rows` <= 16 rows; the blocks from kb0 on up to kb1, groups of four of them, every `stride`-th from
 // `first` on.  Lane l holds column n = n0 + l % 16 of Y, element e of the result is row 4 (l / 16) + e.
@@ -125,18 +126,17 @@ __device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, 
 {
     const int r = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
     const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(X, (size_t)rows * K * 4);
-    const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(masks, (size_t)kb1 * n_pad * 16);
     float4v top{0.f, 0.f, 0.f, 0.f}, low = top, large = top, up = top, down = top;
     auto multiply = [](float4v &c, uint4v a, bf16x8 b) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
     };
     for (int group = first; kb0 + 4 * group < kb1; group += stride) {
-        const unsigned kb = kb0 + 4 * group + g;
-        const uint4v w = load16(wbuf, (kb * (unsigned)n_pad + (unsigned)n) * 16u);
+        const int kb = kb0 + 4 * group + g;
+        const uint4v w = kb < kb1 ? masks[(size_t)kb * n_pad + n] : uint4v{0, 0, 0, 0};
         for (int h = 0; h < 2; ++h) {
             const unsigned plus = h ? w[1] : w[0], minus = h ? w[3] : w[2];
             const SignedWord both(plus, minus), of_plus(plus, 0), of_minus(minus, 0);
-            const unsigned off = r < rows ? ((unsigned)r * (unsigned)K + 64 * kb + 32 * h) * 4u : kNowhere;
+            const unsigned off = r < rows ? ((unsigned)r * (unsigned)K + 64u * kb + 32u * h) * 4u : kNowhere;
             float4v x0[4], x1[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
@@ -202,11 +202,12 @@ __device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, 
 
 struct MatrixArgs {
     const float *X;
-    const uint4v *masks;             // [n_kblocks][n_pad] {+1 rows low, high, -1 rows low, high}
+    const uint4v *masks;             // [n_kblocks][n_pad] {+1 rows low, high, -1 rows low, high}; k_rows: or codes
+    const uint4v *row_sets;          // the masks also where the call is on the codes, [n_row_blocks][n_pad]
     const float *b, *alpha;
     float *Y, *partials;             // partials[slice][M][n_pad]
     int alpha_stride;
-    int M, K, N, n_pad, n_kblocks;
+    int M, K, N, n_pad, n_kblocks, n_row_blocks;
     int n_tiles, k_slices, kb_per_slice;
 };
 
@@ -622,24 +623,10 @@ __device__ __forceinline__ unsigned weights_of_code(int code)
     return bits;
 }
 
-// X W for one output from X and the codes, as gather_output().
-__device__ __forceinline__ float gather_packed(const float *__restrict__ X, const uint4v *__restrict__ codes, int n_pad,
-                                               int m, int n, int K)
-{
-    float s = 0.f;
-    const float *x = X + (size_t)m * K;
-    const unsigned char *bytes = reinterpret_cast<const unsigned char *>(codes);
-    for (int group = 0; 5 * group < K; ++group) {
-        const unsigned w = weights_of_code(bytes[((size_t)(group / 16) * n_pad + n) * 16 + group % 16]);
-        for (int i = 0; i < 5 && 5 * group + i < K; ++i)
-            if (w >> (2 * i) & 1) s += (w >> (2 * i) & 2) ? -x[5 * group + i] : x[5 * group + i];
-    }
-    return s;
-}
-
-// (Up to five rows of X and 16 columns: four wavefronts per SIMD, so that four workgroups of four fit side by side.)
+// (Up to five rows of X and 16 columns: four wavefronts per SIMD, three on the codes, so that as many workgroups of four fit
+// side by side.)
 template <int MM, int B, int KW, bool PACKED>
-__global__ void __launch_bounds__(64 * KW, !PACKED && MM <= 5 && B == 1 ? 4 : 1)
+__global__ void __launch_bounds__(64 * KW, MM <= 5 && B == 1 ? (PACKED && MM > 2 ? 3 : 4) : 1)
 k_rows(const MatrixArgs a)
 {
     constexpr int kSteps = PACKED ? 10 : 8;                  // matrix instructions per block of W and tile
@@ -791,31 +778,26 @@ k_rows(const MatrixArgs a)
             for (int k = 0; k < KW; ++k) plane[p] += sums[((k * B + b) * T * 16 + p * M + m) * 16 + c];
         }
         float v = (plane[0] + (plane[1] + plane[2])) * kScaleDown;
-        if (!finite(v)) {
-            if constexpr (PACKED) v = gather_packed(a.X, a.masks, a.n_pad, m, n, a.K);
-            else spoilt = 1;
-        }
+        if (!finite(v)) spoilt = 1;
         a.Y[(size_t)m * a.N + n] = finish(v, bias, slope);
     }
-    if constexpr (!PACKED) {
-        __syncthreads();
-        if (!spoilt) return;
-        // again from X, the groups dealt to the wavefronts as before: [wave][b][row][column]
+    __syncthreads();
+    if (!spoilt) return;
+    // again from X and the row sets, groups of them dealt to the wavefronts as before: [wave][b][row][column]
 #pragma unroll 1
-        for (int b = 0; b < B; ++b) {
-            const float4v v = sums_of_any(a.X, M, a.K, a.masks, a.n_pad, min(n0 + 16 * b + r, a.n_pad - 1), 0, a.n_kblocks, wave, KW);
+    for (int b = 0; b < B; ++b) {
+        const float4v v = sums_of_any(a.X, M, a.K, a.row_sets, a.n_pad, min(n0 + 16 * b + r, a.n_pad - 1), 0, a.n_row_blocks, wave, KW);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sums[((wave * B + b) * 16 + 4 * g + e) * 16 + r] = v[e];
-        }
-        __syncthreads();
-        for (int o = threadIdx.x; o < 16 * B * M; o += 64 * KW) {
-            const int c = o & 15, b = (o >> 4) % B, m = (o >> 4) / B, n = n0 + 16 * b + c;
-            if (n >= a.N || finite(a.Y[(size_t)m * a.N + n])) continue;   // the thread's own store
-            float v = 0.f;
+        for (int e = 0; e < 4; ++e) sums[((wave * B + b) * 16 + 4 * g + e) * 16 + r] = v[e];
+    }
+    __syncthreads();
+    for (int o = threadIdx.x; o < 16 * B * M; o += 64 * KW) {
+        const int c = o & 15, b = (o >> 4) % B, m = (o >> 4) / B, n = n0 + 16 * b + c;
+        if (n >= a.N || finite(a.Y[(size_t)m * a.N + n])) continue;   // the thread's own store
+        float v = 0.f;
 #pragma unroll
-            for (int k = 0; k < KW; ++k) v += sums[((k * B + b) * 16 + m) * 16 + c];
-            a.Y[(size_t)m * a.N + n] = finish(v, finish.bias_of(n), finish.slope_of(n));
-        }
+        for (int k = 0; k < KW; ++k) v += sums[((k * B + b) * 16 + m) * 16 + c];
+        a.Y[(size_t)m * a.N + n] = finish(v, finish.bias_of(n), finish.slope_of(n));
     }
 }
 
@@ -959,6 +941,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     a.alpha = c.act.alpha; a.alpha_stride = c.act.alpha_stride;
     a.partials = reinterpret_cast<float *>(c.ws);
     a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_kblocks;
+    a.row_sets = a.masks; a.n_row_blocks = l.n_kblocks;
     if (p.rows) return launch_rows<false>(a, p, c);
     const TileShape &s = kTiles[p.shape];
     a.n_tiles = (l.n_pad + s.cols - 1) / s.cols;
@@ -996,7 +979,8 @@ hipError_t launch_packed_rows(const MatrixPlan &p, const float *X, const tcsc *t
     const tcsc_layout_t &l = t->layout;
     MatrixArgs a{};
     a.X = X; a.masks = reinterpret_cast<const uint4v *>(device_view(t).packed); a.b = b; a.Y = Y;
-    a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_chunks5;
+    a.row_sets = reinterpret_cast<const uint4v *>(device_view(t).masks);   // (the codes are built from them)
+    a.M = M; a.K = l.K; a.N = l.N; a.n_pad = l.n_pad; a.n_kblocks = l.n_chunks5; a.n_row_blocks = l.n_kblocks;
     return launch_rows<true>(a, p, c);
 }
 
