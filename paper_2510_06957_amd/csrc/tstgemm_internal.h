@@ -166,6 +166,7 @@ void large_workspace_bytes(int M, int K, int n_pad, size_t *min_bytes, size_t *b
 struct MatrixPlan {
     bool rows;          // k_rows (shape: tiles of 16 columns, split: wavefronts), else k_matrix (tile shape, K slices)
     int shape, split;
+    bool digits;        // k_matrix: X cut into digits beforehand
     bool taken() const { return split > 0; }
 };
 MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c);

@@ -12,9 +12,10 @@
 // X held an infinity, a NaN or something beyond about 2^100 -- is taken again from X by sums_of_any(), which keeps such
 // entries apart, so an entry of X under a zero weight never reaches Y here either.
 //
-// k_matrix is for M > 8, k_rows for M <= 10; choose_tile(), rows_plan() and matrix_plan() have the rules, with what was
-// measured.
+// k_matrix is for M > 8, k_rows for M <= 10; choose_tile(), with_digits(), rows_plan() and matrix_plan() have the rules, with
+// what was measured.  k_matrix also multiplies X cut into 6-bit digits by k_digits beforehand, where a call is large enough.
 #include <cmath>
+#include <type_traits>
 
 #include "tstgemm_internal.h"
 
@@ -24,7 +25,12 @@ namespace {
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any float's address
 typedef float float16v __attribute__((ext_vector_type(16)));
+typedef float float32v __attribute__((ext_vector_type(32)));
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef int int8v __attribute__((ext_vector_type(8)));
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+typedef unsigned uint6v __attribute__((ext_vector_type(6)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kScaleUp = 16777216.f;            // 2^24
@@ -206,10 +212,158 @@ struct MatrixArgs {
     const uint4v *row_sets;          // the masks also where the call is on the codes, [n_row_blocks][n_pad]
     const float *b, *alpha;
     float *Y, *partials;             // partials[slice][M][n_pad]
+    const char *digits;              // k_matrix with X cut beforehand: units of 64 rows x 64 entries, [row tile][K-block] ...
+    const unsigned char *counts;     // ... and how many planes of digits each has
     int alpha_stride;
     int M, K, N, n_pad, n_kblocks, n_row_blocks;
     int n_tiles, k_slices, kb_per_slice;
 };
+
+// ------------------------------------------------------------------------------------------------------------------
+// X in digits.  32 entries of a row share an exponent (that of the largest, E); an entry is a sum of 6-bit floats (e2m3, the
+// matrix cores' fp6), each the nearest to what the ones before it leave.  Digit j is a multiple of 2^(E - 4 - 5 j + (j == 0)),
+// so three planes of digits hold 14 bits below the largest entry, five 24 and seven 34.  A unit of 64 rows x 64 entries has as
+// many of these as leave nothing over, three, five or seven (integers and 16-bit activations mostly three or five, uniform X
+// five, normal X seven); a unit that seven do not hold -- entries so much smaller than their neighbours that
+// what is left over of the 32 is more than 2^-31 of the largest, infinities, NaNs, exponents out of range -- is marked
+// kNoDigits, and its tile is multiplied in bf16 planes.  The sums of planes 0 to 2 and of the others are kept apart: the
+// upper ones are whole numbers of a unit, exact as long as they have 24 bits, so the result is rounded little more than once
+// (M = 4096, K = N = 8192: 3.6e-8 of the norm against 64 bits, in bf16 planes 6.1e-8).  fp6 x fp4 runs at 3.3 times the rate of
+// bf16 under the power limit (instructions alone, on random operands: 6.4 and 1.93 PFLOP/s): five planes cost 0.5 of the three
+// in bf16, seven 0.7.
+// In the workspace a unit is [planes 0-2][exponents][planes 3-4][planes 5-6], a plane two fragments (32 rows) as a wavefront
+// holds them: lane l has row l % 32 and entries 32 (l / 32) .. + 31, 16 bytes of each lane, then 8.
+constexpr int kPlaneBytes = 2 * 64 * 24, kExponents = 3 * kPlaneBytes, kUpperPlanes = 10240, kUnitBytes = 22528;
+constexpr int kNoDigits = 8;
+constexpr int kMaxDigitBlocks = 1984;   // K-blocks whose counts k_matrix keeps in the LDS
+__host__ __device__ constexpr int plane_offset(int j) { return j < 3 ? j * kPlaneBytes : kUpperPlanes + (j - 3) * kPlaneBytes; }
+// Exponent of plane j's digits below plane 0's: in steps of 5, but 4 to plane 1 (the top digit of the largest entry, 2 to 4
+// units of its plane, is rounded to a quarter)
+__host__ __device__ constexpr int plane_shift(int j) { return j == 0 ? 0 : 5 * j - 1; }
+
+// k_digits: one lane cuts 32 entries of a row.  Position 8 d + n of a lane's digits is entry 4 n + d, the order in which
+// FourBitWord spreads the weights.  Bound by memory: 134 MB of X and 130 MB of planes in 44 us (6 TB/s; 57 us with every lane
+// reading its own 128 bytes and the planes left to the L2), 16 MB in 4 to 5 us, of which launch and one trip are most.
+__global__ void __launch_bounds__(128)
+k_digits(const float *X, int M, int K, int n_kblocks, char *units, unsigned char *counts)
+{
+    __shared__ uint4v staged[2][32 * 17];   // (17 units a row: other banks)
+    __shared__ int need[2];
+    const int lane = threadIdx.x & 63, frag = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = blockIdx.x / n_kblocks, kb = blockIdx.x % n_kblocks;
+    const int rows = min(64, M - 64 * tile), k0 = 64 * kb + 32 * (lane >> 5);
+    const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(X + (size_t)64 * tile * K, (size_t)rows * K * 4);
+    // four rows of 256 bytes at a time, through the LDS to the lane that cuts them
+    uint4v v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int row = 32 * frag + 4 * j + (lane >> 4);
+        v[j] = load16(xbuf, row < rows ? ((unsigned)row * (unsigned)K + 64 * kb + 4 * (lane & 15)) * 4u : kNowhere);
+    }
+    uint4v *mine = staged[frag];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mine[(4 * j + (lane >> 4)) * 17 + (lane & 15)] = v[j];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wavefront's own piece of the LDS
+    float x[32];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float4v w = __builtin_bit_cast(float4v, mine[(lane & 31) * 17 + 8 * (lane >> 5) + j]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * j + e] = w[e];
+    }
+    if (64 * kb + 64 > K) {   // entries beyond the row belong to the next one
+#pragma unroll
+        for (int i = 0; i < 32; ++i) x[i] = k0 + i < K ? x[i] : 0.f;
+    }
+    float largest = 0.f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) largest = fmaxf(largest, fabsf(x[i]));
+    const unsigned exponent = __float_as_uint(largest) >> 23;   // (a NaN shows in what is left over)
+    const bool fits = largest == 0.f || (exponent >= 31 && exponent <= 230);
+    const unsigned top = fits && largest != 0.f ? exponent - 1 : 126;   // of the unit of plane 0
+    float16v a, b;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        a[i] = x[8 * (i & 3) + (i >> 2)];
+        b[i] = x[8 * (i & 3) + 4 + (i >> 2)];
+    }
+    uint6v digit[7];
+    int planes = 3;
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        digit[j] = uint6v{0, 0, 0, 0, 0, 0};
+        if (j >= planes) continue;
+        const float scale = __uint_as_float((top - plane_shift(j)) << 23);
+        digit[j] = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, scale);
+        const float32v back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(digit[j], scale);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            a[i] -= back[2 * i];
+            b[i] -= back[2 * i + 1];
+        }
+        if (j != 2 && j != 4 && j != 6) continue;
+        float rest = 0.f, more = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            rest += fabsf(a[i]);
+            more += fabsf(b[i]);
+        }
+        rest += more;
+        if (j < 6 && __any(rest != 0.f)) planes = j + 3;
+        if (j == 6 && __any(!(rest <= largest * 0x1p-31f))) planes = kNoDigits;
+    }
+    if (__any(!fits)) planes = kNoDigits;
+    if (lane == 0) need[frag] = planes;
+    __syncthreads();
+    planes = __builtin_amdgcn_readfirstlane(max(need[0], need[1]));
+    const size_t unit = (size_t)tile * n_kblocks + kb;
+    if (frag == 0 && lane == 0) counts[unit] = (unsigned char)planes;
+    if (planes == kNoDigits) return;
+    const __amdgpu_buffer_rsrc_t out = raw_buffer(units + unit * kUnitBytes, kUnitBytes);
+    // scales of planes 0 .. 3, times 2^24 as everywhere
+    const unsigned e0 = top + 24;
+    __builtin_amdgcn_raw_buffer_store_b32(
+        e0 | (e0 - plane_shift(1)) << 8 | (e0 - plane_shift(2)) << 16 | (e0 - plane_shift(3)) << 24, out,
+        kExponents + 256 * frag + 4 * lane, 0, kWriteThrough);
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        if (j >= planes) break;
+        const int at = plane_offset(j) + frag * (kPlaneBytes / 2);
+        __builtin_amdgcn_raw_buffer_store_b128(uint4v{digit[j][0], digit[j][1], digit[j][2], digit[j][3]}, out, at + 16 * lane, 0,
+                                               kWriteThrough);
+        __builtin_amdgcn_raw_buffer_store_b64(uint2v{digit[j][4], digit[j][5]}, out, at + 1024 + 8 * lane, 0, kWriteThrough);
+    }
+}
+
+// 32 rows of a column as fp4 weights, 2.0 with its sign: bit 2 of four says non-zero, bit 3 is the sign.
+struct FourBitWord {
+    int4v w;   // dword d: rows 4 n + d
+    __device__ __forceinline__ FourBitWord(unsigned pos, unsigned neg)
+    {
+        const unsigned nz = pos | neg;
+        const unsigned even = (nz & 0x55555555u) | ((neg << 1) & 0xAAAAAAAAu);
+        const unsigned odd = ((nz >> 1) & 0x55555555u) | (neg & 0xAAAAAAAAu);
+        w[0] = (int)((even << 2) & 0xCCCCCCCCu);
+        w[1] = (int)((odd << 2) & 0xCCCCCCCCu);
+        w[2] = (int)(even & 0xCCCCCCCCu);
+        w[3] = (int)(odd & 0xCCCCCCCCu);
+    }
+};
+
+// 1024 bytes from `buf` straight into the LDS, 16 per lane; counted by vmcnt, which the caller waits for.
+__device__ __forceinline__ void copy_to_lds(uint4v buf, unsigned lds_byte, unsigned offset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds_byte), "v"(offset), "s"(buf) : "memory");
+}
+__device__ __forceinline__ uint4v descriptor(const void *p, size_t bytes)
+{
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned n = p == nullptr ? 0 : (unsigned)min(bytes, (size_t)kNowhere);
+    return uint4v{(unsigned)__builtin_amdgcn_readfirstlane((int)a), (unsigned)__builtin_amdgcn_readfirstlane((int)(a >> 32)) & 0xffffu,
+                  (unsigned)__builtin_amdgcn_readfirstlane((int)n), kRawBuffer};
+}
+template <int N> using Int = std::integral_constant<int, N>;
 
 // ------------------------------------------------------------------------------------------------------------------
 // k_matrix: a workgroup computes TM x TN of Y over one slice of K, WK groups of WM x WN wavefronts each over their
@@ -226,9 +380,16 @@ struct MatrixArgs {
 // to about 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here; without any cutting and spreading, which
 // gives wrong sums, it would take 0.99 ms), short ones by the start of the first loads, the
 // sums at the end and the second launch where K is sliced (M = 256, K = N = 4096: 28 us against 89).
+// DIGITS: X comes from the workspace, straight into the LDS, W too; three steps of 64 rows of W in a ring, copied two steps
+// ahead, one barrier a step, placed before the last plane's products so that the next step's first reads are under way behind
+// them.  A step has 4 products of 32 cycles per plane and wavefront.  Everything else is dealt between them one by one: all
+// copies at once, or the spreading behind the products, cost 3 and 7 % of M = 4096, K = N = 8192 (1035 us in bf16; here 585
+// with uniform X, 760 with normal X, 540 at 1/16 non-zeros, where the products draw less power).  Of the 585, k_digits takes 44, the four
+// rounds' starts and ends about 30; the products by themselves take 430 at the power limit and 273 without it.  64 x 128
+// of Y per wavefront, half the LDS reads, is no faster; a ring of four steps neither.
 // Rows beyond M and rows of W beyond K: X reads as zero, or as the next row of X where the weights are zero.
-template <int WK, int WM, int WN, int RF, int CF>
-__global__ void __launch_bounds__(64 * WK * WM * WN, 2)
+template <int WK, int WM, int WN, int RF, int CF, bool DIGITS>
+__global__ void __launch_bounds__(64 * WK * WM * WN, CF == 4 ? 1 : 2)
 k_matrix(const MatrixArgs a)
 {
     constexpr int NG = 64 * WM * WN, TM = 32 * RF * WM, TN = 32 * CF * WN, PD = 2;
@@ -238,7 +399,10 @@ k_matrix(const MatrixArgs a)
     constexpr int kChunk = TM + 2;                          // 16-byte units per plane and piece; + 2: other banks
     constexpr int kPlane = 4 * kChunk, kBuffer = 3 * kPlane;
     constexpr int kStageUnits = WK * 2 * kBuffer, kSumUnits = (WK / 2) * (TM * TN / 4);
-    __shared__ uint4v lds_all[kStageUnits > kSumUnits ? kStageUnits : kSumUnits];
+    // digits: three steps of X and W per group, then the counts
+    constexpr int kDigitStep = kUnitBytes + 512 * CF * WN, kDigitRing = 3 * kDigitStep, kDigitUnits = WK * (kDigitRing + 2048) / 16;
+    constexpr int kBf16Units = kStageUnits > kSumUnits ? kStageUnits : kSumUnits;
+    __shared__ uint4v lds_all[DIGITS && kDigitUnits > kBf16Units ? kDigitUnits : kBf16Units];
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = wave / (WM * WN), wave_in_group = wave % (WM * WN);
@@ -315,7 +479,7 @@ k_matrix(const MatrixArgs a)
         for (int j = 0; j < CF; ++j) bw[j] = SignedWord(w[set][j][t] >> (4 * g), w[set][j][2 + t] >> (4 * g)).eight(8 * u);
     };
 
-    const int col0 = n0 + wc * CF * 32 + l32;
+    int col0 = n0 + wc * CF * 32 + l32, row0 = wr * RF * 32 + 4 * g;
     const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);
     float bias[CF], slope[CF];
 #pragma unroll
@@ -325,77 +489,274 @@ k_matrix(const MatrixArgs a)
     }
 
     float16v acc[2][RF][CF];   // [hi | mid + lo]
-#pragma unroll
-    for (int d = 0; d < 2; ++d)
+    auto merge = [&]() {
 #pragma unroll
         for (int i = 0; i < RF; ++i)
 #pragma unroll
-            for (int j = 0; j < CF; ++j)
+            for (int j = 0; j < CF; ++j) acc[0][i][j] += acc[1][i][j];
+    };
+    auto clear = [&]() {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[d][i][j][e] = 0.f;
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int i = 0; i < RF; ++i)
+#pragma unroll
+                for (int j = 0; j < CF; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[d][i][j][e] = 0.f;
+    };
 
+    bool in_digits = false;
+    if constexpr (DIGITS) {
+        static_assert(WM == 1 && RF == 2 && CF % 2 == 0, "a unit is the tile's rows, a wavefront's columns come 64 at a time");
+        typedef __attribute__((address_space(3))) const char *Lds;
+        constexpr int kChunks = kUnitBytes / 1024, kCopies = (kChunks + WN - 1) / WN, kLoads = kCopies + CF / 2;
+        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) uint4v *)lds_all;
+        const unsigned ring = lds0 + group * kDigitRing;
+        unsigned char *const counted = reinterpret_cast<unsigned char *>(lds_all) + WK * kDigitRing;   // of the slice's blocks
+        int *const flags = reinterpret_cast<int *>(counted + kMaxDigitBlocks);
+        const int slice_kb0 = slice * a.kb_per_slice, slice_blocks = min(a.kb_per_slice, a.n_kblocks - slice_kb0);
+        const size_t tile_unit = (size_t)(m0 / 64) * a.n_kblocks;
+        const uint4v dbuf = descriptor(a.digits + tile_unit * kUnitBytes, (size_t)kb1 * kUnitBytes);
+        const uint4v sbuf = descriptor(a.masks, (size_t)kb1 * a.n_pad * 16);
+        unsigned scol[CF / 2];
 #pragma unroll
-    for (int s = 0; s < PD; ++s) load_x(s, 2 * kb0 + s);
-    load_w(0, kb0);
-    load_w(1, kb0 + 1);
+        for (int j = 0; j < CF / 2; ++j) scol[j] = (unsigned)min(n0 + wc * 32 * CF + 64 * j + lane, a.n_pad - 1) * 16u;
+        auto copy_w = [&](int step, unsigned to) {   // W of the wavefront's columns
 #pragma unroll
-    for (int i = 0; i < kPairs; ++i) cut_pair(0, i);
-    store_planes(0);
-    load_x(0, 2 * kb0 + PD);
-    bf16x8 bw[2][CF];
-    spread_w(bw[0], 0, 0, 0);
-    for (int i0 = 0; i0 < blocks; i0 += 2) {
+            for (int j = 0; j < CF / 2; ++j)
+                copy_to_lds(sbuf, to + kUnitBytes + (wave_in_group * (CF / 2) + j) * 1024,
+                            scol[j] + (unsigned)(kb0 + step) * (unsigned)a.n_pad * 16u);
+        };
+        auto copy_x = [&](int i, int step, unsigned to, int planes) {   // the wavefront's i-th piece of the group's X
+            const int c = min(wave_in_group + i * WN, kChunks - 1), chunks = planes > 5 ? kChunks : planes > 3 ? 16 : 10;
+            copy_to_lds(dbuf, to + c * 1024, (c < chunks ? (unsigned)(kb0 + step) * kUnitBytes + c * 1024u : 0xfffff000u) + lane * 16);
+        };
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (i0 + q >= blocks) break;
-            const int kb = kb0 + i0 + q;
+        for (int s = 0; s < 2; ++s) {
+            copy_w(s, ring + s * kDigitStep);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {   // half of the block: 32 rows of W, LDS buffer t
-                const int next = (t + 1) % PD;
-                bf16x8 x[2][RF];
-                auto read_x = [&](int s) {   // stage s: plane s % 3 of 16 rows
+            for (int i = 0; i < kCopies; ++i) copy_x(i, s, ring + s * kDigitStep, 7);
+        }
+        copy_w(2, ring + 2 * kDigitStep);
+        bool wide = false;
+        for (int i = threadIdx.x; i < WK * blocks + 4; i += 64 * WK * WN) {
+            const unsigned char n = i < slice_blocks ? a.counts[tile_unit + slice_kb0 + i] : 3;
+            counted[i] = n;
+            wide |= n == kNoDigits;
+        }
+        if (__any(wide)) wide = true;
+        if (lane == 0) flags[wave] = wide;
+        __syncthreads();
+        int any_wide = 0;
 #pragma unroll
-                    for (int i = 0; i < RF; ++i)
-                        x[s & 1][i] = __builtin_bit_cast(
-                            bf16x8, lds[t * kBuffer + (s % 3) * kPlane + (2 * (s / 3) + g) * kChunk + (wr * RF + i) * 32 + l32]);
+        for (int i = 0; i < WK * WN; ++i) any_wide |= flags[i];
+        in_digits = !__builtin_amdgcn_readfirstlane(any_wide);
+        if (in_digits) {
+            clear();
+            const unsigned char *const count = counted + group * blocks;
+            int8v x[2][RF];
+            int4v bw[2][CF];
+            unsigned scale[2][RF], sets[CF][2];
+            const unsigned lane16 = lane * 16, lane8 = 1024 + lane * 8, lane4 = kExponents + lane * 4;
+            const unsigned lane_w = kUnitBytes + (wave_in_group * 32 * CF + l32) * 16 + g * 4;
+            auto word = [](unsigned at) { return *(__attribute__((address_space(3))) const unsigned *)(size_t)at; };
+            auto read_x = [&](auto cur, unsigned at16, unsigned at8, int offset) {   // a plane's two fragments
+#pragma unroll
+                for (int i = 0; i < RF; ++i) {
+                    const uint4v u = *(__attribute__((address_space(3))) const uint4v *)((Lds)(size_t)at16 + offset + i * (kPlaneBytes / 2));
+                    const uint2v v = *(__attribute__((address_space(3))) const volatile uint2v *)((Lds)(size_t)at8 + offset + i * (kPlaneBytes / 2));
+                    x[cur][i] = int8v{(int)u[0], (int)u[1], (int)u[2], (int)u[3], (int)v[0], (int)v[1], 0, 0};
+                }
+            };
+            auto first_plane = [&](int planes) { return planes > 5 ? plane_offset(5) : planes > 3 ? plane_offset(3) : plane_offset(1); };
+            auto read_w = [&](unsigned at) {
+#pragma unroll
+                for (int j = 0; j < CF; ++j) {
+                    sets[j][0] = word(at + lane_w + j * 512);
+                    sets[j][1] = word(at + lane_w + j * 512 + 8);
+                }
+            };
+            // a plane's products; between them, `between(k)` behind the k-th: a wavefront issues in order, and what it has to do
+            // beside the products fits into the cycles they take
+            auto multiply = [&](auto plane, auto cur, auto step, auto between) {
+                constexpr int P = decltype(plane)::value, kByte = P < 4 ? P : P - 3, S = decltype(step)::value;
+#pragma unroll
+                for (int i = 0; i < RF; ++i) {
+                    const int s = (int)(P < 4 ? scale[S][i] : scale[S][i] - 0x0F0F0F0Fu);
+#pragma unroll
+                    for (int j = 0; j < CF; ++j) {
+                        float16v &c = acc[P < 3 ? 0 : 1][i][j];
+                        const int4v b = bw[S][j];
+                        const int8v w{b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+                        c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x[cur][i], w, c, 2, 4, kByte, s, 0, 127);
+                        between(i * CF + j);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            };
+            auto uniform = [](unsigned char n) { return __builtin_amdgcn_readfirstlane((int)n); };
+            int planes = uniform(count[0]), planes1 = uniform(count[1]), planes2 = uniform(count[2]);
+            unsigned char count3 = count[3];
+            unsigned at = ring, next = ring + kDigitStep, third = ring + 2 * kDigitStep, at16 = at + lane16, at8 = at + lane8;
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoads + CF / 2) : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            read_w(at);
+#pragma unroll
+            for (int i = 0; i < RF; ++i) scale[0][i] = word(at + lane4 + i * 256);
+            {
+                const int first = first_plane(planes);
+                read_x(Int<0>{}, at16 + first, at8 + first, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < CF; ++j) bw[0][j] = FourBitWord(sets[j][0], sets[j][1]).w;
+            constexpr int kProducts = RF * CF;
+            // one step: x[A] holds its first plane, x[B] will hold the next step's; weights and exponents are in [A]
+            auto step_of = [&](auto parity, int step) {
+                constexpr int A = decltype(parity)::value, B = 1 - A;
+                auto then_read = [&](auto cur, int offset) {
+                    return [&, offset](int k) {
+                        if (k == 0) read_x(decltype(cur){}, at16, at8, offset);
+                    };
                 };
-                // this step's planes are written, the other buffer's have been read.  Only LDS traffic is waited for:
-                // the loads of the coming steps stay in flight
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                read_x(0);
-#pragma unroll
-                for (int s = 0; s < 6; ++s) {
-                    if (s < 5) read_x(s + 1);
-#pragma unroll
-                    for (int i = s * kPairs / 5; i < (s + 1) * kPairs / 5 && i < kPairs; ++i) cut_pair(next, i);
-                    if (s == 1) spread_w(bw[1], q, t, 1);
-                    if (s == 4) {
-                        if (t == 1) load_w(q, kb + 2);
-                        spread_w(bw[0], t ? q ^ 1 : q, t ^ 1, 0);
-                    }
-                    if (s == 5) {
-                        // (behind the last block this writes once more what nothing reads)
-                        store_planes(t ^ 1);
-                        load_x(next, 2 * kb + t + 1 + PD);
+                if (planes > 5) {
+                    multiply(Int<5>{}, Int<A>{}, Int<A>{}, then_read(Int<B>{}, plane_offset(6)));
+                    multiply(Int<6>{}, Int<B>{}, Int<A>{}, then_read(Int<A>{}, plane_offset(3)));
+                }
+                if (planes > 3) {
+                    multiply(Int<3>{}, Int<A>{}, Int<A>{}, then_read(Int<B>{}, plane_offset(4)));
+                    multiply(Int<4>{}, Int<B>{}, Int<A>{}, then_read(Int<A>{}, plane_offset(1)));
+                }
+                multiply(Int<1>{}, Int<A>{}, Int<A>{}, [&](int k) {
+                    if (k == 0) read_x(Int<B>{}, at16, at8, plane_offset(2));
+                    if (k == 1) {
+                        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoads) : "memory");   // the next step's W, its own copy
+                        read_w(next);
                     }
 #pragma unroll
-                    for (int i = 0; i < RF; ++i)
+                    for (int i = 0; i < kCopies; ++i)
+                        if (k >= 2 && k == 2 + i) copy_x(i, step + 2, third, planes2);
+                });
+                constexpr int kEarly = kCopies < kProducts - 2 ? kCopies : kProducts - 2;   // copies issued above
+                multiply(Int<2>{}, Int<B>{}, Int<A>{}, [&](int k) {
+                    if (k == 0) read_x(Int<A>{}, at16, at8, plane_offset(0));
 #pragma unroll
-                        for (int j = 0; j < CF; ++j) {
-                            float16v &c = acc[s % 3 ? 1 : 0][i][j];
-                            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[s & 1][i], bw[s / 3][j], c, 0, 0, 0);
+                    for (int j = 0; j < CF; ++j)
+                        if (k == 1 + j * (kProducts - 2) / CF) {
+                            bw[B][j] = FourBitWord(sets[j][0], sets[j][1]).w;
+                            asm volatile("" : "+v"(bw[B][j]));   // here, not where it is used first
                         }
-                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = kEarly; i < kCopies; ++i)
+                        if (k == kProducts - 1) copy_x(i, step + 2, third, planes2);
+                });
+                // the next step's X is there (every wavefront's part of it), and nobody needs this step's any more
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(kLoads) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                multiply(Int<0>{}, Int<A>{}, Int<A>{}, [&](int k) {
+                    if (k == 0) {
+                        const int first = first_plane(planes1);
+                        read_x(Int<B>{}, next + lane16 + first, next + lane8 + first, 0);
+                    }
+                    if (k == 1) {
+#pragma unroll
+                        for (int i = 0; i < RF; ++i) scale[B][i] = word(next + lane4 + i * 256);
+                    }
+                    if (k == 2) copy_w(step + 3, at);
+                });
+                planes = planes1;
+                planes1 = planes2;
+                planes2 = uniform(count3);
+                count3 = count[step + 4];
+                const unsigned free = at;
+                at = next;
+                next = third;
+                third = free;
+                at16 = at + lane16;
+                at8 = at + lane8;
+            };
+            for (int i = 0; i < blocks; i += 2) {
+                step_of(Int<0>{}, i);
+                if (i + 1 < blocks) step_of(Int<1>{}, i + 1);
+            }
+            merge();
+        }
+        // nothing is on its way to the LDS any more
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    if (!in_digits) {
+        clear();
+#pragma unroll
+        for (int s = 0; s < PD; ++s) load_x(s, 2 * kb0 + s);
+        load_w(0, kb0);
+        load_w(1, kb0 + 1);
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) cut_pair(0, i);
+        store_planes(0);
+        load_x(0, 2 * kb0 + PD);
+        bf16x8 bw[2][CF];
+        spread_w(bw[0], 0, 0, 0);
+        for (int i0 = 0; i0 < blocks; i0 += 2) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (i0 + q >= blocks) break;
+                const int kb = kb0 + i0 + q;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {   // half of the block: 32 rows of W, LDS buffer t
+                    const int next = (t + 1) % PD;
+                    bf16x8 x[2][RF];
+                    auto read_x = [&](int s) {   // stage s: plane s % 3 of 16 rows
+#pragma unroll
+                        for (int i = 0; i < RF; ++i)
+                            x[s & 1][i] = __builtin_bit_cast(
+                                bf16x8, lds[t * kBuffer + (s % 3) * kPlane + (2 * (s / 3) + g) * kChunk + (wr * RF + i) * 32 + l32]);
+                    };
+                    // this step's planes are written, the other buffer's have been read.  Only LDS traffic is waited for:
+                    // the loads of the coming steps stay in flight
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                    __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                    read_x(0);
+#pragma unroll
+                    for (int s = 0; s < 6; ++s) {
+                        if (s < 5) read_x(s + 1);
+#pragma unroll
+                        for (int i = s * kPairs / 5; i < (s + 1) * kPairs / 5 && i < kPairs; ++i) cut_pair(next, i);
+                        if (s == 1) spread_w(bw[1], q, t, 1);
+                        if (s == 4) {
+                            if (t == 1) load_w(q, kb + 2);
+                            spread_w(bw[0], t ? q ^ 1 : q, t ^ 1, 0);
+                        }
+                        if (s == 5) {
+                            // (behind the last block this writes once more what nothing reads)
+                            store_planes(t ^ 1);
+                            load_x(next, 2 * kb + t + 1 + PD);
+                        }
+#pragma unroll
+                        for (int i = 0; i < RF; ++i)
+#pragma unroll
+                            for (int j = 0; j < CF; ++j) {
+                                float16v &c = acc[s % 3 ? 1 : 0][i][j];
+                                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[s & 1][i], bw[s / 3][j], c, 0, 0, 0);
+                            }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
         }
+        merge();
     }
+
+    if constexpr (DIGITS) {   // (the two ways to the sums end here: what follows is not made twice)
 #pragma unroll
-    for (int i = 0; i < RF; ++i)
+        for (int i = 0; i < RF; ++i)
 #pragma unroll
-        for (int j = 0; j < CF; ++j) acc[0][i][j] += acc[1][i][j];
+            for (int j = 0; j < CF; ++j) asm volatile("" : "+v"(acc[0][i][j]));
+        asm volatile("" : "+v"(col0), "+v"(row0));
+    }
 
     if constexpr (WK > 1) {   // sums of the groups: the upper half's into the lower half's, until one is left
         float *sums = reinterpret_cast<float *>(lds_all);
@@ -427,7 +788,6 @@ k_matrix(const MatrixArgs a)
 
     // element e of a fragment is row 8 (e / 4) + 4 g + e % 4, column l32.  The stores are range-checked (rows beyond M,
     // columns beyond the last): guarded by branches they waited for each other, 1.4 us of a short call
-    const int row0 = wr * RF * 32 + 4 * g;
     auto row_of = [&](int i, int e) { return row0 + 32 * i + 8 * (e / 4) + e % 4; };
     const bool sliced = a.k_slices > 1;
     float *out = sliced ? a.partials + ((size_t)slice * a.M + m0) * a.n_pad : a.Y + (size_t)m0 * a.N;
@@ -525,17 +885,12 @@ hipError_t launch_sum(const MatrixArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int WK, int WM, int WN, int RF, int CF>
+template <int WK, int WM, int WN, int RF, int CF, bool DIGITS>
 hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 {
-    hipError_t e;
-    if ((e = c.record_before()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_matrix<WK, WM, WN, RF, CF>), dim3((unsigned)(m_tiles * a.n_tiles * a.k_slices)),
+    hipLaunchKernelGGL((k_matrix<WK, WM, WN, RF, CF, DIGITS>), dim3((unsigned)(m_tiles * a.n_tiles * a.k_slices)),
                        dim3(64 * WK * WM * WN), 0, c.stream, a);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = c.record_after();
-    if (e != hipSuccess || a.k_slices == 1) return e;
-    return launch_sum(a, c.stream);
+    return hipGetLastError();
 }
 
 // Tile and K slices of a call: the combination whose estimated time is least.  A workgroup takes `fixed` us and `step`
@@ -562,7 +917,78 @@ constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us 
 struct TilePlan {
     int tile, k_slices;
     double us;
+    bool digits = false;
 };
+// A tile of 64 rows in digits, and how many of them a call cuts at a time: as many as fit in `room`, evenly dealt.
+size_t digit_tile_bytes(const tcsc_layout_t &l) { return (size_t)l.n_kblocks * (kUnitBytes + 1); }
+long long digit_slab(const tcsc_layout_t &l, long long m_tiles, size_t room)
+{
+    long long fit = (long long)(room / digit_tile_bytes(l));
+    const long long launch = 0xffffffffll / 128 / l.n_kblocks;   // threads of k_digits
+    if (fit > launch) fit = launch;
+    if (fit < 1 || fit >= m_tiles) return fit < 1 ? 0 : m_tiles;
+    const long long slabs = (m_tiles + fit - 1) / fit;
+    return (m_tiles + slabs - 1) / slabs;
+}
+
+// X in digits: us of a call on one of the first three tiles with k slices of K, or none where it cannot be.  The three tiles
+// have their own figures, `peak` is for seven planes (X of the normal distribution; five, uniform X, are 20 % faster);
+// kCallDigits and kCutMb (per million entries of X) are for k_digits too, kOutMb per MB of Y.  Fitted to 94 shapes (M = 64 ..
+// 4096, K and N = 512 .. 16384) x 3 tiles x 8 slice counts, 5 % off on average.
+struct DigitTile {
+    double fixed, step, work, peak;
+};
+constexpr DigitTile kDigitTiles[] = {
+    {3.21, 0.54, 0.926, 3.94e8},
+    {2.79, 0.62, 0.498, 3.82e8},
+    {4.15, 1.02, 1.015, 3.65e8},
+};
+constexpr int kDigitTileCount = sizeof(kDigitTiles) / sizeof(kDigitTiles[0]);
+constexpr double kCallDigits = 5.19, kCutMb = 1.436, kOutMb = 0.198, kSliceDigits = 2.88, kSliceMbDigits = 0.307;
+
+bool digits_us(const tcsc_layout_t &l, int M, size_t ws_bytes, int tile, int k, double *us)
+{
+    const TileShape &s = kTiles[tile];
+    const DigitTile &d = kDigitTiles[tile];
+    const int units = compute_units(), per = (l.n_kblocks + k - 1) / k;
+    const long long m_tiles = ((long long)M + s.rows - 1) / s.rows;
+    const size_t partial = k > 1 ? (size_t)4 * k * M * l.n_pad : 0;
+    if (per + 8 > kMaxDigitBlocks || partial > ws_bytes || (k > 1 && ((l.n_kblocks + per - 1) / per != k || M > 65535))) return false;
+    const long long slab = digit_slab(l, m_tiles, ws_bytes - partial);
+    if (slab < 1 || (k > 1 && slab < m_tiles)) return false;
+    const double slabs = ceil((double)m_tiles / slab), tiles = (double)slab * ceil((double)l.n_pad / s.cols);
+    if (tiles * k * (64 * s.waves) >= 4294967296.0) return false;
+    const double load = ceil(tiles * k / units), rounds = ceil(load / s.per_cu), steps = (per + s.groups - 1) / s.groups;
+    const double step_us = d.step * rounds > d.work * load ? d.step * rounds : d.work * load;
+    double t = d.fixed * rounds + steps * step_us;
+    const double floor_us = tiles * s.rows * s.cols * 1e-6 * l.K / (d.peak * 1e-6);
+    if (t < floor_us) t = floor_us;
+    *us = slabs * (kCallDigits + t) + kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N +
+          (k > 1 ? kSliceDigits + kSliceMbDigits * 1e-6 * partial : 0.0);
+    return true;
+}
+
+// Digits in place of bf16 planes where that is estimated to be 4 % faster or more: on the tile and slices chosen for bf16 if it
+// is one of the three, or else, or where it is 10 % faster than there, on the best of the three.  (256 x 4096 x 4096: 28.7 us in
+// bf16, 25.4 with uniform X and 28.0 with normal; 1024 x 4096 x 4096 74 us, 48 and 59; M = 4096, K = N = 8192 1035 us, 585 and
+// 760.  Smaller calls, and X that is large beside Y, do not earn the launch of k_digits and its traffic: 512 x 1024 x 4096 15
+// against 19 us, 1024 x 16384 x 1024 77 against 82.  Over the fitted shapes the choice is 0.7 % behind the best on average.)
+TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TilePlan &p)
+{
+    TilePlan same{-1, 1, 0.0}, best{-1, 1, 0.0};
+    for (int i = 0; i < kDigitTileCount; ++i)
+        for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks; ++k) {
+            double us;
+            const double tiles = ceil((double)M / kTiles[i].rows) * ceil((double)l.n_pad / kTiles[i].cols);
+            if ((k > 1 && tiles * k > 2.0 * compute_units() * kTiles[i].per_cu) || !digits_us(l, M, ws_bytes, i, k, &us)) continue;
+            const TilePlan q{i, k, us, true};
+            if (best.tile < 0 || us < best.us) best = q;
+            if (i == p.tile && k == p.k_slices) same = q;
+        }
+    if (same.tile >= 0 && same.us <= 1.1 * best.us) best = same;
+    return best.tile >= 0 && best.us < 0.96 * p.us ? best : p;
+}
+
 TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
 {
     TilePlan best{-1, 1, 0.0};
@@ -588,7 +1014,7 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
             if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
         }
     }
-    return best;
+    return best.tile < 0 ? best : with_digits(l, M, ws_bytes, best);
 }
 
 // ------------------------------------------------------------------------------------------------------------------
@@ -905,7 +1331,7 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
                                         : 1.6 + 0.67 * M + 2.0 * floor(M * (double)l.K / 38400.0) +
                                               entries * d * (0.22 + 0.08 * M);
             if (r.us >= lists) return none;
-            return MatrixPlan{true, r.tiles, r.waves};
+            return MatrixPlan{true, r.tiles, r.waves, false};
         }
     }
     const TilePlan p = choose_tile(l, M, c.ws_bytes);
@@ -917,12 +1343,12 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
         other = (M <= 16 ? 1.0 : M <= 32 ? 1.3 : 1.7) *
                 ((l.K <= 1024 ? 6.1 : 9.6) + 0.1e-3 * l.K + entries * (0.12 + 0.8 * d));
     } else {
-        if (l.n_pad % 128 != 0) return MatrixPlan{false, p.tile, p.k_slices};
+        if (l.n_pad % 128 != 0) return MatrixPlan{false, p.tile, p.k_slices, p.digits};
         const double groups = ceil(M / 256.0) * (l.n_pad / 128);
         other = 20.0 + ceil(groups / (2.0 * compute_units())) * l.K * (0.0281 + 0.464 * d);
     }
     if (us >= other) return none;
-    return rows ? MatrixPlan{true, r.tiles, r.waves} : MatrixPlan{false, p.tile, p.k_slices};
+    return rows ? MatrixPlan{true, r.tiles, r.waves, false} : MatrixPlan{false, p.tile, p.k_slices, p.digits};
 }
 
 void matrix_tile(const MatrixPlan &p, int M, tstgemm_route_t *out)
@@ -948,14 +1374,48 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     a.k_slices = p.split;
     a.kb_per_slice = (l.n_kblocks + p.split - 1) / p.split;
     const long long m_tiles = ((long long)M + s.rows - 1) / s.rows;
-    switch (p.shape) {
-    case 0: return launch_tiles<1, 1, 8, 2, 2>(a, m_tiles, c);
-    case 1: return launch_tiles<1, 1, 4, 2, 2>(a, m_tiles, c);
-    case 2: return launch_tiles<2, 1, 4, 2, 2>(a, m_tiles, c);
-    case 3: return launch_tiles<1, 1, 4, 2, 1>(a, m_tiles, c);
-    case 4: return launch_tiles<4, 1, 2, 1, 1>(a, m_tiles, c);
-    default: return launch_tiles<2, 1, 4, 1, 1>(a, m_tiles, c);
+    const auto tiles = [&](long long n) {
+        if (p.digits) {
+            switch (p.shape) {
+            case 0: return launch_tiles<1, 1, 8, 2, 2, true>(a, n, c);
+            case 1: return launch_tiles<1, 1, 4, 2, 2, true>(a, n, c);
+            default: return launch_tiles<2, 1, 4, 2, 2, true>(a, n, c);
+            }
+        }
+        switch (p.shape) {
+        case 0: return launch_tiles<1, 1, 8, 2, 2, false>(a, n, c);
+        case 1: return launch_tiles<1, 1, 4, 2, 2, false>(a, n, c);
+        case 2: return launch_tiles<2, 1, 4, 2, 2, false>(a, n, c);
+        case 3: return launch_tiles<1, 1, 4, 2, 1, false>(a, n, c);
+        case 4: return launch_tiles<4, 1, 2, 1, 1, false>(a, n, c);
+        default: return launch_tiles<2, 1, 4, 1, 1, false>(a, n, c);
+        }
+    };
+    hipError_t e = hipSuccess;
+    if (!p.digits) {
+        if ((e = c.record_before()) != hipSuccess || (e = tiles(m_tiles)) != hipSuccess) return e;
+    } else {
+        // X in slabs of as many tiles as the workspace holds in digits
+        const size_t partial_bytes = p.split > 1 ? (size_t)p.split * M * l.n_pad * 4 : 0, tile_bytes = digit_tile_bytes(l);
+        const long long slab = digit_slab(l, m_tiles, c.ws_bytes - partial_bytes);
+        char *units = c.ws + partial_bytes;
+        unsigned char *counts = reinterpret_cast<unsigned char *>(units + slab * (tile_bytes - l.n_kblocks));
+        a.digits = units;
+        a.counts = counts;
+        for (long long t = 0; t < m_tiles; t += slab) {
+            const long long n = slab < m_tiles - t ? slab : m_tiles - t;
+            a.X = X + (size_t)t * 64 * l.K;
+            a.Y = Y + (size_t)t * 64 * l.N;
+            a.M = (int)(M - t * 64 < n * 64 ? M - t * 64 : n * 64);
+            hipLaunchKernelGGL(k_digits, dim3((unsigned)(n * l.n_kblocks)), dim3(128), 0, c.stream, a.X, a.M, l.K,
+                               l.n_kblocks, units, counts);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            if (t == 0 && (e = c.record_before()) != hipSuccess) return e;
+            if ((e = tiles(n)) != hipSuccess) return e;
+        }
     }
+    if ((e = c.record_after()) != hipSuccess || a.k_slices == 1) return e;
+    return launch_sum(a, c.stream);
 }
 
 // Whether k_rows takes the base-3 codes, or k_packed, which multiplies on the vector ALU: a workgroup of that takes
@@ -971,7 +1431,7 @@ MatrixPlan packed_plan(const tcsc_layout_t &l, int M)
     const double rounds = ceil((double)groups * parts / units);
     const double other = 2.6 + rounds * l.K / parts * 1e-3 * (0.65 + 0.43 * M) + (parts > 1 ? 3.0 : 0.0);
     const RowsPlan r = rows_plan(l, M, true);
-    return r.us < other ? MatrixPlan{true, r.tiles, r.waves} : MatrixPlan{};
+    return r.us < other ? MatrixPlan{true, r.tiles, r.waves, false} : MatrixPlan{};
 }
 
 hipError_t launch_packed_rows(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)

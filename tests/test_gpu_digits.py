@@ -1,0 +1,168 @@
+"""k_matrix with X in digits (6-bit floats, one exponent for 32 entries of a row), which calls large enough take: every number
+of planes, tiles that go back to bf16 planes beside tiles that do not, remainders of rows, entries and columns, K slices and
+slabs, against float64 products."""
+import numpy as np
+import pytest
+
+import paper_2510_06957_amd as tg
+
+pytestmark = pytest.mark.gpu
+
+# (M, K, N, slices of K): calls that are estimated to be faster in digits by more than a tenth, on each tile, K whole and sliced;
+# rows one more and less than a tile, K at a block's edge, inside one and odd, columns of a part of a tile
+SHAPES = [(129, 8192, 8192), (513, 4161, 4100), (1023, 2047, 8200), (2049, 1985, 4097), (191, 16380, 4090), (777, 4099, 8190),
+          (1300, 4100, 5000)]
+
+
+def problem(M, K, N, seed, values, density=0.5):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    u = torch.rand((K, N), generator=g, device="cuda")
+    W = (u < density / 2).to(torch.int8) - ((u >= density / 2) & (u < density)).to(torch.int8)
+    if values == "normal":
+        X = torch.randn((M, K), generator=g, device="cuda")
+    elif values == "uniform":
+        X = torch.rand((M, K), generator=g, device="cuda") * 2 - 1
+    elif values == "int":
+        X = torch.randint(-100, 101, (M, K), generator=g, device="cuda").float()
+    else:   # bf16: activations that come out of a 16-bit layer
+        X = torch.randn((M, K), generator=g, device="cuda").bfloat16().float()
+    b = torch.randint(-8, 9, (N,), generator=g, device="cuda").float()
+    t = tg.tcsc_upload(tg.tcsc_build(W.cpu().numpy()), forms=tg.FORM_ROWSETS)
+    return W.double(), X, b, t
+
+
+def workspace(M, K, N):
+    import torch
+    return torch.empty(tg.tstgemm_workspace_bytes(M, K, N)[1] + (96 << 20), dtype=torch.uint8, device="cuda")
+
+
+# Bound on the error: the sums of the upper digits and of the lower are rounded once per 64 rows of W, and what the cut leaves
+# over is less than 2^-31 of an entry of each 32; measured at 3e-8 of sum |X W|.
+TIGHT = 1e-6
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+@pytest.mark.parametrize("values", ["normal", "uniform", "int", "bf16"])
+def test_planes(M, K, N, values):
+    W, X, b, t = problem(M, K, N, 900 + M, values)
+    Y = tg.tstgemm(X, t, b, workspace=workspace(M, K, N)).double()
+    E = X.double() @ W + b.double()
+    if values == "int":
+        assert (Y == E).all()
+    else:
+        A = X.double().abs() @ W.abs() + b.double().abs()
+        assert ((Y - E).abs() <= TIGHT * A).all()
+        assert (Y - E).norm() <= 1e-7 * E.norm()
+
+
+def test_every_entry_alone():
+    """One entry of W in a column: an output is an entry of X, exactly where seven planes hold it, and to half of their last
+    bit elsewhere."""
+    import torch
+    M, K = 2048, 4096
+    perm = np.random.default_rng(910).permutation(K)
+    W = np.zeros((K, K), np.int8)
+    W[perm, np.arange(K)] = 1
+    t = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_ROWSETS)
+    g = torch.Generator(device="cuda").manual_seed(911)
+    ws = workspace(M, K, K)
+    for values in ("powers", "normal", "full"):
+        if values == "powers":
+            # +-2^e, and a third of them one less in the last place.  Seven planes hold multiples of 2^(E - 33), E the exponent of
+            # the largest entry (0 here): an entry of exponent e has multiples of 2^(e - 23), so all is held from e = -10 on,
+            # which is what one less than 2^-9 has
+            e = torch.randint(-9, 1, (M, K), generator=g, device="cuda").float()
+            X = torch.exp2(e) * torch.where(torch.rand((M, K), generator=g, device="cuda") < 0.5, -1.0, 1.0)
+            X[:, ::3] = torch.nextafter(X[:, ::3], torch.zeros_like(X[:, ::3]))
+            X[:, ::32] = 1.0
+        elif values == "normal":
+            X = torch.randn((M, K), generator=g, device="cuda")
+        else:                      # all 24 bits set at random, large scale
+            X = (torch.randint(2**23, 2**24, (M, K), generator=g, device="cuda") * 2.0**40).float()
+        Y = tg.tstgemm(X, t, None, workspace=ws)
+        want = X[:, torch.from_numpy(perm).cuda()]
+        if values == "normal":
+            top = X.view(M, K // 32, 32).abs().amax(2).log2().floor().exp2()
+            bound = top.repeat_interleave(32, dim=1)[:, torch.from_numpy(perm).cuda()] * 2.0**-34
+            assert ((Y - want).abs() <= bound).all()
+            assert (Y == want).double().mean() > 0.99
+        else:
+            assert torch.equal(Y, want)
+
+
+@pytest.mark.parametrize("M,K,N", [(513, 4161, 4100), (191, 16380, 4090)])
+def test_tiles_that_digits_do_not_hold(M, K, N):
+    """Rows with entries too far apart, beyond the exponents' range, infinite or NaN: their tiles go back to bf16 planes (and
+    from there, where a sum is not finite, to the sums of any X); the others keep their digits.  What no infinity or NaN
+    reaches is right, what one reaches is not finite."""
+    import torch
+    W, X, b, t = problem(M, K, N, 920, "normal")
+    g = torch.Generator(device="cuda").manual_seed(921)
+    X[70] *= torch.exp2(torch.randint(-60, 20, (K,), generator=g, device="cuda").float())
+    X[3] *= 1e-36
+    X[140] *= 1e33
+    X[150, 100], X[150, K - 1], X[151, K - 1] = float("inf"), float("-inf"), float("nan")
+    X[190, 0] = float("nan")
+    Y = tg.tstgemm(X, t, b, workspace=workspace(M, K, N)).double()
+    bad = ~torch.isfinite(X)
+    E = X.double().masked_fill(bad, 0) @ W + b.double()
+    A = X.double().abs().masked_fill(bad, 0) @ W.abs() + b.double().abs()
+    reached = (bad.double() @ W.abs()) > 0
+    assert torch.equal(~torch.isfinite(Y), reached) and reached.any()
+    assert ((Y - E).abs() <= TIGHT * A)[~reached].all()
+
+
+@pytest.mark.parametrize("M,K,N", [(1023, 2047, 8200), (2049, 1985, 4097)])
+def test_slabs_of_rows(M, K, N):
+    """A workspace that holds only some of the tiles in digits, down to the least that a call needs: the same results."""
+    import torch
+    W, X, b, t = problem(M, K, N, 930, "normal")
+    Y = tg.tstgemm(X, t, b, workspace=workspace(M, K, N))
+    E = X.double() @ W + b.double()
+    A = X.double().abs() @ W.abs() + b.double().abs()
+    least = tg.tstgemm_workspace_bytes(M, K, N)[0]
+    for size in (M * K * 4, M * K * 3, M * K * 2, least):
+        size = size // 256 * 256
+        ws = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
+        ws[size:] = 77
+        Z = tg.tstgemm(X, t, b, workspace=ws[:size])
+        assert ((Z.double() - E).abs() <= TIGHT * A).all() and (ws[size:] == 77).all()
+    assert ((Y.double() - E).abs() <= TIGHT * A).all()
+
+
+@pytest.mark.parametrize("count", ["one", "column"])
+def test_prelu_and_rows_behind_y(count):
+    import torch
+    M, K, N = 513, 4161, 4100
+    W, X, b, t = problem(M, K, N, 940, "int")
+    alpha = torch.exp2(torch.randint(-3, 3, (1 if count == "one" else N,), device="cuda").float())
+    out = torch.full((M + 2, N), float("nan"), device="cuda")
+    Y = tg.tstgemm(X, t, b, Y=out[:M], alpha=alpha, workspace=workspace(M, K, N)).double()
+    E = X.double() @ W + b.double()
+    assert (Y == torch.where(E > 0, E, alpha.double() * E)).all()
+    assert torch.isnan(out[M:]).all()
+
+
+def test_under_graph_capture():
+    """Recorded once and replayed on new X, with eager work in between: the number of planes follows the X of the replay."""
+    import torch
+    M, K, N = 1023, 2047, 8200
+    W, X, b, t = problem(M, K, N, 950, "int")
+    ws, Y = workspace(M, K, N), torch.empty((M, N), device="cuda")
+    tg.tstgemm(X, t, b, Y, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tg.tstgemm(X, t, b, Y, workspace=ws)
+    for seed, values in enumerate(("normal", "int", "uniform", "wide", "int")):
+        _, Xs, _, _ = problem(M, K, 64, 951 + seed, "normal" if values == "wide" else values)
+        if values == "wide":
+            Xs[::64] *= torch.exp2(torch.arange(K, device="cuda") % 60 - 30.0)
+        X.copy_(Xs)
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        E = X.double() @ W + b.double()
+        A = X.double().abs() @ W.abs() + b.double().abs()
+        assert ((Y.double() - E).abs() <= TIGHT * A).all(), values
