@@ -13,6 +13,8 @@ import numpy as np
 _HERE = pathlib.Path(__file__).resolve().parent
 _LIB_PATH = _HERE / "libtstgemm.so"
 _lib = None
+_launch = None   # the native half (csrc/launch.cpp), once _load() has bound it to the library
+_GEMM, _PACKED, _SIGNED, _NOALLOC = range(4)   # its entries
 
 
 class TstgemmError(RuntimeError):
@@ -111,7 +113,21 @@ def _load():
                  "tstgemm_noalloc", "tstgemm_query_route"):
         getattr(lib, name).restype = ci
     _lib = lib
+    _bind_launcher(lib)
     return lib
+
+
+def _bind_launcher(lib):
+    """The native half of the calls on tensors.  It only saves host time: without it (not built, or built for another torch) the
+    calls go through ctypes."""
+    global _launch
+    try:
+        from . import _launch as native
+    except ImportError:
+        return
+    native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.tstgemm, lib.tstgemm_packed, lib.tstgemm_signed,
+                                                                  lib.tstgemm_noalloc, lib.tstgemm_prelu)))
+    _launch = native.launch
 
 
 def tcsc_strerror(code: int) -> str:
@@ -132,6 +148,7 @@ class Tcsc:
 
     def __init__(self, handle: int):
         self._h = ctypes.c_void_p(handle)
+        self._raw = handle   # the same as an int, for the native half
         self.device_buffer = None
         self.K, self.N, self.nnz_pos, self.nnz_neg = tcsc_dims(self)
 
@@ -323,6 +340,10 @@ def tstgemm(X, t: Tcsc, b=None, Y=None, stream=None, alpha=None, **options):
 
     Launches on `stream` (default: torch's current stream) of the current device, which must be the device the
     handle was uploaded to and the one holding X, b, alpha and Y."""
+    if _launch is not None and not options:
+        done = _launch(_GEMM, X, t, b, Y, stream, alpha)
+        if done is not None:
+            return done
     M, K, N, b_ptr, Y, dev = _gemm_args(X, t, b, Y)
     o = _opts(X, N, 0, alpha, **options)
     if o is None:
@@ -337,7 +358,11 @@ def tstgemm(X, t: Tcsc, b=None, Y=None, stream=None, alpha=None, **options):
     return Y
 
 
-def _variant(name, encoding, X, t, b, Y, stream, options):
+def _variant(name, entry, encoding, X, t, b, Y, stream, options):
+    if _launch is not None and not options:
+        done = _launch(entry, X, t, b, Y, stream, None)
+        if done is not None:
+            return done
     M, K, N, b_ptr, Y, dev = _gemm_args(X, t, b, Y)
     if options:
         o = _opts(X, N, encoding, None, **options)
@@ -357,6 +382,10 @@ def tstgemm_noalloc(X, t: Tcsc, b, Y, stream=None):
     wrapper allocates nothing either."""
     if Y is None:
         raise ValueError("tstgemm_noalloc needs an output tensor")
+    if _launch is not None:
+        done = _launch(_NOALLOC, X, t, b, Y, stream, None)
+        if done is not None:
+            return done
     M, K, N, b_ptr, Y, dev = _gemm_args(X, t, b, Y)
     rc = _load().tstgemm_noalloc(X.data_ptr(), t.handle, b_ptr, Y.data_ptr(), M, K, N, _launch_stream(stream, dev))
     if rc != 0:
@@ -366,13 +395,13 @@ def tstgemm_noalloc(X, t: Tcsc, b, Y, stream=None):
 
 def tstgemm_signed(X, t: Tcsc, b=None, Y=None, stream=None, **options):
     """Y = X W + b for M <= 8 from the inverted-index form of the uploaded matrix (tstgemm_signed of the C ABI)."""
-    return _variant("tstgemm_signed", 1, X, t, b, Y, stream, options)
+    return _variant("tstgemm_signed", _SIGNED, 1, X, t, b, Y, stream, options)
 
 
 def tstgemm_packed(X, t: Tcsc, b=None, Y=None, stream=None, **options):
     """Y = X W + b for M <= 8 from the value-compression form of the uploaded matrix (tstgemm_packed of the C ABI);
     X must be finite."""
-    return _variant("tstgemm_packed", 2, X, t, b, Y, stream, options)
+    return _variant("tstgemm_packed", _PACKED, 2, X, t, b, Y, stream, options)
 
 
 def tstgemm_query_route(t: Tcsc, M: int, encoding=0, workspace_bytes=0, cols_per_wave=0, k_slices=0, slab_tiles=0, list_walk=0,
@@ -432,5 +461,5 @@ def tstgemm_probe_tile_copy(buf, iters: int, stream=None) -> int:
 def tcsc_destroy(t: Tcsc):
     if getattr(t, "_h", None) is not None:
         _load().tcsc_destroy(t._h)
-        t._h = None
+        t._h = t._raw = None
         t.device_buffer = None

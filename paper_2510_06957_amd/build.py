@@ -1,4 +1,5 @@
-"""Build libtstgemm.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libtstgemm.so (HIP, gfx950 only) in-tree with hipcc, and _launch.so, the binding's native half (host code on torch's
+C++ headers), with g++.
 
     python -m paper_2510_06957_amd.build
 
@@ -17,6 +18,7 @@ HERE = pathlib.Path(__file__).resolve().parent
 ROOT = HERE.parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libtstgemm.so"
+LAUNCH = HERE / "_launch.so"
 SOURCES = ["tcsc_host.cpp", "reblock.hip", "tstgemm_side.hip", "tstgemm_large.hip", "tstgemm_small.hip", "tstgemm_matrix.hip",
            "tstgemm_decode.hip", "tstgemm_packed.hip", "probes.hip", "tstgemm_noalloc.hip"]
 ARCH = "gfx950"
@@ -40,17 +42,35 @@ def command(out: pathlib.Path = LIB, extra: list[str] | None = None) -> list[str
     return cmd
 
 
-def build(verbose: bool = False) -> pathlib.Path:
-    cmd = command()
+def launch_command(out: pathlib.Path = LAUNCH) -> list[str]:
+    import sysconfig
+
+    import torch
+    home = pathlib.Path(torch.__file__).resolve().parent
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for path in (home / "include", home / "include" / "torch" / "csrc" / "api" / "include",
+                 pathlib.Path(hipcc()).resolve().parent.parent / "include", sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", str(path)]
+    cmd += [str(CSRC / "launch.cpp"), f"-L{home / 'lib'}", "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10", "-o", str(out)]
+    return cmd
+
+
+def _run(cmd: list[str], verbose: bool):
     if verbose:
         print(" ".join(cmd))
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({r.returncode}):\n{err}")
+        raise RuntimeError(f"{cmd[0]} failed ({r.returncode}):\n{err}")
     if verbose and err.strip():
         print(err)
+
+
+def build(verbose: bool = False) -> pathlib.Path:
+    _run(command(), verbose)
+    _run(launch_command(), verbose)
     return LIB
 
 
