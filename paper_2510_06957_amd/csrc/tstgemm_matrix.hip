@@ -946,26 +946,46 @@ constexpr DigitTile kDigitTiles[] = {
 constexpr int kDigitTileCount = sizeof(kDigitTiles) / sizeof(kDigitTiles[0]);
 constexpr double kCallDigits = 5.19, kCutMb = 1.436, kOutMb = 0.198, kSliceDigits = 2.88, kSliceMbDigits = 0.307;
 
-bool digits_us(const tcsc_layout_t &l, int M, size_t ws_bytes, int tile, int k, double *us)
+// Whole numbers from x up, x >= 0 and below 2^62 (ceil() is a library call here, and the estimates make many).
+inline double up(double x)
+{
+    const double whole = (double)(long long)x;
+    return whole < x ? whole + 1.0 : whole;
+}
+
+// The best of a tile's slice counts in digits (tile < 0: none can be), and the one for `same_k` slices.
+void digit_plans(const tcsc_layout_t &l, int M, size_t ws_bytes, int tile, int same_k, TilePlan *best, TilePlan *same)
 {
     const TileShape &s = kTiles[tile];
     const DigitTile &d = kDigitTiles[tile];
-    const int units = compute_units(), per = (l.n_kblocks + k - 1) / k;
+    const int units = compute_units();
     const long long m_tiles = ((long long)M + s.rows - 1) / s.rows;
-    const size_t partial = k > 1 ? (size_t)4 * k * M * l.n_pad : 0;
-    if (per + 8 > kMaxDigitBlocks || partial > ws_bytes || (k > 1 && ((l.n_kblocks + per - 1) / per != k || M > 65535))) return false;
-    const long long slab = digit_slab(l, m_tiles, ws_bytes - partial);
-    if (slab < 1 || (k > 1 && slab < m_tiles)) return false;
-    const double slabs = ceil((double)m_tiles / slab), tiles = (double)slab * ceil((double)l.n_pad / s.cols);
-    if (tiles * k * (64 * s.waves) >= 4294967296.0) return false;
-    const double load = ceil(tiles * k / units), rounds = ceil(load / s.per_cu), steps = (per + s.groups - 1) / s.groups;
-    const double step_us = d.step * rounds > d.work * load ? d.step * rounds : d.work * load;
-    double t = d.fixed * rounds + steps * step_us;
-    const double floor_us = tiles * s.rows * s.cols * 1e-6 * l.K / (d.peak * 1e-6);
-    if (t < floor_us) t = floor_us;
-    *us = slabs * (kCallDigits + t) + kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N +
-          (k > 1 ? kSliceDigits + kSliceMbDigits * 1e-6 * partial : 0.0);
-    return true;
+    const double n_tiles = (l.n_pad + s.cols - 1) / s.cols, all_tiles = (double)m_tiles * n_tiles;
+    const double cut_out = kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N;
+    const double sum_bytes = 4.0 * M * l.n_pad, tile_bytes = (double)digit_tile_bytes(l) * (double)m_tiles;
+    const double work = 1.0 * s.rows * s.cols * l.K / d.peak;
+    for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || all_tiles * k <= 2.0 * units * s.per_cu); ++k) {
+        const int per = (l.n_kblocks + k - 1) / k;
+        if (per + 8 > kMaxDigitBlocks) continue;
+        double slabs = 1.0, tiles = all_tiles, slices_us = 0.0;
+        if (k > 1) {   // all of X in digits and the partial sums
+            if (per * (k - 1) >= l.n_kblocks || M > 65535 || sum_bytes * k + tile_bytes > (double)ws_bytes) continue;
+            slices_us = kSliceDigits + kSliceMbDigits * 1e-6 * sum_bytes * k;
+        } else {
+            const long long slab = digit_slab(l, m_tiles, ws_bytes);
+            if (slab < 1) continue;
+            slabs = up((double)m_tiles / (double)slab);
+            tiles = (double)slab * n_tiles;
+        }
+        if (tiles * k * (64 * s.waves) >= 4294967296.0) continue;
+        const double load = up(tiles * k / units), rounds = up(load / s.per_cu), steps = (per + s.groups - 1) / s.groups;
+        const double step_us = d.step * rounds > d.work * load ? d.step * rounds : d.work * load;
+        double us = d.fixed * rounds + steps * step_us;
+        if (us < tiles * work) us = tiles * work;
+        us = slabs * (kCallDigits + us) + cut_out + slices_us;
+        if (best->tile < 0 || us < best->us) *best = TilePlan{tile, k, us, true};
+        if (k == same_k) *same = TilePlan{tile, k, us, true};
+    }
 }
 
 // Digits in place of bf16 planes where that is estimated to be 4 % faster or more: on the tile and slices chosen for bf16 if it
@@ -975,16 +995,11 @@ bool digits_us(const tcsc_layout_t &l, int M, size_t ws_bytes, int tile, int k, 
 // against 19 us, 1024 x 16384 x 1024 77 against 82.  Over the fitted shapes the choice is 0.7 % behind the best on average.)
 TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TilePlan &p)
 {
+    // (what any of them takes at least: most short calls end here)
+    const double least = kCallDigits + 2.79 + kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N;
+    if (least >= 0.96 * p.us) return p;
     TilePlan same{-1, 1, 0.0}, best{-1, 1, 0.0};
-    for (int i = 0; i < kDigitTileCount; ++i)
-        for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks; ++k) {
-            double us;
-            const double tiles = ceil((double)M / kTiles[i].rows) * ceil((double)l.n_pad / kTiles[i].cols);
-            if ((k > 1 && tiles * k > 2.0 * compute_units() * kTiles[i].per_cu) || !digits_us(l, M, ws_bytes, i, k, &us)) continue;
-            const TilePlan q{i, k, us, true};
-            if (best.tile < 0 || us < best.us) best = q;
-            if (i == p.tile && k == p.k_slices) same = q;
-        }
+    for (int i = 0; i < kDigitTileCount; ++i) digit_plans(l, M, ws_bytes, i, i == p.tile ? p.k_slices : 0, &best, &same);
     if (same.tile >= 0 && same.us <= 1.1 * best.us) best = same;
     return best.tile >= 0 && best.us < 0.96 * p.us ? best : p;
 }
@@ -995,7 +1010,7 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
     const int units = compute_units();
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const TileShape &s = kTiles[i];
-        const double tiles = ceil((double)M / s.rows) * ceil((double)l.n_pad / s.cols);
+        const double tiles = (double)(((long long)M + s.rows - 1) / s.rows) * ((l.n_pad + s.cols - 1) / s.cols);
         const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
         // a launch has less than 2^32 threads; a call with more tiles than that (K slices are for few tiles only) goes to
         // k_large, which takes X in slabs
@@ -1004,8 +1019,8 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
         for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || tiles * k <= 2.0 * units * s.per_cu); ++k) {
             const int per = (l.n_kblocks + k - 1) / k;
             const double mb = 4e-6 * (double)k * M * l.n_pad;
-            if (k > 1 && ((l.n_kblocks + per - 1) / per != k || M > 65535 || mb * 1e6 > (double)ws_bytes)) continue;
-            const double load = ceil(tiles * k / units), rounds = ceil(load / s.per_cu);
+            if (k > 1 && (per * (k - 1) >= l.n_kblocks || M > 65535 || mb * 1e6 > (double)ws_bytes)) continue;
+            const double load = up(tiles * k / units), rounds = up(load / s.per_cu);
             const double steps = 2.0 * ((per + s.groups - 1) / s.groups);
             const double step_us = s.step * rounds > s.work * load ? s.step * rounds : s.work * load;
             double us = s.fixed * rounds + steps * step_us;
