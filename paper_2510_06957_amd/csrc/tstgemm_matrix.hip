@@ -1037,12 +1037,13 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
 // rows of X cost one matrix instruction where k_matrix would need three.  A workgroup is KW wavefronts with the same 16 B
 // columns, each with every KW-th group of four blocks (256 rows of W): a lane's 16-byte load is one block of one column,
 // and serves eight matrix instructions, so the row sets are read once, 2 bits an entry, with no LDS in between.  A group of X
-// is cut by its wavefront alone and goes through a piece of the LDS of its own, a plane at a time, into fragments that all
+// is cut by its wavefront alone and goes through a piece of the LDS of its own into fragments that all
 // B tiles of columns use; the next group's loads are under way meanwhile.  The sums of the KW wavefronts meet in the LDS.
 // Bound by the latency of that chain (2.5 us with one group a wavefront, of which launch and first loads are most) and
-// then by spreading and cutting on the vector ALU.  Against the lists, at 50 % non-zeros: M = 1, 4096 x 11008 10.4 -> 5.5 us,
-// M = 8 23.7 -> 7.9 us, M = 4, 16384 x 4096 31 -> 11 us.  Without the next group's loads 6.7, 8.9 and 13.9 us; KW = 16
-// gains 5 % at K = 16384 and loses 2 % at 4096.
+// then by spreading and cutting on the vector ALU and by the LDS: all three planes are staged before any is read, so that a
+// fragment is one read of all lanes; plane by plane, each lane waiting for its own, it was three.  M = 1, 4096 x 11008
+// 5.3 -> 4.9 us, M = 8 7.9 -> 7.5, M = 8, 4096 x 4096 5.8 -> 5.3, M = 2, 11008 x 4096 6.4 -> 5.2 (lists, at 50 % non-zeros: 10.0, 23.7, 10.7, 10.7).
+// Without the next group's loads 20 % more.
 //
 // PACKED: W from the base-3 codes (a.masks, a.n_kblocks: 16-byte pieces of 80 rows, [piece][n_pad]).  A table in the LDS
 // gives the five weights of a code, sign and non-zero bit side by side; the words of codes j and j + 8 make dwords for
@@ -1074,7 +1075,7 @@ k_rows(const MatrixArgs a)
     constexpr int kUnits = 4 * kSteps, kRowUnits = kUnits + 1;   // 16-byte units per staged row of a group (+ 1: other banks)
     constexpr int kBlockRows = 8 * kSteps, kPartner = PACKED ? 40 : 16;
     constexpr int T = (3 * MM + 15) / 16, kItems = (MM * kUnits + 63) / 64;
-    constexpr int kStage = KW * MM * kRowUnits, kSums = KW * B * T * 64;
+    constexpr int kStage = KW * 3 * MM * kRowUnits, kSums = KW * B * T * 64;
     __shared__ uint4v lds[kStage > kSums ? kStage : kSums];
     __shared__ unsigned table[PACKED ? 256 : 1];
     __shared__ int spoilt;   // a sum was not finite
@@ -1082,7 +1083,7 @@ k_rows(const MatrixArgs a)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int n0 = blockIdx.x * (16 * B), M = a.M, n_groups = (a.n_kblocks + 3) / 4;
-    uint4v *stage = lds + wave * (MM * kRowUnits);
+    uint4v *stage = lds + wave * (3 * MM * kRowUnits);   // [plane][row]
     const __amdgpu_buffer_rsrc_t wbuf = raw_buffer(a.masks, (size_t)a.n_kblocks * a.n_pad * 16);
     const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(a.X, (size_t)M * a.K * 4);
 
@@ -1131,16 +1132,11 @@ k_rows(const MatrixArgs a)
             x1[i] = x1_next[i] * kScaleUp;
         }
         if (group + KW < n_groups) load(group + KW);
-        bf16x8 x[T][kSteps];
 #pragma unroll
-        for (int t = 0; t < T; ++t)
+        for (int i = 0; i < kItems; ++i) {
+            const int it = lane + 64 * i, m = it / kUnits, unit = it % kUnits;
 #pragma unroll
-            for (int s = 0; s < kSteps; ++s) x[t][s] = __builtin_bit_cast(bf16x8, uint4v{0, 0, 0, 0});
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-#pragma unroll
-            for (int i = 0; i < kItems; ++i) {
-                const int it = lane + 64 * i, m = it / kUnits, unit = it % kUnits;
+            for (int p = 0; p < 3; ++p) {
                 uint4v d;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -1148,20 +1144,19 @@ k_rows(const MatrixArgs a)
                     x0[i][e] = below_top(x0[i][e]);
                     x1[i][e] = below_top(x1[i][e]);
                 }
-                if (m < M) stage[m * kRowUnits + unit] = d;
+                if (m < M) stage[(p * M + m) * kRowUnits + unit] = d;
             }
-            // the wavefront's own piece of the LDS, and its LDS operations stay in order: no barrier
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int m = 16 * t + r - p * M;   // row 16 t + r of A is row m of this plane
-                if (m >= 0 && m < M)
-#pragma unroll
-                    for (int s = 0; s < kSteps; ++s)
-                        x[t][s] = __builtin_bit_cast(bf16x8, stage[m * kRowUnits + kSteps * g + s]);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
+        // the wavefront's own piece of the LDS, and its LDS operations stay in order: no barrier
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        bf16x8 x[T][kSteps];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int row = min(16 * t + r, 3 * M - 1);   // (rows of A beyond the planes give rows nobody reads)
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) x[t][s] = __builtin_bit_cast(bf16x8, stage[row * kRowUnits + kSteps * g + s]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             auto multiply = [&](int step, bf16x8 bw) {
@@ -1255,8 +1250,8 @@ hipError_t launch_rows_kernel(const MatrixArgs &a, const Call &c)
 
 // Shape of a call with M <= 10: eight wavefronts from five groups of 256 rows on, else four; as few tiles of 16 columns per
 // workgroup as leave one workgroup per compute unit (more of the small ones: they fit side by side), because every
-// workgroup cuts X anew.  us: 2.0 .. 2.7 + turns through the groups x (cutting + spreading) (microseconds, measured on
-// M = 1 .. 10, K = 512 .. 16384, N = 512 .. 16384).
+// workgroup cuts X anew.  us: 2.0 .. 2.6 + turns through the groups x (cutting + spreading) (fitted to 119 calls, M = 1 .. 8,
+// K and N = 512 .. 16384: 7 % off on average, 24 % at worst).
 struct RowsPlan {
     int tiles, waves;
     double us;
@@ -1270,12 +1265,12 @@ RowsPlan rows_plan(const tcsc_layout_t &l, int M, bool packed)
     const int slots = p.waves == 8 ? units : M <= 5 && !packed ? 4 * units : 2 * units;
     p.tiles = (int)fmin(ceil(tiles / slots), p.waves == 8 ? 4.0 : 2.0);
     const double rounds = fmax(1.0, tiles / ((double)p.tiles * slots));
-    double start = p.waves == 4 ? 2.0 : M <= 2 ? 2.5 : 2.7;
-    double cut = M <= 2 ? 0.45 : M <= 5 ? 0.70 : 1.1, spread = M <= 2 ? 0.35 : M <= 5 ? 0.37 : 0.55;
+    double start = p.waves == 4 ? 2.03 : M <= 2 ? 2.25 : M <= 5 ? 2.45 : 2.59;
+    double cut = M <= 2 ? 0.10 : M <= 5 ? 0.42 : 0.58, spread = M <= 2 ? 0.46 : M <= 5 ? 0.47 : 0.66;
     if (packed) {
-        start = p.waves == 4 ? 2.2 : M <= 5 ? 2.9 : 3.2;
-        cut = M <= 2 ? 0.48 : M <= 5 ? 1.0 : 1.35;
-        spread = 0.70;
+        start = p.waves == 4 ? 2.34 : M <= 2 ? 2.73 : M <= 5 ? 3.02 : 3.33;
+        cut = M <= 2 ? 0.20 : M <= 5 ? 0.61 : 1.02;
+        spread = M <= 2 ? 0.64 : M <= 5 ? 0.67 : 0.75;
     }
     p.us = start + ((groups + p.waves - 1) / p.waves) * rounds * (cut + spread * p.tiles);
     return p;
@@ -1328,11 +1323,11 @@ double density(const tcsc_layout_t &l) { return (double)(l.nnz_pos + l.nnz_neg) 
 //    + 0.1 per 1000 rows of W + 0.12 per million entries + 0.8 per million non-zeros, 1.3 and 1.7 times that for 32 and
 //    64 rows (M = 16: 1024 x 4096 at 1/16 6.6 against 7.4 us, 15000 x 600 12.6 against 14.2; from 17 rows on it is behind
 //    everywhere, down to an empty W).
-//  * M <= 8: k_decode takes 2.7 + 0.3 M + (0.17 + 0.08 M) us per million non-zeros for one or two rows, 1.6 + 0.67 M +
-//    (0.22 + 0.08 M) for more, and 2 us for each further time that X fills the LDS (less than measured wherever K is
-//    long, so that a tie goes to the lists).  It stays ahead
-//    for one or two rows at 1/8 and below (M = 1, 16384 x 4096: 5.1 against 9.1 us at 1/8; at 1/4 8.8 against 9.1, at 1/2
-//    14.1 against 9.1) and for a few columns over a long K (M = 1, 15000 x 600 at 1/4: 5.0 against 7.6).
+//  * M <= 8: k_decode takes 2.55 + 0.5 M + 0.04 us per 1000 rows of W + (0.265 + 0.016 M) us per million non-zeros for one or
+//    two rows, 2.03 + 0.58 M + 0.13 + (0.353 + 0.066 M) for more, and 3.5 us for each further time that X fills the LDS (fitted
+//    to 17 shapes x 4 densities x M = 1 .. 8; the choice is 0.6 % behind the better of the two on average, 69 % at worst, 3 x 4096
+//    x 11008 at 1/16).  It stays ahead for few non-zeros and a long K (M = 1, 16384 x 4096 at 1/8: 4.7 us against 7.2; at 1/4
+//    8.6 against 7.3), and k_rows otherwise (M = 1, 4096 x 11008 at 1/2 10.0 against 5.2; M = 3, 2053 x 1531 5.7 against 3.6).
 MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
 {
     MatrixPlan none{};
@@ -1342,9 +1337,10 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
     if (M <= kMaxRows) {
         r = rows_plan(l, M, false);
         if (M <= 8) {
-            const double lists = M <= 2 ? 2.7 + 0.3 * M + entries * d * (0.17 + 0.08 * M)
-                                        : 1.6 + 0.67 * M + 2.0 * floor(M * (double)l.K / 38400.0) +
-                                              entries * d * (0.22 + 0.08 * M);
+            const double ones = 1e-3 * l.K, hits = entries * d;
+            const double lists = M <= 2 ? 2.55 + 0.5 * M + 0.04 * ones + hits * (0.265 + 0.016 * M)
+                                        : 2.03 + 0.58 * M + 0.13 * ones + 3.54 * floor(M * (double)l.K / 38400.0) +
+                                              hits * (0.353 + 0.066 * M);
             if (r.us >= lists) return none;
             return MatrixPlan{true, r.tiles, r.waves, false};
         }
@@ -1435,8 +1431,8 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
 
 // Whether k_rows takes the base-3 codes, or k_packed, which multiplies on the vector ALU: a workgroup of that takes
 // 2.6 us + (0.65 + 0.43 M) us per 1000 rows of W, and 3 us more where it deals K to several workgroups (measured
-// M = 1 .. 8, the shapes of rows_plan()).  k_packed stays ahead on one row over many columns (M = 1, 4096 x 11008 7.6
-// against 8.1 us) and on short K (M <= 5, 512 x 16384; M <= 3, 512 x 512).
+// M = 1 .. 8, the shapes of rows_plan()).  k_packed stays ahead on short K over many columns (M <= 5, 512 x 16384, M = 5: 4.6 against
+// 4.8 us); M = 1, 4096 x 11008 7.1 against 6.8 here.  The choice is 0.3 % behind the better of the two on average.
 MatrixPlan packed_plan(const tcsc_layout_t &l, int M)
 {
     if (l.K > kMaxExtent || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return MatrixPlan{};
