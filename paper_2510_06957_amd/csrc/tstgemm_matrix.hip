@@ -528,9 +528,18 @@ k_matrix(const MatrixArgs a)
                 copy_to_lds(sbuf, to + kUnitBytes + (wave_in_group * (CF / 2) + j) * 1024,
                             scol[j] + (unsigned)(kb0 + step) * (unsigned)a.n_pad * 16u);
         };
-        auto copy_x = [&](int i, int step, unsigned to, int planes) {   // the wavefront's i-th piece of the group's X
-            const int c = min(wave_in_group + i * WN, kChunks - 1), chunks = planes > 5 ? kChunks : planes > 3 ? 16 : 10;
-            copy_to_lds(dbuf, to + c * 1024, (c < chunks ? (unsigned)(kb0 + step) * kUnitBytes + c * 1024u : 0xfffff000u) + lane * 16);
+        // the wavefront's pieces of the group's X: from byte `piece` of a unit, where there are more planes than `above`
+        unsigned piece[kCopies], lane_piece[kCopies];
+        int above[kCopies];
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) {
+            const int c = min(wave_in_group + i * WN, kChunks - 1);
+            piece[i] = c * 1024;
+            lane_piece[i] = c * 1024 + lane * 16;
+            above[i] = c < 10 ? 0 : c < 16 ? 3 : 5;
+        }
+        auto copy_x = [&](int i, int step, unsigned to, int planes) {   // (0xffff0000 and what is added to it: beyond the buffer)
+            copy_to_lds(dbuf, to + piece[i], (planes > above[i] ? (unsigned)(kb0 + step) * kUnitBytes : 0xffff0000u) + lane_piece[i]);
         };
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -560,7 +569,12 @@ k_matrix(const MatrixArgs a)
             unsigned scale[2][RF], sets[CF][2];
             const unsigned lane16 = lane * 16, lane8 = 1024 + lane * 8, lane4 = kExponents + lane * 4;
             const unsigned lane_w = kUnitBytes + (wave_in_group * 32 * CF + l32) * 16 + g * 4;
-            auto word = [](unsigned at) { return *(__attribute__((address_space(3))) const unsigned *)(size_t)at; };
+            typedef __attribute__((address_space(3))) const unsigned *Words;
+            auto read_scale = [&](unsigned (&to)[RF], unsigned at) {
+                const Words p = (Words)(size_t)(at + lane4);
+#pragma unroll
+                for (int i = 0; i < RF; ++i) to[i] = p[64 * i];
+            };
             auto read_x = [&](auto cur, unsigned at16, unsigned at8, int offset) {   // a plane's two fragments
 #pragma unroll
                 for (int i = 0; i < RF; ++i) {
@@ -571,10 +585,11 @@ k_matrix(const MatrixArgs a)
             };
             auto first_plane = [&](int planes) { return planes > 5 ? plane_offset(5) : planes > 3 ? plane_offset(3) : plane_offset(1); };
             auto read_w = [&](unsigned at) {
+                const Words p = (Words)(size_t)(at + lane_w);
 #pragma unroll
                 for (int j = 0; j < CF; ++j) {
-                    sets[j][0] = word(at + lane_w + j * 512);
-                    sets[j][1] = word(at + lane_w + j * 512 + 8);
+                    sets[j][0] = p[128 * j];
+                    sets[j][1] = p[128 * j + 2];
                 }
             };
             // a plane's products; between them, `between(k)` behind the k-th: a wavefront issues in order, and what it has to do
@@ -603,8 +618,7 @@ k_matrix(const MatrixArgs a)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             read_w(at);
-#pragma unroll
-            for (int i = 0; i < RF; ++i) scale[0][i] = word(at + lane4 + i * 256);
+            read_scale(scale[0], at);
             {
                 const int first = first_plane(planes);
                 read_x(Int<0>{}, at16 + first, at8 + first, 0);
@@ -660,10 +674,7 @@ k_matrix(const MatrixArgs a)
                         const int first = first_plane(planes1);
                         read_x(Int<B>{}, next + lane16 + first, next + lane8 + first, 0);
                     }
-                    if (k == 1) {
-#pragma unroll
-                        for (int i = 0; i < RF; ++i) scale[B][i] = word(next + lane4 + i * 256);
-                    }
+                    if (k == 1) read_scale(scale[B], next);
                     if (k == 2) copy_w(step + 3, at);
                 });
                 planes = planes1;
