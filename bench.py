@@ -32,6 +32,8 @@ PEAK_ALU_ADD_TFLOPS = 157.3 / 2
 PEAK_HBM_GBS = 8000.0
 # The matrix-core path multiplies three bf16 planes of X by W, zeros included: 6 M K N floating-point operations.
 PEAK_BF16_TFLOPS = 2516.0
+# With X in digits it is one product of 6-bit floats per plane, at four times that rate.
+PEAK_FP6_TFLOPS = 4 * PEAK_BF16_TFLOPS
 PEAK_ALU_INSTR_T = 256 * 64 * 2.4e9 / 1e12     # vector lane-instructions per second (an FMA counts once)
 
 # HBM bytes (read + written) of one launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
@@ -49,6 +51,21 @@ MEASURED_TRAFFIC = {
 }
 ORACLE_FLAGS = "gcc -O3 -fstrict-aliasing -DNDEBUG -fopenmp (the paper's flags, Sec. 4, without -march=native)"
 INFINITY_CACHE_BYTES = 256 << 20
+
+
+def digit_planes(X):
+    """Planes of 6-bit digits that X has, on average over units of 64 rows x 64 entries: 3, 5 or 7, as many as hold multiples of
+    2^(E - 13), 2^(E - 23) or less, E the exponent of the largest of 32 entries."""
+    M, K = X.shape
+    Xp = np.zeros((-(-M // 64) * 64, -(-K // 64) * 64))
+    Xp[:M, :K] = X
+    blocks = Xp.reshape(Xp.shape[0], -1, 32)
+    top = np.frexp(np.abs(blocks).max(axis=2, keepdims=True))[1] - 1
+    planes = np.full(blocks.shape[:2], 7)
+    for n, bits in ((5, 23), (3, 13)):
+        scaled = np.ldexp(blocks, bits - top)
+        planes[(scaled == np.rint(scaled)).all(axis=2)] = n
+    return float(planes.reshape(Xp.shape[0] // 64, 64, -1, 2).max(axis=(1, 3)).mean())
 
 
 def cpu_baseline(W, X, b, nnz, variant="tcsc", budget_s=10.0):
@@ -239,6 +256,7 @@ def main():
     kernel = route.kernel
     decode = wl.M <= 8
     matrix = kernel == "k_matrix"
+    digits = matrix and not tuning and tg.tstgemm_query_digits(t, wl.M)
     rows = kernel in ("k_rows", "k_rows_packed")
     # index data one call reads (what must not be in the Infinity Cache for an HBM figure)
     narrow = (kernel == "k_decode" and bool(lay.has_lists16) and not args.wide_lists
@@ -346,8 +364,8 @@ def main():
     kernel_ms = kernel_raw_ms - pair_ms
     kernel_ms_median = float(np.median(kernel_raw)) - pair_ms
     kernel_ms_min = float(np.min(kernel_raw)) - pair_ms
-    if decode or rows or (matrix and route.k_slices == 1):
-        # The paths for few rows, and k_matrix with K whole, are ONE kernel per call: the time per call of the back-to-back
+    if decode or rows or (matrix and route.k_slices == 1 and not digits):
+        # The paths for few rows, and k_matrix with K whole and X in bf16 planes, are ONE kernel per call: the time per call of the back-to-back
         # timed region is that kernel's time (with the gap between two launches), and it is what agrees with the profiler's
         # average duration; the event pair between two such kernels delays them and then takes off too much.
         kernel_ms, kernel_ms_median, kernel_ms_min = call_ms, float(np.median(region_ms)), float(np.min(region_ms))
@@ -378,9 +396,14 @@ def main():
     elif matrix:
         # the row sets, X, Y and b once; the work is the dense one, whatever the density
         alg_bytes = 16 * lay.n_kblocks * lay.n_pad + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
-        roof = {"bound": "mfma", "achieved": 6.0 * wl.M * wl.K * wl.N / (kernel_ms * 1e-3) / 1e12, "peak": PEAK_BF16_TFLOPS,
-                "unit": "TFLOP/s", "traffic": traffic,
-                "note": "three bf16 planes of X times W, zeros included: 6 M K N operations; peak = dense bf16"}
+        planes = digit_planes(X) if digits else 3.0
+        roof = {"bound": "mfma", "achieved": 2 * planes * wl.M * wl.K * wl.N / (kernel_ms * 1e-3) / 1e12,
+                "peak": PEAK_FP6_TFLOPS if digits else PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                "traffic": None if digits else traffic,
+                "note": f"{planes:.2f} planes of 6-bit digits of X times W, zeros included: 2 M K N operations each; peak = dense fp6"
+                if digits else "three bf16 planes of X times W, zeros included: 6 M K N operations; peak = dense bf16"}
+        if digits:
+            traffic = measured = None   # (the counter runs were of the bf16 planes)
     else:
         # index data the kernel reads (small tile: the TCSC row numbers and the list cuts; else the 64-bit row sets)
         # + X + Y + b

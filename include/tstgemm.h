@@ -267,6 +267,12 @@ typedef struct tstgemm_route {
 int tstgemm_query_route(const tcsc_t *t, int M, const tstgemm_opts_t *opts, tstgemm_route_t *out);
 
 /*
+ * Whether "k_matrix" takes X in digits (cut beforehand by "k_digits" in the workspace, for large calls) and not in bf16 planes,
+ * by the same rule: 1 or 0 (0 also for the other kernels), or an error of tstgemm_query_route().
+ */
+int tstgemm_query_digits(const tcsc_t *t, int M, const tstgemm_opts_t *opts);
+
+/*
  * Y = PReLU(X W + b): tstgemm() with the activation fused behind the bias add.  The paper fuses
  * PReLU into its vectorised kernels (Sec. 2 "Implementation Note", Sec. 4) without giving the
  * formula or the slope; here it is the usual one, PReLU(v) = v for v > 0 and alpha * v otherwise,

@@ -100,6 +100,7 @@ def _load():
     lib.tstgemm_ex.argtypes = [vp, vp, vp, vp, ci, ci, ci, ctypes.POINTER(TstgemmOpts), vp]
     lib.tstgemm_workspace_bytes.argtypes = [ci, ci, ci, ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t)]
     lib.tstgemm_query_route.argtypes = [vp, ci, ctypes.POINTER(TstgemmOpts), ctypes.POINTER(TstgemmRoute)]
+    lib.tstgemm_query_digits.argtypes = [vp, ci, ctypes.POINTER(TstgemmOpts)]
     lib.tcsc_select_forms.argtypes = [vp, ctypes.c_uint32]
     lib.tstgemm_probe_lds_read.argtypes = [ci, ctypes.POINTER(ctypes.c_int64), vp]
     lib.tstgemm_probe_lds_read.restype = ci
@@ -110,7 +111,7 @@ def _load():
     for name in ("tcsc_build", "tcsc_from_arrays", "tcsc_to_dense", "tcsc_dims", "tcsc_arrays", "tcsc_device_bytes",
                  "tcsc_layout", "tcsc_upload", "tstgemm", "tstgemm_prelu", "tstgemm_signed", "tstgemm_packed",
                  "tcsc_signed_arrays", "tcsc_packed_codes", "tstgemm_ex", "tstgemm_workspace_bytes", "tcsc_select_forms",
-                 "tstgemm_noalloc", "tstgemm_query_route"):
+                 "tstgemm_noalloc", "tstgemm_query_route", "tstgemm_query_digits"):
         getattr(lib, name).restype = ci
     _lib = lib
     _bind_launcher(lib)
@@ -417,6 +418,18 @@ def tstgemm_query_route(t: Tcsc, M: int, encoding=0, workspace_bytes=0, cols_per
     route = TstgemmRoute()
     _check(_load().tstgemm_query_route(t.handle, int(M), ctypes.byref(o), ctypes.byref(route)), "tstgemm_query_route")
     return route
+
+
+def tstgemm_query_digits(t: Tcsc, M: int, workspace_bytes=0) -> bool:
+    """Whether tstgemm() for M rows of X takes k_matrix with X in digits (host only; workspace_bytes as in tstgemm_query_route())."""
+    o = TstgemmOpts()
+    o.struct_size = ctypes.sizeof(TstgemmOpts)
+    if workspace_bytes:
+        o.workspace, o.workspace_bytes = 256, int(workspace_bytes)
+    rc = _load().tstgemm_query_digits(t.handle, int(M), ctypes.byref(o))
+    if rc < 0:
+        raise TstgemmError(rc, "tstgemm_query_digits")
+    return bool(rc)
 
 
 def tcsc_signed_arrays(t: Tcsc):

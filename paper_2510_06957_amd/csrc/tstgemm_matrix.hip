@@ -942,20 +942,20 @@ long long digit_slab(const tcsc_layout_t &l, long long m_tiles, size_t room)
     return (m_tiles + slabs - 1) / slabs;
 }
 
-// X in digits: us of a call on one of the first three tiles with k slices of K, or none where it cannot be.  The three tiles
-// have their own figures, `peak` is for seven planes (X of the normal distribution; five, uniform X, are 20 % faster);
-// kCallDigits and kCutMb (per million entries of X) are for k_digits too, kOutMb per MB of Y.  Fitted to 94 shapes (M = 64 ..
-// 4096, K and N = 512 .. 16384) x 3 tiles x 8 slice counts, 5 % off on average.
+// X in digits: us of a call on one of the first three tiles with k slices of K.  The three tiles have their own figures, `peak`
+// is for seven planes (X of the normal distribution; with five, uniform X, a call is up to 22 % faster); kCallDigits and kCutMb
+// (per million entries of X) are for k_digits too, kOutMb per MB of Y.  Fitted to 101 shapes (M = 64 .. 4096, K and N = 512 ..
+// 16384) x 3 tiles x 8 slice counts: 6 % off on average.
 struct DigitTile {
     double fixed, step, work, peak;
 };
 constexpr DigitTile kDigitTiles[] = {
-    {3.21, 0.54, 0.926, 3.94e8},
-    {2.79, 0.62, 0.498, 3.82e8},
-    {4.15, 1.02, 1.015, 3.65e8},
+    {3.49, 0.873, 0.533, 3.91e8},
+    {3.14, 0.573, 0.482, 3.75e8},
+    {4.72, 0.938, 0.808, 3.64e8},
 };
 constexpr int kDigitTileCount = sizeof(kDigitTiles) / sizeof(kDigitTiles[0]);
-constexpr double kCallDigits = 5.19, kCutMb = 1.436, kOutMb = 0.198, kSliceDigits = 2.88, kSliceMbDigits = 0.307;
+constexpr double kCallDigits = 5.08, kCutMb = 1.338, kOutMb = 0.183, kSliceDigits = 2.56, kSliceMbDigits = 0.298;
 
 // Whole numbers from x up, x >= 0 and below 2^62 (ceil() is a library call here, and the estimates make many).
 inline double up(double x)
@@ -999,20 +999,23 @@ void digit_plans(const tcsc_layout_t &l, int M, size_t ws_bytes, int tile, int s
     }
 }
 
-// Digits in place of bf16 planes where that is estimated to be 4 % faster or more: on the tile and slices chosen for bf16 if it
-// is one of the three, or else, or where it is 10 % faster than there, on the best of the three.  (256 x 4096 x 4096: 28.7 us in
-// bf16, 25.4 with uniform X and 28.0 with normal; 1024 x 4096 x 4096 74 us, 48 and 59; M = 4096, K = N = 8192 1035 us, 585 and
-// 760.  Smaller calls, and X that is large beside Y, do not earn the launch of k_digits and its traffic: 512 x 1024 x 4096 15
-// against 19 us, 1024 x 16384 x 1024 77 against 82.  Over the fitted shapes the choice is 0.7 % behind the best on average.)
+// Digits in place of bf16 planes where that is estimated to be 6 % faster or more, or 10.5 % where bf16 takes K whole (there the
+// lines cross more slowly: 1410 x 1529 x 1955, at 10 %, 26.7 us in bf16, 25.5 and 30.4 in digits): on the tile and slices chosen for
+// bf16 if it is one of the three, or else, or where it is 15 % faster than there, on the best of the three.  us in bf16, in digits with
+// uniform and with normal X: 256 x 4096 x 4096 28.7, 25.0, 27.8; 64 x 16384 x 4096 31.4, 27.1, 30.9; 1024 x 4096 x 4096 74, 47,
+// 58; M = 4096, K = N = 8192 1035, 577, 748.  Smaller calls, and X that is large beside Y, do not earn the launch of k_digits and
+// its traffic: 512 x 1024 x 4096 15, 16.5, 19; 1024 x 16384 x 1024 77, 67, 80; nor do up to 64 rows, unless K is long: 64 x 8192
+// x 8192 26.8, 25.1, 28.2.  Of the fitted shapes that are taken all but one are ahead with both (777 x 16384 x 1024 66.6, 58, 69).
 TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TilePlan &p)
 {
     // (what any of them takes at least: most short calls end here)
-    const double least = kCallDigits + 2.79 + kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N;
-    if (least >= 0.96 * p.us) return p;
+    const double least = kCallDigits + 3.14 + kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N;
+    const double line = (p.k_slices > 1 ? 0.94 : 0.895) * p.us;
+    if (least >= line || (M <= 64 && l.K < 2 * (long long)l.N)) return p;
     TilePlan same{-1, 1, 0.0}, best{-1, 1, 0.0};
     for (int i = 0; i < kDigitTileCount; ++i) digit_plans(l, M, ws_bytes, i, i == p.tile ? p.k_slices : 0, &best, &same);
-    if (same.tile >= 0 && same.us <= 1.1 * best.us) best = same;
-    return best.tile >= 0 && best.us < 0.96 * p.us ? best : p;
+    if (same.tile >= 0 && same.us <= 1.15 * best.us) best = same;
+    return best.tile >= 0 && best.us < line ? best : p;
 }
 
 TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)

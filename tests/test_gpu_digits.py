@@ -8,9 +8,8 @@ import paper_2510_06957_amd as tg
 
 pytestmark = pytest.mark.gpu
 
-# (M, K, N, slices of K): calls that are estimated to be faster in digits by more than a tenth, on each tile, K whole and sliced;
-# rows one more and less than a tile, K at a block's edge, inside one and odd, columns of a part of a tile
-SHAPES = [(129, 8192, 8192), (513, 4161, 4100), (1023, 2047, 8200), (2049, 1985, 4097), (191, 16380, 4090), (777, 4099, 8190),
+# Calls that take digits, on each tile, K whole and sliced (tests/test_host_api_digits.py has the list); rows one more and less than a tile, K at a block's edge, inside one and odd, columns of a part of a tile
+SHAPES = [(129, 8192, 8192), (513, 4161, 4100), (1023, 2047, 8200), (2049, 1985, 4097), (191, 16380, 4090), (900, 4100, 4103), (640, 4099, 4098),
           (1300, 4100, 5000)]
 
 
@@ -29,6 +28,7 @@ def problem(M, K, N, seed, values, density=0.5):
         X = torch.randn((M, K), generator=g, device="cuda").bfloat16().float()
     b = torch.randint(-8, 9, (N,), generator=g, device="cuda").float()
     t = tg.tcsc_upload(tg.tcsc_build(W.cpu().numpy()), forms=tg.FORM_ROWSETS)
+    assert N == 64 or tg.tstgemm_query_digits(t, M, workspace(M, K, N).numel())
     return W.double(), X, b, t
 
 
