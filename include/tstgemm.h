@@ -115,7 +115,7 @@ int tcsc_device_bytes(const tcsc_t *t, size_t *bytes);
  *                                             columns >= N hold code 0.  n_chunks5 = ceil(ceil(K/5) / 16).
  *                                             Read by tstgemm_packed().
  *   workspace  bytes  [workspace_bytes]       scratch for calls that bring none of their own: split-K partial sums and
- *                                             a tiled, transposed copy of (a slab of rows of) X; 160 MiB, or 32 MiB + one
+ *                                             a tiled copy of (a slab of rows of) X, transposed or in digits; 160 MiB, or 32 MiB + one
  *                                             tile of 256 rows over the padded K if that is larger
  * n_pad = N rounded up to a multiple of 64; columns >= N have empty sets.
  * Which of these the buffer holds is the handle's choice of forms (tcsc_select_forms; default: all); a form
@@ -182,7 +182,9 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * X, lists read from the TCSC arrays between the list cuts; not for matrices with 2^30 or more entries of one sign,
  * whose lists its 32-bit byte offsets do not reach), everything else the large-M path (row sets).  Where the buffer
  * holds the row sets and W is not too sparse for it to pay, a call goes through the matrix cores instead: X is cut
- * exactly into three bf16 planes and multiplied by the row sets, spread into weights, with fp32 sums.  What a call
+ * exactly into three bf16 planes and multiplied by the row sets, spread into weights, with fp32 sums; large calls cut X into
+ * 6-bit digits in the workspace first, which is exact too but for entries below 2^-10 of the largest of their 32 neighbours: of
+ * what 32 such entries hold, less than 2^-31 of that largest one is lost (X of wider range goes back to the planes).  What a call
  * needs (its form, the least workspace) is the same either way.  Rows of X with an infinity, a NaN or entries beyond about
  * 2^100 give the same results there, at the price of taking these rows (16 at a time) once more: a call with one such
  * row takes two to three times as long, about what the list and row-set kernels take; one where every row is such, up to

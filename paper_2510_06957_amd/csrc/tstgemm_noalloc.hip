@@ -48,7 +48,8 @@ extern "C" int tstgemm_noalloc(const float *X, const tcsc_t *t, const float *b, 
     void *ws = nullptr;
     if (int rc = scratch_address(&ws)) return rc;
     // Nothing in the workspace has to start at zero: the packing pre-pass writes every entry of the tiles it lays out
-    // (padding included) and every K slice stores its whole partial tile before the reduction reads it.
+    // (padding included), X in digits is read only as far as it was written, and every K slice stores its whole partial tile
+    // before the reduction reads it.
     tstgemm_opts_t o{};
     o.struct_size = sizeof(o);
     o.workspace = ws;
