@@ -1058,7 +1058,9 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
 // then by spreading and cutting on the vector ALU and by the LDS: all three planes are staged before any is read, so that a
 // fragment is one read of all lanes; plane by plane, each lane waiting for its own, it was three.  M = 1, 4096 x 11008
 // 5.3 -> 4.9 us, M = 8 7.9 -> 7.5, M = 8, 4096 x 4096 5.8 -> 5.3, M = 2, 11008 x 4096 6.4 -> 5.2 (lists, at 50 % non-zeros: 10.0, 23.7, 10.7, 10.7).
-// Without the next group's loads 20 % more.
+// Without the next group's loads 20 % more.  Over 220 shapes (K, N = 700 .. 16384) all planes at once take 2 to 23 % less time
+// from the row sets; from the codes 17 % less to 2 % more at M <= 5 (M <= 3: the rule below takes k_rows more often, up to
+// 33 %), 8 % less to 3 % more at M = 6, 7, and the same at M = 8 (2 % less to 3 % more: 2500 x 5000 6.1 -> 6.3 us).
 //
 // PACKED: W from the base-3 codes (a.masks, a.n_kblocks: 16-byte pieces of 80 rows, [piece][n_pad]).  A table in the LDS
 // gives the five weights of a code, sign and non-zero bit side by side; the words of codes j and j + 8 make dwords for
