@@ -183,8 +183,8 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * whose lists its 32-bit byte offsets do not reach), everything else the large-M path (row sets).  Where the buffer
  * holds the row sets and W is not too sparse for it to pay, a call goes through the matrix cores instead: X is cut
  * exactly into three bf16 planes and multiplied by the row sets, spread into weights, with fp32 sums; large calls cut X into
- * 6-bit digits in the workspace first, which is exact too but for entries below 2^-10 of the largest of their 32 neighbours: of
- * what 32 such entries hold, less than 2^-31 of that largest one is lost (X of wider range goes back to the planes).  What a call
+ * 6-bit digits in the workspace first, just as exactly (rows of which seven digits do not hold every bit go back to the
+ * planes, together with the up to 63 others of their tile).  What a call
  * needs (its form, the least workspace) is the same either way.  Rows of X with an infinity, a NaN or entries beyond about
  * 2^100 give the same results there, at the price of taking these rows (16 at a time) once more: a call with one such
  * row takes two to three times as long, about what the list and row-set kernels take; one where every row is such, up to

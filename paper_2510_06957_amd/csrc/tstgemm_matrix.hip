@@ -220,11 +220,11 @@ struct MatrixArgs {
 
 // ------------------------------------------------------------------------------------------------------------------
 // X in digits.  32 entries of a row share an exponent (that of the largest, E); an entry is a sum of 6-bit floats (e2m3, the
-// matrix cores' fp6), each the nearest to what the ones before it leave.  Digit j is a multiple of 2^(E - 4 - 5 j + (j == 0)),
+// matrix cores' fp6), each the nearest to what the ones before it leave.  Digit j is a multiple of 2^(E - 4 - 5 j + (j != 0)),
 // so three planes of digits hold 14 bits below the largest entry, five 24 and seven 34.  A unit of 64 rows x 64 entries has as
-// many of these as leave nothing over, three, five or seven (integers and 16-bit activations mostly three or five, uniform X
-// five, normal X seven); a unit that seven do not hold -- entries so much smaller than their neighbours that
-// what is left over of the 32 is more than 2^-31 of the largest, infinities, NaNs, exponents out of range -- is marked
+// many of these as leave nothing of any entry, three, five or seven (integers and 16-bit activations mostly three or five,
+// uniform X five).  No bit of X is lost: a unit that seven do not hold -- entries with bits below 2^-33 of the largest of their 32, as
+// normal X has in nearly every unit, infinities, NaNs, exponents out of range -- is marked
 // kNoDigits, and its tile is multiplied in bf16 planes.  The sums of planes 0 to 2 and of the others are kept apart: the
 // upper ones are whole numbers of a unit, exact as long as they have 24 bits, so the result is rounded little more than once
 // (M = 4096, K = N = 8192: 3.6e-8 of the norm against 64 bits, in bf16 planes 6.1e-8).  fp6 x fp4 runs at 3.3 times the rate of
@@ -301,15 +301,10 @@ k_digits(const float *X, int M, int K, int n_kblocks, char *units, unsigned char
             b[i] -= back[2 * i + 1];
         }
         if (j != 2 && j != 4 && j != 6) continue;
-        float rest = 0.f, more = 0.f;
+        unsigned rest = 0;   // (a NaN is not zero either)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            rest += fabsf(a[i]);
-            more += fabsf(b[i]);
-        }
-        rest += more;
-        if (j < 6 && __any(rest != 0.f)) planes = j + 3;
-        if (j == 6 && __any(!(rest <= largest * 0x1p-31f))) planes = kNoDigits;
+        for (int i = 0; i < 16; ++i) rest |= __float_as_uint(a[i]) | __float_as_uint(b[i]);
+        if (__any((rest & 0x7fffffffu) != 0)) planes = j < 6 ? j + 3 : kNoDigits;
     }
     if (__any(!fits)) planes = kNoDigits;
     if (lane == 0) need[frag] = planes;
