@@ -240,92 +240,104 @@ __host__ __device__ constexpr int plane_offset(int j) { return j < 3 ? j * kPlan
 // units of its plane, is rounded to a quarter)
 __host__ __device__ constexpr int plane_shift(int j) { return j == 0 ? 0 : 5 * j - 1; }
 
-// k_digits: one lane cuts 32 entries of a row.  Position 8 d + n of a lane's digits is entry 4 n + d, the order in which
-// FourBitWord spreads the weights.  Bound by memory: 134 MB of X and 130 MB of planes in 44 us (6 TB/s; 57 us with every lane
-// reading its own 128 bytes and the planes left to the L2), 16 MB in 4 to 5 us, of which launch and one trip are most.
+// k_digits: one lane cuts 32 entries of a row, a workgroup up to kRun units of a tile one after the other.  Position 8 d + n of a
+// lane's digits is entry 4 n + d, the order in which FourBitWord spreads the weights.  Bound by memory where X is held (134 MB of X
+// and 130 MB of planes in 44 us, 6 TB/s; 57 us with every lane reading its own 128 bytes and the planes left to the L2).  Where it
+// is not, a run ends at the first unit that says so: 4096 x 8192 x 8192 with normal X 1087 us with runs of one unit, 1070 of
+// eight (1064 without k_digits); with uniform X no difference there, and 1 to 4 % more on calls of 1024 to 2048 rows.
+constexpr int kRun = 8;
+__host__ __device__ constexpr int digit_runs(int n_kblocks) { return (n_kblocks + kRun - 1) / kRun; }
 __global__ void __launch_bounds__(128)
 k_digits(const float *X, int M, int K, int n_kblocks, char *units, unsigned char *counts)
 {
     __shared__ uint4v staged[2][32 * 17];   // (17 units a row: other banks)
-    __shared__ int need[2];
+    __shared__ int need[2][2];
     const int lane = threadIdx.x & 63, frag = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tile = blockIdx.x / n_kblocks, kb = blockIdx.x % n_kblocks;
-    const int rows = min(64, M - 64 * tile), k0 = 64 * kb + 32 * (lane >> 5);
+    const int n_runs = digit_runs(n_kblocks), tile = blockIdx.x / n_runs;
+    const int first = blockIdx.x % n_runs * kRun, last = min(first + kRun, n_kblocks);
+    const int rows = min(64, M - 64 * tile);
     const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(X + (size_t)64 * tile * K, (size_t)rows * K * 4);
-    // four rows of 256 bytes at a time, through the LDS to the lane that cuts them
-    uint4v v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int row = 32 * frag + 4 * j + (lane >> 4);
-        v[j] = load16(xbuf, row < rows ? ((unsigned)row * (unsigned)K + 64 * kb + 4 * (lane & 15)) * 4u : kNowhere);
-    }
     uint4v *mine = staged[frag];
+    for (int kb = first; kb < last; ++kb) {
+        const int k0 = 64 * kb + 32 * (lane >> 5);
+        // four rows of 256 bytes at a time, through the LDS to the lane that cuts them
+        uint4v v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) mine[(4 * j + (lane >> 4)) * 17 + (lane & 15)] = v[j];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wavefront's own piece of the LDS
-    float x[32];
+        for (int j = 0; j < 8; ++j) {
+            const int row = 32 * frag + 4 * j + (lane >> 4);
+            v[j] = load16(xbuf, row < rows ? ((unsigned)row * (unsigned)K + 64 * kb + 4 * (lane & 15)) * 4u : kNowhere);
+        }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float4v w = __builtin_bit_cast(float4v, mine[(lane & 31) * 17 + 8 * (lane >> 5) + j]);
+        for (int j = 0; j < 8; ++j) mine[(4 * j + (lane >> 4)) * 17 + (lane & 15)] = v[j];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wavefront's own piece of the LDS
+        float x[32];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * j + e] = w[e];
-    }
-    if (64 * kb + 64 > K) {   // entries beyond the row belong to the next one
+        for (int j = 0; j < 8; ++j) {
+            const float4v w = __builtin_bit_cast(float4v, mine[(lane & 31) * 17 + 8 * (lane >> 5) + j]);
 #pragma unroll
-        for (int i = 0; i < 32; ++i) x[i] = k0 + i < K ? x[i] : 0.f;
-    }
-    float largest = 0.f;
+            for (int e = 0; e < 4; ++e) x[4 * j + e] = w[e];
+        }
+        if (64 * kb + 64 > K) {   // entries beyond the row belong to the next one
 #pragma unroll
-    for (int i = 0; i < 32; ++i) largest = fmaxf(largest, fabsf(x[i]));
-    const unsigned exponent = __float_as_uint(largest) >> 23;   // (a NaN shows in what is left over)
-    const bool fits = largest == 0.f || (exponent >= 31 && exponent <= 230);
-    const unsigned top = fits && largest != 0.f ? exponent - 1 : 126;   // of the unit of plane 0
-    float16v a, b;
+            for (int i = 0; i < 32; ++i) x[i] = k0 + i < K ? x[i] : 0.f;
+        }
+        float largest = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        a[i] = x[8 * (i & 3) + (i >> 2)];
-        b[i] = x[8 * (i & 3) + 4 + (i >> 2)];
-    }
-    uint6v digit[7];
-    int planes = 3;
-#pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        digit[j] = uint6v{0, 0, 0, 0, 0, 0};
-        if (j >= planes) continue;
-        const float scale = __uint_as_float((top - plane_shift(j)) << 23);
-        digit[j] = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, scale);
-        const float32v back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(digit[j], scale);
+        for (int i = 0; i < 32; ++i) largest = fmaxf(largest, fabsf(x[i]));
+        const unsigned exponent = __float_as_uint(largest) >> 23;   // (a NaN shows in what is left over)
+        const bool fits = largest == 0.f || (exponent >= 31 && exponent <= 230);
+        const unsigned top = fits && largest != 0.f ? exponent - 1 : 126;   // of the unit of plane 0
+        float16v a, b;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            a[i] -= back[2 * i];
-            b[i] -= back[2 * i + 1];
+            a[i] = x[8 * (i & 3) + (i >> 2)];
+            b[i] = x[8 * (i & 3) + 4 + (i >> 2)];
         }
-        if (j != 2 && j != 4 && j != 6) continue;
-        unsigned rest = 0;   // (a NaN is not zero either)
+        uint6v digit[7];
+        int planes = 3;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) rest |= __float_as_uint(a[i]) | __float_as_uint(b[i]);
-        if (__any((rest & 0x7fffffffu) != 0)) planes = j < 6 ? j + 3 : kNoDigits;
-    }
-    if (__any(!fits)) planes = kNoDigits;
-    if (lane == 0) need[frag] = planes;
-    __syncthreads();
-    planes = __builtin_amdgcn_readfirstlane(max(need[0], need[1]));
-    const size_t unit = (size_t)tile * n_kblocks + kb;
-    if (frag == 0 && lane == 0) counts[unit] = (unsigned char)planes;
-    if (planes == kNoDigits) return;
-    const __amdgpu_buffer_rsrc_t out = raw_buffer(units + unit * kUnitBytes, kUnitBytes);
-    // scales of planes 0 .. 3, times 2^24 as everywhere
-    const unsigned e0 = top + 24;
-    __builtin_amdgcn_raw_buffer_store_b32(
-        e0 | (e0 - plane_shift(1)) << 8 | (e0 - plane_shift(2)) << 16 | (e0 - plane_shift(3)) << 24, out,
-        kExponents + 256 * frag + 4 * lane, 0, kWriteThrough);
+        for (int j = 0; j < 7; ++j) {
+            digit[j] = uint6v{0, 0, 0, 0, 0, 0};
+            if (j >= planes) continue;
+            const float scale = __uint_as_float((top - plane_shift(j)) << 23);
+            digit[j] = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(a, b, scale);
+            const float32v back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(digit[j], scale);
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        if (j >= planes) break;
-        const int at = plane_offset(j) + frag * (kPlaneBytes / 2);
-        __builtin_amdgcn_raw_buffer_store_b128(uint4v{digit[j][0], digit[j][1], digit[j][2], digit[j][3]}, out, at + 16 * lane, 0,
-                                               kWriteThrough);
-        __builtin_amdgcn_raw_buffer_store_b64(uint2v{digit[j][4], digit[j][5]}, out, at + 1024 + 8 * lane, 0, kWriteThrough);
+            for (int i = 0; i < 16; ++i) {
+                a[i] -= back[2 * i];
+                b[i] -= back[2 * i + 1];
+            }
+            if (j != 2 && j != 4 && j != 6) continue;
+            unsigned rest = 0;   // (a NaN is not zero either)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) rest |= __float_as_uint(a[i]) | __float_as_uint(b[i]);
+            if (__any((rest & 0x7fffffffu) != 0)) planes = j < 6 ? j + 3 : kNoDigits;
+        }
+        if (__any(!fits)) planes = kNoDigits;
+        int *const needed = need[kb & 1];   // (the unit before may still be looking at its own)
+        if (lane == 0) needed[frag] = planes;
+        __syncthreads();
+        planes = __builtin_amdgcn_readfirstlane(max(needed[0], needed[1]));
+        const size_t unit = (size_t)tile * n_kblocks + kb;
+        if (planes == kNoDigits) {   // the tile goes back to bf16 planes: the rest of the run is not looked at
+            if ((int)threadIdx.x < last - kb) counts[unit + threadIdx.x] = kNoDigits;
+            return;
+        }
+        if (threadIdx.x == 0) counts[unit] = (unsigned char)planes;
+        const __amdgpu_buffer_rsrc_t out = raw_buffer(units + unit * kUnitBytes, kUnitBytes);
+        // scales of planes 0 .. 3, times 2^24 as everywhere
+        const unsigned e0 = top + 24;
+        __builtin_amdgcn_raw_buffer_store_b32(
+            e0 | (e0 - plane_shift(1)) << 8 | (e0 - plane_shift(2)) << 16 | (e0 - plane_shift(3)) << 24, out,
+            kExponents + 256 * frag + 4 * lane, 0, kWriteThrough);
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            if (j >= planes) break;
+            const int at = plane_offset(j) + frag * (kPlaneBytes / 2);
+            __builtin_amdgcn_raw_buffer_store_b128(uint4v{digit[j][0], digit[j][1], digit[j][2], digit[j][3]}, out, at + 16 * lane, 0,
+                                                   kWriteThrough);
+            __builtin_amdgcn_raw_buffer_store_b64(uint2v{digit[j][4], digit[j][5]}, out, at + 1024 + 8 * lane, 0, kWriteThrough);
+        }
     }
 }
 
@@ -377,8 +389,8 @@ template <int N> using Int = std::integral_constant<int, N>;
 // DIGITS: X comes from the workspace, straight into the LDS, W too; three steps of 64 rows of W in a ring, copied two steps
 // ahead, one barrier a step, placed before the last plane's products so that the next step's first reads are under way behind
 // them.  A step has 4 products of 32 cycles per plane and wavefront.  Everything else is dealt between them one by one: all
-// copies at once, or the spreading behind the products, cost 3 and 7 % of M = 4096, K = N = 8192 (1035 us in bf16; here 585
-// with uniform X, 760 with normal X, 540 at 1/16 non-zeros, where the products draw less power).  Of the 585, k_digits takes 44, the four
+// copies at once, or the spreading behind the products, cost 3 and 7 % of M = 4096, K = N = 8192 (1010 to 1045 us in bf16; here 580
+// to 605 with five planes, 750 with seven, 530 with five at 1/16 non-zeros, where the products draw less power).  Of the 585, k_digits takes 44, the four
 // rounds' starts and ends about 30; the products by themselves take 430 at the power limit and 273 without it.  64 x 128
 // of Y per wavefront, half the LDS reads, is no faster; a ring of four steps neither.
 // Rows beyond M and rows of W beyond K: X reads as zero, or as the next row of X where the weights are zero.
@@ -919,6 +931,7 @@ constexpr TileShape kTiles[] = {
     {32, 64, 4, 8, 2, 0.65, 0.501, 0.461, 1.30e9},    // small Y
     {32, 128, 2, 8, 2, 0.34, 0.456, 0.383, 1.40e9},   // M <= 32
 };
+constexpr int kDigitTiles = 2;   // the first two can take X in digits
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
 
 struct TilePlan {
@@ -931,27 +944,12 @@ size_t digit_tile_bytes(const tcsc_layout_t &l) { return (size_t)l.n_kblocks * (
 long long digit_slab(const tcsc_layout_t &l, long long m_tiles, size_t room)
 {
     long long fit = (long long)(room / digit_tile_bytes(l));
-    const long long launch = 0xffffffffll / 128 / l.n_kblocks;   // threads of k_digits
+    const long long launch = 0xffffffffll / 128 / digit_runs(l.n_kblocks);   // threads of k_digits
     if (fit > launch) fit = launch;
     if (fit < 1 || fit >= m_tiles) return fit < 1 ? 0 : m_tiles;
     const long long slabs = (m_tiles + fit - 1) / fit;
     return (m_tiles + slabs - 1) / slabs;
 }
-
-// X in digits: us of a call on one of the first three tiles with k slices of K.  The three tiles have their own figures, `peak`
-// is for seven planes (X of the normal distribution; with five, uniform X, a call is up to 22 % faster); kCallDigits and kCutMb
-// (per million entries of X) are for k_digits too, kOutMb per MB of Y.  Fitted to 101 shapes (M = 64 .. 4096, K and N = 512 ..
-// 16384) x 3 tiles x 8 slice counts: 6 % off on average.
-struct DigitTile {
-    double fixed, step, work, peak;
-};
-constexpr DigitTile kDigitTiles[] = {
-    {3.49, 0.873, 0.533, 3.91e8},
-    {3.14, 0.573, 0.482, 3.75e8},
-    {4.72, 0.938, 0.808, 3.64e8},
-};
-constexpr int kDigitTileCount = sizeof(kDigitTiles) / sizeof(kDigitTiles[0]);
-constexpr double kCallDigits = 5.08, kCutMb = 1.338, kOutMb = 0.183, kSliceDigits = 2.56, kSliceMbDigits = 0.298;
 
 // Whole numbers from x up, x >= 0 and below 2^62 (ceil() is a library call here, and the estimates make many).
 inline double up(double x)
@@ -960,58 +958,32 @@ inline double up(double x)
     return whole < x ? whole + 1.0 : whole;
 }
 
-// The best of a tile's slice counts in digits (tile < 0: none can be), and the one for `same_k` slices.
-void digit_plans(const tcsc_layout_t &l, int M, size_t ws_bytes, int tile, int same_k, TilePlan *best, TilePlan *same)
-{
-    const TileShape &s = kTiles[tile];
-    const DigitTile &d = kDigitTiles[tile];
-    const int units = compute_units();
-    const long long m_tiles = ((long long)M + s.rows - 1) / s.rows;
-    const double n_tiles = (l.n_pad + s.cols - 1) / s.cols, all_tiles = (double)m_tiles * n_tiles;
-    const double cut_out = kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N;
-    const double sum_bytes = 4.0 * M * l.n_pad, tile_bytes = (double)digit_tile_bytes(l) * (double)m_tiles;
-    const double work = 1.0 * s.rows * s.cols * l.K / d.peak;
-    for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || all_tiles * k <= 2.0 * units * s.per_cu); ++k) {
-        const int per = (l.n_kblocks + k - 1) / k;
-        if (per + 8 > kMaxDigitBlocks) continue;
-        double slabs = 1.0, tiles = all_tiles, slices_us = 0.0;
-        if (k > 1) {   // all of X in digits and the partial sums
-            if (per * (k - 1) >= l.n_kblocks || M > 65535 || sum_bytes * k + tile_bytes > (double)ws_bytes) continue;
-            slices_us = kSliceDigits + kSliceMbDigits * 1e-6 * sum_bytes * k;
-        } else {
-            const long long slab = digit_slab(l, m_tiles, ws_bytes);
-            if (slab < 1) continue;
-            slabs = up((double)m_tiles / (double)slab);
-            tiles = (double)slab * n_tiles;
-        }
-        if (tiles * k * (64 * s.waves) >= 4294967296.0) continue;
-        const double load = up(tiles * k / units), rounds = up(load / s.per_cu), steps = (per + s.groups - 1) / s.groups;
-        const double step_us = d.step * rounds > d.work * load ? d.step * rounds : d.work * load;
-        double us = d.fixed * rounds + steps * step_us;
-        if (us < tiles * work) us = tiles * work;
-        us = slabs * (kCallDigits + us) + cut_out + slices_us;
-        if (best->tile < 0 || us < best->us) *best = TilePlan{tile, k, us, true};
-        if (k == same_k) *same = TilePlan{tile, k, us, true};
-    }
-}
-
-// Digits in place of bf16 planes where that is estimated to be 6 % faster or more, or 10.5 % where bf16 takes K whole (there the
-// lines cross more slowly: 1410 x 1529 x 1955, at 10 %, 26.7 us in bf16, 25.5 and 30.4 in digits): on the tile and slices chosen for
-// bf16 if it is one of the three, or else, or where it is 15 % faster than there, on the best of the three.  us in bf16, in digits with
-// uniform and with normal X: 256 x 4096 x 4096 28.7, 25.0, 27.8; 64 x 16384 x 4096 31.4, 27.1, 30.9; 1024 x 4096 x 4096 74, 47,
-// 58; M = 4096, K = N = 8192 1035, 577, 748.  Smaller calls, and X that is large beside Y, do not earn the launch of k_digits and
-// its traffic: 512 x 1024 x 4096 15, 16.5, 19; 1024 x 16384 x 1024 77, 67, 80; nor do up to 64 rows, unless K is long: 64 x 8192
-// x 8192 26.8, 25.1, 28.2.  Of the fitted shapes that are taken all but one are ahead with both (777 x 16384 x 1024 66.6, 58, 69).
+// Digits in place of bf16 planes, on the tile and the slices of K chosen for those.  What X holds is not known here: if digits do
+// not hold it, the cut is lost and the products are the same, so a call takes digits where what is lost is at most 2.5 % of it,
+// 6 us per slab + 0.08 per million entries of X, and where slabs do not add rounds of workgroups.  Such calls are long and Y is wide,
+// and X that digits hold gains far more.  us in bf16 with uniform and normal X, then in digits: M = 4096, K = N = 8192 1024 and 1033,
+// 587 and 1034; 4096 x 4096 x 16384 1046 and 1057, 593 and 1068; 2048 x 8192 x 8192 502 and 508, 290 and 516; 1500 x 8192 x 8192 399
+// and 404, 234 and 412.  Not taken (same two pairs): 4096 x 4096 x 4096 265 and 270, 171 and 278; 1024 x 4096 x 4096 74 and 75, 58
+// and 81; 512 x 4096 x 4096 45 and 46, 46 and 51; up to 64 rows, where calls of that length have 10^9 weights, are not measured.
+constexpr double kLost = 6.0, kLostMb = 0.08, kLostPart = 0.025;
+// Where W is sparse enough for k_large to be near, the products draw less power and the bf16 planes, too, take 0.92 of the estimate,
+// which then is what X that digits do not hold takes: M = 4096, K = N = 8192 at 1/16 non-zeros 955 us, k_large 928, digits 531; M =
+// 2048 475, 473, 262.
+constexpr double kSparsePart = 0.92;
 TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TilePlan &p)
 {
-    // (what any of them takes at least: most short calls end here)
-    const double least = kCallDigits + 3.14 + kCutMb * 1e-6 * M * (l.n_kblocks * 64.0) + kOutMb * 4e-6 * M * l.N;
-    const double line = (p.k_slices > 1 ? 0.94 : 0.895) * p.us;
-    if (least >= line || (M <= 64 && l.K < 2 * (long long)l.N)) return p;
-    TilePlan same{-1, 1, 0.0}, best{-1, 1, 0.0};
-    for (int i = 0; i < kDigitTileCount; ++i) digit_plans(l, M, ws_bytes, i, i == p.tile ? p.k_slices : 0, &best, &same);
-    if (same.tile >= 0 && same.us <= 1.15 * best.us) best = same;
-    return best.tile >= 0 && best.us < line ? best : p;
+    const double room = kLostPart * p.us - kLostMb * 1e-6 * M * l.K;
+    if (p.tile >= kDigitTiles || M <= 64 || room < kLost) return p;
+    const TileShape &s = kTiles[p.tile];
+    const long long m_tiles = ((long long)M + 63) / 64, n_tiles = (l.n_pad + s.cols - 1) / s.cols;
+    const size_t partial_bytes = p.k_slices > 1 ? (size_t)p.k_slices * M * l.n_pad * 4 : 0;
+    if ((l.n_kblocks + p.k_slices - 1) / p.k_slices + 8 > kMaxDigitBlocks || partial_bytes >= ws_bytes) return p;
+    const long long slab = digit_slab(l, m_tiles, ws_bytes - partial_bytes);
+    if (slab < 1 || (p.k_slices > 1 && slab < m_tiles)) return p;
+    const long long slabs = (m_tiles + slab - 1) / slab, slots = (long long)compute_units() * s.per_cu;
+    const auto rounds = [&](long long tiles) { return (tiles * n_tiles * p.k_slices + slots - 1) / slots; };
+    if (room < kLost * slabs || slabs * rounds(slab) > rounds(m_tiles)) return p;
+    return TilePlan{p.tile, p.k_slices, kSparsePart * p.us, true};
 }
 
 TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
@@ -1401,8 +1373,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
         if (p.digits) {
             switch (p.shape) {
             case 0: return launch_tiles<1, 1, 8, 2, 2, true>(a, n, c);
-            case 1: return launch_tiles<1, 1, 4, 2, 2, true>(a, n, c);
-            default: return launch_tiles<2, 1, 4, 2, 2, true>(a, n, c);
+            default: return launch_tiles<1, 1, 4, 2, 2, true>(a, n, c);
             }
         }
         switch (p.shape) {
@@ -1430,7 +1401,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
             a.X = X + (size_t)t * 64 * l.K;
             a.Y = Y + (size_t)t * 64 * l.N;
             a.M = (int)(M - t * 64 < n * 64 ? M - t * 64 : n * 64);
-            hipLaunchKernelGGL(k_digits, dim3((unsigned)(n * l.n_kblocks)), dim3(128), 0, c.stream, a.X, a.M, l.K,
+            hipLaunchKernelGGL(k_digits, dim3((unsigned)(n * digit_runs(l.n_kblocks))), dim3(128), 0, c.stream, a.X, a.M, l.K,
                                l.n_kblocks, units, counts);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if (t == 0 && (e = c.record_before()) != hipSuccess) return e;

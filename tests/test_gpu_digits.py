@@ -8,9 +8,9 @@ import paper_2510_06957_amd as tg
 
 pytestmark = pytest.mark.gpu
 
-# Calls that take digits, on each tile, K whole and sliced (tests/test_host_api_digits.py has the list); rows one more and less than a tile, K at a block's edge, inside one and odd, columns of a part of a tile
-SHAPES = [(129, 8192, 8192), (513, 4161, 4100), (1023, 2047, 8200), (2049, 1985, 4097), (191, 16380, 4090), (900, 4100, 4103), (640, 4099, 4098),
-          (1300, 4100, 5000)]
+# Calls that take digits, on each tile, K whole and sliced (tests/test_host_api_digits.py has the list); rows one more than a tile and
+# parts of one, K at a block's edge, inside one and odd, columns of a part of a tile
+SHAPES = [(1025, 4161, 17950), (4097, 2047, 9000), (1471, 16380, 4100), (777, 16380, 5900), (1300, 16380, 3600), (2049, 8129, 4500)]
 
 
 def problem(M, K, N, seed, values, density=0.5):
@@ -59,13 +59,14 @@ def test_planes(M, K, N, values):
 def test_every_entry_alone():
     """One entry of W in a column: an output is an entry of X, exactly."""
     import torch
-    M, K = 2048, 4096
+    M, K = 4800, 4160
     perm = np.random.default_rng(910).permutation(K)
     W = np.zeros((K, K), np.int8)
     W[perm, np.arange(K)] = 1
     t = tg.tcsc_upload(tg.tcsc_build(W), forms=tg.FORM_ROWSETS)
     g = torch.Generator(device="cuda").manual_seed(911)
     ws = workspace(M, K, K)
+    assert tg.tstgemm_query_digits(t, M, ws.numel())
     for values in ("powers", "normal", "full"):
         if values == "powers":
             # +-2^e, and a third of them one less in the last place.  Seven planes hold multiples of 2^(E - 33), E the exponent of
@@ -90,7 +91,7 @@ def test_entries_beside_larger_ones(values):
     """Large entries of X, mostly under zero weights, beside ordinary ones: no output loses a bit of the small entries to them, so
     the bound of ordinary X holds for every output."""
     import torch
-    M, K, N = 1100, 4161, 8200
+    M, K, N = 2300, 4161, 8200
     W, X, b, t = problem(M, K, N, 960, "normal", 1 / 16)
     g = torch.Generator(device="cuda").manual_seed(961)
     kind, size = (values + " 0").split()[:2]
@@ -116,13 +117,13 @@ def test_entries_beside_larger_ones(values):
     assert ((Y - E).abs() <= TIGHT * A).all()
 
 
-@pytest.mark.parametrize("M,K,N", [(513, 4161, 4100), (191, 16380, 4090)])
+@pytest.mark.parametrize("M,K,N", [(1025, 4161, 17950), (777, 16380, 5900)])
 def test_tiles_that_digits_do_not_hold(M, K, N):
     """Rows with entries too far apart, beyond the exponents' range, infinite or NaN: their tiles go back to bf16 planes (and
     from there, where a sum is not finite, to the sums of any X); the others keep their digits.  What no infinity or NaN
     reaches is right, what one reaches is not finite."""
     import torch
-    W, X, b, t = problem(M, K, N, 920, "normal")
+    W, X, b, t = problem(M, K, N, 920, "uniform")
     g = torch.Generator(device="cuda").manual_seed(921)
     X[70] *= torch.exp2(torch.randint(-60, 20, (K,), generator=g, device="cuda").float())
     X[3] *= 1e-36
@@ -138,7 +139,27 @@ def test_tiles_that_digits_do_not_hold(M, K, N):
     assert ((Y - E).abs() <= TIGHT * A)[~reached].all()
 
 
-@pytest.mark.parametrize("M,K,N", [(1023, 2047, 8200), (2049, 1985, 4097)])
+@pytest.mark.parametrize("M,K,N", [(4097, 2047, 9000), (1471, 16380, 4100), (777, 16380, 5900), (1300, 16380, 3600)])
+def test_one_entry_gives_a_tile_up(M, K, N):
+    """k_digits gives the rest of a run of units up where one is not held: every other tile of rows has one such entry, at the
+    start of K, at its end and between, beside tiles that keep their digits; the workspace holds noise before."""
+    import torch
+    W, X, b, t = problem(M, K, N, 970, "uniform")
+    blocks = (K + 63) // 64
+    for i in range(0, (M + 63) // 64, 2):
+        kb = (0, blocks - 1, blocks // 2, 7, 8, 9, blocks - 2, 3)[i // 2 % 8]
+        k, m = min(64 * kb + 37, K - 1), min(64 * i + 5 * i % 64, M - 1)
+        X[m, k] = 1.2345678e-15
+    ws = workspace(M, K, N)
+    ws.random_(0, 256)
+    Y = tg.tstgemm(X, t, b, workspace=ws).double()
+    E = X.double() @ W + b.double()
+    A = X.double().abs() @ W.abs() + b.double().abs()
+    assert ((Y - E).abs() <= TIGHT * A).all()
+    assert torch.equal(Y, tg.tstgemm(X, t, b, workspace=ws).double())
+
+
+@pytest.mark.parametrize("M,K,N", [(4097, 2047, 9000), (2049, 8129, 4500)])
 def test_slabs_of_rows(M, K, N):
     """A workspace that holds only some of the tiles in digits, down to the least that a call needs: the same results."""
     import torch
@@ -159,7 +180,7 @@ def test_slabs_of_rows(M, K, N):
 @pytest.mark.parametrize("count", ["one", "column"])
 def test_prelu_and_rows_behind_y(count):
     import torch
-    M, K, N = 513, 4161, 4100
+    M, K, N = 2300, 4161, 8200
     W, X, b, t = problem(M, K, N, 940, "int")
     alpha = torch.exp2(torch.randint(-3, 3, (1 if count == "one" else N,), device="cuda").float())
     out = torch.full((M + 2, N), float("nan"), device="cuda")
@@ -172,7 +193,7 @@ def test_prelu_and_rows_behind_y(count):
 def test_under_graph_capture():
     """Recorded once and replayed on new X, with eager work in between: the number of planes follows the X of the replay."""
     import torch
-    M, K, N = 1023, 2047, 8200
+    M, K, N = 4097, 2047, 9000
     W, X, b, t = problem(M, K, N, 950, "int")
     ws, Y = workspace(M, K, N), torch.empty((M, N), device="cuda")
     tg.tstgemm(X, t, b, Y, workspace=ws)

@@ -13,16 +13,19 @@ def empty_matrix(K, N):
 
 
 def test_large_calls_take_digits():
-    t = empty_matrix(4096, 4096)
-    assert not any(tg.tstgemm_query_digits(t, M) for M in (1, 8, 10, 17, 64))
-    assert all(tg.tstgemm_query_digits(t, M) for M in (512, 1000, 2048))   # (an empty W: beyond, k_large is faster)
-    # X large beside Y; no room for a tile in digits; K beyond what the kernel counts the planes of
-    assert not tg.tstgemm_query_digits(empty_matrix(16384, 64), 4096)
-    assert not tg.tstgemm_query_digits(t, 1000, workspace_bytes=1 << 20)
-    assert not tg.tstgemm_query_digits(empty_matrix(1 << 21, 128), 1000, workspace_bytes=1 << 40)
+    t = empty_matrix(8192, 8200)
+    assert not any(tg.tstgemm_query_digits(t, M) for M in (1, 8, 10, 17, 64, 256, 600))
+    assert all(tg.tstgemm_query_digits(t, M) for M in (1536, 2048))
+    # (k_large is faster on an empty W of this width)
+    assert not tg.tstgemm_query_digits(empty_matrix(8192, 8192), 4096)
+    # X large beside Y; no room for a tile in digits, or for a few only; K beyond what the kernel counts the planes of
+    assert not tg.tstgemm_query_digits(empty_matrix(65536, 1000), 1024, 1 << 30)
+    for size, taken in ((1 << 20, False), (16 << 20, False), (72 << 20, True)):
+        assert tg.tstgemm_query_digits(t, 1536, workspace_bytes=size) == taken
+    assert not tg.tstgemm_query_digits(empty_matrix(1 << 21, 8200), 1000, workspace_bytes=1 << 40)
     tg.tcsc_select_forms(t, tg.FORM_CUTS)
     with pytest.raises(tg.TstgemmError) as e:
-        tg.tstgemm_query_digits(t, 1000)
+        tg.tstgemm_query_digits(t, 1536)
     assert e.value.code == -7
     lib = tg.binding._load()
     assert lib.tstgemm_query_digits(None, 1, None) == -1 and lib.tstgemm_query_digits(t.handle, 0, None) == -1
@@ -40,4 +43,4 @@ def test_digit_tests_take_every_tile():
         assert tg.tstgemm_query_digits(t, M, size)
         r = tg.tstgemm_query_route(t, M, workspace_bytes=size)
         taken.add((r.tile_rows, r.tile_cols, r.k_groups, r.k_slices > 1))
-    assert taken >= {(64, 512, 1, False), (64, 256, 1, False), (64, 256, 1, True), (64, 256, 2, False), (64, 256, 2, True)}, taken
+    assert taken == {(64, 512, 1, False), (64, 512, 1, True), (64, 256, 1, False), (64, 256, 1, True)}, taken
