@@ -202,8 +202,8 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
 int tstgemm(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K, int N, void *stream);
 
 /*
- * Scratch memory a call with these dimensions needs (the tiled, transposed copy of X of the paths for M > 8 and
- * the partial sums of K slices; Sec. 3 "Blocking" is where the tiles come from).  *min_bytes: the least a call
+ * Scratch memory a call with these dimensions needs (the tiled, transposed copy of X of the paths for M > 8, or X in digits,
+ * and the partial sums of K slices; Sec. 3 "Blocking" is where the tiles come from).  *min_bytes: the least a call
  * runs with (one row tile of X over the padded K; rows then go through in slabs and K is not sliced);
  * *best_bytes: what it takes to run every shape the library would choose by itself in one slab.  M <= 8: 0
  * and the (small) partial sums tstgemm_packed() may use.  Either pointer may be NULL.  Errors: EINVAL.

@@ -1,6 +1,7 @@
 // Host side of libtstgemm: handle, TCSC construction and validation (Sec. 2 of the paper), the matrix in the paper's
 // two other encodings (Sec. 3), device-buffer layout, upload and the dispatch of the tstgemm*() entry points.
 #include <algorithm>
+#include <climits>
 #include <cstring>
 #include <new>
 
@@ -331,6 +332,11 @@ int tstgemm_workspace_bytes(int M, int K, int N, size_t *min_bytes, size_t *best
     } else {
         const int n_pad = (N + tst::kColPad - 1) / tst::kColPad * tst::kColPad;
         tst::large_workspace_bytes(M, K, n_pad, &lo, &hi);
+    }
+    if (M > 8) {
+        const long long n_pad = ((long long)N + tst::kColPad - 1) / tst::kColPad * tst::kColPad;
+        const size_t matrix = n_pad <= INT_MAX ? tst::matrix_workspace_bytes(M, K, N, (int)n_pad) : 0;
+        hi = hi > matrix ? hi : matrix;
     }
     if (min_bytes) *min_bytes = lo;
     if (best_bytes) *best_bytes = hi;

@@ -161,8 +161,8 @@ size_t small_tile_bytes(int M, int K);   // one tile of X for M <= 64 over the p
 hipError_t launch_large(const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);
 void large_workspace_bytes(int M, int K, int n_pad, size_t *min_bytes, size_t *best_bytes);
 // tstgemm_matrix.hip -- matrix-core kernels on the row sets.  matrix_plan: how they would take a call, or taken() == false
-// where the lists or the row-set walk are the faster choice (the workspace, which holds partial sums only and is not used
-// for M <= 8, is the caller's to check); packed_plan: the same for M <= 8 from the base-3 codes.
+// where the lists or the row-set walk are the faster choice (the workspace, which holds partial sums and X in digits and is not
+// used for M <= 8, is the caller's to check); packed_plan: the same for M <= 8 from the base-3 codes.
 struct MatrixPlan {
     bool rows;          // k_rows (shape: tiles of 16 columns, split: wavefronts), else k_matrix (tile shape, K slices)
     int shape, split;
@@ -171,6 +171,7 @@ struct MatrixPlan {
 };
 MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c);
 MatrixPlan packed_plan(const tcsc_layout_t &l, int M);
+size_t matrix_workspace_bytes(int M, int K, int N, int n_pad);   // what k_matrix would use of a workspace that holds all it wants
 void matrix_tile(const MatrixPlan &p, int M, tstgemm_route_t *out);   // tile of Y, groups and slices of K
 hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);
 hipError_t launch_packed_rows(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);

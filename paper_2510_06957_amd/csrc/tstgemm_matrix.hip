@@ -1293,6 +1293,18 @@ double density(const tcsc_layout_t &l) { return (double)(l.nnz_pos + l.nnz_neg) 
 
 }  // namespace
 
+// Partial sums and X in digits of the plan that a call has where the workspace does not bound it.
+size_t matrix_workspace_bytes(int M, int K, int N, int n_pad)
+{
+    tcsc_layout_t l{};
+    l.K = K; l.N = N; l.n_pad = n_pad; l.n_kblocks = (K - 1) / kKBlock + 1;
+    if (!offsets_fit(l)) return 0;
+    const TilePlan p = choose_tile(l, M, (size_t)1 << 62);
+    if (p.tile < 0) return 0;
+    const size_t partial_bytes = p.k_slices > 1 ? (size_t)p.k_slices * M * n_pad * 4 : 0;
+    return partial_bytes + (p.digits ? ((size_t)M + 63) / 64 * digit_tile_bytes(l) : 0);
+}
+
 // Whether the matrix cores take a call (the lists or the row-set walk being the other choice).  They do unless W is so
 // sparse that those, whose time goes with the number of non-zeros, are ahead.  Measured on 12 shapes (K, N = 512 .. 16384),
 // M = 1 .. 4096 and densities from 1/16 to 0: a call taken here is never more than 4 % behind the lists or the row-set walk

@@ -219,7 +219,10 @@ def test_workspace_bytes():
     lo, hi = tg.tstgemm_workspace_bytes(256, 4096, 4096)
     assert lo == 256 * 4096 * 4 and hi == lo + 8 * 256 * 4096 * 4               # C2: one tile + 8 K slices of Y
     lo, hi = tg.tstgemm_workspace_bytes(4096, 8192, 8192)
-    assert lo == 256 * 8192 * 4 and hi == 16 * lo                               # C5: 16 tiles, K not sliced
+    # C5: 16 tiles, K not sliced; X in digits (22528 bytes and a count per 64 x 64 entries) takes more than that
+    assert lo == 256 * 8192 * 4 and hi == 64 * 128 * 22529 > 16 * lo
+    lo, hi = tg.tstgemm_workspace_bytes(2048, 4096, 4096)
+    assert hi == 8 * lo
     assert tg.tstgemm_workspace_bytes(100, 70, 5)[0] == 128 * 128 * 4           # 128-row tile, K padded to 128
     # a matrix that can hold 2^30 entries per sign may have to go through the large-M kernel for any M > 8 (the
     # small-tile kernel addresses its lists with 32-bit byte offsets): the figures then cover both

@@ -39,8 +39,29 @@ def test_digit_tests_take_every_tile():
     taken = set()
     for M, K, N in SHAPES:
         t = empty_matrix(K, N)
-        size = tg.tstgemm_workspace_bytes(M, K, N)[1] + (96 << 20)
+        size = tg.tstgemm_workspace_bytes(M, K, N)[1]
         assert tg.tstgemm_query_digits(t, M, size)
         r = tg.tstgemm_query_route(t, M, workspace_bytes=size)
         taken.add((r.tile_rows, r.tile_cols, r.k_groups, r.k_slices > 1))
     assert taken == {(64, 512, 1, False), (64, 512, 1, True), (64, 256, 1, False), (64, 256, 1, True)}, taken
+
+
+@pytest.mark.parametrize("M", [9, 33, 64, 65, 128, 300, 777, 1500, 2048, 4096, 5000])
+def test_best_workspace_is_as_good_as_any(M):
+    """With the best_bytes of tstgemm_workspace_bytes() a call takes what it takes with more room than it can use, X in digits in
+    one slab."""
+    digits = 0
+    for K, N in ((8192, 8192), (8191, 8201), (16384, 4096), (16380, 4100), (4096, 16384), (4161, 17950), (16384, 1000), (4096, 4096), (700, 9000), (65536, 600)):
+        t = empty_matrix(K, N)
+        best = tg.tstgemm_workspace_bytes(M, K, N)[1]
+
+        def taken(size):
+            r = tg.tstgemm_query_route(t, M, workspace_bytes=size)
+            return r.kernel, r.tile_rows, r.tile_cols, r.k_groups, r.k_slices, tg.tstgemm_query_digits(t, M, size)
+
+        assert taken(best) == taken(1 << 50), (M, K, N)
+        if taken(best)[-1]:
+            slices = r[4] if (r := taken(best))[4] > 1 else 0
+            assert best >= -(-M // 64) * -(-K // 64) * 22529 + slices * M * (-(-N // 64) * 64) * 4
+            digits += 1
+    assert digits >= (2 if M >= 1500 else 0)
