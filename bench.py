@@ -364,10 +364,11 @@ def main():
     kernel_ms = kernel_raw_ms - pair_ms
     kernel_ms_median = float(np.median(kernel_raw)) - pair_ms
     kernel_ms_min = float(np.min(kernel_raw)) - pair_ms
-    if decode or rows or (matrix and route.k_slices == 1 and not digits):
+    if decode or rows or digits or (matrix and route.k_slices == 1):
         # The paths for few rows, and k_matrix with K whole and X in bf16 planes, are ONE kernel per call: the time per call of the back-to-back
         # timed region is that kernel's time (with the gap between two launches), and it is what agrees with the profiler's
-        # average duration; the event pair between two such kernels delays them and then takes off too much.
+        # average duration; the event pair between two such kernels delays them and then takes off too much.  With X in digits a
+        # pair brackets the last slab of rows only, so there the time is the call's, k_digits included.
         kernel_ms, kernel_ms_median, kernel_ms_min = call_ms, float(np.median(region_ms)), float(np.min(region_ms))
 
     measured = None if tuning else MEASURED_TRAFFIC.get((wl.name, args.variant))

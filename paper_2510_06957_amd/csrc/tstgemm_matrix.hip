@@ -1381,7 +1381,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
     a.k_slices = p.split;
     a.kb_per_slice = (l.n_kblocks + p.split - 1) / p.split;
     const long long m_tiles = ((long long)M + s.rows - 1) / s.rows;
-    const auto tiles = [&](long long n) {
+    const auto launch = [&](long long n) {
         if (p.digits) {
             switch (p.shape) {
             case 0: return launch_tiles<1, 1, 8, 2, 2, true>(a, n, c);
@@ -1397,9 +1397,14 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
         default: return launch_tiles<2, 1, 4, 1, 1, false>(a, n, c);
         }
     };
+    const auto tiles = [&](long long n) {   // n tiles of rows, between the call's events
+        hipError_t e = c.record_before();
+        if (e == hipSuccess) e = launch(n);
+        return e == hipSuccess ? c.record_after() : e;
+    };
     hipError_t e = hipSuccess;
     if (!p.digits) {
-        if ((e = c.record_before()) != hipSuccess || (e = tiles(m_tiles)) != hipSuccess) return e;
+        if ((e = tiles(m_tiles)) != hipSuccess) return e;
     } else {
         // X in slabs of as many tiles as the workspace holds in digits
         const size_t partial_bytes = p.split > 1 ? (size_t)p.split * M * l.n_pad * 4 : 0, tile_bytes = digit_tile_bytes(l);
@@ -1416,12 +1421,10 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
             hipLaunchKernelGGL(k_digits, dim3((unsigned)(n * digit_runs(l.n_kblocks))), dim3(128), 0, c.stream, a.X, a.M, l.K,
                                l.n_kblocks, units, counts);
             if ((e = hipGetLastError()) != hipSuccess) return e;
-            if (t == 0 && (e = c.record_before()) != hipSuccess) return e;
             if ((e = tiles(n)) != hipSuccess) return e;
         }
     }
-    if ((e = c.record_after()) != hipSuccess || a.k_slices == 1) return e;
-    return launch_sum(a, c.stream);
+    return a.k_slices == 1 ? hipSuccess : launch_sum(a, c.stream);
 }
 
 // Whether k_rows takes the base-3 codes, or k_packed, which multiplies on the vector ALU: a workgroup of that takes

@@ -159,22 +159,55 @@ def test_one_entry_gives_a_tile_up(M, K, N):
     assert torch.equal(Y, tg.tstgemm(X, t, b, workspace=ws).double())
 
 
-@pytest.mark.parametrize("M,K,N", [(4097, 2047, 9000), (2049, 8129, 4500)])
-def test_slabs_of_rows(M, K, N):
-    """A workspace that holds only some of the tiles in digits, down to the least that a call needs: the same results."""
+def slab_workspace(M, K, slabs):
+    """Bytes for X in digits in so many slabs, the last of them the shortest."""
+    return int(-(-M // 64) * -(-K // 64) * 22529 / slabs * 1.06) // 256 * 256
+
+
+# (more slabs than one, last slabs of fewer tiles, last tiles of fewer rows, K at a block's edge and inside)
+SLABS = [(5000, 4100, 9100, 2), (4000, 4161, 17950, 3), (8090, 4160, 8100, 2)]
+
+
+@pytest.mark.parametrize("M,K,N,slabs", SLABS)
+def test_slabs_of_rows(M, K, N, slabs):
+    """A workspace that holds only some of the tiles in digits: the same results as with room for all, to the bit, also where a tile
+    of the first and one of the last slab go back to bf16 planes."""
     import torch
-    W, X, b, t = problem(M, K, N, 930, "normal")
+    W, X, b, t = problem(M, K, N, 930, "uniform")
+    X[7, K // 2] = X[M - 1, K - 1] = 1.2345678e-15
     Y = tg.tstgemm(X, t, b, workspace=workspace(M, K, N))
     E = X.double() @ W + b.double()
     A = X.double().abs() @ W.abs() + b.double().abs()
-    least = tg.tstgemm_workspace_bytes(M, K, N)[0]
-    for size in (M * K * 4, M * K * 3, M * K * 2, least):
-        size = size // 256 * 256
-        ws = torch.empty(size + 256, dtype=torch.uint8, device="cuda")
-        ws[size:] = 77
-        Z = tg.tstgemm(X, t, b, workspace=ws[:size])
-        assert ((Z.double() - E).abs() <= TIGHT * A).all() and (ws[size:] == 77).all()
     assert ((Y.double() - E).abs() <= TIGHT * A).all()
+    size = slab_workspace(M, K, slabs)
+    assert tg.tstgemm_query_digits(t, M, size) and size < -(-M // 64) * -(-K // 64) * 22529
+    ws = torch.full((size + 256,), 77, dtype=torch.uint8, device="cuda")
+    assert torch.equal(tg.tstgemm(X, t, b, workspace=ws[:size]), Y) and (ws[size:] == 77).all()
+    # and down to the least that a call needs, which digits do without
+    least = tg.tstgemm_workspace_bytes(M, K, N)[0]
+    Z = tg.tstgemm(X, t, b, workspace=ws[:least])
+    assert ((Z.double() - E).abs() <= TIGHT * A).all()
+
+
+@pytest.mark.parametrize("M,K,N,slabs", [(5000, 4100, 9100, 1), (5000, 4100, 9100, 2), (4000, 4161, 17950, 3)])
+def test_events_around_the_last_slab(M, K, N, slabs):
+    """The pair of events of a call brackets the products of the last slab, without k_digits and the other slabs."""
+    import torch
+    W, X, b, t = problem(M, K, N, 980, "uniform")
+    ws = torch.empty(slab_workspace(M, K, slabs), dtype=torch.uint8, device="cuda")
+    assert tg.tstgemm_query_digits(t, M, ws.numel())
+    pair, whole = ([torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(2))
+    for e in pair:
+        e.record()
+    shares = []
+    for _ in range(5):
+        whole[0].record()
+        Y = tg.tstgemm(X, t, b, workspace=ws, events=pair)
+        whole[1].record()
+        torch.cuda.synchronize()
+        shares.append(pair[0].elapsed_time(pair[1]) / whole[0].elapsed_time(whole[1]))
+    # (of the whole, k_digits is about a tenth)
+    assert 0.6 / slabs < sorted(shares)[2] < (1.0, 0.65, 0.5)[slabs - 1], shares
 
 
 @pytest.mark.parametrize("count", ["one", "column"])
