@@ -54,18 +54,22 @@ INFINITY_CACHE_BYTES = 256 << 20
 
 
 def digit_planes(X):
-    """Planes of 6-bit digits that X has, on average over units of 64 rows x 64 entries: 3, 5 or 7, as many as hold multiples of
-    2^(E - 13), 2^(E - 23) or less, E the exponent of the largest of 32 entries."""
+    """What X in 6-bit digits is multiplied by, as the library cuts it: (share of the tiles of 64 rows that digits hold, average planes
+    of their units of 64 rows x 64 entries).  A unit has 3, 5 or 7 planes, as many as hold every entry: multiples of 2^(E - 13),
+    2^(E - 23) or 2^(E - 33), E the exponent of the largest of 32 entries.  A tile with a unit that 7 do not hold goes in bf16 planes."""
     M, K = X.shape
     Xp = np.zeros((-(-M // 64) * 64, -(-K // 64) * 64))
     Xp[:M, :K] = X
     blocks = Xp.reshape(Xp.shape[0], -1, 32)
-    top = np.frexp(np.abs(blocks).max(axis=2, keepdims=True))[1] - 1
-    planes = np.full(blocks.shape[:2], 7)
-    for n, bits in ((5, 23), (3, 13)):
+    largest = np.abs(blocks).max(axis=2, keepdims=True)
+    top = np.frexp(largest)[1] - 1
+    planes = np.where((largest[..., 0] == 0) | ((top[..., 0] >= -96) & (top[..., 0] <= 103)), 8, 9)
+    for n, bits in ((7, 33), (5, 23), (3, 13)):
         scaled = np.ldexp(blocks, bits - top)
-        planes[(scaled == np.rint(scaled)).all(axis=2)] = n
-    return float(planes.reshape(Xp.shape[0] // 64, 64, -1, 2).max(axis=(1, 3)).mean())
+        planes[(scaled == np.rint(scaled)).all(axis=2) & (planes < 9)] = n
+    units = planes.reshape(Xp.shape[0] // 64, 64, -1, 2).max(axis=(1, 3))
+    held = (units <= 7).all(axis=1)
+    return float(held.mean()), float(units[held].mean()) if held.any() else 0.0
 
 
 def cpu_baseline(W, X, b, nnz, variant="tcsc", budget_s=10.0):
@@ -397,12 +401,18 @@ def main():
     elif matrix:
         # the row sets, X, Y and b once; the work is the dense one, whatever the density
         alg_bytes = 16 * lay.n_kblocks * lay.n_pad + 4 * wl.M * wl.K + 4 * wl.M * wl.N + 4 * wl.N
-        planes = digit_planes(X) if digits else 3.0
-        roof = {"bound": "mfma", "achieved": 2 * planes * wl.M * wl.K * wl.N / (kernel_ms * 1e-3) / 1e12,
-                "peak": PEAK_FP6_TFLOPS if digits else PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                "traffic": None if digits else traffic,
-                "note": f"{planes:.2f} planes of 6-bit digits of X times W, zeros included: 2 M K N operations each; peak = dense fp6"
-                if digits else "three bf16 planes of X times W, zeros included: 6 M K N operations; peak = dense bf16"}
+        dense = 2.0 * wl.M * wl.K * wl.N
+        held, planes = digit_planes(X) if digits else (0.0, 0.0)
+        operations, peak = dense * 3 * (1 - held), PEAK_BF16_TFLOPS
+        note = "three bf16 planes of X times W, zeros included: 6 M K N operations; peak = dense bf16"
+        if held:
+            # (the peak of a mixture: all its operations over the time they take at their own peaks)
+            operations += dense * planes * held
+            peak = operations / (dense * (3 * (1 - held) / PEAK_BF16_TFLOPS + planes * held / PEAK_FP6_TFLOPS))
+            note = (f"{planes:.2f} planes of 6-bit digits of X times W, zeros included: 2 M K N operations each; peak = dense fp6"
+                    + (f"; {1 - held:.2f} of the rows in three bf16 planes, peak of the mixture" if held < 1 else ""))
+        roof = {"bound": "mfma", "achieved": operations / (kernel_ms * 1e-3) / 1e12, "peak": peak, "unit": "TFLOP/s",
+                "traffic": None if digits else traffic, "note": note}
         if digits:
             traffic = measured = None   # (the counter runs were of the bf16 planes)
     else:

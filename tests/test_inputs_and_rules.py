@@ -171,3 +171,18 @@ def test_bench_traffic_table_names_real_workloads():
         si.workload(name)
         assert variant in ("tcsc", "signed", "packed") and ast.literal_eval(nbytes) > 0
         assert (ROOT / source).is_file(), source
+
+
+def test_bench_counts_the_digits_of_x_as_the_library_cuts_it():
+    sys.path.insert(0, str(ROOT))
+    import bench
+    rng = np.random.default_rng(11)
+    assert bench.digit_planes(np.round(rng.random((130, 100)) * 200).astype(np.float32)) == (1.0, 3.0)
+    assert bench.digit_planes(si.draw_dense(rng, (256, 512), "uniform")) == (1.0, 5.0)
+    assert bench.digit_planes(si.draw_dense(rng, (256, 4096), "normal")) == (0.0, 0.0)
+    assert bench.digit_planes(np.full((64, 64), 2.0**104, np.float32)) == (0.0, 0.0)
+    X = np.ones((128, 64), np.float32)
+    X[70, 3] = 2.0**-33
+    assert bench.digit_planes(X) == (1.0, 5.0)
+    X[70, 3] = 2.0**-34
+    assert bench.digit_planes(X) == (0.5, 3.0)
