@@ -193,8 +193,9 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * synchronisation, no allocation.
  * Device data are not validated.  Errors: EINVAL, ENOTUPLOADED, ENOFORM, EWORKSPACE, EHIP (launch failure).
  * Rounding: fp32 accumulation in an order fixed by (M, K, N), the matrix, the launch-shape options and the
- * size of the workspace; repeated calls give bit-identical results.  Integer-valued inputs small enough
- * for fp32 give exact results.
+ * size of the workspace; repeated calls give bit-identical results.  In calls with X in digits (tstgemm_query_digits()) the
+ * order in a row also depends on whether digits hold all of the 64 rows of its tile, that is on X in up to 63 neighbours.
+ * Integer-valued inputs small enough for fp32 give exact results.
  * Scratch memory (M > 8): this call uses the workspace inside the handle's device buffer (TCSC_FORM_WORKSPACE),
  * so two calls on the same handle must be ordered (same stream, or an event between them).  tstgemm_ex() takes
  * a workspace argument instead.
