@@ -122,9 +122,12 @@ def _bind_launcher(lib):
     """The native half of the calls on tensors.  It only saves host time: without it (not built, or built for another torch) the
     calls go through ctypes."""
     global _launch
+    import torch
     try:
         from . import _launch as native
     except ImportError:
+        return
+    if getattr(native, "torch_version", None) != torch.__version__:
         return
     native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.tstgemm, lib.tstgemm_packed, lib.tstgemm_signed,
                                                                   lib.tstgemm_noalloc, lib.tstgemm_prelu)))

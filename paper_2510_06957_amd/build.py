@@ -1,5 +1,5 @@
-"""Build libtstgemm.so (HIP, gfx950 only) in-tree with hipcc, and _launch.so, the binding's native half (host code on torch's
-C++ headers), with g++.
+"""Build libtstgemm.so (HIP, gfx950 only) in-tree with hipcc, and _launch, the binding's native half (host code on torch's C++
+headers), with g++.  The second needs the headers of Python and torch; where it cannot be built, the binding does without.
 
     python -m paper_2510_06957_amd.build
 
@@ -13,12 +13,14 @@ import os
 import pathlib
 import shutil
 import subprocess
+import sys
+import sysconfig
 
 HERE = pathlib.Path(__file__).resolve().parent
 ROOT = HERE.parent
 CSRC = HERE / "csrc"
 LIB = HERE / "libtstgemm.so"
-LAUNCH = HERE / "_launch.so"
+LAUNCH = HERE / ("_launch" + sysconfig.get_config_var("EXT_SUFFIX"))   # of this Python; the torch it is for is in the module
 SOURCES = ["tcsc_host.cpp", "reblock.hip", "tstgemm_side.hip", "tstgemm_large.hip", "tstgemm_small.hip", "tstgemm_matrix.hip",
            "tstgemm_decode.hip", "tstgemm_packed.hip", "probes.hip", "tstgemm_noalloc.hip"]
 ARCH = "gfx950"
@@ -43,12 +45,10 @@ def command(out: pathlib.Path = LIB, extra: list[str] | None = None) -> list[str
 
 
 def launch_command(out: pathlib.Path = LAUNCH) -> list[str]:
-    import sysconfig
-
     import torch
     home = pathlib.Path(torch.__file__).resolve().parent
     cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-           "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1", f'-DBUILT_FOR_TORCH="{torch.__version__}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     for path in (home / "include", home / "include" / "torch" / "csrc" / "api" / "include",
                  pathlib.Path(hipcc()).resolve().parent.parent / "include", sysconfig.get_paths()["include"]):
         cmd += ["-isystem", str(path)]
@@ -70,7 +70,11 @@ def _run(cmd: list[str], verbose: bool):
 
 def build(verbose: bool = False) -> pathlib.Path:
     _run(command(), verbose)
-    _run(launch_command(), verbose)
+    try:
+        _run(launch_command(), verbose)
+    except (RuntimeError, ImportError, OSError) as e:   # no g++, no headers, no torch
+        LAUNCH.unlink(missing_ok=True)
+        print(f"{LAUNCH.name} was not built (calls from Python take 3 us longer without it): {e}", file=sys.stderr)
     return LIB
 
 

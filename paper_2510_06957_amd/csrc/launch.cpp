@@ -142,5 +142,8 @@ PyMODINIT_FUNC PyInit__launch()
     s_n = PyUnicode_InternFromString("N");
     s_device_index = PyUnicode_InternFromString("device_index");
     s_cuda_stream = PyUnicode_InternFromString("cuda_stream");
-    return PyModule_Create(&module_def);
+    PyObject *module = PyModule_Create(&module_def);
+    // what it reads of a tensor is laid out as in the torch it was built for
+    if (module != nullptr && PyModule_AddStringConstant(module, "torch_version", BUILT_FOR_TORCH) < 0) Py_CLEAR(module);
+    return module;
 }

@@ -25,6 +25,45 @@ def test_it_is_built_and_hands_back_what_is_not_on_a_gpu():
     assert binding._launch(0, torch.ones(2, 4), t, None, None, None, None) is None
 
 
+def test_it_is_not_bound_when_built_for_another_torch(monkeypatch):
+    import types
+
+    import torch
+
+    def bind(*addresses):
+        bound.append(addresses)
+
+    lib, bound = binding._load(), []
+    for version, taken in (("0.0.1", False), (None, False), (torch.__version__, True)):
+        fake = types.SimpleNamespace(bind=bind, launch="launch")
+        if version is not None:
+            fake.torch_version = str(version)
+        monkeypatch.setattr(binding, "_launch", None)
+        monkeypatch.setattr(tg, "_launch", fake, raising=False)
+        binding._bind_launcher(lib)
+        assert (binding._launch == "launch") == taken == bool(bound)
+
+
+def test_the_library_is_built_where_it_cannot_be(monkeypatch, tmp_path, capfd):
+    """Without a compiler for it, or without torch's headers, the build goes on, says so, and leaves no older one behind."""
+    from paper_2510_06957_amd import build
+
+    def no_torch():
+        raise ImportError("no torch")
+
+    monkeypatch.setattr(build, "command", lambda: ["true"])
+    for command in (lambda: ["/nonexistent/g++"], lambda: ["false"], no_torch):
+        old = tmp_path / "_launch.so"
+        old.write_bytes(b"")
+        monkeypatch.setattr(build, "LAUNCH", old)
+        monkeypatch.setattr(build, "launch_command", command)
+        assert build.build() == build.LIB and not old.exists()
+        assert "not built" in capfd.readouterr().err
+    monkeypatch.setattr(build, "command", lambda: ["false"])
+    with pytest.raises(RuntimeError):
+        build.build()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M", [1, 3, 20, 70])
 def test_the_same_results_both_ways(M, monkeypatch):
