@@ -130,7 +130,7 @@ def _bind_launcher(lib):
     if getattr(native, "torch_version", None) != torch.__version__:
         return
     native.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.tstgemm, lib.tstgemm_packed, lib.tstgemm_signed,
-                                                                  lib.tstgemm_noalloc, lib.tstgemm_prelu)))
+                                                                  lib.tstgemm_noalloc, lib.tstgemm_prelu)), TstgemmError)
     _launch = native.launch
 
 

@@ -48,7 +48,7 @@ def launch_command(out: pathlib.Path = LAUNCH) -> list[str]:
     import torch
     home = pathlib.Path(torch.__file__).resolve().parent
     cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-           "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1", f'-DBUILT_FOR_TORCH="{torch.__version__}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1", f'-DBUILT_FOR_TORCH="{torch.__version__}"', f"-I{ROOT / 'include'}", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     for path in (home / "include", home / "include" / "torch" / "csrc" / "api" / "include",
                  pathlib.Path(hipcc()).resolve().parent.parent / "include", sysconfig.get_paths()["include"]):
         cmd += ["-isystem", str(path)]

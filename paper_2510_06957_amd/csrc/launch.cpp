@@ -3,8 +3,9 @@
 // 1.4 into torch.empty and 0.7 into ctypes; here the whole call takes 4.0 us, 3.4 with Y given, of which the launch is 2.5.
 //
 // launch() returns None, without having done anything, for whatever is not plain -- a tensor of another class, type, layout or
-// device, a shape that does not fit, a dispatch or function mode, an error of the library -- and the caller goes the long way,
-// which refuses what it refuses with the message that belongs to it.
+// device, a shape that does not fit, a dispatch or function mode, a call that the library refuses -- and the caller goes the long
+// way, which refuses what it refuses with the message that belongs to it.  An error of the GPU, which kernels of the call may have
+// gone before, is raised here: nothing is launched twice.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -12,6 +13,8 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
+
+#include "tstgemm.h"
 
 namespace {
 
@@ -21,6 +24,7 @@ typedef int (*Prelu)(const float *, const void *, const float *, const float *, 
 enum Entry { kGemm, kPacked, kSigned, kNoalloc, kEntries };
 Gemm g_entry[kEntries];
 Prelu g_prelu;
+PyObject *g_error;   // TstgemmError
 PyObject *s_raw, *s_n, *s_device_index, *s_cuda_stream;
 
 // An attribute that is an int; false (no error set) if it is not there or something else.
@@ -106,6 +110,13 @@ PyObject *launch(PyObject *, PyObject *const *a, Py_ssize_t n_args)
             rc = alpha ? g_prelu(xp, handle, bias, alpha, alpha_count, yp, M, K, N, s)
                        : g_entry[entry](xp, handle, bias, yp, M, K, N, s);
         }
+        if (rc == TSTGEMM_EHIP) {
+            static const char *const names[kEntries] = {"tstgemm", "tstgemm_packed", "tstgemm_signed", "tstgemm_noalloc"};
+            PyObject *e = PyObject_CallFunction(g_error, "is", rc, names[entry]);
+            if (e != nullptr) PyErr_SetObject(g_error, e);
+            Py_XDECREF(e);
+            return nullptr;
+        }
         if (rc != 0) Py_RETURN_NONE;
         if (a[4] != Py_None) {
             Py_INCREF(a[4]);
@@ -118,11 +129,14 @@ PyObject *launch(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     }
 }
 
-// bind(tstgemm, tstgemm_packed, tstgemm_signed, tstgemm_noalloc, tstgemm_prelu): their addresses in the loaded library
+// bind(tstgemm, tstgemm_packed, tstgemm_signed, tstgemm_noalloc, tstgemm_prelu, TstgemmError): addresses in the loaded library
 PyObject *bind(PyObject *, PyObject *args)
 {
     unsigned long long p[kEntries + 1];
-    if (!PyArg_ParseTuple(args, "KKKKK", &p[0], &p[1], &p[2], &p[3], &p[4])) return nullptr;
+    PyObject *error;
+    if (!PyArg_ParseTuple(args, "KKKKKO", &p[0], &p[1], &p[2], &p[3], &p[4], &error)) return nullptr;
+    Py_INCREF(error);
+    Py_XSETREF(g_error, error);
     for (int i = 0; i < kEntries; ++i) g_entry[i] = reinterpret_cast<Gemm>(p[i]);
     g_prelu = reinterpret_cast<Prelu>(p[kEntries]);
     Py_RETURN_NONE;

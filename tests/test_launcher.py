@@ -146,3 +146,39 @@ def test_modes_and_subclasses_see_what_they_saw():
         Y = tg.tstgemm(X, t)
     assert torch.empty in seen and torch.equal(Y, torch.full((4, N), float(K), device="cuda"))
     assert torch.equal(tg.tstgemm(X.as_subclass(Other), t), Y)
+
+
+@pytest.mark.gpu
+def test_an_error_of_the_gpu_is_raised_at_once(monkeypatch):
+    """What the library refuses before it launches anything goes the long way; an error of the GPU does not, so no kernel of the
+    call is launched a second time."""
+    import ctypes
+
+    import torch
+
+    t = tg.tcsc_upload(tg.tcsc_build(np.ones((64, 32), np.int8)), forms=tg.FORM_ROWSETS)
+    X, b, Y = torch.ones(4, 64, device="cuda"), torch.ones(32, device="cuda"), torch.empty(4, 32, device="cuda")
+    lib, vp, ci, calls = binding._load(), ctypes.c_void_p, ctypes.c_int, []
+
+    def library(code, *types):
+        return ctypes.CFUNCTYPE(ci, *types)(lambda *a: calls.append(code) or code)
+
+    from paper_2510_06957_amd import _launch as native
+    for code in (-4, -1):
+        plain = library(code, vp, vp, vp, vp, ci, ci, ci, vp)
+        prelu = library(code, vp, vp, vp, vp, ci, vp, ci, ci, ci, vp)
+        address = [ctypes.cast(f, vp).value for f in (plain, plain, plain, plain, prelu)]
+        native.bind(*address, tg.TstgemmError)
+        try:
+            for entry, name, alpha in ((0, "tstgemm", None), (0, "tstgemm", b), (1, "tstgemm_packed", None), (3, "tstgemm_noalloc", None)):
+                calls.clear()
+                if code == -4:
+                    with pytest.raises(tg.TstgemmError, match=name) as e:
+                        native.launch(entry, X, t, b, Y, None, alpha)
+                    assert e.value.code == code
+                else:
+                    assert native.launch(entry, X, t, b, Y, None, alpha) is None
+                assert calls == [code]
+        finally:
+            binding._bind_launcher(lib)
+    assert torch.equal(tg.tstgemm(X, t, b, Y), torch.full((4, 32), 65.0, device="cuda"))
