@@ -81,8 +81,16 @@ def test_the_same_results_both_ways(M, monkeypatch):
     if M <= 8:
         calls += [lambda: tg.tstgemm_packed(X, t, b), lambda: tg.tstgemm_signed(X, t, b)]
     torch.cuda.synchronize()
+    taken, native_half = [], binding._launch
+
+    def watched(*args):
+        taken.append(native_half(*args))
+        return taken[-1]
+
+    monkeypatch.setattr(binding, "_launch", watched)
     native = [f() for f in calls]
     torch.cuda.synchronize()
+    assert len(taken) == len(calls) and all(done is y for done, y in zip(taken, native))   # each call went that way
     monkeypatch.setattr(binding, "_launch", None)
     for f, y in zip(calls, native):
         z = f()
