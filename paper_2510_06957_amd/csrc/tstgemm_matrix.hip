@@ -356,7 +356,8 @@ struct FourBitWord {
     }
 };
 
-// 1024 bytes from `buf` straight into the LDS, 16 per lane; counted by vmcnt, which the caller waits for.
+// 1024 bytes from `buf` straight into the LDS, 16 per lane; counted by vmcnt, which the caller waits for.  (m0 is reserved: it cannot be
+// named as clobbered, and the compiler sets it before each use of its own.)
 __device__ __forceinline__ void copy_to_lds(uint4v buf, unsigned lds_byte, unsigned offset)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
@@ -390,7 +391,7 @@ template <int N> using Int = std::integral_constant<int, N>;
 // ahead, one barrier a step, placed before the last plane's products so that the next step's first reads are under way behind
 // them.  A step has 4 products of 32 cycles per plane and wavefront.  Everything else is dealt between them one by one: all
 // copies at once, or the spreading behind the products, cost 3 and 7 % of M = 4096, K = N = 8192 (1010 to 1045 us in bf16; here 580
-// to 605 with five planes, 750 with seven, 530 with five at 1/16 non-zeros, where the products draw less power).  Of the 585, k_digits takes 44, the four
+// to 605 with five planes, 750 with seven, 530 with five at 1/16 non-zeros, where the products draw less power).  Of 587, k_digits takes 44, the four
 // rounds' starts and ends about 30; the products by themselves take 430 at the power limit and 273 without it.  64 x 128
 // of Y per wavefront, half the LDS reads, is no faster; a ring of four steps neither.
 // Rows beyond M and rows of W beyond K: X reads as zero, or as the next row of X where the weights are zero.
