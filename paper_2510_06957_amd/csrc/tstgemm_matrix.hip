@@ -12,7 +12,7 @@
 // X held an infinity, a NaN or something beyond about 2^100 -- is taken again from X by sums_of_any(), which keeps such
 // entries apart, so an entry of X under a zero weight never reaches Y here either.
 //
-// k_matrix is for M > 8, k_rows for M <= 10; choose_tile(), with_digits(), rows_plan() and matrix_plan() have the rules, with
+// k_matrix is for M > 8, k_waves for those of its calls that have few tiles, k_rows for M <= 10; choose_tile(), with_digits(), rows_plan() and matrix_plan() have the rules, with
 // what was measured.  k_matrix also multiplies X cut into 6-bit digits by k_digits beforehand, where a call is large enough.
 #include <cmath>
 #include <type_traits>
@@ -854,6 +854,229 @@ k_matrix(const MatrixArgs a)
     }
 }
 
+// ------------------------------------------------------------------------------------------------------------------
+// k_waves: Y in tiles of 32 x 32 CF for calls with up to some hundred such tiles.  A workgroup is four wavefronts, each with the
+// whole tile over a quarter of the workgroup's K: nothing is shared until the sums meet in the LDS at the end, so the loop has
+// no barrier, and K is seldom cut into slices.  Per block of 64 rows of W a wavefront copies 32 x 64 floats of X and the row sets of its
+// columns straight into a ring of two blocks in the LDS that is its own, the next block's while it is at this one; lane l cuts
+// row l % 32, entries 32 (l / 32) .. + 31 of the block, in registers, and spreads that half of each row set.  12 CF matrix
+// instructions of 32 cycles per block, the cuts and the spreading of the next 16 rows dealt between them one by one.
+// Bound: a SIMD issues a vector instruction in 4.1 cycles beside a matrix instruction, which takes 8 of its own (measured), so a
+// block is 48 x 8 + 366 x 4.1 cycles of issue for CF = 4 against 48 x 32 of products; with all compute units at it the power
+// limit takes another fifth (2.2 us per block and pair of wavefronts, 1.65 on one compute unit alone, 1.8 for the products by
+// themselves).  M = 256, K = N = 4096: 21.8 us, 29.4 as 64 x 256 tiles over four slices of K with a second launch for their sums;
+// 64 x 16384 x 4096 25.1 (31.7), 32 x 4096 x 4096 9.3 (10.6), 768 x 1024 x 1024 7.9 (10.5), 512 x 512 x 512 5.0 (5.9).  Eight
+// wavefronts a workgroup: 1 to 5 % slower; v_dot2_f32_bf16 for what a plane leaves: 64 instructions a block less, 15 % slower.
+// The copies take 16 bytes a lane and want every row of X on such a border; other calls go to k_matrix.
+template <int CF>
+__global__ void __launch_bounds__(256, 2)
+k_waves(const MatrixArgs a)
+{
+    constexpr int KW = 4, TN = 32 * CF, kX = 8192, kSlot = kX + 16 * TN;   // a block in the ring: X, then row sets
+    constexpr int kCopiesW = TN / 64, kCopies = 8 + kCopiesW, kQuads = 4 * CF;
+    static_assert(CF == 2 || CF == 4, "columns come 64 at a time, the sums fit the ring");
+    static_assert((32ull + 4) * kMaxExtent * 4 < kNowhere, "offsets inside a tile, two blocks beyond it");
+    __shared__ uint4v lds[KW * 2 * kSlot / 16];
+    typedef __attribute__((address_space(3))) const char *Lds;
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    // consecutive tiles of a row of tiles on one XCD, as in k_matrix
+    int id = blockIdx.x;
+    const int per_xcd = gridDim.x / 8;
+    if (id < 8 * per_xcd) id = (id & 7) * per_xcd + (id >> 3);
+    const int slice = id % a.k_slices;
+    id /= a.k_slices;
+    const int m0 = id / a.n_tiles * 32, n0 = id % a.n_tiles * TN, rows = min(32, a.M - m0);
+    const int slice0 = slice * a.kb_per_slice, slice1 = min(slice0 + a.kb_per_slice, a.n_kblocks);
+    const int blocks = (slice1 - slice0 + KW - 1) / KW, first = slice0 + wave * blocks, end = min(first + blocks, slice1);
+
+    float16v acc[2][CF];   // [hi | mid + lo]
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int j = 0; j < CF; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[d][j][e] = 0.f;
+
+    if (first < end) {   // (the last wavefronts may have no block)
+        // Where the next block's copies come from.  A copy of X is four rows of 256 bytes; piece c (16 bytes) of row r lies at place
+        // c ^ (r % 16) of its row, so that lanes with different rows read different banks.
+        const uint4v xbuf = descriptor(a.X + (size_t)m0 * a.K, (size_t)rows * a.K * 4);
+        const uint4v wbuf = descriptor(a.masks, (size_t)a.n_kblocks * a.n_pad * 16);
+        unsigned from[kCopies];
+#pragma unroll
+        for (int i = 0; i < kCopiesW; ++i) from[i] = ((unsigned)first * (unsigned)a.n_pad + (unsigned)min(n0 + 64 * i + lane, a.n_pad - 1)) * 16u;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            from[kCopiesW + i] = (unsigned)(4 * i + (lane >> 4)) * (unsigned)a.K * 4u + (unsigned)first * 256u +
+                                 16u * (unsigned)((lane & 15) ^ ((4 * i + (lane >> 4)) & 15));
+        const unsigned ring = (unsigned)(size_t)(__attribute__((address_space(3))) uint4v *)lds + wave * (2 * kSlot);
+        auto copy = [&](int i, unsigned slot) {
+            copy_to_lds(i < kCopiesW ? wbuf : xbuf, ring + slot + (i < kCopiesW ? kX + 1024 * i : 1024 * (i - kCopiesW)), from[i]);
+            from[i] += i < kCopiesW ? (unsigned)a.n_pad * 16u : 256u;   // (behind the last block: what nobody multiplies, or nothing)
+        };
+        // What lies beyond the rows of X is not to look like a NaN of an earlier kernel, whether or not such a copy writes zeros
+        if (rows < 32 || (end == a.n_kblocks && a.K % 64 != 0)) {
+            for (int i = lane; i < 2 * kSlot / 16; i += 64) lds[wave * (2 * kSlot / 16) + i] = uint4v{0, 0, 0, 0};
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) copy(i, 0);
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) copy(i, kSlot);
+
+        // Stage s of a block: rows 4 s .. + 3 and 16 + 4 s .. + 3 of each half.  [.][s % 2]: X as it is, its planes, weights
+        float4v raw[2][2];
+        uint4v planes[2][3], bw[2][CF];
+        unsigned pos[CF], neg[CF], even[CF], odd[CF];
+        Lds xat[4][2];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) xat[s][h] = (Lds)(size_t)(ring + l32 * 256 + 16 * ((8 * g + 4 * h + s) ^ (l32 & 15)));
+        const Lds wat = (Lds)(size_t)(ring + kX + l32 * 16 + g * 4);
+        auto read_x = [&](int set, int s, unsigned slot) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) raw[set][h] = *(__attribute__((address_space(3))) const float4v *)(xat[s][h] + slot);
+        };
+        auto read_w = [&](unsigned slot) {
+            const auto p = (__attribute__((address_space(3))) const unsigned *)(wat + slot);
+#pragma unroll
+            for (int j = 0; j < CF; ++j) {
+                pos[j] = p[128 * j];
+                neg[j] = p[128 * j + 2];
+            }
+        };
+        auto words = [&](int j) {
+            const SignedWord w(pos[j], neg[j]);
+            even[j] = w.even;
+            odd[j] = w.odd;
+        };
+        auto spread = [&](int set, int s, int d) {   // dword d % 4 of SignedWord::eight(4 s) for column d / 4
+            bw[set][d / 4][d % 4] = ((d & 1 ? odd : even)[d / 4] << ((d & 2 ? 12 : 14) - 4 * s)) & 0xC000C000u;
+        };
+        float x0 = 0.f, x1 = 0.f;
+        auto cut = [&](int set, int part) {   // plane part % 3 of pair part / 3
+            if (part % 3 == 0) {
+                x0 = raw[set][0][part / 3] * kScaleUp;
+                x1 = raw[set][1][part / 3] * kScaleUp;
+            } else {
+                x0 = below_top(x0);
+                x1 = below_top(x1);
+            }
+            planes[set][part % 3][part / 3] = top_halves(x0, x1);
+        };
+        auto stage = [&](auto number, unsigned at, unsigned other) __attribute__((always_inline)) {
+            constexpr int S = decltype(number)::value, A = S % 2, B = 1 - A, kProducts = 3 * CF;
+            // the next block is there; all of this one has been read, and makes room for the one after the next
+            if constexpr (S == 2) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int q = 0; q < kProducts; ++q) {
+                float16v &c = acc[q < CF ? 0 : 1][q % CF];
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, planes[A][q / CF]),
+                                                            __builtin_bit_cast(bf16x8, bw[A][q % CF]), c, 0, 0, 0);
+                if (q == 0) read_x(A, (S + 2) % 4, S < 2 ? at : other);
+                if (S == 2 && q == 1) read_w(other);
+                if (S == 2 && q >= 2) {
+#pragma unroll
+                    for (int i = (q - 2) * kCopies / (kProducts - 2); i < (q - 1) * kCopies / (kProducts - 2); ++i) copy(i, at);
+                }
+#pragma unroll
+                for (int i = q * 12 / kProducts; i < (q + 1) * 12 / kProducts; ++i) cut(B, i);
+#pragma unroll
+                for (int d = q * (4 * CF) / kProducts; d < (q + 1) * (4 * CF) / kProducts; ++d) {
+                    if (S == 3 && d % 4 == 0) words(d / 4);
+                    spread(B, (S + 1) % 4, d);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto block = [&](unsigned at, unsigned other) __attribute__((always_inline)) {
+            stage(Int<0>{}, at, other);
+            stage(Int<1>{}, at, other);
+            stage(Int<2>{}, at, other);
+            stage(Int<3>{}, at, other);
+        };
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kCopies) : "memory");
+        read_w(0);
+        read_x(0, 0, 0);
+        read_x(1, 1, 0);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) cut(0, i);
+#pragma unroll
+        for (int d = 0; d < 4 * CF; ++d) {
+            if (d % 4 == 0) words(d / 4);
+            spread(0, 0, d);
+        }
+        for (int kb = first; kb < end; kb += 2) {
+            block(0, kSlot);
+            if (kb + 1 < end) block(kSlot, 0);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing is on its way to the LDS any more
+    }
+
+    // Sums of the wavefronts, [wave][quad][lane]: quad 4 j + q is elements 4 q .. of column fragment j, rows 8 q + 4 g .. + 3 of
+    // column 32 j + l32.  A wavefront finishes CF quads: 16 rows or all 32 of 32 columns.
+    float4v *const sums = reinterpret_cast<float4v *>(lds);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < CF; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float4v v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[0][j][4 * q + e] + acc[1][j][4 * q + e];
+            sums[(wave * kQuads + 4 * j + q) * 64 + lane] = v;
+        }
+    const int quad0 = wave * CF, row0 = 8 * (quad0 % 4), col0 = n0 + 32 * (quad0 / 4), n = col0 + l32;
+    const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);
+    const float bias = finish.bias_of(n), slope = finish.slope_of(n);
+    const bool sliced = a.k_slices > 1;
+    float *out = sliced ? a.partials + ((size_t)slice * a.M + m0) * a.n_pad : a.Y + (size_t)m0 * a.N;
+    const int width = sliced ? a.n_pad : a.N;
+    const __amdgpu_buffer_rsrc_t obuf = raw_buffer(out, (size_t)rows * width * 4);
+    float spoilt = 0.f;   // NaN as soon as one sum is not finite
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < CF; ++q) {
+        float4v part[KW];
+#pragma unroll
+        for (int w = 0; w < KW; ++w) part[w] = sums[(w * kQuads + quad0 + q) * 64 + lane];
+        const float4v v = (part[0] + part[2]) + (part[1] + part[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            spoilt = fmaf(v[e], 0.f, spoilt);
+            const float y = v[e] * kScaleDown;
+            const unsigned row = row0 + 8 * q + 4 * g + e;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sliced ? y : finish(y, bias, slope)), obuf,
+                                                  (int)(n < width ? (row * (unsigned)width + n) * 4u : kNowhere), 0, kWriteThrough);
+        }
+    }
+    if (!__any(spoilt != 0.f)) return;
+
+    // again, from X, as in k_matrix
+    __threadfence();
+    const int r16 = lane & 15, g16 = lane >> 4;
+    for (int piece = 0; piece < CF; ++piece) {
+        const int row = row0 + 16 * (piece / 2), col = col0 + 16 * (piece % 2) + r16;
+        if (row >= rows) break;
+        bool bad[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int m = row + 4 * g16 + e;
+            bad[e] = m < rows && col < width && !finite(out[(size_t)m * width + col]);
+        }
+        if (!__any(bad[0] || bad[1] || bad[2] || bad[3])) continue;
+        const float4v v = sums_of_any(a.X + (size_t)(m0 + row) * a.K, min(rows - row, 16), a.K, a.masks, a.n_pad,
+                                      min(col, a.n_pad - 1), slice0, slice1, 0, 1);
+        const float bias_c = finish.bias_of(col), slope_c = finish.slope_of(col);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (bad[e]) out[(size_t)(row + 4 * g16 + e) * width + col] = sliced ? v[e] : finish(v[e], bias_c, slope_c);
+    }
+}
+
 // k_matrix_sum: Y = slice 0 + slice 1 + ... + b, then the optional PReLU; four columns per thread, all slices
 // requested together.  Bound by its launch and one trip to memory (4 slices of 256 x 4096: about 5 us).  Y is written through the
 // L2 (512 x 4096 x 4096 41.0 -> 40.3 us a call, 777 x 3001 x 2999 41.3 -> 40.8; below 1 MB of Y no difference).
@@ -905,6 +1128,13 @@ hipError_t launch_sum(const MatrixArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
+template <int CF>
+hipError_t launch_waves(const MatrixArgs &a, long long m_tiles, const Call &c)
+{
+    hipLaunchKernelGGL(k_waves<CF>, dim3((unsigned)(m_tiles * a.n_tiles * a.k_slices)), dim3(256), 0, c.stream, a);
+    return hipGetLastError();
+}
+
 template <int WK, int WM, int WN, int RF, int CF, bool DIGITS>
 hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 {
@@ -918,8 +1148,10 @@ hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 // (per_cu workgroups at a time); a call takes kCall us more, slices kSlice us and 0.4 us per MB of partial sums; and no
 // call is faster than `peak` operations per us, what the tile reaches on long calls under the power limit (64 x 512 against
 // 64 x 256: M = 4096, K = N = 8192 1073 -> 1038 us, 2048 x 4096 x 4096 138 -> 132, 1024 x 2048 x 8192 74 -> 70).  Fitted to 13 tiles x 6 slice counts on 77
-// shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five is 2 % slower than the best of all on
-// average, 16 % at worst.
+// shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five of k_matrix is 2 % slower than the best of
+// all on average, 16 % at worst.  k_waves is fitted to 1014 timings (M = 11 .. 768, the same K and N), with figures that are high by
+// some 5 % on long calls, where those of k_matrix are: of 120 shapes the choice is 0.7 % slower than the better of the two on average, and
+// three are slower than k_matrix alone by more than 2 % (16 x 2048 x 2048, 11 x 2048 x 2048, 192 x 4096 x 11008: 7.5 %, 516 tiles on 512 places).
 struct TileShape {
     int rows, cols, groups, waves, per_cu;
     double fixed, step, work, peak;
@@ -931,8 +1163,14 @@ constexpr TileShape kTiles[] = {
     {64, 128, 1, 4, 3, 0.31, 0.420, 0.311, 1.45e9},   // short K: little to start with
     {32, 64, 4, 8, 2, 0.65, 0.501, 0.461, 1.30e9},    // small Y
     {32, 128, 2, 8, 2, 0.34, 0.456, 0.383, 1.40e9},   // M <= 32
+    {32, 64, 4, 4, 2, 0.50, 0.262, 0.370, 2.30e9},    // k_waves
+    {32, 128, 4, 4, 2, 1.20, 0.451, 0.490, 1.28e9},
 };
 constexpr int kDigitTiles = 2;   // the first two can take X in digits
+constexpr int kFirstOfWaves = 6;
+// The last two are k_waves, whose copies of X need every row of X on a 16-byte border; K of less than a block per wavefront leaves
+// wavefronts without work.
+bool waves_can(const tcsc_layout_t &l, bool x_aligned) { return x_aligned && l.K % 4 == 0 && l.n_kblocks >= 4; }
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
 
 struct TilePlan {
@@ -987,11 +1225,16 @@ TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TileP
     return TilePlan{p.tile, p.k_slices, kSparsePart * p.us, true};
 }
 
-TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
+TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_aligned)
 {
     TilePlan best{-1, 1, 0.0};
     const int units = compute_units();
-    for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+    const int n_shapes = waves_can(l, x_aligned) ? (int)(sizeof(kTiles) / sizeof(kTiles[0])) : kFirstOfWaves;
+    for (int i = 0; i < n_shapes; ++i) {
+        if (i == kFirstOfWaves && best.tile >= 0) {   // a call that k_matrix takes in digits stays there
+            const TilePlan p = with_digits(l, M, ws_bytes, best);
+            if (p.digits) return p;
+        }
         const TileShape &s = kTiles[i];
         const double tiles = (double)(((long long)M + s.rows - 1) / s.rows) * ((l.n_pad + s.cols - 1) / s.cols);
         const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
@@ -1300,10 +1543,15 @@ size_t matrix_workspace_bytes(int M, int K, int N, int n_pad)
     tcsc_layout_t l{};
     l.K = K; l.N = N; l.n_pad = n_pad; l.n_kblocks = (K - 1) / kKBlock + 1;
     if (!offsets_fit(l)) return 0;
-    const TilePlan p = choose_tile(l, M, (size_t)1 << 62);
-    if (p.tile < 0) return 0;
-    const size_t partial_bytes = p.k_slices > 1 ? (size_t)p.k_slices * M * n_pad * 4 : 0;
-    return partial_bytes + (p.digits ? ((size_t)M + 63) / 64 * digit_tile_bytes(l) : 0);
+    size_t most = 0;
+    for (const bool x_aligned : {false, true}) {
+        const TilePlan p = choose_tile(l, M, (size_t)1 << 62, x_aligned);
+        if (p.tile < 0) continue;
+        const size_t partial_bytes = p.k_slices > 1 ? (size_t)p.k_slices * M * n_pad * 4 : 0;
+        const size_t bytes = partial_bytes + (p.digits ? ((size_t)M + 63) / 64 * digit_tile_bytes(l) : 0);
+        most = most > bytes ? most : bytes;
+    }
+    return most;
 }
 
 // Whether the matrix cores take a call (the lists or the row-set walk being the other choice).  They do unless W is so
@@ -1342,7 +1590,7 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
             return MatrixPlan{true, r.tiles, r.waves, false};
         }
     }
-    const TilePlan p = choose_tile(l, M, c.ws_bytes);
+    const TilePlan p = choose_tile(l, M, c.ws_bytes, c.x_aligned);
     const bool rows = M <= kMaxRows && (p.tile < 0 || r.us < p.us);
     if (!rows && p.tile < 0) return none;
     const double us = rows ? r.us : p.us;
@@ -1395,7 +1643,9 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
         case 2: return launch_tiles<2, 1, 4, 2, 2, false>(a, n, c);
         case 3: return launch_tiles<1, 1, 4, 2, 1, false>(a, n, c);
         case 4: return launch_tiles<4, 1, 2, 1, 1, false>(a, n, c);
-        default: return launch_tiles<2, 1, 4, 1, 1, false>(a, n, c);
+        case 5: return launch_tiles<2, 1, 4, 1, 1, false>(a, n, c);
+        case 6: return launch_waves<2>(a, n, c);
+        default: return launch_waves<4>(a, n, c);
         }
     };
     const auto tiles = [&](long long n) {   // n tiles of rows, between the call's events

@@ -1,0 +1,68 @@
+"""The matrix-core kernel whose wavefronts share nothing but their sums (32 x 64 and 32 x 128 of Y, four groups of wavefronts over K):
+shapes at the edges of its tiles, blocks and copies, and X off the border that its copies need, against the oracle element by
+element."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2510_06957_amd as tg
+import synth_inputs as si
+from gpu_util import gpu_tstgemm
+from test_gpu_matrix import _same, tight
+
+# rows: one, all but one, all of a tile and one more; K: four blocks of 64 and the last of them in part, one wavefront with a block more
+# or with none, many blocks, an odd and an even number of them a wavefront; columns: of a fragment, of a tile, one more or less, odd.
+NARROW = [(11, 256, 1), (31, 252, 63), (32, 260, 64), (33, 316, 65), (64, 320, 130), (95, 580, 257), (129, 1024, 1000), (40, 1796, 100),
+          (36, 4100, 700), (256, 2048, 2048), (32, 2048, 7950), (65, 2052, 3001), (96, 2308, 4031)]
+WIDE = [(33, 4096, 5000), (255, 4092, 4031), (256, 512, 4096), (64, 8196, 4100), (128, 8196, 1000),
+        (300, 2048, 4100)]
+
+
+def route(t, M):
+    r = tg.tstgemm_query_route(t, M)
+    return r.kernel, r.tile_rows, r.tile_cols, r.k_groups
+
+
+@pytest.mark.parametrize("M,K,N", NARROW + WIDE)
+def test_routes(M, K, N):
+    none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
+    t = tg.tcsc_from_arrays(starts, starts, none, none, K, N)
+    if M > 64:   # (with few rows an empty matrix is the lists')
+        assert route(t, M) == ("k_matrix", 32, 64 if (M, K, N) in NARROW else 128, 4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", NARROW + WIDE)
+def test_tile_edges(M, K, N):
+    import torch
+    W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=300 + M + K + N)
+    ot = oracle.tcsc_build(W)
+    Yd, A, _ = oracle.tstgemm(X, ot, b)
+    Y, t = gpu_tstgemm(W, X, b)
+    assert route(t, M) == ("k_matrix", 32, 64 if (M, K, N) in NARROW else 128, 4)
+    tight(Y, Yd, A, f"{M}x{K}x{N}")
+    _, Xi, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=301 + M)
+    Yi = oracle.tstgemm(Xi, ot, b)[0].astype(np.float32)
+    assert np.array_equal(gpu_tstgemm(W, Xi, b, handle=t)[0], Yi)
+    # X four bytes off the border: another kernel, the same sums
+    off = torch.empty(M * K + 1, device="cuda")[1:].view(M, K)
+    off.copy_(torch.from_numpy(Xi))
+    Yo = torch.full((M, N), float("nan"), device="cuda")
+    tg.tstgemm(off, t, torch.from_numpy(b).cuda(), Yo)
+    assert np.array_equal(Yo.cpu().numpy(), Yi)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(31, 252, 63), (33, 316, 65), (36, 4100, 700), (65, 2052, 3001), (64, 8196, 1100)])
+def test_infinities_beyond_the_rows(M, K, N):
+    """A row's last entries and the first of the row behind it are infinite or NaN: only outputs whose lists hold them show it, also
+    where the last block of K reaches into the next row."""
+    W, X, b = si.make_inputs(M, K, N, 0.25, "normal", seed=320 + M)
+    X[1, K - 1], X[2, 0], X[M - 1, K - 1], X[M - 1, 3] = np.inf, -np.inf, np.nan, np.inf
+    with np.errstate(invalid="ignore"):
+        Yd = np.stack([np.where(W != 0, X[m][:, None].astype(np.float64) * W, 0.0).sum(axis=0) for m in range(M)]) + b
+    A = np.abs(np.where(np.isfinite(X), X, 0)).astype(np.float64) @ np.abs(W) + np.abs(b)
+    Y, _ = gpu_tstgemm(W, X, b)
+    ok = np.isfinite(Yd)
+    assert ok.any() and not ok.all() and _same(Y, Yd)
+    assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-6 * A[ok])
