@@ -1229,33 +1229,41 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_alig
 {
     TilePlan best{-1, 1, 0.0};
     const int units = compute_units();
-    const int n_shapes = waves_can(l, x_aligned) ? (int)(sizeof(kTiles) / sizeof(kTiles[0])) : kFirstOfWaves;
-    for (int i = 0; i < n_shapes; ++i) {
-        if (i == kFirstOfWaves && best.tile >= 0) {   // a call that k_matrix takes in digits stays there
-            const TilePlan p = with_digits(l, M, ws_bytes, best);
-            if (p.digits) return p;
-        }
+    const auto consider = [&](int i, int k) {
         const TileShape &s = kTiles[i];
         const double tiles = (double)(((long long)M + s.rows - 1) / s.rows) * ((l.n_pad + s.cols - 1) / s.cols);
-        const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
         // a launch has less than 2^32 threads; a call with more tiles than that (K slices are for few tiles only) goes to
-        // k_large, which takes X in slabs
-        if (tiles * (64 * s.waves) >= 4294967296.0) continue;
-        // (slices beyond two full rounds only add partial sums)
-        for (int k = 1; k <= kMaxKSlices && k <= l.n_kblocks && (k == 1 || tiles * k <= 2.0 * units * s.per_cu); ++k) {
-            const int per = (l.n_kblocks + k - 1) / k;
-            const double mb = 4e-6 * (double)k * M * l.n_pad;
-            if (k > 1 && (per * (k - 1) >= l.n_kblocks || M > 65535 || mb * 1e6 > (double)ws_bytes)) continue;
-            const double load = up(tiles * k / units), rounds = up(load / s.per_cu);
-            const double steps = 2.0 * ((per + s.groups - 1) / s.groups);
-            const double step_us = s.step * rounds > s.work * load ? s.step * rounds : s.work * load;
-            double us = s.fixed * rounds + steps * step_us;
-            if (us < floor_us) us = floor_us;
-            us += kCall + (k > 1 ? kSlice + kSliceMb * mb : 0.0);
-            if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
-        }
+        // k_large, which takes X in slabs.  (Slices beyond two full rounds only add partial sums)
+        if (tiles * (64 * s.waves) >= 4294967296.0 || (k > 1 && tiles * k > 2.0 * units * s.per_cu)) return false;
+        const int per = (l.n_kblocks + k - 1) / k;
+        const double mb = 4e-6 * (double)k * M * l.n_pad;
+        if (k > 1 && (per * (k - 1) >= l.n_kblocks || M > 65535 || mb * 1e6 > (double)ws_bytes)) return true;
+        const double load = up(tiles * k / units), rounds = up(load / s.per_cu);
+        const double steps = 2.0 * ((per + s.groups - 1) / s.groups);
+        const double step_us = s.step * rounds > s.work * load ? s.step * rounds : s.work * load;
+        const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
+        double us = s.fixed * rounds + steps * step_us;
+        if (us < floor_us) us = floor_us;
+        us += kCall + (k > 1 ? kSlice + kSliceMb * mb : 0.0);
+        if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
+        return true;
+    };
+    // K whole first: most short calls are then seen to gain nothing from slices (64 x 512 x 512: 8 estimates in place of 64, 0.4 us)
+    const auto choose = [&](int from, int to) {
+        for (int i = from; i < to; ++i) consider(i, 1);
+        for (int i = from; i < to; ++i)
+            for (int k = 2; k <= kMaxKSlices && k <= l.n_kblocks; ++k) {
+                const double least = kCall + kSlice + kSliceMb * 4e-6 * (double)k * M * l.n_pad + kTiles[i].fixed + 2.0 * kTiles[i].step;
+                if ((best.tile >= 0 && least >= best.us) || !consider(i, k)) break;
+            }
+    };
+    choose(0, kFirstOfWaves);
+    if (best.tile >= 0) {   // a call that k_matrix takes in digits stays there
+        const TilePlan p = with_digits(l, M, ws_bytes, best);
+        if (p.digits) return p;
     }
-    return best.tile < 0 ? best : with_digits(l, M, ws_bytes, best);
+    if (waves_can(l, x_aligned)) choose(kFirstOfWaves, (int)(sizeof(kTiles) / sizeof(kTiles[0])));
+    return best;
 }
 
 // ------------------------------------------------------------------------------------------------------------------
