@@ -717,6 +717,29 @@ k_matrix(const MatrixArgs a)
         load_x(0, 2 * kb0 + PD);
         bf16x8 bw[2][CF];
         spread_w(bw[0], 0, 0, 0);
+        bf16x8 x[2][RF];
+        auto read_x = [&](int t, int s) {   // stage s: plane s % 3 of 16 rows
+#pragma unroll
+            for (int i = 0; i < RF; ++i)
+                x[s & 1][i] = __builtin_bit_cast(
+                    bf16x8, lds[t * kBuffer + (s % 3) * kPlane + (2 * (s / 3) + g) * kChunk + (wr * RF + i) * 32 + l32]);
+        };
+        // The next step's planes are written, this step's have been read.  Only LDS traffic is waited for: the loads of the
+        // coming steps stay in flight
+        auto meet = [&]() {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        };
+        // The wavefronts meet in front of a step's last products, which are under way meanwhile (600 x 600 x 3000 in 64 x 128 tiles 11.5 ->
+        // 11.1 us, 100 x 4099 x 500 in 32 x 128 13.4 -> 12.5, 64 x 512 up to 1 %).  In front of the first where that is 1 % better: with four
+        // groups of wavefronts, and in 64 x 256 tiles, two of which share a compute unit and fill each other's waits.
+        constexpr bool kEarly = WK < 4 && !(CF == 2 && WK * WN == 4);
+        constexpr int kCutStages = kEarly ? 4 : 5, kStore = kEarly ? 4 : 5, kSpread = kEarly ? 5 : 4;
+        if (kEarly) {
+            meet();
+            read_x(0, 0);
+        }
         for (int i0 = 0; i0 < blocks; i0 += 2) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
@@ -725,33 +748,33 @@ k_matrix(const MatrixArgs a)
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {   // half of the block: 32 rows of W, LDS buffer t
                     const int next = (t + 1) % PD;
-                    bf16x8 x[2][RF];
-                    auto read_x = [&](int s) {   // stage s: plane s % 3 of 16 rows
-#pragma unroll
-                        for (int i = 0; i < RF; ++i)
-                            x[s & 1][i] = __builtin_bit_cast(
-                                bf16x8, lds[t * kBuffer + (s % 3) * kPlane + (2 * (s / 3) + g) * kChunk + (wr * RF + i) * 32 + l32]);
-                    };
-                    // this step's planes are written, the other buffer's have been read.  Only LDS traffic is waited for:
-                    // the loads of the coming steps stay in flight
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                    read_x(0);
+                    if (!kEarly) {
+                        meet();
+                        read_x(t, 0);
+                    }
 #pragma unroll
                     for (int s = 0; s < 6; ++s) {
-                        if (s < 5) read_x(s + 1);
+                        if (s < 5) {
+                            read_x(t, s + 1);
+                        } else if (kEarly) {
+                            meet();
+                            read_x(t ^ 1, 0);
+                        }
 #pragma unroll
-                        for (int i = s * kPairs / 5; i < (s + 1) * kPairs / 5 && i < kPairs; ++i) cut_pair(next, i);
+                        for (int i = s * kPairs / kCutStages; i < (s + 1) * kPairs / kCutStages && i < kPairs; ++i) cut_pair(next, i);
                         if (s == 1) spread_w(bw[1], q, t, 1);
-                        if (s == 4) {
+                        if (s == 4 && kSpread == 4) {
                             if (t == 1) load_w(q, kb + 2);
                             spread_w(bw[0], t ? q ^ 1 : q, t ^ 1, 0);
                         }
-                        if (s == 5) {
+                        if (s == kStore) {
                             // (behind the last block this writes once more what nothing reads)
                             store_planes(t ^ 1);
                             load_x(next, 2 * kb + t + 1 + PD);
+                        }
+                        if (s == 5 && kSpread == 5) {
+                            if (t == 1) load_w(q, kb + 2);
+                            spread_w(bw[0], t ? q ^ 1 : q, t ^ 1, 0);
                         }
 #pragma unroll
                         for (int i = 0; i < RF; ++i)
@@ -1078,7 +1101,7 @@ k_waves(const MatrixArgs a)
 }
 
 // k_matrix_sum: Y = slice 0 + slice 1 + ... + b, then the optional PReLU; four columns per thread, all slices
-// requested together.  Bound by its launch and one trip to memory (4 slices of 256 x 4096: about 5 us).  Y is written through the
+// requested together and added in pairs (error of the norm 5.9e-8 where it was 6.6e-8 one after the other, seven slices).  Bound by its launch and one trip to memory (4 slices of 256 x 4096: about 5 us).  Y is written through the
 // L2 (512 x 4096 x 4096 41.0 -> 40.3 us a call, 777 x 3001 x 2999 41.3 -> 40.8; below 1 MB of Y no difference).
 template <int S>
 __global__ void __launch_bounds__(256)
@@ -1091,9 +1114,11 @@ k_matrix_sum(const MatrixArgs a)
     float4v part[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) part[s] = *reinterpret_cast<const float4v *>(P + s * stride);
-    float4v y = part[0];
 #pragma unroll
-    for (int s = 1; s < S; ++s) y += part[s];
+    for (int half = (S + 1) / 2, n_left = S; n_left > 1; n_left = half, half = (half + 1) / 2)
+#pragma unroll
+        for (int s = 0; s + half < n_left; ++s) part[s] += part[s + half];
+    float4v y = part[0];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (n + i >= a.N) break;
