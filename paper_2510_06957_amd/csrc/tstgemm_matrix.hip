@@ -1101,7 +1101,8 @@ k_waves(const MatrixArgs a)
 }
 
 // k_matrix_sum: Y = slice 0 + slice 1 + ... + b, then the optional PReLU; four columns per thread, all slices
-// requested together and added in pairs (error of the norm 5.9e-8 where it was 6.6e-8 one after the other, seven slices).  Bound by its launch and one trip to memory (4 slices of 256 x 4096: about 5 us).  Y is written through the
+// requested together and added in pairs (error of the norm 5.9e-8 where it was 6.6e-8 one after the other, seven slices).  Bias and slopes are requested
+// with them: behind them they were a second trip to memory, 0.33 us (32 x 4096 x 4096 9.45 -> 9.1 us a call).  Bound by its launch and one trip to memory (4 slices of 256 x 4096: about 5 us).  Y is written through the
 // L2 (512 x 4096 x 4096 41.0 -> 40.3 us a call, 777 x 3001 x 2999 41.3 -> 40.8; below 1 MB of Y no difference).
 template <int S>
 __global__ void __launch_bounds__(256)
@@ -1114,18 +1115,17 @@ k_matrix_sum(const MatrixArgs a)
     float4v part[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) part[s] = *reinterpret_cast<const float4v *>(P + s * stride);
+    const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);   // (nothing beyond column N is read)
+    float4v bias = __builtin_bit_cast(float4v, load16(finish.bias, n * 4u)), slope;
+    if (a.alpha_stride) slope = __builtin_bit_cast(float4v, load16(finish.slope, n * 4u));
+    else slope = float4v{1.f, 1.f, 1.f, 1.f} * finish.slope_of(0);
 #pragma unroll
     for (int half = (S + 1) / 2, n_left = S; n_left > 1; n_left = half, half = (half + 1) / 2)
 #pragma unroll
         for (int s = 0; s + half < n_left; ++s) part[s] += part[s + half];
-    float4v y = part[0];
+    float4v y;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (n + i >= a.N) break;
-        float v = y[i];
-        if (a.b != nullptr) v += a.b[n + i];
-        y[i] = activate(v, a.alpha, a.alpha_stride, n + i);
-    }
+    for (int i = 0; i < 4; ++i) y[i] = finish(part[0][i], bias[i], slope[i]);
     float *dst = a.Y + (size_t)m * a.N + n;
     if (n + 4 <= a.N) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v, y), raw_buffer(a.Y + (size_t)m * a.N, (size_t)a.N * 4), n * 4, 0,
