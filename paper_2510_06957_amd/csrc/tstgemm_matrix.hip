@@ -923,8 +923,8 @@ k_waves(const MatrixArgs a)
             for (int e = 0; e < 16; ++e) acc[d][j][e] = 0.f;
 
     if (first < end) {   // (the last wavefronts may have no block)
-        // Where the next block's copies come from.  A copy of X is four rows of 256 bytes; piece c (16 bytes) of row r lies at place
-        // c ^ (r % 16) of its row, so that lanes with different rows read different banks.
+        // Where the next block's copies come from.  A copy of X is four rows of 256 bytes (the last row again in place of those that do not
+        // exist); piece c (16 bytes) of row r lies at place c ^ (r % 16) of its row, so that lanes with different rows read different banks.
         const uint4v xbuf = descriptor(a.X + (size_t)m0 * a.K, (size_t)rows * a.K * 4);
         const uint4v wbuf = descriptor(a.masks, (size_t)a.n_kblocks * a.n_pad * 16);
         unsigned from[kCopies];
@@ -932,15 +932,15 @@ k_waves(const MatrixArgs a)
         for (int i = 0; i < kCopiesW; ++i) from[i] = ((unsigned)first * (unsigned)a.n_pad + (unsigned)min(n0 + 64 * i + lane, a.n_pad - 1)) * 16u;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            from[kCopiesW + i] = (unsigned)(4 * i + (lane >> 4)) * (unsigned)a.K * 4u + (unsigned)first * 256u +
+            from[kCopiesW + i] = (unsigned)min(4 * i + (lane >> 4), rows - 1) * (unsigned)a.K * 4u + (unsigned)first * 256u +
                                  16u * (unsigned)((lane & 15) ^ ((4 * i + (lane >> 4)) & 15));
         const unsigned ring = (unsigned)(size_t)(__attribute__((address_space(3))) uint4v *)lds + wave * (2 * kSlot);
         auto copy = [&](int i, unsigned slot) {
             copy_to_lds(i < kCopiesW ? wbuf : xbuf, ring + slot + (i < kCopiesW ? kX + 1024 * i : 1024 * (i - kCopiesW)), from[i]);
             from[i] += i < kCopiesW ? (unsigned)a.n_pad * 16u : 256u;   // (behind the last block: what nobody multiplies, or nothing)
         };
-        // What lies beyond the rows of X is not to look like a NaN of an earlier kernel, whether or not such a copy writes zeros
-        if (rows < 32 || (end == a.n_kblocks && a.K % 64 != 0)) {
+        // What lies beyond the last row is not to look like a NaN of an earlier kernel, whether or not such a copy writes zeros
+        if (end == a.n_kblocks && a.K % 64 != 0) {
             for (int i = lane; i < 2 * kSlot / 16; i += 64) lds[wave * (2 * kSlot / 16) + i] = uint4v{0, 0, 0, 0};
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
@@ -1599,8 +1599,9 @@ size_t matrix_workspace_bytes(int M, int K, int N, int n_pad)
 //    there the figure above, too high for that, does no harm.
 //  * 8 < M <= 64: k_small, with a tile of 16 rows, takes 6.1 us, or 9.6 us where K is cut into slices (beyond 1024 rows),
 //    + 0.1 per 1000 rows of W + 0.12 per million entries + 0.8 per million non-zeros, 1.3 and 1.7 times that for 32 and
-//    64 rows (M = 16: 1024 x 4096 at 1/16 6.6 against 7.4 us, 15000 x 600 12.6 against 14.2; from 17 rows on it is behind
-//    everywhere, down to an empty W).
+//    64 rows (M = 16: 15000 x 600 at 1/16 12.6 against 14.2; from 17 rows on it is behind everywhere, down to an empty W).  The
+//    6.1 count as 6.7: k_small has a second launch before it and takes more than that on few columns (1024 x 1024, M = 16, from an
+//    empty W to 50 %: 6.2 .. 8.2 against 6.25 here; 14 shapes x 6 densities: k_small ahead by at most 1 % where this path is taken).
 //  * M <= 8: k_decode takes 2.55 + 0.5 M + 0.04 us per 1000 rows of W + (0.265 + 0.016 M) us per million non-zeros for one or
 //    two rows, 2.03 + 0.58 M + 0.13 + (0.353 + 0.066 M) for more, and 3.5 us for each further time that X fills the LDS (fitted
 //    to 17 shapes x 4 densities x M = 1 .. 8; the choice is 0.6 % behind the better of the two on average, 69 % at worst, 3 x 4096
@@ -1630,7 +1631,7 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
     double other;
     if (M <= 64) {
         other = (M <= 16 ? 1.0 : M <= 32 ? 1.3 : 1.7) *
-                ((l.K <= 1024 ? 6.1 : 9.6) + 0.1e-3 * l.K + entries * (0.12 + 0.8 * d));
+                ((l.K <= 1024 ? 6.7 : 9.6) + 0.1e-3 * l.K + entries * (0.12 + 0.8 * d));
     } else {
         if (l.n_pad % 128 != 0) return MatrixPlan{false, p.tile, p.k_slices, p.digits};
         const double groups = ceil(M / 256.0) * (l.n_pad / 128);
