@@ -70,6 +70,39 @@ struct SignedWord {
     }
 };
 
+// A byte of two fp4 weights as a dword of two bf16 weights, the low half first.  One conversion, as long as any vector instruction, where
+// SignedWord takes a shift and an AND: 27 instructions for 32 rows through FourBitWord in place of 38.
+__device__ __forceinline__ unsigned two_weights(unsigned fours, int byte)
+{
+    switch (byte) {   // (known to the compiler)
+    case 0: return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(fours, 1.f, 0));
+    case 1: return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(fours, 1.f, 1));
+    case 2: return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(fours, 1.f, 2));
+    default: return __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(fours, 1.f, 3));
+    }
+}
+
+// 32 rows of a column as fp4 weights, 2.0 with its sign: bit 2 of four says non-zero, bit 3 is the sign.
+struct FourBitWord {
+    int4v w;   // dword d: rows 4 n + d
+    __device__ __forceinline__ FourBitWord(unsigned pos, unsigned neg)
+    {
+        const unsigned nz = pos | neg;
+        const unsigned even = (nz & 0x55555555u) | ((neg << 1) & 0xAAAAAAAAu);
+        const unsigned odd = ((nz >> 1) & 0x55555555u) | (neg & 0xAAAAAAAAu);
+        w[0] = (int)((even << 2) & 0xCCCCCCCCu);
+        w[1] = (int)((odd << 2) & 0xCCCCCCCCu);
+        w[2] = (int)(even & 0xCCCCCCCCu);
+        w[3] = (int)(odd & 0xCCCCCCCCu);
+    }
+    // rows 8 part .. + 7 as bf16 weights: rows d and d + 4 of them in dword d
+    __device__ __forceinline__ bf16x8 eight(int part) const
+    {
+        return __builtin_bit_cast(bf16x8, uint4v{two_weights((unsigned)w[0], part), two_weights((unsigned)w[1], part),
+                                                  two_weights((unsigned)w[2], part), two_weights((unsigned)w[3], part)});
+    }
+};
+
 __device__ __forceinline__ uint4v load16(__amdgpu_buffer_rsrc_t buf, unsigned offset)
 {
     return __builtin_bit_cast(uint4v, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)offset, 0, 0));
@@ -340,21 +373,6 @@ k_digits(const float *X, int M, int K, int n_kblocks, char *units, unsigned char
         }
     }
 }
-
-// 32 rows of a column as fp4 weights, 2.0 with its sign: bit 2 of four says non-zero, bit 3 is the sign.
-struct FourBitWord {
-    int4v w;   // dword d: rows 4 n + d
-    __device__ __forceinline__ FourBitWord(unsigned pos, unsigned neg)
-    {
-        const unsigned nz = pos | neg;
-        const unsigned even = (nz & 0x55555555u) | ((neg << 1) & 0xAAAAAAAAu);
-        const unsigned odd = ((nz >> 1) & 0x55555555u) | (neg & 0xAAAAAAAAu);
-        w[0] = (int)((even << 2) & 0xCCCCCCCCu);
-        w[1] = (int)((odd << 2) & 0xCCCCCCCCu);
-        w[2] = (int)(even & 0xCCCCCCCCu);
-        w[3] = (int)(odd & 0xCCCCCCCCu);
-    }
-};
 
 // 1024 bytes from `buf` straight into the LDS, 16 per lane; counted by vmcnt, which the caller waits for.  (m0 is reserved: it cannot be
 // named as clobbered, and the compiler sets it before each use of its own.)
@@ -1307,13 +1325,15 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_alig
 // 33 %), 8 % less to 3 % more at M = 6, 7, and the same at M = 8 (2 % less to 3 % more: 2500 x 5000 6.1 -> 6.3 us).
 //
 // PACKED: W from the base-3 codes (a.masks, a.n_kblocks: 16-byte pieces of 80 rows, [piece][n_pad]).  A table in the LDS
-// gives the five weights of a code, sign and non-zero bit side by side; the words of codes j and j + 8 make dwords for
-// rows 5 j + i and 40 more, again one shift and one AND each.  A group is 320 rows and ten matrix instructions a tile.
+// gives the five weights of a code, four bits each; those of codes j and j + 8, put side by side, make bytes that are converted to
+// dwords for rows 5 j + i and 40 more (M = 1, 4096 x 11008 7.0 us with a shift and an AND for each, 6.6 so; M = 5 9.05, 8.7).
+// A group is 320 rows and ten matrix instructions a tile.
 // Against the kernel that multiplies on the vector ALU, 4096 x 11008: M = 2 9.3 -> 8.4 us, M = 8 21.5 -> 10.6 us; 4096 x 4096: M = 1 7.3 -> 5.4 us,
 // M = 5 14.8 -> 6.8.  Sixteen copies of the table, so that few lanes meet in a bank, cost more to fill than they saved.
 constexpr int kMaxRows = 10;
 
-// The five weights of a code (81 d0 + 27 d1 + 9 d2 + 3 d3 + d4; digit 1: +1, 2: -1): bits 2 i (non-zero) and 2 i + 1 (sign).
+// The five weights of a code (81 d0 + 27 d1 + 9 d2 + 3 d3 + d4; digit 1: +1, 2: -1) in four bits as in FourBitWord: the first four in the low
+// halves of the bytes, the fifth in the high half of the first byte.
 __device__ __forceinline__ unsigned weights_of_code(int code)
 {
     unsigned bits = 0;
@@ -1321,7 +1341,7 @@ __device__ __forceinline__ unsigned weights_of_code(int code)
     for (int i = 4; i >= 0; --i) {
         const unsigned digit = code % 3;
         code /= 3;
-        bits |= (digit == 0 ? 0u : digit == 1 ? 1u : 3u) << (2 * i);
+        bits |= (digit == 0 ? 0u : digit == 1 ? 4u : 12u) << (i < 4 ? 8 * i : 4);
     }
     return bits;
 }
@@ -1334,7 +1354,11 @@ k_rows(const MatrixArgs a)
 {
     constexpr int kSteps = PACKED ? 10 : 8;                  // matrix instructions per block of W and tile
     constexpr int kUnits = 4 * kSteps, kRowUnits = kUnits + 1;   // 16-byte units per staged row of a group (+ 1: other banks)
-    constexpr int kBlockRows = 8 * kSteps, kPartner = PACKED ? 40 : 16;
+    constexpr int kBlockRows = 8 * kSteps;
+    // Weights through FourBitWord, whose pairs are rows j and j + 4 (M = 1, 4096 x 11008 5.53 -> 5.3 us, M = 5 6.76 -> 6.6).  Where the
+    // loads of X count, a pair is j and j + 16, so that they bring 64 bytes at a time (M = 8, 4096 x 4096 5.42 us, else 5.51; M = 1 3.52, 3.56).
+    constexpr bool kFour = !PACKED && MM <= 5 && (MM > 2 || B > 1);
+    constexpr int kPartner = PACKED ? 40 : kFour ? 4 : 16;
     constexpr int T = (3 * MM + 15) / 16, kItems = (MM * kUnits + 63) / 64;
     constexpr int kStage = KW * 3 * MM * kRowUnits, kSums = KW * B * T * 64;
     __shared__ uint4v lds[kStage > kSums ? kStage : kSums];
@@ -1360,7 +1384,7 @@ k_rows(const MatrixArgs a)
         for (int i = 0; i < kItems; ++i) {
             const int it = lane + 64 * i, m = it / kUnits, unit = it % kUnits, step = unit % kSteps;
             const unsigned k = (unsigned)(kBlockRows * (4 * group + unit / kSteps)) +
-                               (PACKED ? 4 * step : 32 * (step >> 2) + 4 * (step & 3));
+                               (PACKED ? 4 * step : kFour ? 8 * step : 32 * (step >> 2) + 4 * (step & 3));
             const unsigned off = m < M ? ((unsigned)m * (unsigned)a.K + k) * 4u : kNowhere;
             x0_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off));
             x1_next[i] = __builtin_bit_cast(float4v, load16(xbuf, off + 4u * kPartner));
@@ -1426,24 +1450,35 @@ k_rows(const MatrixArgs a)
                     acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t][step], bw, acc[b][t], 0, 0, 0);
             };
             if constexpr (PACKED) {
-                unsigned pair[8];
+                unsigned four[8], fifth[8];   // of codes j (low half of a byte) and j + 8
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    pair[j] = table[w[b][j / 4] >> (8 * (j % 4)) & 255u] | table[w[b][2 + j / 4] >> (8 * (j % 4)) & 255u] << 16;
+                for (int j = 0; j < 8; ++j) {
+                    const unsigned lo = table[w[b][j / 4] >> (8 * (j % 4)) & 255u], hi = table[w[b][2 + j / 4] >> (8 * (j % 4)) & 255u];
+                    four[j] = (hi << 4 & 0xF0F0F0F0u) | (lo & 0x0F0F0F0Fu);
+                    fifth[j] = (lo >> 4 & 0x0Fu) | (hi & ~0x0Fu);
+                }
 #pragma unroll
                 for (int step = 0; step < kSteps; ++step) {
                     uint4v d;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        d[e] = pair[(4 * step + e) / 5] << (14 - 2 * ((4 * step + e) % 5)) & 0xC000C000u;
+                    for (int e = 0; e < 4; ++e) {
+                        const int j = (4 * step + e) / 5, i = (4 * step + e) % 5;
+                        d[e] = i < 4 ? two_weights(four[j], i) : two_weights(fifth[j], 0);
+                    }
                     multiply(step, __builtin_bit_cast(bf16x8, d));
                 }
             } else {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const SignedWord half(w[b][h], w[b][2 + h]);
+                    if constexpr (kFour) {
+                        const FourBitWord half(w[b][h], w[b][2 + h]);
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) multiply(4 * h + s, half.eight(4 * s));
+                        for (int s = 0; s < 4; ++s) multiply(4 * h + s, half.eight(s));
+                    } else {
+                        const SignedWord half(w[b][h], w[b][2 + h]);
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) multiply(4 * h + s, half.eight(4 * s));
+                    }
                 }
             }
         }
