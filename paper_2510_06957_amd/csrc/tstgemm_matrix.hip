@@ -146,34 +146,43 @@ struct Epilogue {
     }
 };
 
-// X W for 16 x 16 outputs over blocks of rows of W whatever X holds: what k_matrix and k_rows do again for outputs whose
+// X W for 16 x 16 NB outputs over blocks of rows of W whatever X holds: what k_matrix, k_waves and k_rows do again for outputs whose
 // scaled sums are not finite.  X is split by size: entries below 2^64 go in times 2^24 as everywhere, larger ones times
 // 2^-24 (2^22 of the largest floats do not overflow so), and infinities and NaNs as ones in two planes of their own (a NaN in
 // both), multiplied by the +1 rows and by the -1 rows, which counts the members that push a sum up and those that push it
 // down.  Bound by cutting X, which every 16 columns do anew, and by the latency of its loads.  Single calls with one
 // infinity (with one in every row; with all of X near 1e35), 50 % non-zeros, against the list and row-set kernels, whose time
-// does not depend on X: 256 x 4096 x 4096 90 us (184; 363) against 108, 1024 x 2048 x 8192 248 (623; 937) against 359,
-// M = 1, 4096 x 4096 16 (14; 24) against 11; finite X 38, 82, 14.  One lane per output that walked the members one by one
-// took 1128 (1630), 442 (9361) and 263, and 508 from the base-3 codes (M = 1, 4096 x 4096, one entry of 1e35; 14 now, from the
+// does not depend on X: 256 x 4096 x 4096 (k_waves, NB = 2) 82 us (124; 207) against 108, 1024 x 2048 x 8192 222 (565; 881) against 359,
+// M = 1, 4096 x 4096 12 (12; 20) against 11; finite X 28, 82, 7.  One lane per output that walked the members one by one
+// took 1128 (1630), 442 (9361) and 263, and 508 from the base-3 codes (M = 1, 4096 x 4096, one entry of 1e35; 12 now, from the
 // row sets, which the codes are built from and uploaded with).  Where K is not a multiple of 64 the first entries of a row also meet the zero
 // weights beyond the end of the row before, so an infinity there sends that row here too.
 // X: the first of `rows` <= 16 rows; the blocks from kb0 on up to kb1, groups of four of them, every `stride`-th from
-// `first` on.  Lane l holds column n = n0 + l % 16 of Y, element e of the result is row 4 (l / 16) + e.
-__device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, const uint4v *masks, int n_pad, int n, int kb0,
-                                               int kb1, int first, int stride)
+// `first` on.  Lane l holds column n[i] = n0 + l % 16 of Y for the i-th 16 columns, element e of v[i] is row 4 (l / 16) + e.
+template <int NB>
+__device__ __forceinline__ void sums_of_any(float4v (&v)[NB], const float *X, int rows, int K, const uint4v *masks, int n_pad,
+                                            const int (&n)[NB], int kb0, int kb1, int first, int stride)
 {
     const int r = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
     const __amdgpu_buffer_rsrc_t xbuf = raw_buffer(X, (size_t)rows * K * 4);
-    float4v top{0.f, 0.f, 0.f, 0.f}, low = top, large = top, up = top, down = top;
+    float4v top[NB], low[NB], large[NB], up[NB], down[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) top[b] = low[b] = large[b] = up[b] = down[b] = float4v{0.f, 0.f, 0.f, 0.f};
     auto multiply = [](float4v &c, uint4v a, bf16x8 b) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
     };
     for (int group = first; kb0 + 4 * group < kb1; group += stride) {
         const int kb = kb0 + 4 * group + g;
-        const uint4v w = kb < kb1 ? masks[(size_t)kb * n_pad + n] : uint4v{0, 0, 0, 0};
+        uint4v w[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w[b] = kb < kb1 ? masks[(size_t)kb * n_pad + n[b]] : uint4v{0, 0, 0, 0};
         for (int h = 0; h < 2; ++h) {
-            const unsigned plus = h ? w[1] : w[0], minus = h ? w[3] : w[2];
-            const SignedWord both(plus, minus), of_plus(plus, 0), of_minus(minus, 0);
+            unsigned plus[NB], minus[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                plus[b] = h ? w[b][1] : w[b][0];
+                minus[b] = h ? w[b][3] : w[b][2];
+            }
             const unsigned off = r < rows ? ((unsigned)r * (unsigned)K + 64u * kb + 32u * h) * 4u : kNowhere;
             float4v x0[4], x1[4];
 #pragma unroll
@@ -183,7 +192,9 @@ __device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, 
             }
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const bf16x8 bw = both.eight(4 * s);
+                bf16x8 bw[NB];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) bw[b] = SignedWord(plus[b], minus[b]).eight(4 * s);
                 uint4v hi, mid, lo;
                 auto cut = [&](int e, float a0, float a1) {
                     hi[e] = top_halves(a0, a1);
@@ -199,9 +210,12 @@ __device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, 
                     rest |= !small0 || !small1;
                     cut(e, small0 ? x0[s][e] * kScaleUp : 0.f, small1 ? x1[s][e] * kScaleUp : 0.f);
                 }
-                multiply(top, hi, bw);
-                multiply(low, mid, bw);
-                multiply(low, lo, bw);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    multiply(top[b], hi, bw[b]);
+                    multiply(low[b], mid, bw[b]);
+                    multiply(low[b], lo, bw[b]);
+                }
                 if (!__any(rest)) continue;
                 uint4v plus_inf, minus_inf;
 #pragma unroll
@@ -217,25 +231,28 @@ __device__ __forceinline__ float4v sums_of_any(const float *X, int rows, int K, 
                     }
                     cut(e, big[0], big[1]);
                 }
-                multiply(large, hi, bw);
-                multiply(large, mid, bw);
-                multiply(large, lo, bw);
-                const bf16x8 pw = of_plus.eight(4 * s), mw = of_minus.eight(4 * s);
-                multiply(up, plus_inf, pw);
-                multiply(up, minus_inf, mw);
-                multiply(down, plus_inf, mw);
-                multiply(down, minus_inf, pw);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    multiply(large[b], hi, bw[b]);
+                    multiply(large[b], mid, bw[b]);
+                    multiply(large[b], lo, bw[b]);
+                    const bf16x8 pw = SignedWord(plus[b], 0).eight(4 * s), mw = SignedWord(minus[b], 0).eight(4 * s);
+                    multiply(up[b], plus_inf, pw);
+                    multiply(up[b], minus_inf, mw);
+                    multiply(down[b], plus_inf, mw);
+                    multiply(down[b], minus_inf, pw);
+                }
             }
         }
     }
-    float4v v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        v[e] = (top[e] + low[e]) * kScaleDown + large[e] * (0.5f * kScaleUp);
-        if (up[e] > 0.f || down[e] > 0.f)
-            v[e] = (up[e] > 0.f ? __builtin_inff() : 0.f) - (down[e] > 0.f ? __builtin_inff() : 0.f);
-    }
-    return v;
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[b][e] = (top[b][e] + low[b][e]) * kScaleDown + large[b][e] * (0.5f * kScaleUp);
+            if (up[b][e] > 0.f || down[b][e] > 0.f)
+                v[b][e] = (up[b][e] > 0.f ? __builtin_inff() : 0.f) - (down[b][e] > 0.f ? __builtin_inff() : 0.f);
+        }
 }
 
 struct MatrixArgs {
@@ -404,7 +421,8 @@ template <int N> using Int = std::integral_constant<int, N>;
 // Bound: long calls by the power limit (M = 4096, K = N = 8192: 1.04 ms, i.e. 1.59 PFLOP/s of bf16 products, the clock down
 // to about 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here; without any cutting and spreading, which
 // gives wrong sums, it would take 0.99 ms), short ones by the start of the first loads, the
-// sums at the end and the second launch where K is sliced (M = 256, K = N = 4096: 28 us against 89).
+// sums at the end and the second launch where K is sliced (777 x 3001 x 2999 in three slices: 39.7 us, 8 of them the second launch).
+// Calls with few tiles and X on 16-byte borders are k_waves's.
 // DIGITS: X comes from the workspace, straight into the LDS, W too; three steps of 64 rows of W in a ring, copied two steps
 // ahead, one barrier a step, placed before the last plane's products so that the next step's first reads are under way behind
 // them.  A step has 4 products of 32 cycles per plane and wavefront.  Everything else is dealt between them one by one: all
@@ -886,12 +904,13 @@ k_matrix(const MatrixArgs a)
             bad[e] = m < rows && n < width && !finite(out[(size_t)m * width + n]);
         }
         if (!__any(bad[0] || bad[1] || bad[2] || bad[3])) continue;
-        const float4v v = sums_of_any(a.X + (size_t)(m0 + row) * a.K, min(rows - row, 16), a.K, a.masks, a.n_pad,
-                                      min(n, a.n_pad - 1), first_block, end_block, 0, 1);
+        float4v v[1];
+        sums_of_any(v, a.X + (size_t)(m0 + row) * a.K, min(rows - row, 16), a.K, a.masks, a.n_pad, {min(n, a.n_pad - 1)}, first_block,
+                    end_block, 0, 1);
         const float bias_n = finish.bias_of(n), slope_n = finish.slope_of(n);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (bad[e]) out[(size_t)(row + 4 * g16 + e) * width + n] = sliced ? v[e] : finish(v[e], bias_n, slope_n);
+            if (bad[e]) out[(size_t)(row + 4 * g16 + e) * width + n] = sliced ? v[0][e] : finish(v[0][e], bias_n, slope_n);
     }
 }
 
@@ -905,8 +924,8 @@ k_matrix(const MatrixArgs a)
 // Bound: a SIMD issues a vector instruction in 4.1 cycles beside a matrix instruction, which takes 8 of its own (measured), so a
 // block is 48 x 8 + 366 x 4.1 cycles of issue for CF = 4 against 48 x 32 of products; with all compute units at it the power
 // limit takes another fifth (2.2 us per block and pair of wavefronts, 1.65 on one compute unit alone, 1.8 for the products by
-// themselves).  M = 256, K = N = 4096: 21.8 us, 29.4 as 64 x 256 tiles over four slices of K with a second launch for their sums;
-// 64 x 16384 x 4096 25.1 (31.7), 32 x 4096 x 4096 9.3 (10.6), 768 x 1024 x 1024 7.9 (10.5), 512 x 512 x 512 5.0 (5.9).  Eight
+// themselves).  M = 256, K = N = 4096: 21.5 us, 26.8 as 64 x 256 tiles over four slices of K with a second launch for their sums;
+// 64 x 16384 x 4096 24.7 (31.4), 32 x 4096 x 4096 9.1 (10.6), 768 x 1024 x 1024 7.9 (10.5), 512 x 512 x 512 5.0 (5.9).  Eight
 // wavefronts a workgroup: 1 to 5 % slower; v_dot2_f32_bf16 for what a plane leaves: 64 instructions a block less, 15 % slower.
 // The copies take 16 bytes a lane and want every row of X on such a border; other calls go to k_matrix.
 template <int CF>
@@ -1096,25 +1115,32 @@ k_waves(const MatrixArgs a)
     }
     if (!__any(spoilt != 0.f)) return;
 
-    // again, from X, as in k_matrix
+    // again, from X, as in k_matrix, but 32 columns from one cut of X: K is whole here, and 16 at a time took longer than k_matrix in slices
+    // (one infinity, 256 x 4096 x 4096: 116 us, so 82, there 88).  In k_matrix the registers would cost the tiles of 32 rows a wavefront a SIMD.
     __threadfence();
     const int r16 = lane & 15, g16 = lane >> 4;
-    for (int piece = 0; piece < CF; ++piece) {
-        const int row = row0 + 16 * (piece / 2), col = col0 + 16 * (piece % 2) + r16;
-        if (row >= rows) break;
-        bool bad[4];
+    for (int row = row0; row < min(rows, row0 + 8 * CF); row += 16) {
+        bool bad[2][4], any_bad = false;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int m = row + 4 * g16 + e;
-            bad[e] = m < rows && col < width && !finite(out[(size_t)m * width + col]);
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int m = row + 4 * g16 + e, col = col0 + 16 * c + r16;
+                bad[c][e] = m < rows && col < width && !finite(out[(size_t)m * width + col]);
+                any_bad |= bad[c][e];
+            }
+        if (!__any(any_bad)) continue;
+        float4v v[2];
+        sums_of_any(v, a.X + (size_t)(m0 + row) * a.K, min(rows - row, 16), a.K, a.masks, a.n_pad,
+                    {min(col0 + r16, a.n_pad - 1), min(col0 + 16 + r16, a.n_pad - 1)}, slice0, slice1, 0, 1);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int col = col0 + 16 * c + r16;
+            const float bias_c = finish.bias_of(col), slope_c = finish.slope_of(col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (bad[c][e]) out[(size_t)(row + 4 * g16 + e) * width + col] = sliced ? v[c][e] : finish(v[c][e], bias_c, slope_c);
         }
-        if (!__any(bad[0] || bad[1] || bad[2] || bad[3])) continue;
-        const float4v v = sums_of_any(a.X + (size_t)(m0 + row) * a.K, min(rows - row, 16), a.K, a.masks, a.n_pad,
-                                      min(col, a.n_pad - 1), slice0, slice1, 0, 1);
-        const float bias_c = finish.bias_of(col), slope_c = finish.slope_of(col);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (bad[e]) out[(size_t)(row + 4 * g16 + e) * width + col] = sliced ? v[e] : finish(v[e], bias_c, slope_c);
     }
 }
 
@@ -1319,7 +1345,7 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_alig
 // Bound by the latency of that chain (2.5 us with one group a wavefront, of which launch and first loads are most) and
 // then by spreading and cutting on the vector ALU and by the LDS: all three planes are staged before any is read, so that a
 // fragment is one read of all lanes; plane by plane, each lane waiting for its own, it was three.  M = 1, 4096 x 11008
-// 5.3 -> 4.9 us, M = 8 7.9 -> 7.5, M = 8, 4096 x 4096 5.8 -> 5.3, M = 2, 11008 x 4096 6.4 -> 5.2 (lists, at 50 % non-zeros: 10.0, 23.7, 10.7, 10.7).
+// 5.3 -> 4.9 us (a call from Python 5.23, 5.01 since the weights are spread by conversions), M = 8 7.9 -> 7.5, M = 8, 4096 x 4096 5.8 -> 5.3, M = 2, 11008 x 4096 6.4 -> 5.2 (lists, at 50 % non-zeros: 10.0, 23.7, 10.7, 10.7).
 // Without the next group's loads 20 % more.  Over 220 shapes (K, N = 700 .. 16384) all planes at once take 2 to 23 % less time
 // from the row sets; from the codes 17 % less to 2 % more at M <= 5 (M <= 3: the rule below takes k_rows more often, up to
 // 33 %), 8 % less to 3 % more at M = 6, 7, and the same at M = 8 (2 % less to 3 % more: 2500 x 5000 6.1 -> 6.3 us).
@@ -1518,9 +1544,10 @@ k_rows(const MatrixArgs a)
     // again from X and the row sets, groups of them dealt to the wavefronts as before: [wave][b][row][column]
 #pragma unroll 1
     for (int b = 0; b < B; ++b) {
-        const float4v v = sums_of_any(a.X, M, a.K, a.row_sets, a.n_pad, min(n0 + 16 * b + r, a.n_pad - 1), 0, a.n_row_blocks, wave, KW);
+        float4v v[1];
+        sums_of_any(v, a.X, M, a.K, a.row_sets, a.n_pad, {min(n0 + 16 * b + r, a.n_pad - 1)}, 0, a.n_row_blocks, wave, KW);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sums[((wave * B + b) * 16 + 4 * g + e) * 16 + r] = v[e];
+        for (int e = 0; e < 4; ++e) sums[((wave * B + b) * 16 + 4 * g + e) * 16 + r] = v[0][e];
     }
     __syncthreads();
     for (int o = threadIdx.x; o < 16 * B * M; o += 64 * KW) {
@@ -1750,7 +1777,7 @@ hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, con
 // Whether k_rows takes the base-3 codes, or k_packed, which multiplies on the vector ALU: a workgroup of that takes
 // 2.6 us + (0.65 + 0.43 M) us per 1000 rows of W, and 3 us more where it deals K to several workgroups (measured
 // M = 1 .. 8, the shapes of rows_plan()).  k_packed stays ahead on short K over many columns (M <= 5, 512 x 16384, M = 5: 4.6 against
-// 4.8 us); M = 1, 4096 x 11008 7.1 against 6.8 here.  The choice is 0.3 % behind the better of the two on average.
+// 4.8 us); M = 1, 4096 x 11008 7.1 against 6.3 here.  The choice is 0.3 % behind the better of the two on average.
 MatrixPlan packed_plan(const tcsc_layout_t &l, int M)
 {
     if (l.K > kMaxExtent || ((long long)l.n_chunks5 + 64) * l.n_pad * 16 >= (1LL << 32)) return MatrixPlan{};
