@@ -1219,8 +1219,7 @@ hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 // 64 x 256: M = 4096, K = N = 8192 1073 -> 1038 us, 2048 x 4096 x 4096 138 -> 132, 1024 x 2048 x 8192 74 -> 70).  Fitted to 13 tiles x 6 slice counts on 77
 // shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five of k_matrix is 2 % slower than the best of
 // all on average, 16 % at worst.  k_waves is fitted to 1014 timings (M = 11 .. 768, the same K and N), with figures that are high by
-// some 5 % on long calls, where those of k_matrix are: of 120 shapes the choice is 0.7 % slower than the better of the two on average, and
-// three are slower than k_matrix alone by more than 2 % (16 x 2048 x 2048, 11 x 2048 x 2048, 192 x 4096 x 11008: 7.5 %, 516 tiles on 512 places).
+// some 5 % on long calls, where those of k_matrix are: where the two meet, kLateRounds has what was measured.
 struct TileShape {
     int rows, cols, groups, waves, per_cu;
     double fixed, step, work, peak;
@@ -1241,6 +1240,11 @@ constexpr int kFirstOfWaves = 6;
 // wavefronts without work.
 bool waves_can(const tcsc_layout_t &l, bool x_aligned) { return x_aligned && l.K % 4 == 0 && l.n_kblocks >= 4; }
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
+// k_waves with K whole and more tiles than two a compute unit: Y is 8 MB and more, and nothing covers the last round's part of it.  Without
+// these two figures (1.04 and 0.3 us per MB of Y) calls stayed that k_matrix takes in less time, up to 6.7 % (192 x 4096 x 11008, 516 tiles on
+// 512 places, 55.6 against 52.2 us, 480 x 5440 x 4992 69.5 against 64.8, 352 x 832 x 12376 29.7 against 28.0); with them no such call of 120 shapes
+// (57 of them with more tiles than places) is more than 1.5 % behind k_matrix, and the choice is 0.3 % behind the better of the two on average.
+constexpr double kLateRounds = 1.04, kLateMb = 0.3;
 
 struct TilePlan {
     int tile, k_slices;
@@ -1313,6 +1317,7 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_alig
         const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
         double us = s.fixed * rounds + steps * step_us;
         if (us < floor_us) us = floor_us;
+        if (i >= kFirstOfWaves && k == 1 && rounds > 1.0) us = kLateRounds * us + kLateMb * mb;
         us += kCall + (k > 1 ? kSlice + kSliceMb * mb : 0.0);
         if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
         return true;

@@ -31,6 +31,16 @@ def test_routes(M, K, N):
         assert route(t, M) == ("k_matrix", 32, 64 if (M, K, N) in NARROW else 128, 4)
 
 
+
+@pytest.mark.parametrize("M,K,N,waves", [(192, 4096, 10880, True), (192, 4096, 11008, False), (352, 4096, 5888, True), (544, 4096, 4096, False),
+                                         (352, 832, 12376, False), (480, 1472, 4480, True), (672, 1536, 6528, True)])
+def test_more_tiles_than_places(M, K, N, waves):
+    """Tiles that start in a second round of the chip cost more than they compute: a few of them leave the call to shared cuts of X."""
+    none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
+    r = tg.tstgemm_query_route(tg.tcsc_from_arrays(starts, starts, none, none, K, N), M)
+    assert (r.kernel == "k_matrix" and r.tile_rows == 32 and r.k_groups == 4) == waves
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N", NARROW + WIDE)
 def test_tile_edges(M, K, N):
