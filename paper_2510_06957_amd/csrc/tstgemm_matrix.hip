@@ -933,8 +933,8 @@ __global__ void __launch_bounds__(256, 2)
 k_waves(const MatrixArgs a)
 {
     constexpr int KW = 4, TN = 32 * CF, kX = 8192, kSlot = kX + 16 * TN;   // a block in the ring: X, then row sets
-    constexpr int kCopiesW = TN / 64, kCopies = 8 + kCopiesW, kQuads = 4 * CF;
-    static_assert(CF == 2 || CF == 4, "columns come 64 at a time, the sums fit the ring");
+    constexpr int kCopiesW = TN / 64, kCopies = 8 + kCopiesW;
+    static_assert(CF == 2 || CF == 4, "columns come 64 at a time");
     static_assert((32ull + 4) * kMaxExtent * 4 < kNowhere, "offsets inside a tile, two blocks beyond it");
     __shared__ uint4v lds[KW * 2 * kSlot / 16];
     typedef __attribute__((address_space(3))) const char *Lds;
@@ -1076,34 +1076,113 @@ k_waves(const MatrixArgs a)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing is on its way to the LDS any more
     }
 
-    // Sums of the wavefronts, [wave][quad][lane]: quad 4 j + q is elements 4 q .. of column fragment j, rows 8 q + 4 g .. + 3 of
-    // column 32 j + l32.  A wavefront finishes CF quads: 16 rows or all 32 of 32 columns.
-    float4v *const sums = reinterpret_cast<float4v *>(lds);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < CF; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float4v v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[0][j][4 * q + e] + acc[1][j][4 * q + e];
-            sums[(wave * kQuads + 4 * j + q) * 64 + lane] = v;
-        }
-    const int quad0 = wave * CF, row0 = 8 * (quad0 % 4), col0 = n0 + 32 * (quad0 / 4), n = col0 + l32;
+    // Sums of the wavefronts.  Where K is whole, those of hi stay apart from those of mid + lo until the end: they are whole numbers of a unit
+    // and mostly exact, so a result is rounded little more than once, as in a kernel where one wavefront has all of K (300 x 832 x 5824 without
+    // a bias: 2.8e-8 of the norm; joined in each wavefront first 4.7e-8).  It is 1.5 times the traffic here, 0.1 to 0.4 us a call
+    // (87 x 408 x 2435 4.9 -> 5.0 us, 196 x 868 x 3375 8.25 -> 8.5, 256 x 4096 x 4096 23.0 -> 23.4).  Slices are rounded once more each by
+    // k_matrix_sum: there a wavefront joins its own first (64 x 16384 x 4096 6.2e-8, apart 5.5e-8).
+    // Quad 4 j + q is elements 4 q .. of column fragment j, rows 8 q + 4 g .. + 3 of column 32 j + l32; a wavefront finishes CF quads from
+    // quad0 on, 16 rows or all 32 of 32 columns, and gives the others away through its own ring.
+    const bool sliced = a.k_slices > 1;
+    const int quad0 = CF * (CF == 2 ? wave : 2 * (wave & 1) + (wave >> 1));
+    const int row0 = 8 * (quad0 % 4), col0 = n0 + 32 * (quad0 / 4), n = col0 + l32;
     const Epilogue finish(a.b, a.alpha, a.alpha_stride, a.N);
     const float bias = finish.bias_of(n), slope = finish.slope_of(n);
-    const bool sliced = a.k_slices > 1;
+    float4v *const sums = reinterpret_cast<float4v *>(lds);
+    constexpr int kRing = 2 * kSlot / 16;
+    float4v mine[2][CF];   // [hi | mid + lo], or [all | zero]
+#pragma unroll
+    for (int i = 0; i < CF; ++i) mine[1][i] = float4v{0.f, 0.f, 0.f, 0.f};
+    if (sliced) {
+#pragma unroll
+        for (int j = 0; j < CF; ++j) acc[0][j] += acc[1][j];
+    }
+    auto quad = [&](int d, int i) {
+        return float4v{acc[d][i / 4][4 * (i % 4)], acc[d][i / 4][4 * (i % 4) + 1], acc[d][i / 4][4 * (i % 4) + 2], acc[d][i / 4][4 * (i % 4) + 3]};
+    };
+    if constexpr (CF == 2) {
+        static_assert(2 * 8 * 64 <= kRing, "a wavefront's sums in its ring");
+        auto place = [&](int w, int d, int i) -> float4v & { return sums[w * kRing + (8 * d + i) * 64 + lane]; };
+        auto give = [&](auto own) {
+            constexpr int OWN = decltype(own)::value;
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                if (d == 1 && sliced) break;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (i / 2 == OWN) mine[d][i % 2] = quad(d, i);
+                    else place(wave, d, i) = quad(d, i);
+                }
+            }
+        };
+        if (wave == 0) give(Int<0>{});
+        else if (wave == 1) give(Int<1>{});
+        else if (wave == 2) give(Int<2>{});
+        else give(Int<3>{});
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            if (d == 1 && sliced) break;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                mine[d][i] = (mine[d][i] + place(wave ^ 1, d, quad0 + i)) + (place(wave ^ 2, d, quad0 + i) + place(wave ^ 3, d, quad0 + i));
+        }
+    } else {
+        // three quarters of the sums do not fit the ring: half of the columns to w ^ 1, then half of what is kept to w ^ 2, through the ring
+        // that this wavefront alone has read
+        static_assert(2 * 8 * 64 <= kRing, "half of a wavefront's sums in its ring");
+        float4v half[2][8];
+        auto place = [&](int w, int d, int i) -> float4v & { return sums[w * kRing + (8 * d + i) * 64 + lane]; };
+        auto give_half = [&](auto keep) {
+            constexpr int KEEP = decltype(keep)::value;
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                if (d == 1 && sliced) break;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    place(wave, d, i) = quad(d, 8 * (1 - KEEP) + i);
+                    half[d][i] = quad(d, 8 * KEEP + i);
+                }
+            }
+        };
+        auto give_quarter = [&](auto keep) {
+            constexpr int KEEP = decltype(keep)::value;
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                if (d == 1 && sliced) break;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    place(wave ^ 1, d, i) = half[d][4 * (1 - KEEP) + i];
+                    mine[d][i] = half[d][4 * KEEP + i];
+                }
+            }
+        };
+        if (wave & 1) give_half(Int<1>{});
+        else give_half(Int<0>{});
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            if (d == 1 && sliced) break;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) half[d][i] += place(wave ^ 1, d, i);
+        }
+        if (wave & 2) give_quarter(Int<1>{});
+        else give_quarter(Int<0>{});
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            if (d == 1 && sliced) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mine[d][i] += place(wave ^ 3, d, i);
+        }
+    }
     float *out = sliced ? a.partials + ((size_t)slice * a.M + m0) * a.n_pad : a.Y + (size_t)m0 * a.N;
     const int width = sliced ? a.n_pad : a.N;
     const __amdgpu_buffer_rsrc_t obuf = raw_buffer(out, (size_t)rows * width * 4);
     float spoilt = 0.f;   // NaN as soon as one sum is not finite
-    __syncthreads();
 #pragma unroll
     for (int q = 0; q < CF; ++q) {
-        float4v part[KW];
-#pragma unroll
-        for (int w = 0; w < KW; ++w) part[w] = sums[(w * kQuads + quad0 + q) * 64 + lane];
-        const float4v v = (part[0] + part[2]) + (part[1] + part[3]);
+        const float4v v = mine[0][q] + mine[1][q];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             spoilt = fmaf(v[e], 0.f, spoilt);

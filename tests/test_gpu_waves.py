@@ -76,3 +76,17 @@ def test_infinities_beyond_the_rows(M, K, N):
     ok = np.isfinite(Yd)
     assert ok.any() and not ok.all() and _same(Y, Yd)
     assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-6 * A[ok])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(256, 2048, 2048), (65, 2052, 3001), (300, 832, 5824), (672, 1536, 6528), (367, 512, 2368), (33, 260, 100)])
+def test_sums_are_rounded_once(M, K, N):
+    """X between 1/2 and 1 in size: the top planes are multiples of 2^-8 and their sums below 2^16, what is left multiples of 2^-24 with sums below 1,
+    so both are exact whatever the order, and the result is their sum rounded once, however many wavefronts share K."""
+    rng = np.random.default_rng(340 + M)
+    X = (rng.uniform(0.5, 1.0, (M, K)) * rng.choice([-1.0, 1.0], (M, K))).astype(np.float32)
+    W = si.draw_ternary(rng, K, N, 0.5)
+    Y, t = gpu_tstgemm(W, X, None)
+    r = tg.tstgemm_query_route(t, M)
+    assert (r.tile_rows, r.k_groups, r.k_slices) == (32, 4, 1)
+    assert np.array_equal(Y, (X.astype(np.float64) @ W).astype(np.float32))
