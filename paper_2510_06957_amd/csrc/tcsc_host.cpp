@@ -333,7 +333,7 @@ int tstgemm_workspace_bytes(int M, int K, int N, size_t *min_bytes, size_t *best
         const int n_pad = (N + tst::kColPad - 1) / tst::kColPad * tst::kColPad;
         tst::large_workspace_bytes(M, K, n_pad, &lo, &hi);
     }
-    if (M > 8) {
+    if (M > 8 && best_bytes) {   // (a search of some hundred ns, which a call that asks for the least size alone is not to wait for)
         const long long n_pad = ((long long)N + tst::kColPad - 1) / tst::kColPad * tst::kColPad;
         const size_t matrix = n_pad <= INT_MAX ? tst::matrix_workspace_bytes(M, K, N, (int)n_pad) : 0;
         hi = hi > matrix ? hi : matrix;

@@ -1,0 +1,81 @@
+"""Host time of what a call decides before its launch: short calls wait for it.  Compared with other calls of the same library in the same
+process, the least of many turns."""
+import subprocess
+
+import pytest
+
+import paper_2510_06957_amd as tg
+from test_host_api import ROOT
+
+PROGRAM = r'''
+#include <stdio.h>
+#include <stdlib.h>
+#include <time.h>
+#include "tstgemm.h"
+static double now(void)
+{
+    struct timespec t;
+    clock_gettime(CLOCK_MONOTONIC, &t);
+    return 1e9 * t.tv_sec + t.tv_nsec;
+}
+/* ns of one call, the least of 40 turns: 0 the route, 1 the least scratch size, 2 both sizes */
+static double ns(int what, const tcsc_t *t, int M, int K, int N)
+{
+    double best = 1e30;
+    for (int turn = 0; turn < 40; ++turn) {
+        const double t0 = now();
+        for (int i = 0; i < 300; ++i) {
+            tstgemm_route_t r;
+            size_t least, most;
+            int rc = what == 0 ? tstgemm_query_route(t, M, NULL, &r) : tstgemm_workspace_bytes(M, K, N, &least, what == 2 ? &most : NULL);
+            if (rc) exit(3);
+        }
+        const double d = (now() - t0) / 300;
+        if (d < best) best = d;
+    }
+    return best;
+}
+int main(int argc, char **argv)
+{
+    const int M = atoi(argv[1]), K = atoi(argv[2]), N = atoi(argv[3]);
+    int32_t *starts = calloc(N + 1, 4), *none = calloc(N + 1, 4), *rows = malloc((size_t)K * N / 8 * 4 + 4096);
+    int n = 0;
+    tcsc_t *t = NULL;
+    (void)argc;
+    for (int c = 0; c < N; ++c) {   /* every eighth row */
+        starts[c] = n;
+        for (int k = c % 8; k < K; k += 8) if ((size_t)n < (size_t)K * N / 8 + 1024) rows[n++] = k;
+    }
+    starts[N] = n;
+    if (tcsc_from_arrays(starts, none, rows, rows, K, N, &t)) return 2;
+    printf("%f %f %f %f\n", ns(0, t, M, K, N), ns(0, t, 5, K, N), ns(1, t, M, K, N), ns(2, t, M, K, N));
+    return 0;
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def timed(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("host_time")
+    src, exe, lib = folder / "times.c", folder / "times", tg.library_path()
+    src.write_text(PROGRAM)
+    cmd = ["gcc", "-O2", "-D_GNU_SOURCE", f"-I{ROOT / 'include'}", str(src), "-o", str(exe), str(lib), f"-Wl,-rpath,{lib.parent}",
+           "-Wl,-rpath,/opt/rocm/lib", "-L/opt/rocm/lib"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(M, K, N):
+        r = subprocess.run([str(exe), str(M), str(K), str(N)], capture_output=True, text=True)
+        assert r.returncode == 0, (r.returncode, r.stderr)
+        return [float(x) for x in r.stdout.split()]
+    return run
+
+
+SHAPES = [(14, 2816, 2944), (32, 4096, 4096), (64, 16384, 1024), (300, 3000, 2000)]
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+def test_the_least_scratch_size_needs_no_search(timed, M, K, N):
+    """tstgemm_noalloc() asks for the least size in every call."""
+    _, _, least, both = timed(M, K, N)
+    assert 3 * least < both, (least, both)
