@@ -1377,45 +1377,74 @@ TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TileP
     return TilePlan{p.tile, p.k_slices, kSparsePart * p.us, true};
 }
 
+// The search.  A short call waits for it, and an estimate takes some 20 ns: K whole for every tile first; then slices of the tile that they can
+// gain most for, and so on until no tile can gain (`least`: the estimate with what does not depend on the number of slices, and the
+// fewest steps).  us of a choice: 14 x 2816 x 2944 0.42 (all 64 estimates one after the other 2.0), 256 x 4096 x 4096 0.38 (1.5), 64 x 512 x 512 0.24 (0.42).
 TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_aligned)
 {
+    constexpr int kCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
     TilePlan best{-1, 1, 0.0};
     const int units = compute_units();
+    const double y_mb = 4e-6 * (double)M * l.n_pad;
+    double tiles[kCount], floor_us[kCount];
     const auto consider = [&](int i, int k) {
         const TileShape &s = kTiles[i];
-        const double tiles = (double)(((long long)M + s.rows - 1) / s.rows) * ((l.n_pad + s.cols - 1) / s.cols);
-        // a launch has less than 2^32 threads; a call with more tiles than that (K slices are for few tiles only) goes to
-        // k_large, which takes X in slabs.  (Slices beyond two full rounds only add partial sums)
-        if (tiles * (64 * s.waves) >= 4294967296.0 || (k > 1 && tiles * k > 2.0 * units * s.per_cu)) return false;
         const int per = (l.n_kblocks + k - 1) / k;
-        const double mb = 4e-6 * (double)k * M * l.n_pad;
-        if (k > 1 && (per * (k - 1) >= l.n_kblocks || M > 65535 || mb * 1e6 > (double)ws_bytes)) return true;
-        const double load = up(tiles * k / units), rounds = up(load / s.per_cu);
+        const double mb = k * y_mb;
+        if (k > 1 && (per * (k - 1) >= l.n_kblocks || (size_t)k * M * l.n_pad * 4 > ws_bytes)) return;
+        const double load = up(tiles[i] * k / units), rounds = s.per_cu == 1 ? load : up(load / s.per_cu);
         const double steps = 2.0 * ((per + s.groups - 1) / s.groups);
         const double step_us = s.step * rounds > s.work * load ? s.step * rounds : s.work * load;
-        const double floor_us = 6.0 * tiles * s.rows * s.cols * l.K / s.peak;
         double us = s.fixed * rounds + steps * step_us;
-        if (us < floor_us) us = floor_us;
+        if (us < floor_us[i]) us = floor_us[i];
         if (i >= kFirstOfWaves && k == 1 && rounds > 1.0) us = kLateRounds * us + kLateMb * mb;
         us += kCall + (k > 1 ? kSlice + kSliceMb * mb : 0.0);
         if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
-        return true;
     };
-    // K whole first: most short calls are then seen to gain nothing from slices (64 x 512 x 512: 8 estimates in place of 64, 0.4 us)
-    const auto choose = [&](int from, int to) {
-        for (int i = from; i < to; ++i) consider(i, 1);
-        for (int i = from; i < to; ++i)
-            for (int k = 2; k <= kMaxKSlices && k <= l.n_kblocks; ++k) {
-                const double least = kCall + kSlice + kSliceMb * 4e-6 * (double)k * M * l.n_pad + kTiles[i].fixed + 2.0 * kTiles[i].step;
-                if ((best.tile >= 0 && least >= best.us) || !consider(i, k)) break;
-            }
+    const auto whole = [&](int from, int to) {
+        for (int i = from; i < to; ++i) {
+            const TileShape &s = kTiles[i];
+            tiles[i] = (double)(((long long)M + s.rows - 1) / s.rows) * ((l.n_pad + s.cols - 1) / s.cols);
+            floor_us[i] = 6.0 * tiles[i] * s.rows * s.cols * l.K / s.peak;
+            // a launch has less than 2^32 threads; a call with more tiles than that goes to k_large, which takes X in slabs
+            if (tiles[i] * (64 * s.waves) < 4294967296.0) consider(i, 1);
+        }
     };
-    choose(0, kFirstOfWaves);
-    if (best.tile >= 0) {   // a call that k_matrix takes in digits stays there
-        const TilePlan p = with_digits(l, M, ws_bytes, best);
-        if (p.digits) return p;
+    const auto sliced = [&](int from, int to) {
+        if (from >= to || l.n_kblocks < 2 || M > 65535) return;
+        double least[kCount];
+        for (int i = from; i < to; ++i) {
+            const TileShape &s = kTiles[i];
+            const int most = kMaxKSlices < l.n_kblocks ? kMaxKSlices : l.n_kblocks;
+            const double steps = 2.0 * (((l.n_kblocks + most - 1) / most + s.groups - 1) / s.groups);
+            double us = steps * s.step, all = 2.0 * l.n_kblocks * tiles[i] * s.work / (s.groups * (double)units);
+            if (us < all) us = all;
+            us += s.fixed;
+            if (us < floor_us[i]) us = floor_us[i];
+            // (slices beyond two full rounds only add partial sums)
+            least[i] = 2.0 * tiles[i] > 2.0 * units * s.per_cu ? 1e300 : us + kCall + kSlice + kSliceMb * 2.0 * y_mb;
+        }
+        for (;;) {
+            int i = from;
+            for (int j = from + 1; j < to; ++j)
+                if (least[j] < least[i]) i = j;
+            if (least[i] >= (best.tile < 0 ? 1e300 : best.us)) return;
+            least[i] = 1e300;
+            for (int k = 2; k <= kMaxKSlices && k <= l.n_kblocks && tiles[i] * k <= 2.0 * units * kTiles[i].per_cu; ++k) consider(i, k);
+        }
+    };
+    const bool waves = waves_can(l, x_aligned);
+    whole(0, kFirstOfWaves);
+    const bool short_call = best.tile >= 0 && kLostPart * best.us < kLost;   // too short for digits, with slices too
+    if (!short_call) {
+        sliced(0, kFirstOfWaves);
+        if (best.tile >= 0) {   // a call that k_matrix takes in digits stays there
+            const TilePlan p = with_digits(l, M, ws_bytes, best);
+            if (p.digits) return p;
+        }
     }
-    if (waves_can(l, x_aligned)) choose(kFirstOfWaves, (int)(sizeof(kTiles) / sizeof(kTiles[0])));
+    if (waves) whole(kFirstOfWaves, kCount);
+    sliced(short_call ? 0 : kFirstOfWaves, waves ? kCount : short_call ? kFirstOfWaves : 0);
     return best;
 }
 
