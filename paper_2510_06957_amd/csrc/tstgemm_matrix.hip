@@ -1248,7 +1248,16 @@ k_matrix_sum(const MatrixArgs a)
         for (int s = 0; s + half < n_left; ++s) part[s] += part[s + half];
     float4v y;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) y[i] = finish(part[0][i], bias[i], slope[i]);
+    for (int i = 0; i < 4; ++i) {
+        float v = part[0][i];
+        if (!finite(v)) {   // on the way, or in all: again where slices of 2^128 do not overflow
+            double sum = 0.0;
+#pragma unroll 1
+            for (int s = 0; s < S; ++s) sum += (double)P[s * stride + i];
+            v = (float)sum;
+        }
+        y[i] = finish(v, bias[i], slope[i]);
+    }
     float *dst = a.Y + (size_t)m * a.N + n;
     if (n + 4 <= a.N) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4v, y), raw_buffer(a.Y + (size_t)m * a.N, (size_t)a.N * 4), n * 4, 0,

@@ -297,3 +297,24 @@ def test_calls_follow_torchs_current_stream():
     Y2 = tg.tstgemm(Xd, t, bd, stream=side)
     side.synchronize()
     assert torch.equal(Y2, Y)
+
+
+@pytest.mark.parametrize("M,K,N", [(32, 4096, 4096), (40, 1796, 100), (100, 4099, 500), (777, 3001, 2999)])
+def test_slices_whose_sums_are_near_the_largest_float(M, K, N):
+    """One entry of 3e38 of either sign, or none, per slice of K and row: where the sum of all of them is a float, it is the result, in whatever
+    order the slices are added."""
+    rng = np.random.default_rng(795 + M)
+    W = si.draw_ternary(rng, K, N, 0.25)
+    t = tg.tcsc_build(W)
+    slices = tg.tstgemm_query_route(t, M).k_slices
+    assert slices > 1
+    rows = np.arange(slices) * -(-(-(-K // 64)) // slices) * 64
+    W[rows] = 1
+    signs = rng.integers(-1, 2, (M, slices))
+    while (wrong := np.abs(signs.sum(axis=1)) > 1).any():
+        signs[wrong] = rng.integers(-1, 2, (int(wrong.sum()), slices))
+    X = np.zeros((M, K), np.float32)
+    X[:, rows] = signs * np.float32(3e38)
+    Y, t = gpu_tstgemm(W, X, None)
+    assert tg.tstgemm_query_route(t, M).k_slices == slices
+    assert np.array_equal(Y, np.repeat(signs.sum(axis=1, keepdims=True) * np.float32(3e38), N, axis=1))
