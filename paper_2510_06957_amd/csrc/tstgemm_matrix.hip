@@ -976,9 +976,11 @@ k_waves(const MatrixArgs a)
             copy_to_lds(i < kCopiesW ? wbuf : xbuf, ring + slot + (i < kCopiesW ? kX + 1024 * i : 1024 * (i - kCopiesW)), from[i]);
             from[i] += i < kCopiesW ? (unsigned)a.n_pad * 16u : 256u;   // (behind the last block: what nobody multiplies, or nothing)
         };
-        // What lies beyond the last row is not to look like a NaN of an earlier kernel, whether or not such a copy writes zeros
-        if (end == a.n_kblocks && a.K % 64 != 0) {
-            for (int i = lane; i < 2 * kSlot / 16; i += 64) lds[wave * (2 * kSlot / 16) + i] = uint4v{0, 0, 0, 0};
+        // What lies beyond the last row is not to look like a NaN of an earlier kernel, whether or not such a copy writes zeros.  It is in the
+        // last block, at the last row and its repeats, and where blocks before used the place, entries of X are there already
+        const int last = end - 1 - first;
+        if (end == a.n_kblocks && a.K % 64 != 0 && last < 2) {
+            for (int i = 16 * (rows - 1) + lane; i < kX / 16; i += 64) lds[(2 * wave + last) * (kSlot / 16) + i] = uint4v{0, 0, 0, 0};
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
 #pragma unroll
