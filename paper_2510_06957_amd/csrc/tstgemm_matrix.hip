@@ -1308,8 +1308,8 @@ hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 // call is faster than `peak` operations per us, what the tile reaches on long calls under the power limit (64 x 512 against
 // 64 x 256: M = 4096, K = N = 8192 1073 -> 1038 us, 2048 x 4096 x 4096 138 -> 132, 1024 x 2048 x 8192 74 -> 70).  Fitted to 13 tiles x 6 slice counts on 77
 // shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five of k_matrix is 2 % slower than the best of
-// all on average, 16 % at worst.  k_waves is fitted to 1014 timings (M = 11 .. 768, the same K and N), with figures that are high by
-// some 5 % on long calls, where those of k_matrix are: where the two meet, kLateRounds has what was measured.
+// all on average, 16 % at worst.  k_waves in slices is fitted to 1014 timings (M = 11 .. 768, the same K and N), with figures that are high by
+// some 5 % on long calls, where those of k_matrix are; with K whole kWholeOfWaves has what was measured.
 struct TileShape {
     int rows, cols, groups, waves, per_cu;
     double fixed, step, work, peak;
@@ -1330,11 +1330,17 @@ constexpr int kFirstOfWaves = 6;
 // wavefronts without work.
 bool waves_can(const tcsc_layout_t &l, bool x_aligned) { return x_aligned && l.K % 4 == 0 && l.n_kblocks >= 4; }
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
-// k_waves with K whole and more tiles than two a compute unit: Y is 8 MB and more, and nothing covers the last round's part of it.  Without
-// these two figures (1.04 and 0.3 us per MB of Y) calls stayed that k_matrix takes in less time, up to 6.7 % (192 x 4096 x 11008, 516 tiles on
-// 512 places, 55.6 against 52.2 us, 480 x 5440 x 4992 69.5 against 64.8, 352 x 832 x 12376 29.7 against 28.0); with them no such call of 120 shapes
-// (57 of them with more tiles than places) is more than 1.5 % behind k_matrix, and the choice is 0.3 % behind the better of the two on average.
-constexpr double kLateRounds = 1.04, kLateMb = 0.3;
+// k_waves with K whole: a workgroup takes `each` for its sums, which both sets of four wavefronts bring to the LDS, beside its steps, `work` us each, and
+// the workgroups of a compute unit share both; with more tiles than two a compute unit nothing covers what is written last (kLateRounds,
+// kLateMb, us per MB of Y).  Fitted to 771 timings of 415 shapes, with 255 others to test (M = 11 .. 2500, K = 196 .. 9000, N = 64 .. 14000, the
+// estimates of both kernels within 40 %): two of the 670 are more than 1.5 % behind k_matrix (500 x 7296 x 2705 4 %), and the choice is 0.9 % behind the
+// best of all on average.  With `fixed` for a round of workgroups, as in k_matrix, 32 were, up to 13 % (246 x 256 x 6144 7.4 us, k_matrix 7.1 and 6.4; 640 x 256 x 1024
+// 5.7, 5.0), and without the late ones 192 x 4096 x 11008 (516 tiles on 512 places 53.1 us, 48.6).
+struct WholeShape {
+    double start, each;
+};
+constexpr WholeShape kWholeOfWaves[] = {{-0.45, 0.75}, {0.05, 1.20}};
+constexpr double kLateRounds = 1.04, kLateMb = 0.15;
 
 struct TilePlan {
     int tile, k_slices;
@@ -1406,9 +1412,11 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_alig
         const double load = up(tiles[i] * k / units), rounds = s.per_cu == 1 ? load : up(load / s.per_cu);
         const double steps = 2.0 * ((per + s.groups - 1) / s.groups);
         const double step_us = s.step * rounds > s.work * load ? s.step * rounds : s.work * load;
+        const bool whole_of_waves = i >= kFirstOfWaves && k == 1;
         double us = s.fixed * rounds + steps * step_us;
+        if (whole_of_waves) us = kWholeOfWaves[i - kFirstOfWaves].start + (kWholeOfWaves[i - kFirstOfWaves].each + steps * s.work) * load;
         if (us < floor_us[i]) us = floor_us[i];
-        if (i >= kFirstOfWaves && k == 1 && rounds > 1.0) us = kLateRounds * us + kLateMb * mb;
+        if (whole_of_waves && rounds > 1.0) us = kLateRounds * us + kLateMb * mb;
         us += kCall + (k > 1 ? kSlice + kSliceMb * mb : 0.0);
         if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
     };

@@ -41,6 +41,17 @@ def test_more_tiles_than_places(M, K, N, waves):
     assert (r.kernel == "k_matrix" and r.tile_rows == 32 and r.k_groups == 4) == waves
 
 
+@pytest.mark.parametrize("M,K,N,tile", [(246, 256, 6144, (32, 128, 2)), (640, 256, 1024, (32, 128, 2)), (905, 216, 1307, (32, 128, 2)),
+                                        (390, 420, 2685, (64, 128, 1)), (1668, 272, 651, (64, 128, 1)), (113, 204, 4926, (32, 128, 2)),
+                                        (97, 256, 7552, (32, 128, 2)), (303, 204, 522, (32, 64, 4)), (1190, 492, 906, (32, 128, 4)),
+                                        (155, 436, 5861, (32, 128, 4)), (960, 320, 485, (32, 64, 4))])
+def test_few_blocks_on_shared_compute_units(M, K, N, tile):
+    """Up to two blocks a wavefront: the sums at the end take longer than the steps, and two workgroups of a compute unit share the way there.  Timed
+    alternatives: 246 x 256 x 6144 7.1 us in k_matrix and 7.4 in k_waves, 1668 x 272 x 651 7.1 and 8.9, 303 x 204 x 522 4.7 and 4.5, 1190 x 492 x 906 10.1 and 9.3."""
+    none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
+    assert route(tg.tcsc_from_arrays(starts, starts, none, none, K, N), M)[1:] == tile
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N", NARROW + WIDE)
 def test_tile_edges(M, K, N):
