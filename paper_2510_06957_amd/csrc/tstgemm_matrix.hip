@@ -767,8 +767,10 @@ k_matrix(const MatrixArgs a)
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         };
-        // The wavefronts meet in front of a step's last products, which are under way meanwhile (600 x 600 x 3000 in 64 x 128 tiles 11.5 ->
-        // 11.1 us, 100 x 4099 x 500 in 32 x 128 13.4 -> 12.5, 64 x 512 up to 1 %).  In front of the first where that is 1 % better: with four
+        // The wavefronts meet in front of a step's last products, which are under way meanwhile, or in front of its first.  Over 195 calls that 32 x 128
+        // and 64 x 128 tiles get (K = 65 .. 2400 whole) the former is 2 and 1 % ahead on average, each call timed to 2 % (584 x 91 x 2085 6.05 -> 5.55 us,
+        // 135 x 845 x 6476 10.1 -> 9.65, 2104 x 128 x 1621 7.45 -> 7.1; 603 x 579 x 2331 11.6 to 11.9 both ways; 1.3 %, 0.05 us, behind in calls of one step a
+        // group that are bound by their start), in slices 1.5 % (20 calls), in 64 x 512 tiles up to 1 %.  The latter is 1 % ahead with four
         // groups of wavefronts, and in 64 x 256 tiles, two of which share a compute unit and fill each other's waits.
         constexpr bool kEarly = WK < 4 && !(CF == 2 && WK * WN == 4);
         constexpr int kCutStages = kEarly ? 4 : 5, kStore = kEarly ? 4 : 5, kSpread = kEarly ? 5 : 4;
