@@ -192,8 +192,8 @@ int tcsc_upload(tcsc_t *t, void *dev_buf, size_t bytes, void *stream);
  * Asynchronous: the kernels are enqueued on `stream` (a hipStream_t, NULL = null stream), no host
  * synchronisation, no allocation.
  * Device data are not validated.  Errors: EINVAL, ENOTUPLOADED, ENOFORM, EWORKSPACE, EHIP (launch failure).
- * Rounding: fp32 accumulation in an order fixed by (M, K, N), the matrix, the launch-shape options, the
- * size of the workspace and whether X lies on a 16-byte border; repeated calls give bit-identical results.  In calls with X in digits (tstgemm_query_digits()) the
+ * Rounding: fp32 accumulation in an order fixed by (M, K, N), the matrix, the launch-shape options and the
+ * size of the workspace; repeated calls give bit-identical results.  In calls with X in digits (tstgemm_query_digits()) the
  * order in a row also depends on whether digits hold all of the 64 rows of its tile, that is on X in up to 63 neighbours.
  * Integer-valued inputs small enough for fp32 give exact results.
  * Scratch memory (M > 8): this call uses the workspace inside the handle's device buffer (TCSC_FORM_WORKSPACE),
@@ -258,8 +258,8 @@ int tstgemm_ex(const float *X, const tcsc_t *t, const float *b, float *Y, int M,
 /*
  * Which kernel a call of tstgemm_ex() with these arguments launches, for benchmarks and tests: on the host alone, by the
  * rule the call itself follows; the handle need not be uploaded yet (the workspace counts by its size).  kernel: static
- * text, "k_decode", "k_decode_signed", "k_packed", "k_rows_packed", "k_rows", "k_small", "k_large" or "k_matrix" (X is taken to
- * lie on a 16-byte border: else calls of few tiles with K a multiple of 4 may take another tile); for the three on the matrix cores also the rows and columns of Y a workgroup computes, the groups of wavefronts that share K in it
+ * text, "k_decode", "k_decode_signed", "k_packed", "k_rows_packed", "k_rows", "k_small", "k_large" or "k_matrix"; for the
+ * three on the matrix cores also the rows and columns of Y a workgroup computes, the groups of wavefronts that share K in it
  * and the slices of K that workgroups share, else 0.
  * Errors: as tstgemm_ex() for opts, M and the handle's forms (EINVAL, ENOFORM).
  */

@@ -403,8 +403,8 @@ int check_call(const tcsc_t *t, int M, const tstgemm_opts_t &o)
     return TSTGEMM_OK;
 }
 
-// The call's context from its options and the handle.  X: looked at for its alignment only (null: a query, which takes it as aligned).
-tst::Call make_call(const tcsc_t *t, const float *X, const tstgemm_opts_t &o, void *stream)
+// The call's context from its options and the handle.
+tst::Call make_call(const tcsc_t *t, const tstgemm_opts_t &o, void *stream)
 {
     const tcsc_layout_t &l = t->layout;
     tst::Call c{};
@@ -422,7 +422,6 @@ tst::Call make_call(const tcsc_t *t, const float *X, const tstgemm_opts_t &o, vo
     c.slab_tiles = o.slab_tiles;
     c.list_walk = o.list_walk;
     c.decode_wide_lists = o.decode_wide_lists != 0;
-    c.x_aligned = reinterpret_cast<uintptr_t>(X) % 16 == 0;
     c.event_before = static_cast<hipEvent_t>(o.event_before);
     c.event_after = static_cast<hipEvent_t>(o.event_after);
     return c;
@@ -468,7 +467,7 @@ int run(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K,
     if (!X || !t || !Y || K != t->K || N != t->N) return TSTGEMM_EINVAL;
     if (int rc = check_call(t, M, o)) return rc;
     if (!t->uploaded) return TSTGEMM_ENOTUPLOADED;
-    const tst::Call c = make_call(t, X, o, stream);
+    const tst::Call c = make_call(t, o, stream);
     const Route r = choose_route(t->layout, M, o, c);
     if (r.error) return r.error;
     hipError_t e = hipErrorInvalidValue;
@@ -507,7 +506,7 @@ int tstgemm_query_route(const tcsc_t *t, int M, const tstgemm_opts_t *opts, tstg
     if (!out || (opts && opts->struct_size != sizeof(tstgemm_opts_t))) return TSTGEMM_EINVAL;
     const tstgemm_opts_t o = opts ? *opts : default_opts();
     if (int rc = check_call(t, M, o)) return rc;
-    const Route r = choose_route(t->layout, M, o, make_call(t, nullptr, o, nullptr));
+    const Route r = choose_route(t->layout, M, o, make_call(t, o, nullptr));
     if (r.error) return r.error;
     *out = tstgemm_route_t{};
     switch (r.path) {
@@ -528,7 +527,7 @@ int tstgemm_query_digits(const tcsc_t *t, int M, const tstgemm_opts_t *opts)
     if (opts && opts->struct_size != sizeof(tstgemm_opts_t)) return TSTGEMM_EINVAL;
     const tstgemm_opts_t o = opts ? *opts : default_opts();
     if (int rc = check_call(t, M, o)) return rc;
-    const Route r = choose_route(t->layout, M, o, make_call(t, nullptr, o, nullptr));
+    const Route r = choose_route(t->layout, M, o, make_call(t, o, nullptr));
     return r.error ? r.error : r.plan.taken() && r.plan.digits;
 }
 

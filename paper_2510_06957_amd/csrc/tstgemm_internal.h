@@ -91,7 +91,6 @@ struct Call {
     int cols_per_wave, k_slices, slab_tiles;   // 0 = built-in choice
     int list_walk;       // small-tile kernel: 0 = built-in choice, 1 = plain, 2 = requests placed by hand
     bool decode_wide_lists;
-    bool x_aligned;      // X lies on a 16-byte border
     hipEvent_t event_before, event_after;      // both or neither
 
     hipError_t record_before() const { return event_before ? hipEventRecord(event_before, stream) : hipSuccess; }

@@ -422,7 +422,7 @@ template <int N> using Int = std::integral_constant<int, N>;
 // to about 1.85 GHz; 4.4 ms for the lists at 50 % non-zeros, any density here; without any cutting and spreading, which
 // gives wrong sums, it would take 0.99 ms), short ones by the start of the first loads, the
 // sums at the end and the second launch where K is sliced (777 x 3001 x 2999 in three slices: 39.7 us, 8 of them the second launch).
-// Calls with few tiles and X on 16-byte borders are k_waves's.
+// Calls with few tiles and K a multiple of 4 are k_waves's.
 // DIGITS: X comes from the workspace, straight into the LDS, W too; three steps of 64 rows of W in a ring, copied two steps
 // ahead, one barrier a step, placed before the last plane's products so that the next step's first reads are under way behind
 // them.  A step has 4 products of 32 cycles per plane and wavefront.  Everything else is dealt between them one by one: all
@@ -929,13 +929,16 @@ k_matrix(const MatrixArgs a)
 // themselves).  M = 256, K = N = 4096: 21.5 us, 26.8 as 64 x 256 tiles over four slices of K with a second launch for their sums;
 // 64 x 16384 x 4096 24.7 (31.4), 32 x 4096 x 4096 9.1 (10.6), 768 x 1024 x 1024 7.9 (10.5), 512 x 512 x 512 5.0 (5.9).  Eight
 // wavefronts a workgroup: 1 to 5 % slower; v_dot2_f32_bf16 for what a plane leaves: 64 instructions a block less, 15 % slower.
-// The copies take 16 bytes a lane and want every row of X on such a border; other calls go to k_matrix.
-template <int CF>
+// The copies take 16 bytes a lane and want every row of X on such a border; calls whose K is not a multiple of 4 go to k_matrix.  Where X itself lies
+// off the border (ON_BORDER false), X goes through registers instead, and the rest is the same, so that the order of a call's sums does not depend on where
+// X lies: 7 % more on average over 75 calls, 16 % at most (256 x 4096 x 4096 22.3 -> 26.0 us, 29.4 in k_matrix; 12 x 1664 x 7104 8.3 -> 9.7, 9.3).  Copies of 4 bytes a lane
+// in place of the registers: 22 %.
+template <int CF, bool ON_BORDER>
 __global__ void __launch_bounds__(256, 2)
 k_waves(const MatrixArgs a)
 {
     constexpr int KW = 4, TN = 32 * CF, kX = 8192, kSlot = kX + 16 * TN;   // a block in the ring: X, then row sets
-    constexpr int kCopiesW = TN / 64, kCopies = 8 + kCopiesW;
+    constexpr int kCopiesW = TN / 64, kCopies = kCopiesW + (ON_BORDER ? 8 : 0);
     static_assert(CF == 2 || CF == 4, "columns come 64 at a time");
     static_assert((32ull + 4) * kMaxExtent * 4 < kNowhere, "offsets inside a tile, two blocks beyond it");
     __shared__ uint4v lds[KW * 2 * kSlot / 16];
@@ -970,7 +973,7 @@ k_waves(const MatrixArgs a)
 #pragma unroll
         for (int i = 0; i < kCopiesW; ++i) from[i] = ((unsigned)first * (unsigned)a.n_pad + (unsigned)min(n0 + 64 * i + lane, a.n_pad - 1)) * 16u;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; kCopiesW + i < kCopies; ++i)
             from[kCopiesW + i] = (unsigned)min(4 * i + (lane >> 4), rows - 1) * (unsigned)a.K * 4u + (unsigned)first * 256u +
                                  16u * (unsigned)((lane & 15) ^ ((4 * i + (lane >> 4)) & 15));
         const unsigned ring = (unsigned)(size_t)(__attribute__((address_space(3))) uint4v *)lds + wave * (2 * kSlot);
@@ -978,10 +981,28 @@ k_waves(const MatrixArgs a)
             copy_to_lds(i < kCopiesW ? wbuf : xbuf, ring + slot + (i < kCopiesW ? kX + 1024 * i : 1024 * (i - kCopiesW)), from[i]);
             from[i] += i < kCopiesW ? (unsigned)a.n_pad * 16u : 256u;   // (behind the last block: what nobody multiplies, or nothing)
         };
+        // Off the border, four of the eight pieces at a time: requested, and two stages later written to where a copy would have put them.  (Rows
+        // that do not exist read as zero.)
+        const __amdgpu_buffer_rsrc_t xraw = raw_buffer(a.X + (size_t)m0 * a.K, (size_t)rows * a.K * 4);
+        uint4v held[4];
+        unsigned x_row = (unsigned)(lane >> 4) * (unsigned)a.K * 4u, x_piece = 16u * (unsigned)((lane & 15) ^ (lane >> 4)), x_block = (unsigned)first * 256u;
+        auto request = [&](int half) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                unsigned piece = x_piece;
+                asm volatile("" : "+v"(piece));   // here: four of them kept do not fit the registers
+                held[i] = load16(xraw, (piece ^ 64u * i) + x_row + ((16u * half + 4u * i) * (unsigned)a.K * 4u + x_block));
+            }
+            if (half == 1) x_block += 256u;
+        };
+        auto put = [&](int half, unsigned slot) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(__attribute__((address_space(3))) uint4v *)(size_t)(ring + slot + 1024 * (4 * half + i) + 16 * lane) = held[i];
+        };
         // What lies beyond the last row is not to look like a NaN of an earlier kernel, whether or not such a copy writes zeros.  It is in the
         // last block, at the last row and its repeats, and where blocks before used the place, entries of X are there already
         const int last = end - 1 - first;
-        if (end == a.n_kblocks && a.K % 64 != 0 && last < 2) {
+        if (ON_BORDER && end == a.n_kblocks && a.K % 64 != 0 && last < 2) {
             for (int i = 16 * (rows - 1) + lane; i < kX / 16; i += 64) lds[(2 * wave + last) * (kSlot / 16) + i] = uint4v{0, 0, 0, 0};
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
@@ -989,6 +1010,14 @@ k_waves(const MatrixArgs a)
         for (int i = 0; i < kCopies; ++i) copy(i, 0);
 #pragma unroll
         for (int i = 0; i < kCopies; ++i) copy(i, kSlot);
+        if (!ON_BORDER) {
+            request(0);
+            put(0, 0);
+            request(1);
+            put(1, 0);
+            request(0);   // of the second block, which the first one's stages 0 and 1 put into the ring
+            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+        }
 
         // Stage s of a block: rows 4 s .. + 3 and 16 + 4 s .. + 3 of each half.  [.][s % 2]: X as it is, its planes, weights
         float4v raw[2][2];
@@ -1033,7 +1062,12 @@ k_waves(const MatrixArgs a)
         };
         auto stage = [&](auto number, unsigned at, unsigned other) __attribute__((always_inline)) {
             constexpr int S = decltype(number)::value, A = S % 2, B = 1 - A, kProducts = 3 * CF;
+            if constexpr (!ON_BORDER && S == 0) {
+                put(0, other);
+                request(1);
+            }
             // the next block is there; all of this one has been read, and makes room for the one after the next
+            if constexpr (!ON_BORDER && S == 2) put(1, other);
             if constexpr (S == 2) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 #pragma unroll
             for (int q = 0; q < kProducts; ++q) {
@@ -1045,6 +1079,7 @@ k_waves(const MatrixArgs a)
                 if (S == 2 && q >= 2) {
 #pragma unroll
                     for (int i = (q - 2) * kCopies / (kProducts - 2); i < (q - 1) * kCopies / (kProducts - 2); ++i) copy(i, at);
+                    if (!ON_BORDER && q == kProducts - 1) request(0);
                 }
 #pragma unroll
                 for (int i = q * 12 / kProducts; i < (q + 1) * 12 / kProducts; ++i) cut(B, i);
@@ -1292,7 +1327,9 @@ hipError_t launch_sum(const MatrixArgs &a, hipStream_t stream)
 template <int CF>
 hipError_t launch_waves(const MatrixArgs &a, long long m_tiles, const Call &c)
 {
-    hipLaunchKernelGGL(k_waves<CF>, dim3((unsigned)(m_tiles * a.n_tiles * a.k_slices)), dim3(256), 0, c.stream, a);
+    const dim3 grid((unsigned)(m_tiles * a.n_tiles * a.k_slices)), block(256);
+    if (reinterpret_cast<uintptr_t>(a.X) % 16 == 0) hipLaunchKernelGGL((k_waves<CF, true>), grid, block, 0, c.stream, a);
+    else hipLaunchKernelGGL((k_waves<CF, false>), grid, block, 0, c.stream, a);
     return hipGetLastError();
 }
 
@@ -1328,9 +1365,9 @@ constexpr TileShape kTiles[] = {
 };
 constexpr int kDigitTiles = 2;   // the first two can take X in digits
 constexpr int kFirstOfWaves = 6;
-// The last two are k_waves, whose copies of X need every row of X on a 16-byte border; K of less than a block per wavefront leaves
-// wavefronts without work.
-bool waves_can(const tcsc_layout_t &l, bool x_aligned) { return x_aligned && l.K % 4 == 0 && l.n_kblocks >= 4; }
+// The last two are k_waves, whose copies of X need every row of X as far from a 16-byte border as the first; K of less than a block per
+// wavefront leaves wavefronts without work.
+bool waves_can(const tcsc_layout_t &l) { return l.K % 4 == 0 && l.n_kblocks >= 4; }
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
 // k_waves with K whole: a workgroup takes `each` for its sums, which both sets of four wavefronts bring to the LDS, beside its steps, `work` us each, and
 // the workgroups of a compute unit share both; with more tiles than two a compute unit nothing covers what is written last (kLateRounds,
@@ -1399,7 +1436,7 @@ TilePlan with_digits(const tcsc_layout_t &l, int M, size_t ws_bytes, const TileP
 // The search.  A short call waits for it, and an estimate takes some 20 ns: K whole for every tile first; then slices of the tile that they can
 // gain most for, and so on until no tile can gain (`least`: the estimate with what does not depend on the number of slices, and the
 // fewest steps).  us of a choice: 14 x 2816 x 2944 0.42 (all 64 estimates one after the other 2.0), 256 x 4096 x 4096 0.38 (1.5), 64 x 512 x 512 0.24 (0.42).
-TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_aligned)
+TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
 {
     constexpr int kCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
     TilePlan best{-1, 1, 0.0};
@@ -1454,7 +1491,7 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes, bool x_alig
             for (int k = 2; k <= kMaxKSlices && k <= l.n_kblocks && tiles[i] * k <= 2.0 * units * kTiles[i].per_cu; ++k) consider(i, k);
         }
     };
-    const bool waves = waves_can(l, x_aligned);
+    const bool waves = waves_can(l);
     whole(0, kFirstOfWaves);
     const bool short_call = best.tile >= 0 && kLostPart * best.us < kLost;   // too short for digits, with slices too
     if (!short_call) {
@@ -1772,15 +1809,10 @@ size_t matrix_workspace_bytes(int M, int K, int N, int n_pad)
     tcsc_layout_t l{};
     l.K = K; l.N = N; l.n_pad = n_pad; l.n_kblocks = (K - 1) / kKBlock + 1;
     if (!offsets_fit(l)) return 0;
-    size_t most = 0;
-    for (const bool x_aligned : {false, true}) {
-        const TilePlan p = choose_tile(l, M, (size_t)1 << 62, x_aligned);
-        if (p.tile < 0) continue;
-        const size_t partial_bytes = p.k_slices > 1 ? (size_t)p.k_slices * M * n_pad * 4 : 0;
-        const size_t bytes = partial_bytes + (p.digits ? ((size_t)M + 63) / 64 * digit_tile_bytes(l) : 0);
-        most = most > bytes ? most : bytes;
-    }
-    return most;
+    const TilePlan p = choose_tile(l, M, (size_t)1 << 62);
+    if (p.tile < 0) return 0;
+    const size_t partial_bytes = p.k_slices > 1 ? (size_t)p.k_slices * M * n_pad * 4 : 0;
+    return partial_bytes + (p.digits ? ((size_t)M + 63) / 64 * digit_tile_bytes(l) : 0);
 }
 
 // Whether the matrix cores take a call (the lists or the row-set walk being the other choice).  They do unless W is so
@@ -1820,7 +1852,7 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c)
             return MatrixPlan{true, r.tiles, r.waves, false};
         }
     }
-    const TilePlan p = choose_tile(l, M, c.ws_bytes, c.x_aligned);
+    const TilePlan p = choose_tile(l, M, c.ws_bytes);
     const bool rows = M <= kMaxRows && (p.tile < 0 || r.us < p.us);
     if (!rows && p.tile < 0) return none;
     const double us = rows ? r.us : p.us;

@@ -65,7 +65,7 @@ def test_tile_edges(M, K, N):
     _, Xi, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=301 + M)
     Yi = oracle.tstgemm(Xi, ot, b)[0].astype(np.float32)
     assert np.array_equal(gpu_tstgemm(W, Xi, b, handle=t)[0], Yi)
-    # X four bytes off the border: another kernel, the same sums
+    # X four bytes off the border: through registers, the same sums
     off = torch.empty(M * K + 1, device="cuda")[1:].view(M, K)
     off.copy_(torch.from_numpy(Xi))
     Yo = torch.full((M, N), float("nan"), device="cuda")
@@ -131,3 +131,21 @@ def test_a_last_block_in_part_costs_no_more_than_a_whole_one(M, N):
             torch.cuda.synchronize()
             best[K] = min(best[K], e0.elapsed_time(e1))
     assert best[204] <= 1.06 * best[256], best
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", NARROW + WIDE)
+def test_results_do_not_depend_on_where_x_lies(M, K, N):
+    """X four, eight and twelve bytes off a 16-byte border: the same bits.  A NaN beside X does not matter."""
+    import torch
+    W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=360 + M + N)
+    t = tg.tcsc_upload(tg.tcsc_build(W))
+    Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda()
+    Y = tg.tstgemm(Xd, t, bd)
+    assert Xd.data_ptr() % 16 == 0
+    for by in (1, 2, 3):
+        room = torch.full((M * K + 8,), float("nan"), device="cuda")
+        off = room[by:by + M * K].view(M, K)
+        off.copy_(Xd)
+        assert off.data_ptr() % 16 == 4 * by
+        assert torch.equal(tg.tstgemm(off, t, bd), Y)
