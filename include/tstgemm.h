@@ -276,6 +276,13 @@ int tstgemm_query_route(const tcsc_t *t, int M, const tstgemm_opts_t *opts, tstg
 int tstgemm_query_digits(const tcsc_t *t, int M, const tstgemm_opts_t *opts);
 
 /*
+ * Whether a call that tstgemm_query_route() names "k_matrix" runs the kernel "k_waves" (calls with few tiles, whose wavefronts share
+ * nothing but their sums; some of its tiles look like others of "k_matrix"), by the same rule: 1 or 0, or an error of
+ * tstgemm_query_route().
+ */
+int tstgemm_query_waves(const tcsc_t *t, int M, const tstgemm_opts_t *opts);
+
+/*
  * Y = PReLU(X W + b): tstgemm() with the activation fused behind the bias add.  The paper fuses
  * PReLU into its vectorised kernels (Sec. 2 "Implementation Note", Sec. 4) without giving the
  * formula or the slope; here it is the usual one, PReLU(v) = v for v > 0 and alpha * v otherwise,

@@ -101,6 +101,7 @@ def _load():
     lib.tstgemm_workspace_bytes.argtypes = [ci, ci, ci, ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t)]
     lib.tstgemm_query_route.argtypes = [vp, ci, ctypes.POINTER(TstgemmOpts), ctypes.POINTER(TstgemmRoute)]
     lib.tstgemm_query_digits.argtypes = [vp, ci, ctypes.POINTER(TstgemmOpts)]
+    lib.tstgemm_query_waves.argtypes = [vp, ci, ctypes.POINTER(TstgemmOpts)]
     lib.tcsc_select_forms.argtypes = [vp, ctypes.c_uint32]
     lib.tstgemm_probe_lds_read.argtypes = [ci, ctypes.POINTER(ctypes.c_int64), vp]
     lib.tstgemm_probe_lds_read.restype = ci
@@ -111,7 +112,7 @@ def _load():
     for name in ("tcsc_build", "tcsc_from_arrays", "tcsc_to_dense", "tcsc_dims", "tcsc_arrays", "tcsc_device_bytes",
                  "tcsc_layout", "tcsc_upload", "tstgemm", "tstgemm_prelu", "tstgemm_signed", "tstgemm_packed",
                  "tcsc_signed_arrays", "tcsc_packed_codes", "tstgemm_ex", "tstgemm_workspace_bytes", "tcsc_select_forms",
-                 "tstgemm_noalloc", "tstgemm_query_route", "tstgemm_query_digits"):
+                 "tstgemm_noalloc", "tstgemm_query_route", "tstgemm_query_digits", "tstgemm_query_waves"):
         getattr(lib, name).restype = ci
     _lib = lib
     _bind_launcher(lib)
@@ -432,6 +433,18 @@ def tstgemm_query_digits(t: Tcsc, M: int, workspace_bytes=0) -> bool:
     rc = _load().tstgemm_query_digits(t.handle, int(M), ctypes.byref(o))
     if rc < 0:
         raise TstgemmError(rc, "tstgemm_query_digits")
+    return bool(rc)
+
+
+def tstgemm_query_waves(t: Tcsc, M: int, workspace_bytes=0) -> bool:
+    """Whether tstgemm() for M rows of X runs k_waves where tstgemm_query_route() says k_matrix (host only; workspace_bytes as there)."""
+    o = TstgemmOpts()
+    o.struct_size = ctypes.sizeof(TstgemmOpts)
+    if workspace_bytes:
+        o.workspace, o.workspace_bytes = 256, int(workspace_bytes)
+    rc = _load().tstgemm_query_waves(t.handle, int(M), ctypes.byref(o))
+    if rc < 0:
+        raise TstgemmError(rc, "tstgemm_query_waves")
     return bool(rc)
 
 

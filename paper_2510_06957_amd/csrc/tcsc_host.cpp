@@ -531,6 +531,15 @@ int tstgemm_query_digits(const tcsc_t *t, int M, const tstgemm_opts_t *opts)
     return r.error ? r.error : r.plan.taken() && r.plan.digits;
 }
 
+int tstgemm_query_waves(const tcsc_t *t, int M, const tstgemm_opts_t *opts)
+{
+    if (opts && opts->struct_size != sizeof(tstgemm_opts_t)) return TSTGEMM_EINVAL;
+    const tstgemm_opts_t o = opts ? *opts : default_opts();
+    if (int rc = check_call(t, M, o)) return rc;
+    const Route r = choose_route(t->layout, M, o, make_call(t, o, nullptr));
+    return r.error ? r.error : r.path == Path::matrix && tst::matrix_waves(r.plan);
+}
+
 int tstgemm(const float *X, const tcsc_t *t, const float *b, float *Y, int M, int K, int N, void *stream)
 {
     return run(X, t, b, Y, M, K, N, default_opts(), stream);

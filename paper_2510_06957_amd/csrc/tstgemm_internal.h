@@ -164,7 +164,7 @@ void large_workspace_bytes(int M, int K, int n_pad, size_t *min_bytes, size_t *b
 // where the lists or the row-set walk are the faster choice (the workspace, which holds partial sums and X in digits and is not
 // used for M <= 8, is the caller's to check); packed_plan: the same for M <= 8 from the base-3 codes.
 struct MatrixPlan {
-    bool rows;          // k_rows (shape: tiles of 16 columns, split: wavefronts), else k_matrix (tile shape, K slices)
+    bool rows;          // k_rows (shape: tiles of 16 columns, split: wavefronts), else k_matrix or k_waves (tile shape, K slices)
     int shape, split;
     bool digits;        // k_matrix: X cut into digits beforehand
     bool taken() const { return split > 0; }
@@ -173,6 +173,7 @@ MatrixPlan matrix_plan(const tcsc_layout_t &l, int M, const Call &c);
 MatrixPlan packed_plan(const tcsc_layout_t &l, int M);
 size_t matrix_workspace_bytes(int M, int K, int N, int n_pad);   // what k_matrix would use of a workspace that holds all it wants
 void matrix_tile(const MatrixPlan &p, int M, tstgemm_route_t *out);   // tile of Y, groups and slices of K
+bool matrix_waves(const MatrixPlan &p);                               // k_waves, not k_matrix
 hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);
 hipError_t launch_packed_rows(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c);
 // tstgemm_decode.hip -- small-M kernel (M <= 8; X in the LDS, in chunks of K if need be).

@@ -1877,6 +1877,8 @@ void matrix_tile(const MatrixPlan &p, int M, tstgemm_route_t *out)
     out->k_slices = p.rows ? 1 : p.split;
 }
 
+bool matrix_waves(const MatrixPlan &p) { return p.taken() && !p.rows && p.shape >= kFirstOfWaves; }
+
 hipError_t launch_matrix(const MatrixPlan &p, const float *X, const tcsc *t, const float *b, float *Y, int M, const Call &c)
 {
     const tcsc_layout_t &l = t->layout;

@@ -19,17 +19,36 @@ WIDE = [(33, 4096, 5000), (255, 4092, 4031), (256, 512, 4096), (64, 8196, 4100),
 
 
 def route(t, M):
+    """tstgemm_query_route() with the kernel's own name: some tiles of k_matrix look like k_waves'."""
     r = tg.tstgemm_query_route(t, M)
-    return r.kernel, r.tile_rows, r.tile_cols, r.k_groups
+    waves = tg.tstgemm_query_waves(t, M)
+    assert not waves or r.kernel == "k_matrix"
+    return "k_waves" if waves else r.kernel, r.tile_rows, r.tile_cols, r.k_groups
 
 
 @pytest.mark.parametrize("M,K,N", NARROW + WIDE)
 def test_routes(M, K, N):
     none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
-    t = tg.tcsc_from_arrays(starts, starts, none, none, K, N)
-    if M > 64:   # (with few rows an empty matrix is the lists')
-        assert route(t, M) == ("k_matrix", 32, 64 if (M, K, N) in NARROW else 128, 4)
+    if M > 64:
+        t = tg.tcsc_from_arrays(starts, starts, none, none, K, N)
+    else:   # (with few rows an empty matrix is the lists')
+        t = tg.tcsc_build(si.draw_ternary(np.random.default_rng(1), K, N, 0.5))
+    assert route(t, M) == ("k_waves", 32, 64 if (M, K, N) in NARROW else 128, 4)
 
+
+def test_the_kernels_name():
+    """tstgemm_query_waves() tells the two kernels apart where tile and groups are alike, and refuses what tstgemm_query_route() refuses."""
+    t = tg.tcsc_build(si.draw_ternary(np.random.default_rng(1), 1001, 1000, 0.5))
+    assert route(t, 129) == ("k_matrix", 32, 64, 4) and not tg.tstgemm_query_waves(t, 5)
+    t = tg.tcsc_build(si.draw_ternary(np.random.default_rng(1), 1000, 1000, 0.5))
+    assert route(t, 129) == ("k_waves", 32, 64, 4) and not tg.tstgemm_query_waves(t, 5) and not tg.tstgemm_query_waves(t, 4096)
+    with pytest.raises(tg.TstgemmError) as e:
+        tg.tstgemm_query_waves(t, 0)
+    assert e.value.code == -1
+    tg.tcsc_select_forms(t, tg.FORM_CUTS)
+    with pytest.raises(tg.TstgemmError) as e:
+        tg.tstgemm_query_waves(t, 129)
+    assert e.value.code == -7
 
 
 @pytest.mark.parametrize("M,K,N,waves", [(192, 4096, 10880, True), (192, 4096, 11008, False), (352, 4096, 5888, True), (544, 4096, 4096, False),
@@ -37,8 +56,8 @@ def test_routes(M, K, N):
 def test_more_tiles_than_places(M, K, N, waves):
     """Tiles that start in a second round of the chip cost more than they compute: a few of them leave the call to shared cuts of X."""
     none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
-    r = tg.tstgemm_query_route(tg.tcsc_from_arrays(starts, starts, none, none, K, N), M)
-    assert (r.kernel == "k_matrix" and r.tile_rows == 32 and r.k_groups == 4) == waves
+    t = tg.tcsc_from_arrays(starts, starts, none, none, K, N)
+    assert tg.tstgemm_query_waves(t, M) == waves and (not waves or route(t, M)[1::2] == (32, 4))
 
 
 @pytest.mark.parametrize("M,K,N,tile", [(246, 256, 6144, (32, 128, 2)), (640, 256, 1024, (32, 128, 2)), (905, 216, 1307, (32, 128, 2)),
@@ -49,7 +68,7 @@ def test_few_blocks_on_shared_compute_units(M, K, N, tile):
     """Up to two blocks a wavefront: the sums at the end take longer than the steps, and two workgroups of a compute unit share the way there.  Timed
     alternatives: 246 x 256 x 6144 7.1 us in k_matrix and 7.4 in k_waves, 1668 x 272 x 651 7.1 and 8.9, 303 x 204 x 522 4.7 and 4.5, 1190 x 492 x 906 10.1 and 9.3."""
     none, starts = np.zeros(0, np.int32), np.zeros(N + 1, np.int32)
-    assert route(tg.tcsc_from_arrays(starts, starts, none, none, K, N), M)[1:] == tile
+    assert route(tg.tcsc_from_arrays(starts, starts, none, none, K, N), M) == ("k_waves" if tile[2] == 4 else "k_matrix",) + tile
 
 
 @pytest.mark.gpu
@@ -60,7 +79,7 @@ def test_tile_edges(M, K, N):
     ot = oracle.tcsc_build(W)
     Yd, A, _ = oracle.tstgemm(X, ot, b)
     Y, t = gpu_tstgemm(W, X, b)
-    assert route(t, M) == ("k_matrix", 32, 64 if (M, K, N) in NARROW else 128, 4)
+    assert route(t, M) == ("k_waves", 32, 64 if (M, K, N) in NARROW else 128, 4)
     tight(Y, Yd, A, f"{M}x{K}x{N}")
     _, Xi, _ = si.make_inputs(M, K, N, 0.5, "int8", seed=301 + M)
     Yi = oracle.tstgemm(Xi, ot, b)[0].astype(np.float32)
@@ -83,7 +102,8 @@ def test_infinities_beyond_the_rows(M, K, N):
     with np.errstate(invalid="ignore"):
         Yd = np.stack([np.where(W != 0, X[m][:, None].astype(np.float64) * W, 0.0).sum(axis=0) for m in range(M)]) + b
     A = np.abs(np.where(np.isfinite(X), X, 0)).astype(np.float64) @ np.abs(W) + np.abs(b)
-    Y, _ = gpu_tstgemm(W, X, b)
+    Y, t = gpu_tstgemm(W, X, b)
+    assert route(t, M)[0] == "k_waves"
     ok = np.isfinite(Yd)
     assert ok.any() and not ok.all() and _same(Y, Yd)
     assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-6 * A[ok])
@@ -99,7 +119,7 @@ def test_sums_are_rounded_once(M, K, N):
     W = si.draw_ternary(rng, K, N, 0.5)
     Y, t = gpu_tstgemm(W, X, None)
     r = tg.tstgemm_query_route(t, M)
-    assert (r.tile_rows, r.k_groups, r.k_slices) == (32, 4, 1)
+    assert route(t, M)[0] == "k_waves" and r.k_slices == 1
     assert np.array_equal(Y, (X.astype(np.float64) @ W).astype(np.float32))
 
 
@@ -113,7 +133,7 @@ def test_a_last_block_in_part_costs_no_more_than_a_whole_one(M, N):
     for K in (204, 256):
         W, X, b = si.make_inputs(M, K, N, 0.5, "normal", seed=350)
         t = tg.tcsc_upload(tg.tcsc_build(W))
-        assert route(t, M) == ("k_matrix", 32, 64, 4)
+        assert route(t, M) == ("k_waves", 32, 64, 4)
         Xd, bd, Y = torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda(), torch.empty(M, N, device="cuda")
         tg.tstgemm(Xd, t, bd, Y)
         torch.cuda.synchronize()
@@ -142,10 +162,43 @@ def test_results_do_not_depend_on_where_x_lies(M, K, N):
     t = tg.tcsc_upload(tg.tcsc_build(W))
     Xd, bd = torch.from_numpy(X).cuda(), torch.from_numpy(b).cuda()
     Y = tg.tstgemm(Xd, t, bd)
-    assert Xd.data_ptr() % 16 == 0
+    assert Xd.data_ptr() % 16 == 0 and route(t, M)[0] == "k_waves"
     for by in (1, 2, 3):
         room = torch.full((M * K + 8,), float("nan"), device="cuda")
         off = room[by:by + M * K].view(M, K)
         off.copy_(Xd)
         assert off.data_ptr() % 16 == 4 * by
         assert torch.equal(tg.tstgemm(off, t, bd), Y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(33, 4096, 5000), (255, 1532, 4031), (70, 832, 5824), (65, 8196, 1001), (95, 580, 257)])
+@pytest.mark.parametrize("slopes", ["none", "one", "column"])
+@pytest.mark.parametrize("off", [0, 1])
+def test_epilogue_and_what_is_not_finite(M, K, N, slopes, off):
+    """PReLU, and outputs that are taken again: a few infinities, NaNs and numbers beyond the scaled range in rows of both halves of a tile, the last row
+    and the last entries among them, in tiles of either width, K whole and in slices, X on the border and off it."""
+    import torch
+    W, X, b = si.make_inputs(M, K, N, 0.25, "normal", seed=370 + M)
+    rng = np.random.default_rng(371 + M)
+    for m, v in ((0, np.inf), (1, np.nan), (7, 1e36), (16, -np.inf), (31, -1e36), (M - 2, np.inf), (M - 1, np.nan), (M - 1, np.inf)):
+        X[m, rng.integers(0, K)] = v
+    X[20, K - 1], X[21, 0], X[M - 1, K - 1] = np.inf, -np.inf, np.inf
+    rest = ~np.isfinite(X)
+    Xf = np.where(rest, 0, X).astype(np.float64)
+    Yd, A = Xf @ W + b, np.abs(Xf) @ np.abs(W) + np.abs(b)
+    with np.errstate(invalid="ignore"):
+        for m, k in zip(*np.nonzero(rest)):
+            Yd[m, W[k] != 0] += X[m, k] * W[k, W[k] != 0]
+        alpha = None if slopes == "none" else rng.uniform(0.1, 0.4, 1 if slopes == "one" else N).astype(np.float32)
+        if alpha is not None:
+            Yd = np.where(Yd > 0, Yd, alpha * Yd)
+    t = tg.tcsc_upload(tg.tcsc_build(W))
+    assert route(t, M) == ("k_waves", 32, 128 if N > 4000 else 64, 4)
+    room = torch.full((M * K + 4,), float("nan"), device="cuda")
+    Xd = room[off:off + M * K].view(M, K)
+    Xd.copy_(torch.from_numpy(X))
+    Y = tg.tstgemm(Xd, t, torch.from_numpy(b).cuda(), alpha=None if alpha is None else torch.from_numpy(alpha).cuda()).cpu().numpy()
+    ok = np.isfinite(Yd)
+    assert ok.any() and not ok.all() and _same(Y, Yd)
+    assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-6 * A[ok])
