@@ -260,6 +260,8 @@ def main():
     kernel = route.kernel
     decode = wl.M <= 8
     matrix = kernel == "k_matrix"
+    if matrix and not tuning and tg.tstgemm_query_waves(t, wl.M):
+        kernel = "k_waves"
     digits = matrix and not tuning and tg.tstgemm_query_digits(t, wl.M)
     rows = kernel in ("k_rows", "k_rows_packed")
     # index data one call reads (what must not be in the Infinity Cache for an HBM figure)
