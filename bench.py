@@ -43,10 +43,10 @@ PEAK_ALU_INSTR_T = 256 * 64 * 2.4e9 / 1e12     # vector lane-instructions per se
 _T_ALL = "profiles/hbm_traffic_all_configs.md"
 _T_OTHER = "profiles/hbm_traffic_other_workloads.md"
 MEASURED_TRAFFIC = {
-    ("C1", "tcsc"): (970752, _T_ALL), ("C2", "tcsc"): (45524173, _T_ALL), ("C3a", "tcsc"): (45497549, _T_ALL),
-    ("C3b", "tcsc"): (45567181, _T_ALL), ("C4-1", "tcsc"): (11621610, _T_ALL), ("C4-8", "tcsc"): (12881026, _T_ALL),
+    ("C1", "tcsc"): (993286, _T_ALL), ("C2", "tcsc"): (45601587, _T_ALL), ("C3a", "tcsc"): (45489152, _T_ALL),
+    ("C3b", "tcsc"): (45636813, _T_ALL), ("C4-1", "tcsc"): (11621610, _T_ALL), ("C4-8", "tcsc"): (12881026, _T_ALL),
     ("C5a", "tcsc"): (808063679, _T_ALL), ("C5b", "tcsc"): (808058858, _T_ALL), ("C5c", "tcsc"): (902535837, _T_ALL),
-    ("M64-K16384-N4096-d0.5", "tcsc"): (60804096, _T_OTHER),
+    ("M64-K16384-N4096-d0.5", "tcsc"): (60817408, _T_OTHER),
     ("C4-1", "packed"): (9610282, _T_OTHER), ("C4-8", "packed"): (10809682, _T_OTHER),
 }
 ORACLE_FLAGS = "gcc -O3 -fstrict-aliasing -DNDEBUG -fopenmp (the paper's flags, Sec. 4, without -march=native)"
