@@ -12,8 +12,8 @@
 // X held an infinity, a NaN or something beyond about 2^100 -- is taken again from X by sums_of_any(), which keeps such
 // entries apart, so an entry of X under a zero weight never reaches Y here either.
 //
-// k_matrix is for M > 8, k_waves for those of its calls that have few tiles, k_rows for M <= 10; choose_tile(), with_digits(), rows_plan() and matrix_plan() have the rules, with
-// what was measured.  k_matrix also multiplies X cut into 6-bit digits by k_digits beforehand, where a call is large enough.
+// k_matrix is for M > 8, k_waves for those of its calls whose tiles are few or K long for them, k_rows for M <= 10; choose_tile(), with_digits(), rows_plan()
+// and matrix_plan() have the rules, with what was measured.  k_matrix also multiplies X cut into 6-bit digits by k_digits beforehand, where a call is large enough.
 #include <cmath>
 #include <type_traits>
 
@@ -150,7 +150,7 @@ struct Epilogue {
 // scaled sums are not finite.  X is split by size: entries below 2^64 go in times 2^24 as everywhere, larger ones times
 // 2^-24 (2^22 of the largest floats do not overflow so), and infinities and NaNs as ones in two planes of their own (a NaN in
 // both), multiplied by the +1 rows and by the -1 rows, which counts the members that push a sum up and those that push it
-// down.  Bound by cutting X, which every 16 columns do anew, and by the latency of its loads.  Single calls with one
+// down.  Bound by cutting X, which every 16 NB columns do anew, and by the latency of its loads.  Single calls with one
 // infinity (with one in every row; with all of X near 1e35), 50 % non-zeros, against the list and row-set kernels, whose time
 // does not depend on X: 256 x 4096 x 4096 (k_waves, NB = 2) 82 us (124; 207) against 108, 1024 x 2048 x 8192 222 (565; 881) against 359,
 // M = 1, 4096 x 4096 12 (12; 20) against 11; finite X 28, 82, 7.  One lane per output that walked the members one by one
@@ -917,7 +917,7 @@ k_matrix(const MatrixArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------------------------
-// k_waves: Y in tiles of 32 x 32 CF for calls with up to some hundred such tiles.  A workgroup is four wavefronts, each with the
+// k_waves: Y in tiles of 32 x 32 CF, for calls that choose_tile() sends here: from one tile to about a thousand (672 x 1536 x 6528: 1071).  A workgroup is four wavefronts, each with the
 // whole tile over a quarter of the workgroup's K: nothing is shared until the sums meet in the LDS at the end, so the loop has
 // no barrier, and K is seldom cut into slices.  Per block of 64 rows of W a wavefront copies 32 x 64 floats of X and the row sets of its
 // columns straight into a ring of two blocks in the LDS that is its own, the next block's while it is at this one; lane l cuts
@@ -926,8 +926,8 @@ k_matrix(const MatrixArgs a)
 // Bound: a SIMD issues a vector instruction in 4.1 cycles beside a matrix instruction, which takes 8 of its own (measured), so a
 // block is 48 x 8 + 366 x 4.1 cycles of issue for CF = 4 against 48 x 32 of products; with all compute units at it the power
 // limit takes another fifth (2.2 us per block and pair of wavefronts, 1.65 on one compute unit alone, 1.8 for the products by
-// themselves).  M = 256, K = N = 4096: 21.5 us, 26.8 as 64 x 256 tiles over four slices of K with a second launch for their sums;
-// 64 x 16384 x 4096 24.7 (31.4), 32 x 4096 x 4096 9.1 (10.6), 768 x 1024 x 1024 7.9 (10.5), 512 x 512 x 512 5.0 (5.9).  Eight
+// themselves).  M = 256, K = N = 4096: 22.2 us, 28.2 as 64 x 256 tiles over four slices of K with a second launch for their sums;
+// 64 x 16384 x 4096 24.6 (31.1), 32 x 4096 x 4096 9.2 (10.6), 768 x 1024 x 1024 8.3 (10.5), 512 x 512 x 512 4.9 (5.9).  Eight
 // wavefronts a workgroup: 1 to 5 % slower; v_dot2_f32_bf16 for what a plane leaves: 64 instructions a block less, 15 % slower.
 // The copies take 16 bytes a lane and want every row of X on such a border; calls whose K is not a multiple of 4 go to k_matrix.  Where X itself lies
 // off the border (ON_BORDER false), X goes through registers instead, and the rest is the same, so that the order of a call's sums does not depend on where
@@ -1746,6 +1746,8 @@ hipError_t launch_rows_kernel(const MatrixArgs &a, const Call &c)
 // workgroup as leave one workgroup per compute unit (more of the small ones: they fit side by side), because every
 // workgroup cuts X anew.  us: 2.0 .. 2.6 + turns through the groups x (cutting + spreading) (fitted to 119 calls, M = 1 .. 8,
 // K and N = 512 .. 16384: 7 % off on average, 24 % at worst).
+// These figures, and what matrix_plan() and packed_plan() say of the choices that rest on them, are from before the weights were spread by conversions,
+// since when k_rows takes 2 to 6 % less for M <= 5 and from the codes: calls near the line stay with the other kernel.
 struct RowsPlan {
     int tiles, waves;
     double us;
@@ -1829,7 +1831,8 @@ size_t matrix_workspace_bytes(int M, int K, int N, int n_pad)
 //    + 0.1 per 1000 rows of W + 0.12 per million entries + 0.8 per million non-zeros, 1.3 and 1.7 times that for 32 and
 //    64 rows (M = 16: 15000 x 600 at 1/16 12.6 against 14.2; from 17 rows on it is behind everywhere, down to an empty W).  The
 //    6.1 count as 6.7: k_small has a second launch before it and takes more than that on few columns (1024 x 1024, M = 16, from an
-//    empty W to 50 %: 6.2 .. 8.2 against 6.25 here; 14 shapes x 6 densities: k_small ahead by at most 1 % where this path is taken).
+//    empty W to 50 %: 6.2 .. 8.2 against 6.25 in k_waves; 14 shapes x 6 densities: k_small ahead by at most 1 % where this path is taken).
+//    With K not a multiple of 4, where k_matrix is the other side, 6.9 .. 10.3 against 6.1 .. 6.6 on 52 shapes that the 6.7 bring here.
 //  * M <= 8: k_decode takes 2.55 + 0.5 M + 0.04 us per 1000 rows of W + (0.265 + 0.016 M) us per million non-zeros for one or
 //    two rows, 2.03 + 0.58 M + 0.13 + (0.353 + 0.066 M) for more, and 3.5 us for each further time that X fills the LDS (fitted
 //    to 17 shapes x 4 densities x M = 1 .. 8; the choice is 0.6 % behind the better of the two on average, 69 % at worst, 3 x 4096
