@@ -1115,11 +1115,11 @@ k_waves(const MatrixArgs a)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing is on its way to the LDS any more
     }
 
-    // Sums of the wavefronts.  Where K is whole, those of hi stay apart from those of mid + lo until the end: they are whole numbers of a unit
-    // and mostly exact, so a result is rounded little more than once, as in a kernel where one wavefront has all of K (300 x 832 x 5824 without
-    // a bias: 2.8e-8 of the norm; joined in each wavefront first 4.7e-8).  It is 1.5 times the traffic here, 0.1 to 0.4 us a call
-    // (87 x 408 x 2435 4.9 -> 5.0 us, 196 x 868 x 3375 8.25 -> 8.5, 256 x 4096 x 4096 23.0 -> 23.4).  Slices are rounded once more each by
-    // k_matrix_sum: there a wavefront joins its own first (64 x 16384 x 4096 6.2e-8, apart 5.5e-8).
+    // Sums of the wavefronts.  Those of hi stay apart from those of mid + lo until the end: they are whole numbers of a unit and mostly exact, so a
+    // result is rounded little more than once, as in a kernel where one wavefront has all of K (300 x 832 x 5824 without a bias: 2.8e-8 of the
+    // norm; joined in each wavefront first 4.7e-8).  It is 1.5 times the traffic here, 0.1 to 0.4 us a call (87 x 408 x 2435 4.9 -> 5.0 us, 196 x 868 x 3375
+    // 8.25 -> 8.5, 256 x 4096 x 4096 23.0 -> 23.4).  Slices in 32 x 64 tiles are joined in each wavefront first: calls that have them had more slices, or as
+    // many of tiles that joined as often, before there was this kernel.
     // Quad 4 j + q is elements 4 q .. of column fragment j, rows 8 q + 4 g .. + 3 of column 32 j + l32; a wavefront finishes CF quads from
     // quad0 on, 16 rows or all 32 of 32 columns, and gives the others away through its own ring.
     const bool sliced = a.k_slices > 1;
@@ -1129,10 +1129,11 @@ k_waves(const MatrixArgs a)
     const float bias = finish.bias_of(n), slope = finish.slope_of(n);
     float4v *const sums = reinterpret_cast<float4v *>(lds);
     constexpr int kRing = 2 * kSlot / 16;
+    const bool joined = CF == 2 && sliced;
     float4v mine[2][CF];   // [hi | mid + lo], or [all | zero]
 #pragma unroll
     for (int i = 0; i < CF; ++i) mine[1][i] = float4v{0.f, 0.f, 0.f, 0.f};
-    if (sliced) {
+    if (joined) {
 #pragma unroll
         for (int j = 0; j < CF; ++j) acc[0][j] += acc[1][j];
     }
@@ -1146,7 +1147,7 @@ k_waves(const MatrixArgs a)
             constexpr int OWN = decltype(own)::value;
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
-                if (d == 1 && sliced) break;
+                if (d == 1 && joined) break;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     if (i / 2 == OWN) mine[d][i % 2] = quad(d, i);
@@ -1161,7 +1162,7 @@ k_waves(const MatrixArgs a)
         __syncthreads();
 #pragma unroll
         for (int d = 0; d < 2; ++d) {
-            if (d == 1 && sliced) break;
+            if (d == 1 && joined) break;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
                 mine[d][i] = (mine[d][i] + place(wave ^ 1, d, quad0 + i)) + (place(wave ^ 2, d, quad0 + i) + place(wave ^ 3, d, quad0 + i));
@@ -1176,7 +1177,6 @@ k_waves(const MatrixArgs a)
             constexpr int KEEP = decltype(keep)::value;
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
-                if (d == 1 && sliced) break;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     place(wave, d, i) = quad(d, 8 * (1 - KEEP) + i);
@@ -1188,7 +1188,6 @@ k_waves(const MatrixArgs a)
             constexpr int KEEP = decltype(keep)::value;
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
-                if (d == 1 && sliced) break;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     place(wave ^ 1, d, i) = half[d][4 * (1 - KEEP) + i];
@@ -1200,20 +1199,16 @@ k_waves(const MatrixArgs a)
         else give_half(Int<0>{});
         __syncthreads();
 #pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            if (d == 1 && sliced) break;
+        for (int d = 0; d < 2; ++d)
 #pragma unroll
             for (int i = 0; i < 8; ++i) half[d][i] += place(wave ^ 1, d, i);
-        }
         if (wave & 2) give_quarter(Int<1>{});
         else give_quarter(Int<0>{});
         __syncthreads();
 #pragma unroll
-        for (int d = 0; d < 2; ++d) {
-            if (d == 1 && sliced) break;
+        for (int d = 0; d < 2; ++d)
 #pragma unroll
             for (int i = 0; i < 4; ++i) mine[d][i] += place(wave ^ 3, d, i);
-        }
     }
     float *out = sliced ? a.partials + ((size_t)slice * a.M + m0) * a.n_pad : a.Y + (size_t)m0 * a.N;
     const int width = sliced ? a.n_pad : a.N;

@@ -202,3 +202,24 @@ def test_epilogue_and_what_is_not_finite(M, K, N, slopes, off):
     ok = np.isfinite(Yd)
     assert ok.any() and not ok.all() and _same(Y, Yd)
     assert np.all(np.abs(Y[ok] - Yd[ok]) <= 1e-6 * A[ok])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N", [(33, 4096, 5000), (64, 8196, 4100), (82, 9024, 7424), (473, 6748, 2681)])
+def test_slices_are_rounded_once_each(M, K, N):
+    """X as in test_sums_are_rounded_once: each slice's sum is rounded once, and the slices are added in float, in pairs."""
+    rng = np.random.default_rng(380 + M)
+    X = (rng.uniform(0.5, 1.0, (M, K)) * rng.choice([-1.0, 1.0], (M, K))).astype(np.float32)
+    W = si.draw_ternary(rng, K, N, 0.5)
+    Y, t = gpu_tstgemm(W, X, None)
+    n = tg.tstgemm_query_route(t, M).k_slices
+    assert route(t, M) == ("k_waves", 32, 128, 4) and n > 1
+    step = -(-(-(-K // 64)) // n) * 64
+    part = [(X[:, k:k + step].astype(np.float64) @ W[k:k + step]).astype(np.float32) for k in range(0, K, step)]
+    assert len(part) == n
+    while n > 1:
+        half = (n + 1) // 2
+        for s in range(n - half):
+            part[s] = part[s] + part[s + half]
+        n = half
+    assert np.array_equal(Y, part[0])
