@@ -1342,8 +1342,8 @@ hipError_t launch_tiles(const MatrixArgs &a, long long m_tiles, const Call &c)
 // call is faster than `peak` operations per us, what the tile reaches on long calls under the power limit (64 x 512 against
 // 64 x 256: M = 4096, K = N = 8192 1073 -> 1038 us, 2048 x 4096 x 4096 138 -> 132, 1024 x 2048 x 8192 74 -> 70).  Fitted to 13 tiles x 6 slice counts on 77
 // shapes (M = 17 .. 2048, K and N = 512 .. 16384): the tile chosen among the last five of k_matrix is 2 % slower than the best of
-// all on average, 16 % at worst.  k_waves in slices is fitted to 1014 timings (M = 11 .. 768, the same K and N), with figures that are high by
-// some 5 % on long calls, where those of k_matrix are; with K whole kWholeOfWaves has what was measured.
+// all on average, 16 % at worst.  The figures are high by some 5 % on long calls, in slices
+// more; those of k_waves, which kLateRounds tells of, likewise.
 struct TileShape {
     int rows, cols, groups, waves, per_cu;
     double fixed, step, work, peak;
@@ -1355,8 +1355,8 @@ constexpr TileShape kTiles[] = {
     {64, 128, 1, 4, 3, 0.31, 0.420, 0.311, 1.45e9},   // short K: little to start with
     {32, 64, 4, 8, 2, 0.65, 0.501, 0.461, 1.30e9},    // small Y
     {32, 128, 2, 8, 2, 0.34, 0.456, 0.383, 1.40e9},   // M <= 32
-    {32, 64, 4, 4, 2, 0.50, 0.262, 0.370, 2.30e9},    // k_waves
-    {32, 128, 4, 4, 2, 1.20, 0.451, 0.490, 1.28e9},
+    {32, 64, 4, 4, 2, -0.45, 0.75, 0.370, 2.30e9},    // k_waves
+    {32, 128, 4, 4, 2, 0.05, 1.20, 0.490, 1.28e9},
 };
 constexpr int kDigitTiles = 2;   // the first two can take X in digits
 constexpr int kFirstOfWaves = 6;
@@ -1364,16 +1364,13 @@ constexpr int kFirstOfWaves = 6;
 // wavefront leaves wavefronts without work.
 bool waves_can(const tcsc_layout_t &l) { return l.K % 4 == 0 && l.n_kblocks >= 4; }
 constexpr double kCall = 3.36, kSlice = 2.40, kSliceMb = 0.374;   // us, us, us per MB
-// k_waves with K whole: a workgroup takes `each` for its sums, which both sets of four wavefronts bring to the LDS, beside its steps, `work` us each, and
-// the workgroups of a compute unit share both; with more tiles than two a compute unit nothing covers what is written last (kLateRounds,
-// kLateMb, us per MB of Y).  Fitted to 771 timings of 415 shapes, with 255 others to test (M = 11 .. 2500, K = 196 .. 9000, N = 64 .. 14000, the
-// estimates of both kernels within 40 %): two of the 670 are more than 1.5 % behind k_matrix (500 x 7296 x 2705 4 %), and the choice is 0.9 % behind the
-// best of all on average.  With `fixed` for a round of workgroups, as in k_matrix, 32 were, up to 13 % (246 x 256 x 6144 7.4 us, k_matrix 7.1 and 6.4; 640 x 256 x 1024
-// 5.7, 5.0), and without the late ones 192 x 4096 x 11008 (516 tiles on 512 places 53.1 us, 48.6).
-struct WholeShape {
-    double start, each;
-};
-constexpr WholeShape kWholeOfWaves[] = {{-0.45, 0.75}, {0.05, 1.20}};
+// k_waves takes `fixed` us more than its workgroups, and a workgroup `step` us for its sums, which four wavefronts bring to the LDS, beside its steps,
+// `work` us each; the workgroups of a compute unit share both.  With K whole and more tiles than two a compute unit nothing covers what is written last
+// (kLateRounds, kLateMb, us per MB of Y).  Fitted to 771 timings of 415 shapes with K whole, with 515 others to test, 260 of them where slices are near (M = 11 ..
+// 4000, K = 196 .. 16384, N = 64 .. 14000, the estimates of both kernels within 40 %): four of the 930 are more than 1.5 % behind k_matrix (2525 x 15832 x 157 and
+// 500 x 7296 x 2705 6 %), and the choice is 0.7 % behind the best of all on average.  With `fixed` for a round of workgroups, as in k_matrix, 40 were, up to 13 %
+// (246 x 256 x 6144 7.4 us, k_matrix 7.1 and 6.4; 640 x 256 x 1024 5.7, 5.0; 2943 x 2920 x 348 in three slices 28.4, 27.2), and without the late ones 192 x 4096 x 11008
+// (516 tiles on 512 places 53.1 us, 48.6).
 constexpr double kLateRounds = 1.04, kLateMb = 0.15;
 
 struct TilePlan {
@@ -1446,11 +1443,9 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
         const double load = up(tiles[i] * k / units), rounds = s.per_cu == 1 ? load : up(load / s.per_cu);
         const double steps = 2.0 * ((per + s.groups - 1) / s.groups);
         const double step_us = s.step * rounds > s.work * load ? s.step * rounds : s.work * load;
-        const bool whole_of_waves = i >= kFirstOfWaves && k == 1;
-        double us = s.fixed * rounds + steps * step_us;
-        if (whole_of_waves) us = kWholeOfWaves[i - kFirstOfWaves].start + (kWholeOfWaves[i - kFirstOfWaves].each + steps * s.work) * load;
+        double us = i < kFirstOfWaves ? s.fixed * rounds + steps * step_us : s.fixed + (s.step + steps * s.work) * load;
         if (us < floor_us[i]) us = floor_us[i];
-        if (whole_of_waves && rounds > 1.0) us = kLateRounds * us + kLateMb * mb;
+        if (i >= kFirstOfWaves && k == 1 && rounds > 1.0) us = kLateRounds * us + kLateMb * mb;
         us += kCall + (k > 1 ? kSlice + kSliceMb * mb : 0.0);
         if (best.tile < 0 || us < best.us) best = TilePlan{i, k, us};
     };
@@ -1470,9 +1465,9 @@ TilePlan choose_tile(const tcsc_layout_t &l, int M, size_t ws_bytes)
             const TileShape &s = kTiles[i];
             const int most = kMaxKSlices < l.n_kblocks ? kMaxKSlices : l.n_kblocks;
             const double steps = 2.0 * (((l.n_kblocks + most - 1) / most + s.groups - 1) / s.groups);
-            double us = steps * s.step, all = 2.0 * l.n_kblocks * tiles[i] * s.work / (s.groups * (double)units);
+            double us = steps * (i < kFirstOfWaves ? s.step : s.work), all = 2.0 * l.n_kblocks * tiles[i] * s.work / (s.groups * (double)units);
             if (us < all) us = all;
-            us += s.fixed;
+            us += i < kFirstOfWaves ? s.fixed : s.fixed + s.step;
             if (us < floor_us[i]) us = floor_us[i];
             // (slices beyond two full rounds only add partial sums)
             least[i] = 2.0 * tiles[i] > 2.0 * units * s.per_cu ? 1e300 : us + kCall + kSlice + kSliceMb * 2.0 * y_mb;
